@@ -190,6 +190,15 @@ void corr_variant_name(char* buf, size_t len, int32_t tile, const CorrArgs& a, i
     snprintf(buf, len, "%s[m%d,e%c](S=%d,L=%d)", corr_tile_name(tile), a.bounds_mode, e, a.ksplit, launches);
 }
 
+// "corrsplit_<tile>[p<patch units per thread>,e<epilogue form>](S,L)"
+void split_variant_name(char* buf, size_t len, int32_t tile, const CorrArgs& a, int zero_fill) {
+  int32_t bm, bn, mt;
+  split_tile_shape(tile, &bm, &bn, &mt);
+  const char e = a.simple_epilogue ? 's' : ((uint32_t)a.out_elems < (1u << 29) ? 'r' : 'p');
+  snprintf(buf, len, "corrsplit_m%d_%dx%d[p%d,e%c](S=%d,L=%d)", mt, bm, bn, split_patch_units(a.PSZ, bn), e,
+           a.ksplit, 2 + (a.ksplit > 1) + (zero_fill != 0));
+}
+
 uint32_t koff_invalid(int32_t mode) { return mode == 0 ? 0x7FFFFFFCu : mode == 2 ? 0x40000000u : 0u; }
 
 // Decides whether the patch-staged kernel runs this correlation and, if so, fills its fields.
@@ -355,6 +364,219 @@ int32_t configure_thin(CorrArgs& a, PackArgs& k, int64_t cg_in, int64_t n_img, b
   return 1;
 }
 
+// One dimension of an LDS patch (corr_split_kernel, wgrad_split_kernel): `out` positions `stride` apart with windows of
+// `ext` positions over an image of `size` positions behind `pad` zeros.  `share` of the zeros behind the image, which
+// some window reads, are the same ones as those before the next row (image): `pitch` positions from row to row.
+struct PatchDim {
+  int64_t pitch, share;
+};
+
+PatchDim patch_dim(int64_t out, int64_t stride, int64_t ext, int64_t pad, int64_t size) {
+  const int64_t reach = (out - 1) * stride + ext, behind = reach - pad - size;
+  PatchDim r;
+  r.share = behind <= 0 || pad <= 0 ? 0 : behind < pad ? behind : pad;
+  r.pitch = reach - r.share;
+  return r;
+}
+
+// Decides whether corr_split_kernel runs this correlation; fills a, k and the tile.  Returns the bytes of packed
+// weights, 0 if it does not.
+size_t configure_split(const CorrArgs& base, const PackArgs& pbase, int64_t cg_in, int64_t n_img, int64_t out_elems,
+                       CorrArgs& a, PackArgs& k, int32_t& tile) {
+  tile = -1;
+  const double flops = 2.0 * base.Mrows * base.Kred * (double)base.ncols * base.G;
+  if (base.ncols < 1 || (int64_t)base.in_bytes > ((int64_t)1 << 30)) return 0;
+  // Below a GFLOP the two paths are level (100 x 32 -> 64 at 8x8, 5x5, 0.66 GFLOP: 19.4 us fp32, 20.8 split; one image of
+  // 96 -> 256 in two groups at 27x27, 0.45 GFLOP: 22.2 and 20.8).  With one or two taps the patch is staged for too few
+  // steps (256 -> 256 1x1 at 14x14: 26.7 us fp32, 29.6 split), with a short reduction likewise; the patch-staged fp32
+  // kernel keeps reductions under 512.
+  if (flops < 1e9 || base.THW < 3 || base.Kred < (base.use_patch ? 512 : 256)) return 0;
+  const int64_t TH = base.THW / base.TW, PH = base.P / base.PW;
+  const int64_t ext = (TH - 1) * base.dh + 1;
+  const PatchDim dim_w = patch_dim(base.PW, base.sw, (int64_t)(base.TW - 1) * base.dw + 1, base.pw, base.IW);
+  const PatchDim dim_h = patch_dim(PH, base.sh, ext, base.ph, base.IH);
+  const int64_t PWID = dim_w.pitch, RS = dim_h.pitch, share_w = dim_w.share, share_h = dim_h.share;
+  const int64_t chunks = ceil_div(cg_in, 16);
+  if (cg_in * 100 < chunks * 16 * 70) return 0;
+  // Modelled time (us) of every tile and split count: the workgroup that finishes last walks its steps alone on its
+  // compute unit (kAlone per step) or shares it with others (kShared per step and workgroup); a chunk costs its patch
+  // by units per thread; S slices cost the reduce kernel and their partial sums written and read.  The constants are a
+  // least-squares fit to 888 timings -- all tiles, 1 to 12 slices, 38 layers of 0.3 to 57 GFLOP (rms error 8 %); the
+  // choice is 2 % behind the best of each layer on average and 13 % at worst.
+  static const double kAlone[SPLIT_TILE_COUNT] = {0.457, 0.444, 0.414, 0.376, 0.400, 0.298, 0.664};
+  static const double kShared[SPLIT_TILE_COUNT] = {0.423, 0.424, 0.250, 0.340, 0.248, 0.166, 0.613};
+  double best = 0;
+  int64_t best_psz = 0, best_S = 1;
+  for (int32_t t = 0; t < SPLIT_TILE_COUNT; ++t) {
+    int32_t bm, bn, mt;
+    split_tile_shape(t, &bm, &bn, &mt);
+    int64_t max_rows = 0;
+    for (int64_t c0 = 0; c0 < base.ncols; c0 += bn) {
+      const int64_t c1 = (c0 + bn < base.ncols ? c0 + bn : base.ncols) - 1;
+      const int64_t n0 = c0 / base.P, a0 = (c0 % base.P) / base.PW, n1 = c1 / base.P, a1 = (c1 % base.P) / base.PW;
+      const int64_t R0 = (PH - 1 - a0) * base.sh + ext - share_h;
+      const int64_t rows = (n1 == n0 ? (a1 - a0) * base.sh : R0 + (n1 - n0 - 1) * RS + a1 * base.sh) + ext;
+      if (rows > max_rows) max_rows = rows;
+    }
+    const int64_t psz = max_rows * PWID + share_w;
+    if (psz > 512) continue;
+    const int64_t units = (int64_t)base.G * ceil_div(base.Mrows, bm) * ceil_div(base.ncols, bn);
+    const int64_t tps = mt == 32 ? 1 : 2, spc = ceil_div(base.THW, tps);
+    const double out_mb = 4e-6 * (double)out_elems;
+    const double units_per_thread = (double)split_patch_units(psz, bn);
+    for (int64_t S = 1; S <= 16 && S <= chunks; ++S) {
+      if (S > 1 && (units * S > 2048 || units > 512)) break;
+      const int64_t per_cu = ceil_div(units * S, 256), cps = ceil_div(chunks, S);
+      const double steps = (double)(cps * spc);
+      double cost = per_cu == 1 ? steps * kAlone[t] + 0.39 * (double)cps * units_per_thread
+                                : (double)per_cu * (steps * kShared[t] + 0.25 * (double)cps * units_per_thread);
+      if (S > 1) cost += 3.3 + 0.46 * (double)S * out_mb;
+      if (tile < 0 || cost < best) {
+        best = cost;
+        tile = t;
+        best_psz = psz;
+        best_S = S;
+      }
+    }
+  }
+  if (tile < 0) return 0;
+  int32_t bm, bn, mt;
+  split_tile_shape(tile, &bm, &bn, &mt);
+  a = base;
+  k = pbase;
+  a.use_patch = 0;
+  a.Cg_in = (int32_t)cg_in;
+  a.NS = (int32_t)chunks;
+  a.PH = (int32_t)PH;
+  a.Nimg = (int32_t)n_img;
+  a.PWID = (int32_t)PWID;
+  a.share_w = (int32_t)share_w;
+  a.share_h = (int32_t)share_h;
+  a.PSZ = (int32_t)best_psz;
+  a.patch_stages = best_psz <= 426 ? 2 : 1;  // two workgroups per compute unit either way
+  a.mPWID = make_magic((uint32_t)PWID);
+  a.mRSEG = make_magic((uint32_t)RS);
+  a.m_tiles = (int32_t)ceil_div(a.Mrows, bm);
+  a.MP = a.m_tiles * bm;
+  a.col_tiles = (int32_t)ceil_div(a.ncols, bn);
+  a.out_elems = (int32_t)out_elems;
+  a.chunks_per_split = (int32_t)ceil_div(chunks, best_S);
+  a.ksplit = (int32_t)ceil_div(chunks, a.chunks_per_split);
+  k.split_chunks = a.NS;
+  const int64_t tps = mt == 32 ? 1 : 2;
+  return (size_t)a.G * a.m_tiles * chunks * ceil_div(a.THW, tps) * (bm / mt) * 3072;
+}
+
+// Decides whether wgrad_split_kernel runs the backward filter; fills a and returns its tile, -1 if it does not.
+int32_t configure_wgrad_split(const WgradArgs& w, int64_t N, int64_t K, int64_t w_elems, WgradSplitArgs& a) {
+  const double flops = 2.0 * w.Kg * w.Kred * (double)w.ncols * w.G;
+  if (w.ncols < 1 || flops < 4e8 || w.x_bytes > (1u << 30) || w.dy_bytes > (1u << 31) - 32) return -1;
+  if (4 * (int64_t)w.Kg * w.Kred > ((int64_t)1 << 30)) return -1;
+  const int64_t TH = w.khw / w.kw, PH = w.P / w.PW;
+  const int64_t ext = (TH - 1) * w.dh + 1;
+  const PatchDim dim_w = patch_dim(w.PW, w.sw, (int64_t)(w.kw - 1) * w.dw + 1, w.pw, w.W);
+  const PatchDim dim_h = patch_dim(PH, w.sh, ext, w.ph, w.H);
+  const int64_t PWID = dim_w.pitch, RS = dim_h.pitch;
+  const int64_t runs = ceil_div(w.P, 8), total_runs = N * runs, chunk_runs = wgrad_split_chunk_runs();
+  int64_t max_rows = 0;
+  for (int64_t q = 0; q < total_runs; q += chunk_runs) {
+    const int64_t q1 = (q + chunk_runs < total_runs ? q + chunk_runs : total_runs) - 1;
+    const int64_t n0 = q / runs, a0 = q % runs * 8 / w.PW, n1 = q1 / runs;
+    const int64_t p1 = q1 % runs * 8 + 7 < w.P ? q1 % runs * 8 + 7 : w.P - 1, a1 = p1 / w.PW;
+    const int64_t R0 = (PH - 1 - a0) * w.sh + ext - dim_h.share;
+    const int64_t rows = (n1 == n0 ? (a1 - a0) * w.sh : R0 + (n1 - n0 - 1) * RS + a1 * w.sh) + ext;
+    if (rows > max_rows) max_rows = rows;
+  }
+  const int64_t psz = max_rows * PWID + dim_w.share;
+  if (psz > 512) return -1;
+  const int64_t c16 = ceil_div(w.Cg, 16);
+  // Splits: the whole grid resident at once (two workgroups per compute unit) or half of that, partials at most 32 MiB.
+  // Tile and splits by modelled time (us), as in configure_split: a chunk is four steps; a fit to 580 timings of
+  // all tiles and 1 to 12 quarters of a resident grid on the same layers (rms error 5 %; the choice is 1 % behind the
+  // best on average, 12 % at worst).
+  static const double kAlone[WSPLIT_TILE_COUNT] = {1.40, 1.19, 1.18, 1.06, 0.64, 1.04};
+  static const double kShared[WSPLIT_TILE_COUNT] = {1.09, 0.985, 0.97, 0.90, 0.52, 0.89};
+  const int64_t chunks = ceil_div(total_runs, chunk_runs), max_by_ws = ((int64_t)8 << 20) / w_elems;
+  const double units_per_thread = (double)split_patch_units(psz), w_mb = 4e-6 * (double)w_elems;
+  int32_t best = -1;
+  int64_t best_cps = 0;
+  double best_cost = 0, least_work = 0;
+  for (int32_t t = 0; t < WSPLIT_TILE_COUNT; ++t) {
+    int32_t rows, taps;
+    wgrad_split_shape(t, &rows, &taps);
+    const double work = (double)round_up(w.Kg, rows) * (double)round_up(w.khw, taps) * (double)(16 * c16);
+    if (least_work == 0 || work < least_work) least_work = work;
+    const int64_t tiles = (int64_t)w.G * ceil_div(w.Kg, rows) * ceil_div(w.khw, taps) * c16;
+    for (int64_t places = 256; places <= 512; places += 256) {
+      int64_t S = places / tiles;
+      if (S > max_by_ws) S = max_by_ws;
+      if (S > 256) S = 256;
+      if (S > chunks) S = chunks;
+      if (S < 1) S = 1;
+      const int64_t cps = ceil_div(chunks, S), per_cu = ceil_div(tiles * ceil_div(chunks, cps), 256);
+      const double cost = 0.66 * (double)S * w_mb + 0.73 * (double)per_cu +
+                          (per_cu == 1 ? (double)cps * (4 * kAlone[t] + 0.37 * units_per_thread)
+                                       : (double)(per_cu * cps) * (4 * kShared[t] + 0.16 * units_per_thread));
+      if (best < 0 || cost < best_cost) {
+        best = t;
+        best_cost = cost;
+        best_cps = cps;
+      }
+    }
+  }
+  // What the blocks pad more than the fp32 tile costs the advantage: up to twice its work on a large problem (202 -> 14
+  // channels, 5x3: 1.6 times the work, 186 -> 156 us), 1.12 times on one under 2.5 GFLOP (64 -> 96 channels, 3x1 at
+  // 28x28, twice the work: 38 -> 42 us; 300 -> 200, 3x3 at 12x12, 1.11 times: 38 -> 33 us).
+  int32_t bm, bn, bk;
+  wgrad_tile_shape(pick_wgrad_tile(w.Kg, w.Kred), &bm, &bn, &bk);
+  if (least_work > (flops < 2.5e9 ? 1.12 : 2.0) * (double)round_up(w.Kg, bm) * (double)round_up(w.Kred, bn)) return -1;
+  int32_t rows, taps;
+  wgrad_split_shape(best, &rows, &taps);
+  a = WgradSplitArgs();
+  a.dy_bytes = w.dy_bytes;
+  a.x_bytes = w.x_bytes;
+  a.N = (int32_t)N;
+  a.P = w.P;
+  a.PW = w.PW;
+  a.PH = (int32_t)PH;
+  a.mPW = w.mPW;
+  a.runs = (int32_t)runs;
+  a.mRuns = make_magic((uint32_t)runs);
+  a.Kg = w.Kg;
+  a.Ktot = w.Ktot;
+  a.Cg = w.Cg;
+  a.C = w.C;
+  a.H = w.H;
+  a.W = w.W;
+  a.kw = w.kw;
+  a.khw = w.khw;
+  a.sh = w.sh;
+  a.sw = w.sw;
+  a.dh = w.dh;
+  a.dw = w.dw;
+  a.ph = w.ph;
+  a.pw = w.pw;
+  a.Kred = w.Kred;
+  a.part_stride = (int32_t)w_elems;
+  a.G = w.G;
+  a.m_tiles = (int32_t)ceil_div(w.Kg, rows);
+  a.tap_tiles = (int32_t)ceil_div(w.khw, taps);
+  a.n_tiles = (int32_t)(c16 * a.tap_tiles);
+  a.PWID = (int32_t)PWID;
+  a.PSZ = (int32_t)psz;
+  a.ext = (int32_t)ext;
+  a.share_h = (int32_t)dim_h.share;
+  a.patch_stages = psz <= 416 ? 2 : 1;  // two workgroups per compute unit either way
+  a.mPWID = make_magic((uint32_t)PWID);
+  a.mRSEG = make_magic((uint32_t)RS);
+  a.chunks = (int32_t)chunks;
+  a.chunks_per_split = (int32_t)best_cps;
+  a.S = (int32_t)ceil_div(chunks, best_cps);
+  const int64_t tiles = (int64_t)a.G * a.m_tiles * a.n_tiles;
+  if (a.S * (w_elems + a.n_tiles * K) >= kMaxElems || tiles * a.S >= ((int64_t)1 << 31)) return -1;
+  return best;
+}
+
 }  // namespace
 
 namespace mi355conv {
@@ -386,21 +608,23 @@ int run_forward(const conv_desc* d, const float* x, const float* w, const float*
     return ed ? record_hip_error(ed) : CONV_OK;
   }
   if (d->fwd_ws > 0 && (!ws || ws_bytes < d->fwd_ws)) return CONV_EWORKSPACE;
-  PackArgs k = d->fwd_pack;
+  const bool split = d->fwd_split >= 0;
+  PackArgs k = split ? d->fwd_sp_pack : d->fwd_pack;
   k.w = w;
   k.A = static_cast<float*>(ws);
   k.ktab = reinterpret_cast<KTabEntry*>(k.A + (size_t)k.G * k.KP * k.MP);
   const bool in_place = d->fwd_thin && d->fwd.use_patch;  // that kernel reads the weight blob itself
-  int e = in_place ? 0 : launch_pack(k, hip_stream);
+  int e = split ? launch_pack_split(d->fwd_split, k, hip_stream) : in_place ? 0 : launch_pack(k, hip_stream);
   if (e) return record_hip_error(e);
-  CorrArgs a = d->fwd;
+  CorrArgs a = split ? d->fwd_sp : d->fwd;
   a.A = in_place ? w : k.A;
   a.ktab = k.ktab;
   a.in = x;
   a.bias = bias;
   a.out = y;
   a.part = reinterpret_cast<float*>(static_cast<char*>(ws) + d->fwd_pack_bytes);
-  e = d->fwd_thin    ? launch_corr_thin(a, hip_stream)
+  e = split          ? launch_corr_split(d->fwd_split, a, hip_stream)
+      : d->fwd_thin ? launch_corr_thin(a, hip_stream)
       : a.use_patch ? launch_corr_patch(d->fwd_tile, a, hip_stream)
                     : launch_corr(d->fwd_tile, a, hip_stream);
   if (e) return record_hip_error(e);
@@ -437,14 +661,15 @@ int run_backward_data(const conv_desc* d, const float* w, const float* dy, float
     return ed ? record_hip_error(ed) : CONV_OK;
   }
   if (d->bwd_ws > 0 && (!ws || ws_bytes < d->bwd_ws)) return CONV_EWORKSPACE;
-  PackArgs k = d->bwd_pack;
+  const bool split = d->bwd_split >= 0;
+  PackArgs k = split ? d->bwd_sp_pack : d->bwd_pack;
   k.w = w;
   k.A = static_cast<float*>(ws);
   k.ktab = reinterpret_cast<KTabEntry*>(k.A + (size_t)k.G * k.KP * k.MP);
   const bool in_place = d->bwd_thin && d->bwd.use_patch;  // that kernel reads the weight blob itself
-  int e = in_place ? 0 : launch_pack(k, hip_stream);
+  int e = split ? launch_pack_split(d->bwd_split, k, hip_stream) : in_place ? 0 : launch_pack(k, hip_stream);
   if (e) return record_hip_error(e);
-  CorrArgs a = d->bwd;
+  CorrArgs a = split ? d->bwd_sp : d->bwd;
   a.A = in_place ? w : k.A;
   a.ktab = k.ktab;
   a.in = dy;
@@ -459,7 +684,8 @@ int run_backward_data(const conv_desc* d, const float* w, const float* dy, float
       e = launch_fill_zero(dx, (size_t)a.out_elems * 4, hip_stream);
     if (e) return record_hip_error(e);
   }
-  e = d->bwd_thin    ? launch_corr_thin(a, hip_stream)
+  e = split          ? launch_corr_split(d->bwd_split, a, hip_stream)
+      : d->bwd_thin ? launch_corr_thin(a, hip_stream)
       : a.use_patch ? launch_corr_patch(d->bwd_tile, a, hip_stream)
                     : launch_corr(d->bwd_tile, a, hip_stream);
   if (e) return record_hip_error(e);
@@ -500,6 +726,16 @@ int run_backward_filter(const conv_desc* d, const float* x, const float* dy, flo
     a.n_tiles = 1;
     if (db) da.bias_part = a.bias_part = a.part + (size_t)da.S * w_elems;
     if (!empty) e = launch_direct(2, da, false, hip_stream);
+  } else if (d->wg_split >= 0) {
+    WgradSplitArgs sa = d->wg_sp;
+    a.S = sa.S;
+    a.n_tiles = sa.n_tiles;
+    if (db) a.bias_part = a.part + (size_t)a.S * w_elems;
+    sa.dy = dy;
+    sa.x = x;
+    sa.part = a.part;
+    sa.bias_part = a.bias_part;
+    if (!empty) e = launch_wgrad_split(d->wg_split, sa, hip_stream);
   } else if (!empty) {
     if (db) a.bias_part = a.part + (size_t)a.S * w_elems;  // row sums of dy ride along, behind the filter partials
     e = launch_wgrad(d->wg_tile, a, hip_stream);
@@ -517,6 +753,12 @@ int run_backward_filter(const conv_desc* d, const float* x, const float* dy, flo
   r.mChanElems = make_magic(r.chan_elems);
   r.mChannels = make_magic(r.channels);
   r.relu = extras.relu;
+  if (d->wg_split >= 0 && !d->use_direct) {
+    r.taps = d->wg_sp.khw;
+    r.tap_channels = d->wg_sp.Cg;
+    r.mRow = make_magic((uint32_t)d->wg_sp.Kred);
+    r.mTapChannels = make_magic((uint32_t)d->wg_sp.Cg);
+  }
   if (db) {  // the same launch finishes db from the S * n_tiles shares of the row sums
     r.part2 = empty ? nullptr : a.bias_part;
     r.dst2 = db;
@@ -644,7 +886,11 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
       return CONV_ESHAPE;
     }
     d->fwd_pack_bytes = (size_t)pack_elems * 4 + (size_t)a.KP * sizeof(KTabEntry);
-    d->fwd_ws = d->fwd_pack_bytes + (a.ksplit > 1 ? (size_t)a.ksplit * y_elems * 4 : 0);
+    d->fwd_split = -1;
+    const size_t sp = d->fwd_thin ? 0 : configure_split(a, k, Cg, N, y_elems, d->fwd_sp, d->fwd_sp_pack, d->fwd_split);
+    if (sp) d->fwd_pack_bytes = sp;
+    const int32_t S = sp ? d->fwd_sp.ksplit : a.ksplit;
+    d->fwd_ws = d->fwd_pack_bytes + (S > 1 ? (size_t)S * y_elems * 4 : 0);
   }
 
   // ---- backward data: a stride-1 correlation over dy whose rows are (c, row phase, column
@@ -760,7 +1006,11 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
       return CONV_ESHAPE;
     }
     d->bwd_pack_bytes = (size_t)pack_elems * 4 + (size_t)a.KP * sizeof(KTabEntry);
-    d->bwd_ws = d->bwd_pack_bytes + (a.ksplit > 1 ? (size_t)a.ksplit * x_elems * 4 : 0);
+    d->bwd_split = -1;
+    const size_t sp = d->bwd_thin ? 0 : configure_split(a, k, Kg, N, x_elems, d->bwd_sp, d->bwd_sp_pack, d->bwd_split);
+    if (sp) d->bwd_pack_bytes = sp;
+    const int32_t S = sp ? d->bwd_sp.ksplit : a.ksplit;
+    d->bwd_ws = d->bwd_pack_bytes + (S > 1 ? (size_t)S * x_elems * 4 : 0);
   }
 
   // ---- backward filter: rows = output channels, columns = (c, i, j), reduction over (n, oh, ow)
@@ -847,6 +1097,11 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
     if (a.S * (w_elems + a.n_tiles * K) >= kMaxElems) {
       delete d;
       return CONV_ESHAPE;
+    }
+    d->wg_split = configure_wgrad_split(a, N, K, w_elems, d->wg_sp);
+    if (d->wg_split >= 0) {
+      d->wg_ws = (size_t)d->wg_sp.S * (size_t)w_elems * 4;
+      d->wgb_ws = (size_t)d->wg_sp.S * (size_t)(w_elems + d->wg_sp.n_tiles * K) * 4;
     }
   }
 
@@ -1018,8 +1273,17 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
     char f[64], b[64], wg[64];
     corr_variant_name(f, sizeof(f), d->fwd_tile, d->fwd, 0, d->fwd_thin);
     corr_variant_name(b, sizeof(b), d->bwd_tile, d->bwd, d->bwd_zero_fill, d->bwd_thin);
+    if (d->fwd_split >= 0) split_variant_name(f, sizeof(f), d->fwd_split, d->fwd_sp, 0);
+    if (d->bwd_split >= 0) split_variant_name(b, sizeof(b), d->bwd_split, d->bwd_sp, d->bwd_zero_fill);
     snprintf(wg, sizeof(wg), "%s[m%d,%s,e%c](S=%d,L=2)", wgrad_tile_name(d->wg_tile), d->wg.bounds_mode,
              d->wg_tile == WGRAD_128x128 ? "lds" : "reg", 4 * Kg * kred <= ((int64_t)1 << 30) ? 'r' : 'p', d->wg.S);
+    if (d->wg_split >= 0) {
+      int32_t rows, taps;
+      wgrad_split_shape(d->wg_split, &rows, &taps);
+      const int32_t psz = d->wg_sp.PSZ;
+      snprintf(wg, sizeof(wg), "splitwgrad_%dx%dx16[p%d,st%d](S=%d,L=2)", rows, taps, split_patch_units(psz),
+               d->wg_sp.patch_stages, d->wg_sp.S);
+    }
     if (d->use_direct) {
       char df[3][32];
       for (int pass = 0; pass < 3; ++pass) direct_form_name(pass, d->dir, df[pass], sizeof(df[pass]));

@@ -93,6 +93,8 @@ struct CorrArgs {
   int32_t Nimg;        // images
   int32_t PWID, PSZ;   // patch row length (PW + TW - 1); floats per channel of an LDS patch stage
   Magic mPWID, mRSEG;  // divisions by PWID and by the patch rows of a full image (PH + TH - 1)
+  int32_t patch_stages;      // corr_split_kernel: patch stages in LDS (1 or 2)
+  int32_t share_w, share_h;  // corr_split_kernel: padding columns / rows that neighbouring patch rows / images share
   int32_t simple_epilogue;  // one phase per channel and an output of at most 2^30 bytes: offset-only epilogue
   // LDS-staged form of corr_thin_kernel: A is the weight blob itself (no pack kernel); element strides of
   // a GEMM row, a gathered channel and a group in it, and whether the taps run backwards (backward data)
@@ -122,6 +124,7 @@ struct PackArgs {
   int32_t phase_h[kMaxPhases], phase_w[kMaxPhases];
   int32_t Kred, KP, Mrows, MP;
   int32_t kperm_T;  // 0, or the tap count T: k runs (8-channel chunk, tap, channel in chunk) instead of (c, tap)
+  int32_t split_chunks;  // corr_split_kernel: chunks of 16 channels
 };
 
 // Backward filter: part[s][g][k][nn] = sum over the split's columns of dy * gathered x.
@@ -150,6 +153,28 @@ struct WgradArgs {
   float* bias_part;
 };
 
+// The same on the bf16 matrix instructions (wgrad_split_kernel): columns in blocks of one tap x 16 channels, the
+// reduction in runs of eight pixels of one image.
+struct WgradSplitArgs {
+  const float* dy;
+  const float* x;
+  float* part;
+  float* bias_part;            // as in WgradArgs
+  uint32_t dy_bytes, x_bytes;  // at most 2^31 - 32 and 2^30
+  int32_t N, P, PW, PH;
+  Magic mPW;
+  int32_t runs;                // runs of eight pixels per image
+  Magic mRuns;
+  int32_t Kg, Ktot, Cg, C, H, W;
+  int32_t kw, khw, sh, sw, dh, dw, ph, pw;
+  int32_t Kred, part_stride;
+  int32_t G, m_tiles, n_tiles, tap_tiles;  // n_tiles = ceil(Cg / 16) * tap_tiles
+  int32_t S, chunks, chunks_per_split;
+  // patch geometry (see corr_split_kernel)
+  int32_t PWID, PSZ, ext, share_h, patch_stages;
+  Magic mPWID, mRSEG;
+};
+
 struct ReduceArgs {
   const float* part;  // [S][stride]: elements [0, count) of a slice go to dst
   float* dst;         // [count]
@@ -166,6 +191,10 @@ struct ReduceArgs {
   int32_t chan_elems, channels;
   Magic mChanElems, mChannels;
   int32_t relu;  // clamp the finished value at zero from below
+  // partials in the order [row][tap][channel] of wgrad_split_kernel, dst in that of the weight blob, [row][channel][tap]
+  // (taps 0: the same order)
+  int32_t taps, tap_channels;
+  Magic mRow, mTapChannels;  // divisions by taps * tap_channels and tap_channels
 };
 
 // Element-wise and column-sum helpers of the InnerProduct layer.
@@ -253,6 +282,25 @@ enum WgradTile : int32_t {
   WGRAD_128x64,       // 2x2 waves of 64x32
   WGRAD_TILE_COUNT
 };
+enum WgradSplitTile : int32_t {  // wgrad_split_kernel: rows x taps (of 16 channels)
+  WSPLIT_128x9 = 0,  // 4x1 waves of 32 rows
+  WSPLIT_128x8,      // 4x1 waves of 32 rows
+  WSPLIT_64x16,      // 2x2 waves of 32 rows x 8 taps
+  WSPLIT_32x28,      // 1x4 waves of 32 rows x 7 taps
+  WSPLIT_32x12,      // 1x4 waves of 32 rows x 3 taps
+  WSPLIT_96x8,       // 2x2 waves of 48 rows x 4 taps
+  WSPLIT_TILE_COUNT
+};
+enum SplitTile : int32_t {  // corr_split_kernel
+  SPLIT_128x128 = 0,  // 32x32x16 bf16 MFMA, 2x2 waves of 64x64
+  SPLIT_64x256,       // 32x32x16, 1x4 waves of 64x64
+  SPLIT_64x128,       // 32x32x16, 2x2 waves of 32x64
+  SPLIT_96x128,       // 32x32x16, 1x4 waves of 96x32
+  SPLIT_32x256,       // 32x32x16, 1x4 waves of 32x64
+  SPLIT_32x128,       // 32x32x16, 1x4 waves of 32x32
+  SPLIT_48x256,       // 16x16x32, 1x4 waves of 48x64
+  SPLIT_TILE_COUNT
+};
 
 void corr_tile_shape(int32_t tile, int32_t* bm, int32_t* bn, int32_t* bk);
 void wgrad_tile_shape(int32_t tile, int32_t* bm, int32_t* bn, int32_t* bk);
@@ -263,6 +311,15 @@ const char* wgrad_tile_name(int32_t tile);
 int launch_pack(const PackArgs& a, void* stream, bool f64 = false);
 int launch_corr(int32_t tile, const CorrArgs& a, void* stream);
 int launch_corr_patch(int32_t tile, const CorrArgs& a, void* stream);
+// Patch units (position x 8 channels) per thread of the kernel instance that takes a patch of psz positions.  The
+// 256-column tiles have no instance for two: 256 columns and their halo need more.
+inline int32_t split_patch_units(int64_t psz, int32_t bn = 128) { return psz <= 256 && bn <= 128 ? 2 : psz <= 384 ? 3 : 4; }
+void split_tile_shape(int32_t tile, int32_t* bm, int32_t* bn, int32_t* mt);
+int launch_pack_split(int32_t tile, const PackArgs& a, void* stream);
+int launch_corr_split(int32_t tile, const CorrArgs& a, void* stream);
+void wgrad_split_shape(int32_t tile, int32_t* rows, int32_t* taps);
+int32_t wgrad_split_chunk_runs();
+int launch_wgrad_split(int32_t tile, const WgradSplitArgs& a, void* stream);
 int launch_corr_thin(const CorrArgs& a, void* stream);  // Mrows <= 4, offset-only epilogue, no split
 int launch_wgrad(int32_t tile, const WgradArgs& a, void* stream);
 int launch_reduce(const ReduceArgs& a, void* stream);
@@ -331,6 +388,10 @@ struct conv_desc {
   mi355conv::CorrArgs fwd;  // pointers left null
   mi355conv::PackArgs fwd_pack;
   size_t fwd_ws, fwd_pack_bytes;
+  // forward on the bf16 matrix instructions (fwd_split: its SplitTile, or -1: the fields above)
+  int32_t fwd_split, bwd_split;
+  mi355conv::CorrArgs fwd_sp, bwd_sp;
+  mi355conv::PackArgs fwd_sp_pack, bwd_sp_pack;
   // backward data
   int32_t bwd_tile;
   mi355conv::CorrArgs bwd;
@@ -342,6 +403,8 @@ struct conv_desc {
   mi355conv::WgradArgs wg;
   size_t wg_ws;
   size_t wgb_ws;  // filter and bias gradient together (conv_backward_filter_bias)
+  int32_t wg_split;  // its WgradSplitTile, or -1: the fields above
+  mi355conv::WgradSplitArgs wg_sp;
   // backward bias
   mi355conv::BiasGradArgs bg;
   size_t bg_ws;

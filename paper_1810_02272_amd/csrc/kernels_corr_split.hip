@@ -1,0 +1,487 @@
+// Implicit-GEMM correlation on the bf16 matrix instructions with fp32 operands split exactly in three
+// (split_bf16.h), for gathers whose input rows fit LDS: forward and, through the sub-pixel rewriting,
+// backward data.  Same problem and epilogue as corr_kernel (kernels_corr.hip):
+//
+//   D[m][col] = sum_k A[m][k] * in[n, g*Cg + c, a*sh - ph + i*dh, b*sw - pw + j*dw],  col = (n, a, b)
+//
+// The reduction runs as (chunk of 16 channels, tap, channel).  A workgroup keeps the raw input rows that its
+// columns touch -- a zero-padded patch of 16 channels -- in LDS, already split: [half of the chunk][position]
+// [h, m, l][8 channels], 48 bytes per position and half.  An element is loaded and split once per tile and
+// chunk however many taps use it, the MFMA B operand of a tap is a 16-byte read at the column's base
+// plus a uniform offset, and padding, ragged borders and columns past the batch are resolved by the range
+// check of the patch's loads.  48 is an odd multiple of 16: 32 consecutive positions hit every bank evenly.
+//
+// The A operand is packed in fragment order -- [m tile][step][row block][h, m, l][lane][8 k] -- so a wave
+// loads what its lanes feed with coalesced 16-byte loads straight from L2 into registers, one step ahead: A
+// never touches LDS, and the waves of a workgroup meet at a barrier once per chunk (T steps) only.
+//
+// Bound by the matrix unit (busy 74-80 % of the compute units' cycles, at the 1.9 GHz that the chip holds under this load),
+// then by the prologue on small problems.  With the pack kernel, against the fp32 kernels: 57.3 GFLOP (96 -> 256 in two
+// groups, 5x5 at 27x27, batch 128) forward 431 -> 247 us, backward data 459 -> 235; 38.3 GFLOP (256 -> 384, 3x3 at 13x13)
+// 292 -> 174 and 309 -> 200; 6.7 GFLOP (45 -> 77, 3x5 at 51x67, stride 2 x 1) 92 -> 54 and 87 -> 53; 1.3 GFLOP (32 -> 32,
+// 5x5 at 16x16, batch 100) 29 -> 24.  172 and 115 us are the matrix instructions of the first two at 2000 TFLOP/s.
+#include <hip/hip_runtime.h>
+
+#include "corr_epilogue.h"
+#include "device_utils.h"
+#include "internal.h"
+#include "split_bf16.h"
+
+namespace mi355conv {
+
+namespace {
+
+constexpr int kThreads = 256;
+
+template <int MT, int MB, int NB, int WM, int WN>
+struct SplitCfg {
+  static constexpr int BM = WM * MB * MT;
+  static constexpr int BN = WN * NB * MT;
+  static constexpr int BLOCKS = WM * MB;            // row blocks of a tile
+  static constexpr int TPS = MT == 32 ? 1 : 2;      // taps per step: a 16-row instruction takes 32 k values
+  static constexpr uint32_t FRAG = 1024;            // bytes of one operand fragment (64 lanes x 8 bf16)
+  static constexpr uint32_t STEP = BLOCKS * 3 * FRAG;
+  // 64x64 per wave: B operands a step ahead, two waves per SIMD.  The smaller tiles run few matrix instructions
+  // per step and, on small grids, alone on their SIMD: A operands several steps ahead.
+  static constexpr bool BDEEP = MT == 32 && MB * NB >= 4;
+  static constexpr int DEPTH = BDEEP || MT == 16 ? 1 : MB == 3 ? 2 : NB == 2 ? 3 : 8;
+  static constexpr int WAVES = MT == 32 && MB == 1 && NB == 2 ? 3 : 2;
+  static_assert(WM * WN == 4, "four waves per workgroup");
+};
+
+// EPT: patch units (one position x 8 channels) per thread, 2*PSZ <= 256*EPT.
+template <int MT, int MB, int NB, int WM, int WN, int EPT>
+__global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) void corr_split_kernel(const CorrArgs a) {
+  using C = SplitCfg<MT, MB, NB, WM, WN>;
+    using M = Mfma<MT>;
+  constexpr int BM = C::BM, BN = C::BN;
+
+  extern __shared__ __align__(16) float smem[];  // one or two patch stages; the epilogue's tables at the end
+
+  const int t = threadIdx.x;
+  const int lane = t & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wm = wv / WN, wn = wv % WN;
+
+  // column tile fastest: the workgroups of an XCD share one row tile's packed weights in its L2
+  uint32_t lin = xcd_contiguous_block_id();
+  const uint32_t col_tile = lin % (uint32_t)a.col_tiles;
+  lin /= (uint32_t)a.col_tiles;
+  const uint32_t m_tile = lin % (uint32_t)a.m_tiles;
+  lin /= (uint32_t)a.m_tiles;
+  const uint32_t g = lin % (uint32_t)a.G;
+  const uint32_t split = lin / (uint32_t)a.G;
+
+  // ---- geometry of this tile's patch (uniform), as in corr_patch_kernel with any stride and dilation:
+  // segment 0 (image n0) starts at output row a0 and owns R0 patch rows, every later image RS of them.  The
+  // zeros right of a row are those left of the next one, and the zeros below an image those above the next
+  // (share_w, share_h): 5x5 "same" columns at 27x27 take 350 positions instead of 465, which is two
+  // workgroups per compute unit instead of one. ----
+  const int TH = a.THW / a.TW;
+  const uint32_t ext = (uint32_t)((TH - 1) * a.dh + 1);
+  const uint32_t col0 = col_tile * BN;
+  const uint32_t n0 = mdiv(col0, a.mP);
+  const uint32_t a0 = mdiv(col0 - n0 * a.P, a.mPW);
+  const uint32_t R0 = ((uint32_t)a.PH - 1 - a0) * a.sh + ext - a.share_h;
+  const uint32_t RS = ((uint32_t)a.PH - 1) * a.sh + ext - a.share_h;
+  auto patch_row_base = [&](uint32_t n, uint32_t pa) {
+    const uint32_t s = n - n0;
+    return s == 0 ? (pa - a0) * a.sh : R0 + (s - 1) * RS + pa * a.sh;
+  };
+  uint32_t col_last = col0 + BN - 1;
+  if (col_last > (uint32_t)a.ncols - 1) col_last = (uint32_t)a.ncols - 1;
+  uint32_t patch_elems;
+  {
+    const uint32_t n = mdiv(col_last, a.mP);
+    const uint32_t pa = mdiv(col_last - n * a.P, a.mPW);
+    patch_elems = (patch_row_base(n, pa) + ext) * (uint32_t)a.PWID + a.share_w;
+  }
+
+  // ---- per-lane B columns: byte address of (column, its half of the chunk) inside a patch stage ----
+  const uint32_t kgrp = lane / MT;  // which 8 k values of a step this lane feeds
+  const uint32_t half = kgrp & 1;
+  uint32_t lanebase[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    uint32_t col = col0 + (wn * NB + j) * MT + lane % MT;
+    if (col > col_last) col = col_last;  // columns past the edge are never stored: any valid address
+    const uint32_t n = mdiv(col, a.mP);
+    const uint32_t pix = col - n * a.P;
+    const uint32_t pa = mdiv(pix, a.mPW);
+    const uint32_t pb = pix - pa * a.PW;
+    lanebase[j] = 48u * (patch_row_base(n, pa) * (uint32_t)a.PWID + pb * a.sw + half * (uint32_t)a.PSZ);
+  }
+
+  // ---- per-thread patch units: where they come from (relative to channel 0 of the group) ----
+  const __amdgpu_buffer_rsrc_t in_rsrc =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.in), 0, (int)a.in_bytes, 0x00020000);
+  const uint32_t chan_bytes = 4u * (uint32_t)a.IHW;
+  uint32_t psrc[EPT];
+#pragma unroll
+  for (int r = 0; r < EPT; ++r) {
+    const uint32_t u = t + r * kThreads;
+    const uint32_t hf = u >= (uint32_t)a.PSZ ? 1u : 0u;
+    const uint32_t e = u - hf * (uint32_t)a.PSZ;
+    uint32_t src = 0x80000000u;  // beyond the blob (which is at most 2^30 bytes): reads as zero
+    if (e < patch_elems && u < 2u * (uint32_t)a.PSZ) {
+      const uint32_t prow = mdiv(e, a.mPWID);
+      const uint32_t pcol = e - prow * a.PWID;
+      uint32_t n = n0, rin = prow, alo = a0;
+      if (prow >= R0) {
+        const uint32_t s1 = mdiv(prow - R0, a.mRSEG);
+        n = n0 + 1 + s1;
+        rin = prow - R0 - s1 * RS;
+        alo = 0;
+      }
+      const int ih = (int)(alo * a.sh + rin) - a.ph, iw = (int)pcol - a.pw;
+      if ((uint32_t)ih < (uint32_t)a.IH && (uint32_t)iw < (uint32_t)a.IW && n < (uint32_t)a.Nimg)
+        src = 4u * (n * (uint32_t)a.in_img_stride + g * (uint32_t)a.in_grp_stride + (uint32_t)ih * a.IW + iw) +
+              hf * 8u * chan_bytes;
+    }
+    psrc[r] = src;
+  }
+  // Channels past the group's last read the next group's (or, past the blob, zero): their packed weights
+  // are zero.
+  float pr[EPT][8];
+  auto patch_load = [&](int cc) {
+    const uint32_t coff = (uint32_t)(cc * 16) * chan_bytes;
+#pragma unroll
+    for (int r = 0; r < EPT; ++r) {
+      uint32_t src = psrc[r];
+      asm volatile("" : "+v"(src));  // or the compiler keeps eight running addresses per unit in registers
+      src += coff;
+#pragma unroll
+      for (int c8 = 0; c8 < 8; ++c8)
+        pr[r][c8] = __builtin_bit_cast(
+            float, __builtin_amdgcn_raw_buffer_load_b32(in_rsrc, src + c8 * chan_bytes, 0, 0));
+    }
+  };
+  const SplitSel sel;
+  const uint32_t stage_bytes = 96u * (uint32_t)a.PSZ;
+  auto patch_store = [&](uint32_t stage_off) {
+#pragma unroll
+    for (int r = 0; r < EPT; ++r) {
+      const Split8 s = split8(pr[r], sel);
+      const uint32_t u = t + r * kThreads;
+      if (u < 2u * (uint32_t)a.PSZ) {
+        u32x4* dst = reinterpret_cast<u32x4*>(reinterpret_cast<char*>(smem) + (stage_off + 48u * u));
+        dst[0] = s.h;
+        dst[1] = s.m;
+        dst[2] = s.l;
+      }
+      __builtin_amdgcn_sched_barrier(0);  // one unit's terms in registers at a time
+    }
+  };
+
+  // ---- A fragments of this workgroup's steps ----
+  const int T = a.THW, SPC = (T + C::TPS - 1) / C::TPS;  // taps and steps per chunk
+  const int cc_first = (int)split * a.chunks_per_split;  // chunks of 16 channels
+  int cc_end = cc_first + a.chunks_per_split;
+  if (cc_end > a.NS) cc_end = a.NS;
+  const char* Ag = reinterpret_cast<const char*>(a.A) +
+                   ((size_t)(g * a.m_tiles + m_tile) * ((size_t)a.NS * SPC) + (size_t)cc_first * SPC) * C::STEP;
+  const uint32_t a_bytes = (uint32_t)((cc_end - cc_first) * SPC) * C::STEP;
+  const __amdgpu_buffer_rsrc_t a_rsrc =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(Ag), 0, (int)a_bytes, 0x00020000);
+  uint32_t alane[MB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i) alane[i] = 16u * lane + (uint32_t)(wm * MB + i) * 3u * C::FRAG;
+  constexpr int DEPTH = C::DEPTH;
+  u32x4 av[DEPTH][MB][3];
+  auto load_a = [&](int d, uint32_t step_off, int i) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      av[d][i][q] = __builtin_bit_cast(
+          u32x4, __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, alane[i] + q * C::FRAG, (int)step_off, 0));
+  };
+
+  typename M::Acc acc[MB][NB], lo[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < M::NR; ++r) acc[i][j][r] = lo[i][j][r] = 0.f;
+
+  // offset of the step DEPTH ahead; behind the last step it stays there (loaded again, never used)
+  uint32_t a_off = 0;
+  auto a_advance = [&]() {
+    if (a_off + C::STEP < a_bytes) a_off += C::STEP;
+  };
+  patch_load(cc_first);
+#pragma unroll
+  for (int d = 0; d < DEPTH; ++d) {
+#pragma unroll
+    for (int i = 0; i < MB; ++i) load_a(d, a_off, i);
+    a_advance();
+  }
+  patch_store(0);
+  __syncthreads();
+
+  // ---- main loop: one step = one tap (two for the 16-row instruction) of one chunk ----
+  // Position of the step's tap in the patch, advanced tap by tap; behind the last tap it stays (the 16-row
+  // instruction reads it once more when their number is odd, against zero weights).
+  const uint32_t tap_w = 48u * (uint32_t)a.dw, tap_h = 48u * (uint32_t)(a.dh * a.PWID) - tap_w * (uint32_t)(a.TW - 1);
+  uint32_t pos = 0;
+  int tap = 0, tj = 0;
+  auto next_tap = [&]() {
+    if (tap + 1 < T) {
+      ++tap;
+      if (++tj == a.TW) {
+        tj = 0;
+        pos += tap_h;
+      } else {
+        pos += tap_w;
+      }
+    }
+  };
+  auto load_b = [&](u32x4(&bv)[NB][3]) {  // the step's B operands; moves on to the next step
+    uint32_t off = pos;
+    next_tap();
+    if (MT == 16) {  // the upper two k groups take the second tap
+      off = kgrp >= 2 ? pos : off;
+      next_tap();
+    }
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const u32x4* src = reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(smem) + (lanebase[j] + off));
+#pragma unroll
+      for (int q = 0; q < 3; ++q) bv[j][q] = src[q];
+    }
+  };
+  // One step.  A row block's A registers are reloaded with the step DEPTH ahead as soon as its last product
+  // is under way; the scheduling barriers keep the compiler from holding more operands than the registers
+  // have room for.
+  auto run_step = [&](int d, const u32x4(&bv)[NB][3]) {
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      mfma_split<MT, NB>(av[d][i], bv, acc[i], lo[i]);
+      load_a(d, a_off, i);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    a_advance();
+  };
+  const bool two = a.patch_stages == 2;
+  uint32_t stage = 0;
+  int cc = cc_first;
+  auto begin_chunk = [&]() {
+    if (cc + 1 < cc_end) patch_load(cc + 1);
+    pos = stage;
+    tap = tj = 0;
+  };
+  // Two stages: the next chunk's patch goes to the other one, whose last readers passed the last barrier; one
+  // stage: to the only one, once every wave has read it.
+  auto end_chunk = [&]() {
+    if (two)
+      stage = stage ? 0 : stage_bytes;
+    else
+      __syncthreads();
+    if (++cc < cc_end) patch_store(stage);
+    __syncthreads();
+  };
+  if constexpr (C::BDEEP) {  // the next step's B operands are read at the start of a step
+    static_assert(DEPTH == 1, "A one step ahead");
+    u32x4 bX[NB][3], bY[NB][3];
+    while (cc < cc_end) {
+      begin_chunk();
+      load_b(bX);
+      for (int s = 0; s < SPC; s += 2) {
+        load_b(bY);
+        run_step(0, bX);
+        if (s + 1 < SPC) {
+          load_b(bX);
+          run_step(0, bY);
+        }
+      }
+      end_chunk();
+    }
+  } else {
+    u32x4 bv[NB][3];
+    int s = 0;
+    begin_chunk();
+    while (cc < cc_end) {
+#pragma unroll
+      for (int d = 0; d < DEPTH; ++d)
+        if (cc < cc_end) {
+          load_b(bv);
+          run_step(d, bv);
+          if (++s == SPC) {
+            s = 0;
+            end_chunk();
+            begin_chunk();
+          }
+        }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < M::NR; ++r) acc[i][j][r] += lo[i][j][r];
+
+  // ---- sums that are not finite once more with fp32 multiply-adds (the weights put back together exactly):
+  // an infinity or NaN among the operands makes the split's differences NaN where the plain sum may be
+  // infinite.  Every wave for itself. ----
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < M::NR; ++r) bad |= not_finite(acc[i][j][r]);
+  if (__any(bad)) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int r = 0; r < M::NR; ++r) acc[i][j][r] = 0.f;
+      uint32_t col = col0 + (wn * NB + j) * MT + lane % MT;
+      if (col > col_last) col = col_last;
+      const uint32_t n = mdiv(col, a.mP);
+      const uint32_t pix = col - n * a.P;
+      const uint32_t pa = mdiv(pix, a.mPW);
+      const int ih0 = (int)pa * a.sh - a.ph, iw0 = (int)(pix - pa * a.PW) * a.sw - a.pw;
+      const uint32_t base = n * (uint32_t)a.in_img_stride + g * (uint32_t)a.in_grp_stride;
+      for (int c = cc_first * 16; c < cc_end * 16 && c < a.Cg_in; ++c)
+        for (int tp = 0; tp < T; ++tp) {
+          const int ih = ih0 + tp / a.TW * a.dh, iw = iw0 + tp % a.TW * a.dw;
+          const bool in = (uint32_t)ih < (uint32_t)a.IH && (uint32_t)iw < (uint32_t)a.IW;
+          const float b = in ? a.in[base + (uint32_t)c * (uint32_t)a.IHW + (uint32_t)ih * a.IW + iw] : 0.f;
+          const int chunk = c / 16 - cc_first, st = chunk * SPC + tp / C::TPS;
+          const uint32_t grp = (uint32_t)((c % 16) / 8 + 2 * (tp % C::TPS));
+          const char* frag = Ag + (size_t)(uint32_t)st * C::STEP + (uint32_t)(wm * MB) * 3u * C::FRAG + (grp * MT * 16u + (uint32_t)(c % 8) * 2u);
+#pragma unroll
+          for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int r = 0; r < M::NR; ++r) {
+              const char* p = frag + (uint32_t)i * 3u * C::FRAG + (uint32_t)M::row(r, lane) * 16u;
+              const float w = join_bf16(*reinterpret_cast<const uint16_t*>(p),
+                                        *reinterpret_cast<const uint16_t*>(p + C::FRAG),
+                                        *reinterpret_cast<const uint16_t*>(p + 2 * C::FRAG));
+              acc[i][j][r] = fmaf(w, b, acc[i][j][r]);
+            }
+        }
+    }
+  }
+
+  corr_epilogue<MT, MB, NB, BM, BN>(a, smem, acc, m_tile, col_tile, g, wm, wn, split);
+}
+
+// Packs the weights into A fragments: thread = (group, m tile, step, row block, lane), eight k values each.
+template <int MT>
+__global__ __launch_bounds__(256) void pack_split_kernel(const PackArgs a, int blocks, int m_tiles, uint32_t total) {
+  const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
+  if (idx >= total) return;
+  const int lane = idx & 63;
+  uint32_t lin = idx >> 6;
+  const int blk = (int)(lin % (uint32_t)blocks);
+  lin /= (uint32_t)blocks;
+  const int T = a.tTHW, tps = MT == 32 ? 1 : 2, spc = (T + tps - 1) / tps;
+  const uint32_t steps = (uint32_t)(a.split_chunks * spc);
+  const int step = (int)(lin % steps);
+  lin /= steps;
+  const int m_tile = (int)(lin % (uint32_t)m_tiles), g = (int)(lin / (uint32_t)m_tiles);
+  const int m = (m_tile * blocks + blk) * MT + lane % MT, kgrp = lane / MT;
+  const int chunk = step / spc, tap = (step % spc) * tps + (kgrp >> 1);
+  const int c0 = chunk * 16 + (kgrp & 1) * 8;
+  // the element of channel c0 and the stride to the next channel; i < 0: no such tap
+  size_t src = 0, stride = 0;
+  int limit = 0;  // channels of the reduction
+  if (m < a.Mrows && tap < T) {
+    if (a.mode == 0) {
+      limit = a.Cg;
+      src = ((size_t)g * a.Kg + m) * ((size_t)a.Cg * T) + (size_t)c0 * T + tap;
+      stride = T;
+    } else {
+      const int qh = a.Qh - 1 - tap / a.Qw, qw = a.Qw - 1 - tap % a.Qw;
+      const int nv = a.nvh * a.nvw, c = m / nv, mr = m % nv;
+      int rh = mr / a.nvw, rw = mr % a.nvw;
+      if (a.tab_h) rh = a.phase_h[rh];
+      if (a.tab_w) rw = a.phase_w[rw];
+      const int th = a.sh * a.eh * qh + rh, tw = a.sw * a.ew * qw + rw;
+      const int i = th / a.dh, j = tw / a.dw;
+      if (i * a.dh == th && j * a.dw == tw && i < a.kh && j < a.kw) {
+        limit = a.Kg;
+        stride = (size_t)a.Cg * a.kh * a.kw;
+        src = ((size_t)g * a.Kg + c0) * stride + ((size_t)c * a.kh + i) * a.kw + j;
+      }
+    }
+  }
+  uint16_t out[3][8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const float v = c0 + e < limit ? a.w[src + e * stride] : 0.f;
+    split1(v, out[0][e], out[1][e], out[2][e]);
+  }
+  char* dst = reinterpret_cast<char*>(a.A) + (size_t)(idx >> 6) * 3072u + 16u * lane;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    u32x4 v;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) v[p] = (uint32_t)out[q][2 * p] | (uint32_t)out[q][2 * p + 1] << 16;
+    *reinterpret_cast<u32x4*>(dst + q * 1024) = v;
+  }
+}
+
+template <int MT, int MB, int NB, int WM, int WN, int EPT>
+int launch_split_e(const CorrArgs& a, hipStream_t s) {
+  using C = SplitCfg<MT, MB, NB, WM, WN>;
+  const size_t tables = 16 * (C::BM + C::BN), patch = 96 * (size_t)a.PSZ * a.patch_stages;
+  const size_t lds = patch > tables ? patch : tables;
+  static LdsOptIn opt_in;  // more than 64 KB of LDS needs an explicit opt-in, once per process
+  if (const int e = lds_opt_in(opt_in, &corr_split_kernel<MT, MB, NB, WM, WN, EPT>, 160 * 1024)) return e;
+  const uint32_t blocks = (uint32_t)a.G * a.m_tiles * a.col_tiles * a.ksplit;
+  hipLaunchKernelGGL((corr_split_kernel<MT, MB, NB, WM, WN, EPT>), dim3(blocks), dim3(kThreads), lds, s, a);
+  return (int)hipGetLastError();
+}
+
+template <int MT, int MB, int NB, int WM, int WN>
+int launch_split_t(const CorrArgs& a, hipStream_t s) {
+  constexpr int BN = SplitCfg<MT, MB, NB, WM, WN>::BN;
+  if constexpr (BN <= 128)
+    if (split_patch_units(a.PSZ, BN) == 2) return launch_split_e<MT, MB, NB, WM, WN, 2>(a, s);
+  if (split_patch_units(a.PSZ, BN) == 3) return launch_split_e<MT, MB, NB, WM, WN, 3>(a, s);
+  return launch_split_e<MT, MB, NB, WM, WN, 4>(a, s);
+}
+
+}  // namespace
+
+void split_tile_shape(int32_t tile, int32_t* bm, int32_t* bn, int32_t* mt) {
+  static const int32_t shapes[SPLIT_TILE_COUNT][3] = {
+      {128, 128, 32}, {64, 256, 32}, {64, 128, 32}, {96, 128, 32}, {32, 256, 32}, {32, 128, 32}, {48, 256, 16}};
+  *bm = shapes[tile][0];
+  *bn = shapes[tile][1];
+  *mt = shapes[tile][2];
+}
+
+int launch_corr_split(int32_t tile, const CorrArgs& a, void* stream) {
+  hipStream_t s = (hipStream_t)stream;
+  switch (tile) {  //                             MT MB NB WM WN
+    case SPLIT_128x128: return launch_split_t<32, 2, 2, 2, 2>(a, s);
+    case SPLIT_64x256:  return launch_split_t<32, 2, 2, 1, 4>(a, s);
+    case SPLIT_64x128:  return launch_split_t<32, 1, 2, 2, 2>(a, s);
+    case SPLIT_96x128:  return launch_split_t<32, 3, 1, 1, 4>(a, s);
+    case SPLIT_32x256:  return launch_split_t<32, 1, 2, 1, 4>(a, s);
+    case SPLIT_32x128:  return launch_split_t<32, 1, 1, 1, 4>(a, s);
+    case SPLIT_48x256:  return launch_split_t<16, 3, 4, 1, 4>(a, s);
+    default: return (int)hipErrorInvalidValue;
+  }
+}
+
+int launch_pack_split(int32_t tile, const PackArgs& a, void* stream) {
+  int32_t bm, bn, mt;
+  split_tile_shape(tile, &bm, &bn, &mt);
+  const int tps = mt == 32 ? 1 : 2, spc = (a.tTHW + tps - 1) / tps, blocks = bm / mt;
+  const int m_tiles = (a.Mrows + bm - 1) / bm;
+  const uint32_t total = (uint32_t)a.G * m_tiles * (uint32_t)(a.split_chunks * spc) * blocks * 64u;
+  const dim3 grid((total + 255) / 256);
+  if (mt == 32)
+    hipLaunchKernelGGL(pack_split_kernel<32>, grid, dim3(256), 0, (hipStream_t)stream, a, blocks, m_tiles, total);
+  else
+    hipLaunchKernelGGL(pack_split_kernel<16>, grid, dim3(256), 0, (hipStream_t)stream, a, blocks, m_tiles, total);
+  return (int)hipGetLastError();
+}
+
+}  // namespace mi355conv

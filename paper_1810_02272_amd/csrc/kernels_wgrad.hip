@@ -446,6 +446,18 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs a) {
     Vec out, old;
     float* const dst = (second ? a.dst2 : a.dst) + i;
     const bool first = !second;
+    if (a.taps > 1 && first) {  // [row][tap][channel] -> [row][channel][tap]
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        const uint32_t row = mdiv((uint32_t)(i + e), a.mRow), rem = (uint32_t)(i + e) - row * (uint32_t)(a.taps * a.tap_channels);
+        const uint32_t tap = mdiv(rem, a.mTapChannels), c = rem - tap * (uint32_t)a.tap_channels;
+        float* const to = a.dst + (size_t)(row * (uint32_t)a.tap_channels + c) * a.taps + tap;
+        float s = (quarter[0][lane].v[e] + quarter[1][lane].v[e]) + (quarter[2][lane].v[e] + quarter[3][lane].v[e]);
+        if (a.beta != 0.f) s += a.beta * *to;
+        *to = s;
+      }
+      return;
+    }
     if (a.beta != 0.f) old = *reinterpret_cast<const Vec*>(dst);
 #pragma unroll
     for (int e = 0; e < V; ++e) {

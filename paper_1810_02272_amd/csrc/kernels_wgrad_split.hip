@@ -1,0 +1,402 @@
+// Backward filter on the bf16 matrix instructions with fp32 operands split exactly in three (split_bf16.h):
+//   dW_g[k][(c,i,j)] = sum over pixels (n,oh,ow) of dy[n, g*Kg + k, oh, ow] * x[n, g*Cg + c, oh*sh - ph + i*dh, ...]
+// Same problem, split over the pixels and partial layout as wgrad_kernel (kernels_wgrad.hip), for layers whose input
+// rows fit LDS.
+//
+// A workgroup takes 16 input channels and up to WN*NB taps of them: a block of 16 columns is one tap of the 16
+// channels.  The reduction runs over runs of eight pixels of one image (an image's last run is filled up with
+// zeros of dy), four runs = 32 pixels to a step, four steps to a chunk.  Per chunk the raw input rows its pixels
+// touch are loaded, split and kept in LDS as [position][h, m, l][16 channels], 96 bytes per position; the matrix
+// operand wants eight consecutive pixels of one channel per lane, which is what the transposing LDS read delivers:
+// 16 lanes name four positions x 16 channels and each receives its channel at the four positions.  A position is
+// split once and read by every tap.  dy runs are contiguous in memory in the order the operand wants: every
+// wave loads and splits the runs of its own rows straight into registers, a step ahead.
+//
+// Bound by the matrix unit: 57.3 GFLOP (96 -> 256 in two groups, 5x5 at 27x27, batch 128) 494 -> 300 us, 38.3 GFLOP
+// (256 -> 384, 3x3 at 13x13) 327 -> 200, 6.7 GFLOP (45 -> 77, 3x5 at 51x67, stride 2 x 1) 95 -> 67, 1.3 GFLOP (32 -> 32,
+// 5x5 at 16x16, batch 100) 35 -> 23, with the reduce kernel, against wgrad_kernel; 172 and 115 us are the matrix
+// instructions of the first two at the 2000 TFLOP/s that a loop of them sustains.
+#include <hip/hip_runtime.h>
+
+#include "device_utils.h"
+#include "internal.h"
+#include "split_bf16.h"
+
+namespace mi355conv {
+
+namespace {
+
+constexpr int kThreads = 256;
+constexpr int kStepRuns = 4, kChunkSteps = 4, kChunkRuns = kStepRuns * kChunkSteps, kChunkPix = 8 * kChunkRuns;
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4* LdsTrPtr;
+typedef __attribute__((address_space(3))) char* LdsChar;
+
+// MB x NB blocks of 16 x 16 per wave; EPT: patch units (position x 8 channels) per thread.
+template <int WM, int WN, int MB, int NB, int EPT>
+__global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSplitArgs a) {
+  using M = Mfma<16>;
+  constexpr int BM = WM * MB * 16;
+  static_assert(WM * WN == 4, "four waves per workgroup");
+
+  extern __shared__ __align__(16) char smem[];  // position tables of two chunks, then one or two patch stages
+
+  const int t = threadIdx.x;
+  const int lane = t & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wm = wv / WN, wn = wv % WN;
+
+  uint32_t lin = xcd_contiguous_block_id();
+  const uint32_t m_tile = lin % (uint32_t)a.m_tiles;
+  lin /= (uint32_t)a.m_tiles;
+  const uint32_t n_tile = lin % (uint32_t)a.n_tiles;
+  lin /= (uint32_t)a.n_tiles;
+  const uint32_t split = lin % (uint32_t)a.S;
+  const uint32_t g = lin / (uint32_t)a.S;
+  const int c16 = (int)(n_tile / (uint32_t)a.tap_tiles);
+  const int tap0 = (int)(n_tile % (uint32_t)a.tap_tiles) * (WN * NB) + wn * NB;  // this wave's first tap
+
+  const int chunk_first = (int)split * a.chunks_per_split;
+  int chunk_end = chunk_first + a.chunks_per_split;
+  if (chunk_end > a.chunks) chunk_end = a.chunks;
+
+  // ---- x patch of a chunk ----
+  const __amdgpu_buffer_rsrc_t x_rsrc =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.x), 0, (int)a.x_bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t dy_rsrc =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.dy), 0, (int)a.dy_bytes, 0x00020000);
+  const uint32_t chan_bytes = 4u * (uint32_t)(a.H * a.W);
+  const uint32_t chan0 = (g * (uint32_t)a.Cg + (uint32_t)c16 * 16u) * chan_bytes;
+  const uint32_t stage_bytes = 96u * (uint32_t)a.PSZ;
+  constexpr uint32_t kTables = 2u * 4u * kChunkPix;
+  // (image, first pixel) of run q
+  auto run_pos = [&](uint32_t q, uint32_t& n, uint32_t& p) {
+    n = mdiv(q, a.mRuns);
+    p = (q - n * (uint32_t)a.runs) * 8u;
+  };
+  float pr[EPT][8];
+  uint32_t entry = 0;  // this thread's entry of the chunk's position table (threads below kChunkPix)
+  // The chunk's first segment starts at output row a0 of image n0; its patch rows and those of later images are
+  // counted as in corr_split_kernel.
+  auto patch_load = [&](int chunk) {
+    uint32_t q0 = (uint32_t)chunk * kChunkRuns, n0, p0;
+    run_pos(q0, n0, p0);
+    const uint32_t a0 = mdiv(p0, a.mPW);
+    const uint32_t R0 = ((uint32_t)a.PH - 1 - a0) * a.sh + a.ext - a.share_h;
+    const uint32_t RS = ((uint32_t)a.PH - 1) * a.sh + a.ext - a.share_h;
+    {
+      uint32_t n, p;
+      run_pos(q0 + (uint32_t)(t >> 3) % kChunkRuns, n, p);
+      p += t & 7;
+      if (p > (uint32_t)a.P - 1) p = (uint32_t)a.P - 1;  // filled-up run: any position, dy is zero
+      if (n > (uint32_t)a.N - 1) n = n0, p = p0;         // past the last image: the same
+      const uint32_t pa = mdiv(p, a.mPW), pb = p - pa * a.PW;
+      const uint32_t s = n - n0;
+      const uint32_t row = s == 0 ? (pa - a0) * a.sh : R0 + (s - 1) * RS + pa * a.sh;
+      entry = 96u * (row * (uint32_t)a.PWID + pb * a.sw);
+    }
+#pragma unroll
+    for (int r = 0; r < EPT; ++r) {
+      const uint32_t u = t + r * kThreads;
+      const uint32_t hf = u >= (uint32_t)a.PSZ ? 1u : 0u;
+      const uint32_t e = u - hf * (uint32_t)a.PSZ;
+      const uint32_t prow = mdiv(e, a.mPWID);
+      const uint32_t pcol = e - prow * a.PWID;
+      uint32_t n = n0, rin = prow, alo = a0;
+      if (prow >= R0) {
+        const uint32_t s1 = mdiv(prow - R0, a.mRSEG);
+        n = n0 + 1 + s1;
+        rin = prow - R0 - s1 * RS;
+        alo = 0;
+      }
+      const int ih = (int)(alo * a.sh + rin) - a.ph, iw = (int)pcol - a.pw;
+      uint32_t src = 0x80000000u;  // beyond the blob (which is at most 2^30 bytes): reads as zero
+      if ((uint32_t)ih < (uint32_t)a.H && (uint32_t)iw < (uint32_t)a.W && n < (uint32_t)a.N && u < 2u * (uint32_t)a.PSZ)
+        src = 4u * (n * (uint32_t)(a.C * a.H * a.W) + (uint32_t)ih * a.W + iw) + chan0 + hf * 8u * chan_bytes;
+      // channels past the group's last read the next group's (or, past the blob, zero): columns never stored
+#pragma unroll
+      for (int c8 = 0; c8 < 8; ++c8)
+        pr[r][c8] = __builtin_bit_cast(
+            float, __builtin_amdgcn_raw_buffer_load_b32(x_rsrc, src + c8 * chan_bytes, 0, 0));
+    }
+  };
+  const SplitSel sel;
+  auto patch_store = [&](uint32_t table, uint32_t stage) {
+    if (t < kChunkPix) *reinterpret_cast<uint32_t*>(smem + table + 4u * t) = entry;
+#pragma unroll
+    for (int r = 0; r < EPT; ++r) {
+      const Split8 s = split8(pr[r], sel);
+      const uint32_t u = t + r * kThreads;
+      if (u < 2u * (uint32_t)a.PSZ) {
+        const uint32_t hf = u >= (uint32_t)a.PSZ ? 1u : 0u;
+        u32x4* dst = reinterpret_cast<u32x4*>(smem + kTables + stage + 96u * (u - hf * (uint32_t)a.PSZ) + 16u * hf);
+        dst[0] = s.h;
+        dst[2] = s.m;
+        dst[4] = s.l;
+      }
+      __builtin_amdgcn_sched_barrier(0);  // one unit's terms in registers at a time
+    }
+  };
+
+  // ---- dy: lane l takes run l/16 of a step and row l%16 of each of its wave's row blocks ----
+  uint32_t arow[MB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i) {
+    uint32_t m = m_tile * BM + (uint32_t)((wm * MB + i) * 16 + (lane & 15));
+    if (m > (uint32_t)a.Kg - 1) m = (uint32_t)a.Kg - 1;  // rows past the edge are never stored
+    arow[i] = 4u * (g * (uint32_t)a.Kg + m) * (uint32_t)a.P;
+  }
+  float raw[MB][8];
+  int valid = 0;  // real pixels of the run in `raw`
+  const uint32_t run_end = (uint32_t)a.N * (uint32_t)a.runs;
+  auto load_dy = [&](int step) {  // step counted from chunk 0
+    const uint32_t q = (uint32_t)step * kStepRuns + (uint32_t)(lane >> 4);
+    uint32_t n, p;
+    run_pos(q, n, p);
+    valid = q < run_end ? a.P - (int)p : 0;
+    const uint32_t base = q < run_end ? 4u * (n * (uint32_t)(a.Ktot * a.P) + p) : 0x80000000u;
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      const uint32_t off = base + arow[i];
+      const u32x4 v0 = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(dy_rsrc, off, 0, 0));
+      const u32x4 v1 = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(dy_rsrc, off + 16u, 0, 0));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        raw[i][e] = __builtin_bit_cast(float, (uint32_t)v0[e]);
+        raw[i][4 + e] = __builtin_bit_cast(float, (uint32_t)v1[e]);
+      }
+    }
+  };
+
+  M::Acc acc[MB][NB], lo[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < M::NR; ++r) acc[i][j][r] = lo[i][j][r] = 0.f;
+
+  // uniform byte offset of each of this wave's taps inside the patch
+  uint32_t tap_off[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    int tp = tap0 + j;
+    if (tp > a.khw - 1) tp = a.khw - 1;  // blocks past the last tap are never stored
+    const int ti = tp / a.kw, tj = tp - ti * a.kw;
+    tap_off[j] = (uint32_t)__builtin_amdgcn_readfirstlane(96 * (ti * a.dh * a.PWID + tj * a.dw));
+  }
+
+  // ---- bias gradient from the same read of dy: every wave sums its rows over the chunks ch with
+  // ch % (n_tiles*WN) == n_tile*WN + wn (see wgrad_kernel) ----
+  const bool row_sums = a.bias_part != nullptr;
+  const uint32_t turn = (uint32_t)(n_tile * WN + wn), turns = (uint32_t)(a.n_tiles * WN);
+  float bsum[MB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i) bsum[i] = 0.f;
+
+  const bool two = a.patch_stages == 2;
+  if (chunk_first < chunk_end) {
+    patch_load(chunk_first);
+    load_dy(chunk_first * kChunkSteps);
+    patch_store(0, 0);
+  }
+  __syncthreads();
+
+  const int last_step = chunk_end * kChunkSteps - 1;
+  uint32_t stage = 0, table = 0;
+  for (int ch = chunk_first; ch < chunk_end; ++ch) {
+    const bool more = ch + 1 < chunk_end;
+    if (more) patch_load(ch + 1);
+    const bool my_turn = row_sums && (uint32_t)(ch - chunk_first) % turns == turn;
+#pragma unroll 1
+    for (int s = 0; s < kChunkSteps; ++s) {
+      // this step's dy operands: masked, summed, split; then the next step's loads
+      u32x4 av[MB][3];
+#pragma unroll
+      for (int i = 0; i < MB; ++i) {
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = e < valid ? raw[i][e] : 0.f;
+        if (my_turn) bsum[i] += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+        const Split8 sp = split8(v, sel);
+        av[i][0] = sp.h;
+        av[i][1] = sp.m;
+        av[i][2] = sp.l;
+      }
+      const int step = ch * kChunkSteps + s;
+      load_dy(step < last_step ? step + 1 : step);
+      // positions of the two quads of pixels this lane names in the transposing reads, with its channel quad
+      const uint32_t px = (uint32_t)s * 32u + (uint32_t)(lane >> 4) * 8u + (uint32_t)((lane & 15) >> 2);
+      const uint32_t fix = kTables + stage + 8u * (uint32_t)(lane & 3);
+      const uint32_t b0 = *reinterpret_cast<const uint32_t*>(smem + table + 4u * px) + fix;
+      const uint32_t b1 = *reinterpret_cast<const uint32_t*>(smem + table + 4u * px + 16u) + fix;
+      u32x4 bv[2][3];
+      auto load_b = [&](int j, u32x4(&b)[3]) {
+        const uint32_t o0 = b0 + tap_off[j], o1 = b1 + tap_off[j];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          const s16x4 x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsTrPtr)((LdsChar)smem + o0 + 32 * q));
+          const s16x4 x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsTrPtr)((LdsChar)smem + o1 + 32 * q));
+          const uint2 y0 = __builtin_bit_cast(uint2, x0), y1 = __builtin_bit_cast(uint2, x1);
+          b[q][0] = y0.x;
+          b[q][1] = y0.y;
+          b[q][2] = y1.x;
+          b[q][3] = y1.y;
+        }
+      };
+      load_b(0, bv[0]);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        if (j + 1 < NB) load_b(j + 1, bv[(j + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);  // the next block's reads before this block's products, not behind them
+        constexpr int pa[5] = {2, 0, 1, 1, 0}, pb[5] = {0, 2, 1, 0, 1};
+#pragma unroll
+        for (int q = 0; q < 5; ++q)
+#pragma unroll
+          for (int i = 0; i < MB; ++i) mfma_bf16<16>(av[i][pa[q]], bv[j & 1][pb[q]], lo[i][j]);
+#pragma unroll
+        for (int i = 0; i < MB; ++i) mfma_bf16<16>(av[i][0], bv[j & 1][0], acc[i][j]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    table ^= 4u * kChunkPix;
+    if (two)
+      stage = stage ? 0 : stage_bytes;
+    else
+      __syncthreads();
+    if (more) patch_store(table, stage);
+    __syncthreads();
+  }
+
+  if (row_sums) {  // uniform over the grid; LDS is free after the loop's last barrier
+    float* red = reinterpret_cast<float*>(smem);  // [WN][BM]
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      float v = bsum[i];
+      v += __shfl_xor(v, 16);
+      v += __shfl_xor(v, 32);
+      if (lane < 16) red[wn * BM + (wm * MB + i) * 16 + lane] = v;
+    }
+    __syncthreads();
+    for (int row = t; row < BM; row += kThreads) {
+      float total = red[row];
+#pragma unroll
+      for (int v = 1; v < WN; ++v) total += red[v * BM + row];
+      const uint32_t k = m_tile * BM + (uint32_t)row;
+      if (k < (uint32_t)a.Kg) a.bias_part[((size_t)split * a.n_tiles + n_tile) * a.Ktot + g * a.Kg + k] = total;
+    }
+  }
+
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < M::NR; ++r) acc[i][j][r] += lo[i][j][r];
+
+  const int c = c16 * 16 + (lane & 15);
+  // ---- sums that are not finite once more with fp32 multiply-adds (see corr_split_kernel) ----
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < M::NR; ++r) bad |= not_finite(acc[i][j][r]);
+  if (__any(bad)) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int r = 0; r < M::NR; ++r) acc[i][j][r] = 0.f;
+      const int tp = tap0 + j;
+      const int ti = tp / a.kw, tj = tp - ti * a.kw;
+      if (tp < a.khw) {
+        for (uint32_t q = (uint32_t)chunk_first * kChunkRuns; q < (uint32_t)chunk_end * kChunkRuns && q < run_end; ++q) {
+          uint32_t n, p;
+          run_pos(q, n, p);
+          for (int e = 0; e < 8 && (int)p + e < a.P; ++e) {
+            const uint32_t pix = p + e, pa = mdiv(pix, a.mPW), pb = pix - pa * a.PW;
+            const int ih = (int)pa * a.sh - a.ph + ti * a.dh, iw = (int)pb * a.sw - a.pw + tj * a.dw;
+            const bool in = c < a.Cg && (uint32_t)ih < (uint32_t)a.H && (uint32_t)iw < (uint32_t)a.W;
+            const float xv = in ? a.x[((size_t)n * a.C + g * a.Cg + c) * (size_t)(a.H * a.W) + (size_t)ih * a.W + iw] : 0.f;
+#pragma unroll
+            for (int i = 0; i < MB; ++i)
+#pragma unroll
+              for (int r = 0; r < M::NR; ++r) {
+                uint32_t m = m_tile * BM + (uint32_t)((wm * MB + i) * 16 + M::row(r, lane));
+                if (m > (uint32_t)a.Kg - 1) m = (uint32_t)a.Kg - 1;
+                acc[i][j][r] = fmaf(a.dy[((size_t)n * a.Ktot + g * a.Kg + m) * (size_t)a.P + pix], xv, acc[i][j][r]);
+              }
+          }
+        }
+      }
+    }
+  }
+
+  // ---- partial block -> workspace [split][g][k][tap][c], the order in which the lanes of a store are neighbours (16
+  // channels, 64 bytes; as [k][c][tap] every lane of a store opened a line of its own, and a 32-row layer with 20 MB
+  // of partials took 42 us instead of 20); the reduce kernel puts them into the weight blob's order.  Rows, channels and
+  // taps past the edge carry offsets beyond the slice (at most 2^30 bytes): the range check of the store drops them. ----
+  float* dst = a.part + (size_t)split * a.part_stride + (size_t)g * ((size_t)a.Kg * a.Kred);
+  const __amdgpu_buffer_rsrc_t out_rsrc =
+      __builtin_amdgcn_make_buffer_rsrc(dst, 0, (int)(4u * (uint32_t)a.Kg * (uint32_t)a.Kred), 0x00020000);
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int r = 0; r < M::NR; ++r) {
+      const uint32_t k = m_tile * BM + (uint32_t)((wm * MB + i) * 16 + M::row(r, lane));
+      const uint32_t ro = k < (uint32_t)a.Kg && c < a.Cg ? 4u * (k * (uint32_t)a.Kred + (uint32_t)c) : 0x80000000u;
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const uint32_t co = tap0 + j < a.khw ? 4u * (uint32_t)((tap0 + j) * a.Cg) : 0x40000000u;
+        const float v = acc[i][j][r];
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), out_rsrc, ro + co, 0, 0);
+      }
+    }
+}
+
+template <int WM, int WN, int MB, int NB, int EPT>
+int launch_e(const WgradSplitArgs& a, hipStream_t s) {
+  const size_t lds = 2 * 4 * kChunkPix + 96 * (size_t)a.PSZ * a.patch_stages;
+  const size_t red = 4 * WN * WM * MB * 16;
+  static LdsOptIn opt_in;  // more than 64 KB of LDS needs an explicit opt-in, once per process
+  if (const int e = lds_opt_in(opt_in, &wgrad_split_kernel<WM, WN, MB, NB, EPT>, 160 * 1024)) return e;
+  const uint32_t blocks = (uint32_t)a.G * a.S * a.m_tiles * a.n_tiles;
+  hipLaunchKernelGGL((wgrad_split_kernel<WM, WN, MB, NB, EPT>), dim3(blocks), dim3(kThreads), lds > red ? lds : red, s, a);
+  return (int)hipGetLastError();
+}
+
+template <int WM, int WN, int MB, int NB>
+int launch_t(const WgradSplitArgs& a, hipStream_t s) {
+  if (split_patch_units(a.PSZ) == 2) return launch_e<WM, WN, MB, NB, 2>(a, s);
+  if (split_patch_units(a.PSZ) == 3) return launch_e<WM, WN, MB, NB, 3>(a, s);
+  return launch_e<WM, WN, MB, NB, 4>(a, s);
+}
+
+}  // namespace
+
+void wgrad_split_shape(int32_t tile, int32_t* rows, int32_t* taps) {
+  static const int32_t shapes[WSPLIT_TILE_COUNT][2] = {{128, 9}, {128, 8}, {64, 16}, {32, 28}, {32, 12}, {96, 8}};
+  *rows = shapes[tile][0];
+  *taps = shapes[tile][1];
+}
+
+int32_t wgrad_split_chunk_runs() { return kChunkRuns; }
+
+int launch_wgrad_split(int32_t tile, const WgradSplitArgs& a, void* stream) {
+  hipStream_t s = (hipStream_t)stream;
+  switch (tile) {  //                     WM WN MB NB
+    case WSPLIT_128x9: return launch_t<4, 1, 2, 9>(a, s);
+    case WSPLIT_128x8: return launch_t<4, 1, 2, 8>(a, s);
+    case WSPLIT_64x16: return launch_t<2, 2, 2, 8>(a, s);
+    case WSPLIT_32x28: return launch_t<1, 4, 2, 7>(a, s);
+    case WSPLIT_32x12: return launch_t<1, 4, 2, 3>(a, s);
+    case WSPLIT_96x8:  return launch_t<2, 2, 3, 4>(a, s);
+    default: return (int)hipErrorInvalidValue;
+  }
+}
+
+}  // namespace mi355conv

@@ -1,0 +1,123 @@
+// Exact three-way bf16 split of fp32 operands for the bf16 matrix instructions of gfx950.
+//
+// A float a (24 significant bits) is h + m + l with h = bf16(a), m = bf16(a - h), l = a - h - m, each
+// rounded to nearest: both differences are exact, and l has at most eight significant bits left, so the
+// three terms hold every bit of a.  A product a*b is taken as the six partial products down to 2^-18 of
+// it -- hh, hm, mh, mm, hl, lh -- each exact, summed in fp32 by the matrix unit; what is left out (ml, lm,
+// ll) is below 2^-24 |ab|, 2^-28 on average and of either sign.  Six bf16 instructions of 16 reduction
+// indices take 6 x 32 cycles where the fp32 instructions they replace take 512: a register-only loop of
+// them sustains 2002 TFLOP/s = 334 TFLOP/s of fp32 products, against 143 for the 32x32x2 fp32 instruction.
+//
+// The bf16 matrix instructions keep denormals, so an operand loses bits only where l falls below the
+// smallest bf16 denormal, i.e. for |a| < 2^-109, by at most 2^-134.  An infinity, a NaN or a value that
+// rounds to a bf16 infinity makes the differences NaN and with them every sum it enters; the kernels
+// look for non-finite sums at their end and compute those again with fp32 multiply-adds.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "device_utils.h"
+
+namespace mi355conv {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+struct Split8 {  // eight consecutive reduction indices of one row or column
+  u32x4 h, m, l;
+};
+
+// The two selectors of the split: dot2(pair, sel, x) = x - (low or high half of the pair).  They live in
+// scalar registers: as a literal the low one is taken for the fp32 constant -1.0 and picks the high half.
+struct SplitSel {
+  uint32_t lo, hi;
+  __device__ __forceinline__ SplitSel() {
+    asm("s_mov_b32 %0, 0xbf80" : "=s"(lo));
+    asm("s_mov_b32 %0, 0xbf800000" : "=s"(hi));
+  }
+};
+
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  bf16x2 v;
+  v[0] = (__bf16)a;
+  v[1] = (__bf16)b;
+  return __builtin_bit_cast(uint32_t, v);
+}
+
+__device__ __forceinline__ float minus_half(uint32_t pair, uint32_t sel, float x) {
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), __builtin_bit_cast(bf16x2, sel), x, false);
+}
+
+// Seven vector instructions per pair.
+__device__ __forceinline__ Split8 split8(const float (&v)[8], const SplitSel& s) {
+  Split8 r;
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const float a = v[2 * p], b = v[2 * p + 1];
+    const uint32_t h = pack_bf16(a, b);
+    const float ra = minus_half(h, s.lo, a), rb = minus_half(h, s.hi, b);
+    const uint32_t m = pack_bf16(ra, rb);
+    r.h[p] = h;
+    r.m[p] = m;
+    r.l[p] = pack_bf16(minus_half(m, s.lo, ra), minus_half(m, s.hi, rb));
+  }
+  return r;
+}
+
+// The same for the pack kernels, where a finite value that would round to a bf16 infinity is truncated
+// instead and an infinity or NaN keeps m = l = 0: h + m + l is the weight again, whatever it is.
+__device__ __forceinline__ void split1(float a, uint16_t& h, uint16_t& m, uint16_t& l) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, a), mag = u & 0x7fffffffu;
+  m = l = 0;
+  if (mag >= 0x7f800000u) {
+    h = (uint16_t)((u >> 16) | (mag > 0x7f800000u ? 0x40u : 0u));
+    return;
+  }
+  auto rne = [](float x) { return __builtin_bit_cast(uint16_t, (__bf16)x); };
+  auto up = [](uint16_t x) { return __builtin_bit_cast(float, (uint32_t)x << 16); };
+  h = mag >= 0x7f7f8000u ? (uint16_t)(u >> 16) : rne(a);
+  const float r = a - up(h);
+  m = rne(r);
+  l = rne(r - up(m));
+}
+
+__device__ __forceinline__ float join_bf16(uint16_t h, uint16_t m, uint16_t l) {
+  auto up = [](uint16_t x) { return __builtin_bit_cast(float, (uint32_t)x << 16); };
+  return (up(h) + up(m)) + up(l);
+}
+
+// bf16 matrix instructions with the accumulator layout of the fp32 ones (Mfma<MT> in device_utils.h):
+//   MT = 32: 16 k-values, lane l feeds A[l%32][8*(l/32) .. +7] and B[8*(l/32) .. +7][l%32]
+//   MT = 16: 32 k-values, lane l feeds A[l%16][8*(l/16) .. +7] and B[8*(l/16) .. +7][l%16]
+template <int MT>
+__device__ __forceinline__ void mfma_bf16(const u32x4& a, const u32x4& b, typename Mfma<MT>::Acc& c) {
+  const bf16x8 av = __builtin_bit_cast(bf16x8, a), bv = __builtin_bit_cast(bf16x8, b);
+  if constexpr (MT == 32)
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, c, 0, 0, 0);
+  else
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, c, 0, 0, 0);
+}
+
+// hi[j] += h h, lo[j] += the five smaller partial products, of one row block and NB column blocks.  Two
+// accumulators because every instruction rounds the sum it adds to: the large one is rounded once per 16
+// (MT = 32) or 32 reduction indices, where the fp32 instructions round eight times, and what the small
+// one is rounded by is 2^-8 of that -- with all six products in one accumulator the sums of a 2304-long
+// reduction were 7 % further from exact than the fp32 instructions' (rms 8.8e-7 against 8.2e-7).
+template <int MT, int NB>
+__device__ __forceinline__ void mfma_split(const u32x4 (&a)[3], const u32x4 (&b)[NB][3],
+                                           typename Mfma<MT>::Acc (&hi)[NB], typename Mfma<MT>::Acc (&lo)[NB]) {
+  constexpr int pa[5] = {2, 0, 1, 1, 0}, pb[5] = {0, 2, 1, 0, 1};
+#pragma unroll
+  for (int q = 0; q < 5; ++q)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) mfma_bf16<MT>(a[pa[q]], b[j][pb[q]], lo[j]);
+#pragma unroll
+  for (int j = 0; j < NB; ++j) mfma_bf16<MT>(a[0], b[j][0], hi[j]);
+}
+
+__device__ __forceinline__ bool not_finite(float v) {
+  return (__builtin_bit_cast(uint32_t, v) & 0x7f800000u) == 0x7f800000u;
+}
+
+}  // namespace mi355conv

@@ -158,6 +158,7 @@ VARIANT_CASES = [
     # the 64-row filter-gradient tile is kept for grids of 256 workgroups or more (48 outputs, 4 column tiles, 86 splits)
     (P(6, 48, 66, 66, 48, 3, 3), "bwd_filter", "wgrad_m32_64x128x32[m0"),
     (P(6, 48, 64, 64, 48, 3, 3, 1, 1, 2, 2, 2, 2), "bwd_filter", "wgrad_m32_64x128x32[m1"),
+    (P(6, 48, 64, 66, 48, 3, 3, 1, 1, 1, 1), "bwd_filter", "wgrad_m32_64x128x32[m2"),
     # at most four GEMM rows per group: corr_thin_kernel, rows x bounds modes (several 64-column workgroups each)
     (P(8, 1, 13, 14, 2, 1, 1, 2, 2), "fwd", "corr_thin_r2[m0"),
     (P(3, 1, 24, 25, 2, 6, 6, 2, 2, 1, 1, 2, 2), "fwd", "corr_thin_r2[m1"),
@@ -187,6 +188,31 @@ VARIANT_CASES = [
     (P(7, 2, 12, 11, 6, 5, 5, 1, 1, 2, 2), "bwd_data", "corr_thin_r2_lds5"),
     (P(3, 3, 20, 31, 9, 5, 5, 1, 1, 4, 4), "bwd_data", "corr_thin_r3_lds5"),
     (P(6, 8, 15, 16, 8, 5, 5, 1, 1, 2, 2, 1, 1, 2), "bwd_data", "corr_thin_r4_lds5"),
+]
+
+# The kernels on three-way split bf16 operands (problems of 0.4 / 1 GFLOP and more): every tile x patch size class of the
+# correlation and of the filter gradient, both passes, both epilogue forms with and without a split reduction, strides,
+# dilations, groups, one and two patch stages, odd tap counts, ragged channels, images whose pixel count is no multiple of
+# eight (test_split_parity_gpu.py checks on the CPU that together they select all of that).
+SPLIT_CASES = [
+    P(27, 170, 27, 10, 158, 4, 4, 2, 1, 2, 3, 2, 2, 2),
+    P(27, 58, 34, 28, 84, 3, 3, 1, 1, 0, 1, 1, 1, 2),
+    P(39, 91, 32, 9, 68, 4, 4, 1, 1, 0, 1, 2, 2, 1),
+    P(8, 132, 26, 22, 110, 4, 4, 1, 1, 3, 0, 1, 1, 2),
+    P(2, 115, 40, 50, 127, 3, 3, 1, 1, 0, 2, 1, 1, 1),
+    P(21, 128, 21, 17, 70, 5, 5, 1, 1, 1, 4, 2, 2, 2),
+    P(27, 186, 15, 7, 169, 3, 5, 1, 1, 1, 0, 1, 1, 1),
+    P(33, 60, 37, 24, 25, 4, 3, 1, 1, 1, 2, 1, 1, 1),
+    P(12, 160, 36, 16, 86, 3, 5, 2, 1, 1, 0, 1, 1, 2),
+    P(12, 105, 24, 10, 123, 4, 4, 1, 1, 0, 0, 1, 1, 1),
+    P(5, 86, 40, 17, 172, 3, 5, 1, 1, 1, 0, 1, 1, 1),
+    P(24, 64, 15, 40, 98, 3, 3, 1, 1, 0, 1, 1, 1, 1),
+    P(7, 127, 12, 10, 114, 5, 5, 1, 1, 2, 4, 2, 2, 1),
+    P(3, 95, 39, 26, 103, 7, 1, 1, 1, 4, 1, 1, 1, 1),
+    P(13, 175, 7, 14, 110, 3, 3, 1, 1, 2, 0, 1, 1, 1),
+    P(30, 138, 25, 8, 112, 3, 3, 2, 2, 0, 2, 1, 1, 1),
+    P(29, 46, 34, 8, 102, 7, 1, 1, 1, 4, 0, 1, 1, 1),
+    P(14, 48, 33, 31, 115, 7, 1, 1, 1, 1, 0, 1, 1, 1),
 ]
 
 

@@ -1,0 +1,120 @@
+"""The kernels on three-way split bf16 operands (corr_split_kernel, wgrad_split_kernel) against the oracle.
+
+Tolerance.  The split holds every bit of an operand, so the error is that of fp32 accumulation: the long sum of K terms is
+rounded once per 16 of them (32 for the 16-row instruction), each rounding at most 2^-24 of a partial sum and of random sign,
+so the 2-norm of the error is below 2^-24 sqrt(K/16 + 32) of the result's (the 32 stand for the split slices and the
+partial products' own accumulator); element by element the suite's bar of 1e-4 applies.
+"""
+import re
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1810_02272_amd as conv
+from oracle import OracleParams
+from paper_1810_02272_amd import workloads
+from parity_cases import SPLIT_CASES, P
+from parity_metric import nerr
+from test_parity_gpu import TOL, check_filter_and_bias_in_one_pass, run_all
+
+DEV = "cuda:0"
+CORR = re.compile(r"corrsplit_(m\d+_\d+x\d+)\[p(\d),e(.)\]\(S=(\d+)")
+WGRAD = re.compile(r"splitwgrad_(\d+x\d+)x16\[p(\d),st(\d)\]")
+
+
+def names(pd):
+    return dict(kv.split("=", 1) for kv in conv.conv_desc_kernel_names(conv.conv_desc_create(conv.ConvParams(**pd))).split(";"))
+
+
+def test_cases_select_every_variant():
+    corr, wgrad = set(), set()
+    for pd in SPLIT_CASES:
+        n = names(pd)
+        for which in ("fwd", "bwd_data"):
+            if m := CORR.match(n[which]):
+                corr |= {(which, m[1]), (m[1], m[2]), (which, m[3], int(m[4]) > 1)}
+        if m := WGRAD.match(n["bwd_filter"]):
+            wgrad |= {(m[1], m[2]), m[3]}
+    tiles = ["m32_128x128", "m32_64x256", "m32_64x128", "m32_96x128", "m32_32x256", "m32_32x128", "m16_48x256"]
+    want = {(w, t) for w in ("fwd", "bwd_data") for t in tiles}
+    want |= {(t, u) for t in tiles for u in ("34" if t.endswith("x256") else "234")}
+    want |= {("fwd", "s", s) for s in (False, True)} | {("bwd_data", e, s) for e in "sr" for s in (False, True)}
+    assert want - corr == set()
+    assert {(t, u) for t in ("128x9", "128x8", "64x16", "32x28", "32x12", "96x8") for u in "234"} | {"1", "2"} <= wgrad
+
+
+def norm_error(g, r):
+    g = g.cpu().double().numpy().reshape(r.shape)
+    return float(np.linalg.norm(g - r) / np.linalg.norm(r))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("i", range(len(SPLIT_CASES)))
+def test_split_full_compare(i):
+    pd = SPLIT_CASES[i]
+    print("split case", i, pd, names(pd), flush=True)
+    op = OracleParams(**pd)
+    ys = oracle.output_shape(op)
+    x, w, b, dy = workloads.random_inputs(oracle.x_shape(op), oracle.w_shape(op), ys, 6100 + 10 * i)
+    d, ws, dev_in, (y, dx, dw, db) = run_all(pd, x, w, b, dy)
+    host = (x.numpy(), w.numpy(), b.numpy(), dy.numpy())
+    taps = pd["kernel_h"] * pd["kernel_w"]
+    db_ref = oracle.backward_bias(op, host[3])
+    for name, got, ref, terms in (
+            ("y", y, oracle.forward(op, *host[:3]), pd["c"] // pd["group"] * taps),
+            ("dx", dx, oracle.backward_data(op, host[1], host[3]), pd["num_output"] // pd["group"] * taps),
+            ("dw", dw, oracle.backward_filter(op, host[0], host[3]), ys[0] * ys[2] * ys[3])):
+        assert nerr(got, ref) <= TOL, (pd, name)
+        assert norm_error(got, ref) <= 2.0 ** -24 * np.sqrt(terms / 16 + 32), (pd, name, norm_error(got, ref))
+    check_filter_and_bias_in_one_pass(pd, op, d, ws, dev_in, dw, db_ref, host)
+    # beta = 1: dw + dw is exact in fp32; the entry point without a workspace gives the same bits
+    xd, _, _, dyd = dev_in
+    dw1, dw2 = dw.clone(), torch.full_like(dw, float("nan"))
+    conv.conv_backward_filter(d, xd, dyd, dw1, 1.0, ws)
+    conv.conv_backward_filter_static(d, xd, dyd, dw2)
+    torch.cuda.synchronize()
+    assert torch.equal(dw1, dw + dw) and torch.equal(dw2, dw)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("pd", [P(20, 48, 29, 30, 60, 5, 5), P(40, 48, 30, 31, 64, 3, 5)],
+                         ids=["5x5", "3x5"])
+@pytest.mark.parametrize("odd", [(float("inf"), float("-inf"), float("nan")), (3.4e38, -3.4028234e38)],
+                         ids=["not_finite", "largest"])
+def test_infinities_nans_and_the_largest_floats(pd, odd):
+    """An infinity or NaN spoils the split's differences and the largest floats round to a bf16 infinity: such sums are computed
+    again, and must come out as plain fp32 arithmetic has them (no padding: a zero times an infinity is not the oracle's)."""
+    assert "split" in names(pd)["fwd"] and "split" in names(pd)["bwd_data"] and "split" in names(pd)["bwd_filter"], names(pd)
+    op = OracleParams(**pd)
+    x, w, b, dy = workloads.random_inputs(oracle.x_shape(op), oracle.w_shape(op), oracle.output_shape(op), 77)
+    x_plain = x.clone()
+    for i, v in enumerate(odd):
+        x[i, 3 * i, 7 + i, 9] = v
+        dy[2 + i, 5 * i, 4, 6 + 2 * i] = v
+    d, ws, (_, _, bd, _), (y, dx, dw, db) = run_all(pd, x, w, b, dy)
+    host = (x.numpy(), w.numpy(), b.numpy(), dy.numpy())
+    # infinite and huge weights: forward only (the data gradient multiplies them with the zeros around dy, as any fp32
+    # kernel does), on plain inputs
+    w_inf = w.clone()
+    w_inf[9, 3, 0, 2] = float("inf")
+    w_inf[7, 2, 1, 1] = 3.4e38
+    y_inf = torch.empty_like(y)
+    conv.conv_forward(d, x_plain.to(DEV), w_inf.to(DEV), bd, y_inf, ws)
+    torch.cuda.synchronize()
+    with np.errstate(all="ignore"):
+        refs = (oracle.forward(op, *host[:3]), oracle.backward_data(op, host[1], host[3]),
+                oracle.backward_filter(op, host[0], host[3]), oracle.forward(op, x_plain.numpy(), w_inf.numpy(), host[2]))
+        mag = [np.abs(v) for v in host]
+        mags = (oracle.forward(op, *mag[:3]), oracle.backward_data(op, mag[1], mag[3]),
+                oracle.backward_filter(op, mag[0], mag[3]), oracle.forward(op, np.abs(x_plain.numpy()), np.abs(w_inf.numpy()), mag[2]))
+    for name, got, ref, size in zip(("y", "dx", "dw", "y, odd weights"), (y, dx, dw, y_inf), refs, mags):
+        g = got.cpu().double().numpy().reshape(ref.shape)
+        r = np.where(np.abs(ref) > 3.4028235e38, np.sign(ref) * np.inf, ref)  # what fp32 cannot hold
+        close = np.isfinite(size) & (size > 1e38)  # terms at the edge of the range: fp32 may or may not overflow on the way
+        with np.errstate(all="ignore"):
+            same = (g == r) | (np.isnan(g) & np.isnan(r)) | close
+            fine = np.isfinite(r) & np.isfinite(g) & (np.abs(g - r) <= TOL * np.maximum(size, 1.0))
+        assert np.all(same | fine), (name, np.argwhere(~(same | fine))[:5])
+        assert np.isinf(r).any() or np.isnan(r).any()
