@@ -190,12 +190,13 @@ void corr_variant_name(char* buf, size_t len, int32_t tile, const CorrArgs& a, i
     snprintf(buf, len, "%s[m%d,e%c](S=%d,L=%d)", corr_tile_name(tile), a.bounds_mode, e, a.ksplit, launches);
 }
 
-// "corrsplit_<tile>[p<patch units per thread>,e<epilogue form>](S,L)"
+// "corrsplit_<tile>[p<patch units per thread>, fold<taps per channel> or cols<channel groups>,e<epilogue form>](S,L)"
 void split_variant_name(char* buf, size_t len, int32_t tile, const CorrArgs& a, int zero_fill) {
   int32_t bm, bn, mt;
   split_tile_shape(tile, &bm, &bn, &mt);
   const char e = a.simple_epilogue ? 's' : ((uint32_t)a.out_elems < (1u << 29) ? 'r' : 'p');
-  snprintf(buf, len, "corrsplit_m%d_%dx%d[p%d,e%c](S=%d,L=%d)", mt, bm, bn, split_patch_units(a.PSZ, bn), e,
+  snprintf(buf, len, "corrsplit_m%d_%dx%d[%s%d,e%c](S=%d,L=%d)", mt, bm, bn, a.fold.subs ? "cols" : a.fold.ff > 1 ? "fold" : "p",
+           a.fold.subs ? a.fold.subs : a.fold.ff > 1 ? a.fold.ff : split_patch_units(a.PSZ, bn), e,
            a.ksplit, 2 + (a.ksplit > 1) + (zero_fill != 0));
 }
 
@@ -379,6 +380,162 @@ PatchDim patch_dim(int64_t out, int64_t stride, int64_t ext, int64_t pad, int64_
   return r;
 }
 
+// The most patch rows that any tile needs: tiles of `tile` units -- `unit` output positions of an image of P -- over `total`
+// units, `per_image` to an image (its last unit may be short).  Ends where the tiles' starts repeat, where `enough` rows are
+// passed and where no tile can need more: walking all 3025 tiles of 128 images of 55x55 took 40 us for each tile shape.
+int64_t max_patch_rows(int64_t total, int64_t per_image, int64_t tile, int64_t unit, int64_t P, int64_t PW, int64_t stride,
+                       int64_t ext, int64_t pitch, int64_t enough) {
+  const int64_t PH = P / PW, extra = pitch - PH * stride, crossed = (per_image + tile - 2) / per_image;
+  const int64_t bound = (PW - 1 + tile * unit - 1) / PW * stride + (extra > 0 ? extra * crossed : 0) + ext;
+  int64_t most = 0, rest = total;
+  uint32_t r = 0;  // the tile's first unit within its image
+  do {
+    const uint32_t last = r + (uint32_t)(rest < tile ? rest : tile) - 1, images = last / (uint32_t)per_image;
+    const int64_t end = (int64_t)(last - images * (uint32_t)per_image) * unit + unit - 1;
+    const int64_t a0 = r * (uint32_t)unit / (uint32_t)PW, a1 = (uint32_t)(end < P ? end : P - 1) / (uint32_t)PW;
+    const int64_t rows = images * pitch + (a1 - a0) * stride + ext;
+    if (rows > most) most = rows;
+    r = (r + (uint32_t)tile) % (uint32_t)per_image;
+    rest -= tile;
+  } while (rest > 0 && r != 0 && most < bound && most <= enough);
+  return most;
+}
+
+// The grid that corr_split_kernel walks (SplitFold in internal.h).
+struct SplitGrid {
+  SplitFold f;
+  int64_t sh, sw, dh, dw, TH, TW;  // strides, dilations and taps on the grid
+};
+
+void plain_grid(int64_t cg, int64_t kh, int64_t kw, int64_t sh, int64_t sw, int64_t dh, int64_t dw, SplitGrid& g) {
+  g = SplitGrid();
+  g.f.fh = g.f.fw = g.f.ff = g.f.Uh = g.f.Uw = 1;
+  g.f.dh = (int32_t)dh;
+  g.f.dw = (int32_t)dw;
+  g.f.V = (int32_t)cg;
+  g.f.mFF = g.f.mFw = make_magic(1);
+  g.sh = sh;
+  g.sw = sw;
+  g.dh = dh;
+  g.dw = dw;
+  g.TH = kh;
+  g.TW = kw;
+}
+
+// The tile's columns, for 1x1 kernels.
+void column_grid(int64_t cg, int64_t sh, int64_t sw, SplitGrid& g) {
+  plain_grid(cg, 1, 1, 1, 1, 1, 1, g);
+  g.f.subs = 4;
+  g.f.Uh = (int32_t)sh;
+  g.f.Uw = (int32_t)sw;
+  g.TH = 4;  // the groups of 16 channels
+}
+
+// Layers whose few channels would leave the 16-channel chunks mostly empty.  Per dimension the taps stay, or the `stride`
+// taps between two positions of a grid of every stride-th pixel are folded (undilated layers), or all of them are; of the
+// nine combinations with at least three taps left (a patch is staged per 16 channels and read once per tap) the one that
+// pads the reduction least.  Only where four channels are one 16-byte load -- 3 channels, 11x11, stride 4: 48 channels and
+// 3x3 taps, 432 reduction indices for 363, 241 -> 195 us; with single loads the patch costs more than the matrix unit
+// gains (3 channels, 5x5 at 64x64: 36 us fp32, 44 folded) -- and up to 1.25 times the reduction.
+bool folded_grid(int64_t cg, int64_t kh, int64_t kw, int64_t sh, int64_t sw, int64_t dh, int64_t dw, int64_t pw,
+                 SplitGrid& g) {
+  plain_grid(cg, kh, kw, sh, sw, dh, dw, g);
+  struct Dim {
+    int64_t f, U, taps, s, d;
+  };
+  auto options = [](int64_t k, int64_t s, int64_t d, Dim* o) {
+    int n = 0;
+    o[n++] = {1, 1, k, s, d};
+    if (s > 1 && d == 1) o[n++] = {s, s, ceil_div(k, s), 1, 1};
+    o[n++] = {k, s, 1, 1, 1};
+    return n;
+  };
+  Dim oh[3], ow[3];
+  const int nh = options(kh, sh, dh, oh), nw = options(kw, sw, dw, ow);
+  int64_t best = 0;
+  for (int i = 0; i < nh; ++i)
+    for (int j = 0; j < nw; ++j) {
+      const int64_t V = cg * oh[i].f * ow[j].f, T = oh[i].taps * ow[j].taps, padded = round_up(V, 16) * T;
+      if (oh[i].f * ow[j].f == 1 || T < 3 || (best && padded >= best)) continue;
+      best = padded;
+      g.f.fh = (int32_t)oh[i].f;
+      g.f.fw = (int32_t)ow[j].f;
+      g.f.Uh = (int32_t)oh[i].U;
+      g.f.Uw = (int32_t)ow[j].U;
+      g.f.V = (int32_t)V;
+      g.sh = oh[i].s;
+      g.sw = ow[j].s;
+      g.dh = oh[i].d;
+      g.dw = ow[j].d;
+      g.TH = oh[i].taps;
+      g.TW = ow[j].taps;
+    }
+  if (!best || best * 4 > cg * kh * kw * 5 || g.f.V > 512 || kh * dh > 16384 || kw * dw > 16384) return false;
+  g.f.ff = g.f.fh * g.f.fw;
+  g.f.mFF = make_magic((uint32_t)g.f.ff);
+  g.f.mFw = make_magic((uint32_t)g.f.fw);
+  return g.f.fw % 4 == 0 && g.f.Uw % 4 == 0 && dw == 1 && pw % 4 == 0;
+}
+
+// Tile and split count of corr_split_kernel on one grid by modelled time (us); tile < 0: the patch fits none.
+// The workgroup that finishes last walks its steps alone on its compute unit (kAlone per step) or shares it with others
+// (kShared per step and workgroup); a chunk costs its patch by units per thread; S slices cost the reduce kernel and their
+// partial sums written and read.  The constants are a least-squares fit to 888 timings -- all tiles, 1 to 12 slices, 38
+// layers of 0.3 to 57 GFLOP (rms error 8 %); the choice is 2 % behind the best of each layer on average, 13 % at worst.
+struct SplitPlan {
+  int32_t tile;
+  int64_t psz, S, units;  // units: output tiles
+  double cost;  // modelled time without the launches and the prologue, about 10 us
+  PatchDim w, h;
+};
+
+SplitPlan plan_split(const CorrArgs& base, const SplitGrid& grid, int64_t out_elems) {
+  static const double kAlone[SPLIT_TILE_COUNT] = {0.457, 0.444, 0.414, 0.376, 0.400, 0.298, 0.664};
+  static const double kShared[SPLIT_TILE_COUNT] = {0.423, 0.424, 0.250, 0.340, 0.248, 0.166, 0.613};
+  SplitPlan plan = {};
+  plan.tile = -1;
+  const bool columns = grid.f.subs != 0, image = grid.f.ff == 1 && !columns;
+  const int64_t T = grid.TH * grid.TW, PH = base.P / base.PW, ext = (grid.TH - 1) * grid.dh + 1;
+  if (!columns) {
+    plan.w = patch_dim(base.PW, grid.sw, (grid.TW - 1) * grid.dw + 1, image ? base.pw : 0, base.IW);
+    plan.h = patch_dim(PH, grid.sh, ext, image ? base.ph : 0, base.IH);
+  }
+  const int64_t chunks = ceil_div(grid.f.V, columns ? 64 : 16);
+  const double out_mb = 4e-6 * (double)out_elems;
+  double best = 0;
+  for (int32_t t = 0; t < SPLIT_TILE_COUNT; ++t) {
+    int32_t bm, bn, mt;
+    split_tile_shape(t, &bm, &bn, &mt);
+    if (!image && (bn > 128 || (columns && bm < 64))) continue;  // the folded and column forms are built for these
+    int64_t psz = 4 * bn;
+    if (!columns) {
+      const int64_t max_rows = max_patch_rows(base.ncols, base.P, bn, 1, base.P, base.PW, grid.sh, ext, plan.h.pitch,
+                                              512 / plan.w.pitch);
+      psz = max_rows * plan.w.pitch + plan.w.share;
+    }
+    if (psz > 512) continue;
+    const int64_t units = (int64_t)base.G * ceil_div(base.Mrows, bm) * ceil_div(base.ncols, bn);
+    const int64_t spc = ceil_div(T, mt == 32 ? 1 : 2);
+    const double units_per_thread = image ? (double)split_patch_units(psz, bn) : 4.0;
+    for (int64_t S = 1; S <= 16 && S <= chunks; ++S) {
+      if (S > 1 && (units * S > 2048 || units > 512)) break;
+      const int64_t per_cu = ceil_div(units * S, 256), cps = ceil_div(chunks, S);
+      const double steps = (double)(cps * spc);
+      double cost = per_cu == 1 ? steps * kAlone[t] + 0.39 * (double)cps * units_per_thread
+                                : (double)per_cu * (steps * kShared[t] + 0.25 * (double)cps * units_per_thread);
+      if (S > 1) cost += 3.3 + 0.46 * (double)S * out_mb;
+      if (plan.tile < 0 || cost < best) {
+        best = plan.cost = cost;
+        plan.tile = t;
+        plan.psz = psz;
+        plan.S = S;
+        plan.units = units;
+      }
+    }
+  }
+  return plan;
+}
+
 // Decides whether corr_split_kernel runs this correlation; fills a, k and the tile.  Returns the bytes of packed
 // weights, 0 if it does not.
 size_t configure_split(const CorrArgs& base, const PackArgs& pbase, int64_t cg_in, int64_t n_img, int64_t out_elems,
@@ -387,84 +544,76 @@ size_t configure_split(const CorrArgs& base, const PackArgs& pbase, int64_t cg_i
   const double flops = 2.0 * base.Mrows * base.Kred * (double)base.ncols * base.G;
   if (base.ncols < 1 || (int64_t)base.in_bytes > ((int64_t)1 << 30)) return 0;
   // Below a GFLOP the two paths are level (100 x 32 -> 64 at 8x8, 5x5, 0.66 GFLOP: 19.4 us fp32, 20.8 split; one image of
-  // 96 -> 256 in two groups at 27x27, 0.45 GFLOP: 22.2 and 20.8).  With one or two taps the patch is staged for too few
-  // steps (256 -> 256 1x1 at 14x14: 26.7 us fp32, 29.6 split), with a short reduction likewise; the patch-staged fp32
-  // kernel keeps reductions under 512.
-  if (flops < 1e9 || base.THW < 3 || base.Kred < (base.use_patch ? 512 : 256)) return 0;
-  const int64_t TH = base.THW / base.TW, PH = base.P / base.PW;
-  const int64_t ext = (TH - 1) * base.dh + 1;
-  const PatchDim dim_w = patch_dim(base.PW, base.sw, (int64_t)(base.TW - 1) * base.dw + 1, base.pw, base.IW);
-  const PatchDim dim_h = patch_dim(PH, base.sh, ext, base.ph, base.IH);
-  const int64_t PWID = dim_w.pitch, RS = dim_h.pitch, share_w = dim_w.share, share_h = dim_h.share;
-  const int64_t chunks = ceil_div(cg_in, 16);
-  if (cg_in * 100 < chunks * 16 * 70) return 0;
-  // Modelled time (us) of every tile and split count: the workgroup that finishes last walks its steps alone on its
-  // compute unit (kAlone per step) or shares it with others (kShared per step and workgroup); a chunk costs its patch
-  // by units per thread; S slices cost the reduce kernel and their partial sums written and read.  The constants are a
-  // least-squares fit to 888 timings -- all tiles, 1 to 12 slices, 38 layers of 0.3 to 57 GFLOP (rms error 8 %); the
-  // choice is 2 % behind the best of each layer on average and 13 % at worst.
-  static const double kAlone[SPLIT_TILE_COUNT] = {0.457, 0.444, 0.414, 0.376, 0.400, 0.298, 0.664};
-  static const double kShared[SPLIT_TILE_COUNT] = {0.423, 0.424, 0.250, 0.340, 0.248, 0.166, 0.613};
-  double best = 0;
-  int64_t best_psz = 0, best_S = 1;
-  for (int32_t t = 0; t < SPLIT_TILE_COUNT; ++t) {
-    int32_t bm, bn, mt;
-    split_tile_shape(t, &bm, &bn, &mt);
-    int64_t max_rows = 0;
-    for (int64_t c0 = 0; c0 < base.ncols; c0 += bn) {
-      const int64_t c1 = (c0 + bn < base.ncols ? c0 + bn : base.ncols) - 1;
-      const int64_t n0 = c0 / base.P, a0 = (c0 % base.P) / base.PW, n1 = c1 / base.P, a1 = (c1 % base.P) / base.PW;
-      const int64_t R0 = (PH - 1 - a0) * base.sh + ext - share_h;
-      const int64_t rows = (n1 == n0 ? (a1 - a0) * base.sh : R0 + (n1 - n0 - 1) * RS + a1 * base.sh) + ext;
-      if (rows > max_rows) max_rows = rows;
-    }
-    const int64_t psz = max_rows * PWID + share_w;
-    if (psz > 512) continue;
-    const int64_t units = (int64_t)base.G * ceil_div(base.Mrows, bm) * ceil_div(base.ncols, bn);
-    const int64_t tps = mt == 32 ? 1 : 2, spc = ceil_div(base.THW, tps);
-    const double out_mb = 4e-6 * (double)out_elems;
-    const double units_per_thread = (double)split_patch_units(psz, bn);
-    for (int64_t S = 1; S <= 16 && S <= chunks; ++S) {
-      if (S > 1 && (units * S > 2048 || units > 512)) break;
-      const int64_t per_cu = ceil_div(units * S, 256), cps = ceil_div(chunks, S);
-      const double steps = (double)(cps * spc);
-      double cost = per_cu == 1 ? steps * kAlone[t] + 0.39 * (double)cps * units_per_thread
-                                : (double)per_cu * (steps * kShared[t] + 0.25 * (double)cps * units_per_thread);
-      if (S > 1) cost += 3.3 + 0.46 * (double)S * out_mb;
-      if (tile < 0 || cost < best) {
-        best = cost;
-        tile = t;
-        best_psz = psz;
-        best_S = S;
-      }
-    }
+  // 96 -> 256 in two groups at 27x27, 0.45 GFLOP: 22.2 and 20.8), the patch-staged fp32 kernel keeps reductions under 512,
+  // and so do the 16-row fp32 tiles what fits them (8 rows on 32-row instructions: 36 us fp32, 66 split; 12 rows: 51 and 64).
+  if (flops < 1e9 || base.Mrows <= 16 || base.Kred < (base.use_patch ? 512 : 128)) return 0;
+  const int64_t kh = base.THW / base.TW, kw = base.TW;
+  SplitGrid grid;
+  SplitPlan plan = {};
+  plan.tile = -1;
+  if (base.THW == 1) {
+    // 256 -> 256 at 14x14, batch 64, 1.6 GFLOP: level; 344 -> 347 at 43x38, batch 23, 9 GFLOP: 94 -> 83 us.  Shorter reductions
+    // want more tiles: 307 -> 314 at 98x98, 5.6 GFLOP: 60 -> 65; the filter gradient of a 128 x 9216 -> 4096 inner product,
+    // whose reduction are the 128 rows, 9.7 GFLOP: 106 -> 79
+    column_grid(cg_in, base.sh, base.sw, grid);
+    if (flops >= (base.Kred < 320 ? 6e9 : 2.5e9)) plan = plan_split(base, grid, out_elems);
+  } else if (cg_in * 100 >= round_up(cg_in, 16) * 70) {
+    plain_grid(cg_in, kh, kw, base.sh, base.sw, base.dh, base.dw, grid);
+    if (base.THW >= 3 && base.Kred >= 256) plan = plan_split(base, grid, out_elems);
+  } else if (pbase.mode == 0 &&  // forward: a backward-data gather has the layer's output channels and stride 1
+             folded_grid(cg_in, kh, kw, base.sh, base.sw, base.dh, base.dw, base.pw, grid)) {
+    plan = plan_split(base, grid, out_elems);
   }
-  if (tile < 0) return 0;
+  if (plan.tile < 0) return 0;
+  // Against the fp32 kernels, modelled as 85 TFLOP/s of rows padded to 16 and 12 us of launches: keeps what the split form is
+  // too coarse for (16 channels to gather, 11x11, are one chunk that no slice can share: 42 us fp32, 53 split).  Reductions
+  // under 800 that the fp32 kernel need not slice are closer: it has no reduce launch there, and what the modelled steps
+  // leave out of a split workgroup (prologue, epilogue, patch of a kernel of 1 to 3 taps) weighs more.  Of 329 passes drawn
+  // over 1 to 30 GFLOP, 305 take the split form, at worst 3 % slower, 48 % faster in the mean; without the second line of
+  // constants 15 were up to 16 % slower (1x1, 141 -> 279 at 103x119: 57 and 67 us; 3x3, 80 -> 229 at 78x84: 31 and 36).
+  // Small strided backward passes stay: their scattered stores cost the gain (17 channels at 43x43, stride 2: 29 and 38).
+  const double flops16 = 2.0 * (double)round_up(base.Mrows, 16) * base.Kred * (double)base.ncols * base.G;
+  double here = plan.cost + 10, fp32 = flops16 / 85e6 + 12;
+  if (base.ksplit == 1 && base.Kred < 800) {
+    const int64_t per_cu = ceil_div(plan.units * plan.S, 256);
+    here += (base.THW <= 3 ? 2.5 : 1.5) * (double)per_cu + (plan.S > 1 ? 4 : 0) + (base.simple_epilogue ? 0 : 6);
+    fp32 = flops16 / 90e6 + 8;
+  }
+  if (here > fp32 || (!base.simple_epilogue && flops < 3e9)) return 0;
+  tile = plan.tile;
   int32_t bm, bn, mt;
   split_tile_shape(tile, &bm, &bn, &mt);
+  const bool columns = grid.f.subs != 0;
+  const int64_t chunks = ceil_div(grid.f.V, columns ? 64 : 16);
   a = base;
   k = pbase;
   a.use_patch = 0;
+  a.fold = k.fold = grid.f;
+  a.sh = (int32_t)grid.sh;
+  a.sw = (int32_t)grid.sw;
+  a.dh = (int32_t)grid.dh;
+  a.dw = (int32_t)grid.dw;
+  a.TW = k.tTW = (int32_t)grid.TW;
+  a.THW = k.tTHW = (int32_t)(grid.TH * grid.TW);
   a.Cg_in = (int32_t)cg_in;
   a.NS = (int32_t)chunks;
-  a.PH = (int32_t)PH;
+  a.PH = base.P / base.PW;
   a.Nimg = (int32_t)n_img;
-  a.PWID = (int32_t)PWID;
-  a.share_w = (int32_t)share_w;
-  a.share_h = (int32_t)share_h;
-  a.PSZ = (int32_t)best_psz;
-  a.patch_stages = best_psz <= 426 ? 2 : 1;  // two workgroups per compute unit either way
-  a.mPWID = make_magic((uint32_t)PWID);
-  a.mRSEG = make_magic((uint32_t)RS);
+  a.PWID = columns ? bn : (int32_t)plan.w.pitch;  // columns: from one group of 16 channels to the next
+  a.share_w = (int32_t)plan.w.share;
+  a.share_h = (int32_t)plan.h.share;
+  a.PSZ = (int32_t)plan.psz;
+  a.patch_stages = plan.psz <= 416 ? 2 : 1;  // two workgroups per compute unit either way
+  a.mPWID = make_magic((uint32_t)a.PWID);
+  a.mRSEG = make_magic((uint32_t)(columns ? 1 : plan.h.pitch));
   a.m_tiles = (int32_t)ceil_div(a.Mrows, bm);
   a.MP = a.m_tiles * bm;
   a.col_tiles = (int32_t)ceil_div(a.ncols, bn);
   a.out_elems = (int32_t)out_elems;
-  a.chunks_per_split = (int32_t)ceil_div(chunks, best_S);
+  a.chunks_per_split = (int32_t)ceil_div(chunks, plan.S);
   a.ksplit = (int32_t)ceil_div(chunks, a.chunks_per_split);
   k.split_chunks = a.NS;
-  const int64_t tps = mt == 32 ? 1 : 2;
-  return (size_t)a.G * a.m_tiles * chunks * ceil_div(a.THW, tps) * (bm / mt) * 3072;
+  return (size_t)a.G * a.m_tiles * chunks * ceil_div(a.THW, mt == 32 ? 1 : 2) * (bm / mt) * 3072;
 }
 
 // Decides whether wgrad_split_kernel runs the backward filter; fills a and returns its tile, -1 if it does not.
@@ -478,15 +627,7 @@ int32_t configure_wgrad_split(const WgradArgs& w, int64_t N, int64_t K, int64_t 
   const PatchDim dim_h = patch_dim(PH, w.sh, ext, w.ph, w.H);
   const int64_t PWID = dim_w.pitch, RS = dim_h.pitch;
   const int64_t runs = ceil_div(w.P, 8), total_runs = N * runs, chunk_runs = wgrad_split_chunk_runs();
-  int64_t max_rows = 0;
-  for (int64_t q = 0; q < total_runs; q += chunk_runs) {
-    const int64_t q1 = (q + chunk_runs < total_runs ? q + chunk_runs : total_runs) - 1;
-    const int64_t n0 = q / runs, a0 = q % runs * 8 / w.PW, n1 = q1 / runs;
-    const int64_t p1 = q1 % runs * 8 + 7 < w.P ? q1 % runs * 8 + 7 : w.P - 1, a1 = p1 / w.PW;
-    const int64_t R0 = (PH - 1 - a0) * w.sh + ext - dim_h.share;
-    const int64_t rows = (n1 == n0 ? (a1 - a0) * w.sh : R0 + (n1 - n0 - 1) * RS + a1 * w.sh) + ext;
-    if (rows > max_rows) max_rows = rows;
-  }
+  const int64_t max_rows = max_patch_rows(total_runs, runs, chunk_runs, 8, w.P, w.PW, w.sh, ext, RS, 512 / PWID);
   const int64_t psz = max_rows * PWID + dim_w.share;
   if (psz > 512) return -1;
   const int64_t c16 = ceil_div(w.Cg, 16);
@@ -524,12 +665,15 @@ int32_t configure_wgrad_split(const WgradArgs& w, int64_t N, int64_t K, int64_t 
       }
     }
   }
+  // Fewer chunks than that cannot be shared out (4 chunks, 0.5 GFLOP: 18.8 us fp32, 21.2 split; 5, 2.4 GFLOP: 58.6, 62.9).
+  if (chunks < 8) return -1;
   // What the blocks pad more than the fp32 tile costs the advantage: up to twice its work on a large problem (202 -> 14
-  // channels, 5x3: 1.6 times the work, 186 -> 156 us), 1.12 times on one under 2.5 GFLOP (64 -> 96 channels, 3x1 at
-  // 28x28, twice the work: 38 -> 42 us; 300 -> 200, 3x3 at 12x12, 1.11 times: 38 -> 33 us).
+  // channels, 5x3: 1.6 times the work, 186 -> 156 us), 1.45 times under 4.5 GFLOP (54 -> 74, 3x3 at 75x60, 1.5 times: 57 ->
+  // 61 us) and 1.12 times under 2.5 GFLOP (64 -> 96 channels, 3x1 at 28x28, twice the work: 38 -> 42 us; 300 -> 200, 3x3
+  // at 12x12, 1.11 times: 38 -> 33 us).
   int32_t bm, bn, bk;
   wgrad_tile_shape(pick_wgrad_tile(w.Kg, w.Kred), &bm, &bn, &bk);
-  if (least_work > (flops < 2.5e9 ? 1.12 : 2.0) * (double)round_up(w.Kg, bm) * (double)round_up(w.Kred, bn)) return -1;
+  if (least_work > (flops < 2.5e9 ? 1.12 : flops < 4.5e9 ? 1.45 : 2.0) * (double)round_up(w.Kg, bm) * (double)round_up(w.Kred, bn)) return -1;
   int32_t rows, taps;
   wgrad_split_shape(best, &rows, &taps);
   a = WgradSplitArgs();

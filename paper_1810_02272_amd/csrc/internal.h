@@ -41,6 +41,24 @@ struct KTabEntry {
 
 constexpr int kMaxPhases = 8;  // phase tables of the backward-data row space (larger sets stay dense)
 
+// What corr_split_kernel's patch holds.
+//  - The image itself (ff = 1, subs = 0): positions are pixels, channels the layer's.
+//  - Layers of few channels and a stride of a multiple of four columns (ff > 1, subs = 0): fh x fw neighbouring taps become
+//    channels of their own, and the patch is a grid of every Uh-th row and Uw-th column of the image.  Channel v = (c, ir, jr)
+//    of grid position (r, q) is input (r*Uh - pad + ir*dh, q*Uw - pad + jr*dw) of channel c, and tap (it, jt) of the grid
+//    stands for the taps (it*fh + ir, jt*fw + jr).  The kernel's strides, dilations and tap counts are then those of the
+//    grid.  Channels 4q .. 4q+3 are four pixels of a row from a column of a multiple of four on.
+//  - The columns (1x1 kernels, subs = 4; Uh, Uw = the strides): the patch is no image but the tile's columns, once for each
+//    of four groups of 16 channels, which take the place of taps.
+struct SplitFold {
+  int32_t fh, fw, ff;  // ff = fh * fw
+  int32_t Uh, Uw;
+  int32_t dh, dw;      // dilations of the layer
+  int32_t V;           // channels: those of the group times ff
+  int32_t subs;        // 0, or the groups of 16 channels of a chunk
+  Magic mFF, mFw;
+};
+
 struct CorrArgs {
   const float* A;     // packed operand, [G][MP][KP] floats, zero padded
   const KTabEntry* ktab;  // [KP], written by the pack kernel
@@ -93,6 +111,7 @@ struct CorrArgs {
   int32_t Nimg;        // images
   int32_t PWID, PSZ;   // patch row length (PW + TW - 1); floats per channel of an LDS patch stage
   Magic mPWID, mRSEG;  // divisions by PWID and by the patch rows of a full image (PH + TH - 1)
+  SplitFold fold;            // corr_split_kernel: what the patch's grid and channels stand for
   int32_t patch_stages;      // corr_split_kernel: patch stages in LDS (1 or 2)
   int32_t share_w, share_h;  // corr_split_kernel: padding columns / rows that neighbouring patch rows / images share
   int32_t simple_epilogue;  // one phase per channel and an output of at most 2^30 bytes: offset-only epilogue
@@ -125,6 +144,7 @@ struct PackArgs {
   int32_t Kred, KP, Mrows, MP;
   int32_t kperm_T;  // 0, or the tap count T: k runs (8-channel chunk, tap, channel in chunk) instead of (c, tap)
   int32_t split_chunks;  // corr_split_kernel: chunks of 16 channels
+  SplitFold fold;
 };
 
 // Backward filter: part[s][g][k][nn] = sum over the split's columns of dy * gathered x.

@@ -49,12 +49,16 @@ struct SplitCfg {
   static_assert(WM * WN == 4, "four waves per workgroup");
 };
 
+enum SplitForm { IMAGE, FOLDED, COLUMNS };
+
 // EPT: patch units (one position x 8 channels) per thread, 2*PSZ <= 256*EPT.
-template <int MT, int MB, int NB, int WM, int WN, int EPT>
+// FORM: what the patch holds (SplitFold in internal.h).
+template <int MT, int MB, int NB, int WM, int WN, int EPT, SplitForm FORM>
 __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) void corr_split_kernel(const CorrArgs a) {
   using C = SplitCfg<MT, MB, NB, WM, WN>;
     using M = Mfma<MT>;
   constexpr int BM = C::BM, BN = C::BN;
+  constexpr bool FOLD = FORM == FOLDED, COLS = FORM == COLUMNS;
 
   extern __shared__ __align__(16) float smem[];  // one or two patch stages; the epilogue's tables at the end
 
@@ -90,8 +94,8 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
   };
   uint32_t col_last = col0 + BN - 1;
   if (col_last > (uint32_t)a.ncols - 1) col_last = (uint32_t)a.ncols - 1;
-  uint32_t patch_elems;
-  {
+  uint32_t patch_elems = (uint32_t)a.PSZ;
+  if (!COLS) {
     const uint32_t n = mdiv(col_last, a.mP);
     const uint32_t pa = mdiv(col_last - n * a.P, a.mPW);
     patch_elems = (patch_row_base(n, pa) + ext) * (uint32_t)a.PWID + a.share_w;
@@ -109,34 +113,60 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
     const uint32_t pix = col - n * a.P;
     const uint32_t pa = mdiv(pix, a.mPW);
     const uint32_t pb = pix - pa * a.PW;
-    lanebase[j] = 48u * (patch_row_base(n, pa) * (uint32_t)a.PWID + pb * a.sw + half * (uint32_t)a.PSZ);
+    lanebase[j] = 48u * (COLS ? col - col0 + half * (uint32_t)a.PSZ
+                              : patch_row_base(n, pa) * (uint32_t)a.PWID + pb * a.sw + half * (uint32_t)a.PSZ);
   }
 
   // ---- per-thread patch units: where they come from (relative to channel 0 of the group) ----
   const __amdgpu_buffer_rsrc_t in_rsrc =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.in), 0, (int)a.in_bytes, 0x00020000);
   const uint32_t chan_bytes = 4u * (uint32_t)a.IHW;
+  const uint32_t stage_bytes = 96u * (uint32_t)a.PSZ;
+  FoldEntry* const fold_tab =
+      reinterpret_cast<FoldEntry*>(reinterpret_cast<char*>(smem) + (uint32_t)a.patch_stages * stage_bytes);
+  if (FOLD) {
+    fill_fold_table(fold_tab, a.NS * 16, a.fold, a.IW, a.IHW, t, kThreads);
+    __syncthreads();
+  }
+  // Unfolded: the byte offset of the unit's first channel in chunk 0.  Folded: that of its position, whose row and
+  // column the channels are checked from.
   uint32_t psrc[EPT];
+  int prow_in[FOLD ? EPT : 1], pcol_in[FOLD ? EPT : 1];
 #pragma unroll
   for (int r = 0; r < EPT; ++r) {
     const uint32_t u = t + r * kThreads;
     const uint32_t hf = u >= (uint32_t)a.PSZ ? 1u : 0u;
     const uint32_t e = u - hf * (uint32_t)a.PSZ;
     uint32_t src = 0x80000000u;  // beyond the blob (which is at most 2^30 bytes): reads as zero
+    if (FOLD) prow_in[r] = -(1 << 28), pcol_in[r] = 0;  // fails every bounds test
     if (e < patch_elems && u < 2u * (uint32_t)a.PSZ) {
-      const uint32_t prow = mdiv(e, a.mPWID);
+      const uint32_t prow = mdiv(e, a.mPWID);  // COLS: the group of 16 channels
       const uint32_t pcol = e - prow * a.PWID;
       uint32_t n = n0, rin = prow, alo = a0;
-      if (prow >= R0) {
-        const uint32_t s1 = mdiv(prow - R0, a.mRSEG);
-        n = n0 + 1 + s1;
-        rin = prow - R0 - s1 * RS;
-        alo = 0;
+      int gr = 0, gc = (int)pcol;
+      if (COLS) {
+        const uint32_t col = col0 + pcol;
+        n = mdiv(col, a.mP);
+        const uint32_t pix = col - n * a.P;
+        gr = (int)mdiv(pix, a.mPW);
+        gc = (int)(pix - (uint32_t)gr * a.PW);
+        if (col > col_last) n = (uint32_t)a.Nimg;
+      } else {
+        if (prow >= R0) {
+          const uint32_t s1 = mdiv(prow - R0, a.mRSEG);
+          n = n0 + 1 + s1;
+          rin = prow - R0 - s1 * RS;
+          alo = 0;
+        }
+        gr = (int)(alo * a.sh + rin);
       }
-      const int ih = (int)(alo * a.sh + rin) - a.ph, iw = (int)pcol - a.pw;
-      if ((uint32_t)ih < (uint32_t)a.IH && (uint32_t)iw < (uint32_t)a.IW && n < (uint32_t)a.Nimg)
-        src = 4u * (n * (uint32_t)a.in_img_stride + g * (uint32_t)a.in_grp_stride + (uint32_t)ih * a.IW + iw) +
-              hf * 8u * chan_bytes;
+      const int ih = (FOLD || COLS ? gr * a.fold.Uh : gr) - a.ph, iw = (FOLD || COLS ? gc * a.fold.Uw : gc) - a.pw;
+      const uint32_t at = 4u * (n * (uint32_t)a.in_img_stride + g * (uint32_t)a.in_grp_stride + (uint32_t)(ih * a.IW + iw));
+      if (FOLD) {
+        if (n < (uint32_t)a.Nimg) src = at, prow_in[r] = ih, pcol_in[r] = iw;
+      } else if ((uint32_t)ih < (uint32_t)a.IH && (uint32_t)iw < (uint32_t)a.IW && n < (uint32_t)a.Nimg) {
+        src = at + (COLS ? prow * 16u + hf * 8u : hf * 8u) * chan_bytes;
+      }
     }
     psrc[r] = src;
   }
@@ -144,20 +174,26 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
   // are zero.
   float pr[EPT][8];
   auto patch_load = [&](int cc) {
-    const uint32_t coff = (uint32_t)(cc * 16) * chan_bytes;
+    const uint32_t coff = (uint32_t)(cc * (COLS ? 64 : 16)) * chan_bytes;
 #pragma unroll
     for (int r = 0; r < EPT; ++r) {
       uint32_t src = psrc[r];
       asm volatile("" : "+v"(src));  // or the compiler keeps eight running addresses per unit in registers
-      src += coff;
+      if (FOLD) {
+        const uint32_t hf = t + r * kThreads >= a.PSZ ? 1u : 0u;
+        const FoldEntry* fe = fold_tab + (cc * 16 + (int)hf * 8);
+        load_folded(in_rsrc, fe, src, prow_in[r], pcol_in[r], a.IH, a.IW, pr[r]);
+        __builtin_amdgcn_sched_barrier(0);  // one unit's table entries in registers at a time
+      } else {
+        src += coff;
 #pragma unroll
-      for (int c8 = 0; c8 < 8; ++c8)
-        pr[r][c8] = __builtin_bit_cast(
-            float, __builtin_amdgcn_raw_buffer_load_b32(in_rsrc, src + c8 * chan_bytes, 0, 0));
+        for (int c8 = 0; c8 < 8; ++c8)
+          pr[r][c8] = __builtin_bit_cast(
+              float, __builtin_amdgcn_raw_buffer_load_b32(in_rsrc, src + c8 * chan_bytes, 0, 0));
+      }
     }
   };
   const SplitSel sel;
-  const uint32_t stage_bytes = 96u * (uint32_t)a.PSZ;
   auto patch_store = [&](uint32_t stage_off) {
 #pragma unroll
     for (int r = 0; r < EPT; ++r) {
@@ -342,15 +378,24 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
       const uint32_t n = mdiv(col, a.mP);
       const uint32_t pix = col - n * a.P;
       const uint32_t pa = mdiv(pix, a.mPW);
-      const int ih0 = (int)pa * a.sh - a.ph, iw0 = (int)(pix - pa * a.PW) * a.sw - a.pw;
+      const int ih0 = (int)pa * a.sh, iw0 = (int)(pix - pa * a.PW) * a.sw;
       const uint32_t base = n * (uint32_t)a.in_img_stride + g * (uint32_t)a.in_grp_stride;
-      for (int c = cc_first * 16; c < cc_end * 16 && c < a.Cg_in; ++c)
-        for (int tp = 0; tp < T; ++tp) {
-          const int ih = ih0 + tp / a.TW * a.dh, iw = iw0 + tp % a.TW * a.dw;
+      constexpr int kChan = COLS ? 64 : 16;  // channels of a chunk
+      for (int c = cc_first * kChan; c < cc_end * kChan && c < (FOLD || COLS ? a.fold.V : a.Cg_in); ++c)
+        for (int tp = 0; tp < (COLS ? 1 : T); ++tp) {
+          int ih = ih0 + tp / a.TW * a.dh, iw = iw0 + tp % a.TW * a.dw, ci = c;
+          if (FOLD || COLS) {
+            ci = c / a.fold.ff;
+            ih = ih * a.fold.Uh + c % a.fold.ff / a.fold.fw * a.fold.dh;
+            iw = iw * a.fold.Uw + c % a.fold.ff % a.fold.fw * a.fold.dw;
+          }
+          ih -= a.ph;
+          iw -= a.pw;
           const bool in = (uint32_t)ih < (uint32_t)a.IH && (uint32_t)iw < (uint32_t)a.IW;
-          const float b = in ? a.in[base + (uint32_t)c * (uint32_t)a.IHW + (uint32_t)ih * a.IW + iw] : 0.f;
-          const int chunk = c / 16 - cc_first, st = chunk * SPC + tp / C::TPS;
-          const uint32_t grp = (uint32_t)((c % 16) / 8 + 2 * (tp % C::TPS));
+          const float b = in ? a.in[base + (uint32_t)ci * (uint32_t)a.IHW + (uint32_t)ih * a.IW + iw] : 0.f;
+          const int tq = COLS ? c % 64 / 16 : tp;  // the tap, or the group of 16 channels in its place
+          const int st = (c / kChan - cc_first) * SPC + tq / C::TPS;
+          const uint32_t grp = (uint32_t)((c % 16) / 8 + 2 * (tq % C::TPS));
           const char* frag = Ag + (size_t)(uint32_t)st * C::STEP + (uint32_t)(wm * MB) * 3u * C::FRAG + (grp * MT * 16u + (uint32_t)(c % 8) * 2u);
 #pragma unroll
           for (int i = 0; i < MB; ++i)
@@ -385,34 +430,31 @@ __global__ __launch_bounds__(256) void pack_split_kernel(const PackArgs a, int b
   const int m_tile = (int)(lin % (uint32_t)m_tiles), g = (int)(lin / (uint32_t)m_tiles);
   const int m = (m_tile * blocks + blk) * MT + lane % MT, kgrp = lane / MT;
   const int chunk = step / spc, tap = (step % spc) * tps + (kgrp >> 1);
-  const int c0 = chunk * 16 + (kgrp & 1) * 8;
-  // the element of channel c0 and the stride to the next channel; i < 0: no such tap
-  size_t src = 0, stride = 0;
-  int limit = 0;  // channels of the reduction
-  if (m < a.Mrows && tap < T) {
-    if (a.mode == 0) {
-      limit = a.Cg;
-      src = ((size_t)g * a.Kg + m) * ((size_t)a.Cg * T) + (size_t)c0 * T + tap;
-      stride = T;
-    } else {
-      const int qh = a.Qh - 1 - tap / a.Qw, qw = a.Qw - 1 - tap % a.Qw;
-      const int nv = a.nvh * a.nvw, c = m / nv, mr = m % nv;
-      int rh = mr / a.nvw, rw = mr % a.nvw;
-      if (a.tab_h) rh = a.phase_h[rh];
-      if (a.tab_w) rw = a.phase_w[rw];
-      const int th = a.sh * a.eh * qh + rh, tw = a.sw * a.ew * qw + rw;
-      const int i = th / a.dh, j = tw / a.dw;
-      if (i * a.dh == th && j * a.dw == tw && i < a.kh && j < a.kw) {
-        limit = a.Kg;
-        stride = (size_t)a.Cg * a.kh * a.kw;
-        src = ((size_t)g * a.Kg + c0) * stride + ((size_t)c * a.kh + i) * a.kw + j;
-      }
-    }
-  }
+  const int subs = a.fold.subs, c0 = (subs ? chunk * subs + tap : chunk) * 16 + (kgrp & 1) * 8;
+  const int fh = a.fold.fh, fw = a.fold.fw, ff = a.fold.ff;
+  // backward data: phases of this row
+  const int nv = a.mode ? a.nvh * a.nvw : 1, mc = m / nv, mr = m % nv;
+  int rh = a.mode ? mr / a.nvw : 0, rw = a.mode ? mr % a.nvw : 0;
+  if (a.mode && a.tab_h) rh = a.phase_h[rh];
+  if (a.mode && a.tab_w) rw = a.phase_w[rw];
   uint16_t out[3][8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    const float v = c0 + e < limit ? a.w[src + e * stride] : 0.f;
+    // channel (c, ir, jr) and grid tap (it, jt) -> channel c of the gather under its tap (it*fh + ir, jt*fw + jr); in the
+    // column form the tap is the group of channels and every tap is in the channel
+    const int c = (c0 + e) / ff, rem = (c0 + e) % ff;
+    const int i = (subs ? 0 : tap / a.tTW * fh) + rem / fw, j = (subs ? 0 : tap % a.tTW * fw) + rem % fw;
+    float v = 0.f;
+    if (m < a.Mrows && tap < T && c0 + e < a.fold.V) {
+      if (a.mode == 0) {
+        if (i < a.kh && j < a.kw) v = a.w[((((size_t)g * a.Kg + m) * a.Cg + c) * a.kh + i) * a.kw + j];
+      } else {
+        const int th = a.sh * a.eh * (a.Qh - 1 - i) + rh, tw = a.sw * a.ew * (a.Qw - 1 - j) + rw;
+        const int ki = th / a.dh, kj = tw / a.dw;
+        if (ki * a.dh == th && kj * a.dw == tw && ki < a.kh && kj < a.kw)
+          v = a.w[((((size_t)g * a.Kg + c) * a.Cg + mc) * a.kh + ki) * a.kw + kj];
+      }
+    }
     split1(v, out[0][e], out[1][e], out[2][e]);
   }
   char* dst = reinterpret_cast<char*>(a.A) + (size_t)(idx >> 6) * 3072u + 16u * lane;
@@ -425,23 +467,32 @@ __global__ __launch_bounds__(256) void pack_split_kernel(const PackArgs a, int b
   }
 }
 
-template <int MT, int MB, int NB, int WM, int WN, int EPT>
+template <int MT, int MB, int NB, int WM, int WN, int EPT, SplitForm FORM = IMAGE>
 int launch_split_e(const CorrArgs& a, hipStream_t s) {
   using C = SplitCfg<MT, MB, NB, WM, WN>;
-  const size_t tables = 16 * (C::BM + C::BN), patch = 96 * (size_t)a.PSZ * a.patch_stages;
+  const size_t tables = 16 * (C::BM + C::BN);
+  const size_t patch = 96 * (size_t)a.PSZ * a.patch_stages + (FORM == FOLDED ? a.NS * 16 * sizeof(FoldEntry) : 0);
   const size_t lds = patch > tables ? patch : tables;
   static LdsOptIn opt_in;  // more than 64 KB of LDS needs an explicit opt-in, once per process
-  if (const int e = lds_opt_in(opt_in, &corr_split_kernel<MT, MB, NB, WM, WN, EPT>, 160 * 1024)) return e;
+  if (const int e = lds_opt_in(opt_in, &corr_split_kernel<MT, MB, NB, WM, WN, EPT, FORM>, 160 * 1024)) return e;
   const uint32_t blocks = (uint32_t)a.G * a.m_tiles * a.col_tiles * a.ksplit;
-  hipLaunchKernelGGL((corr_split_kernel<MT, MB, NB, WM, WN, EPT>), dim3(blocks), dim3(kThreads), lds, s, a);
+  hipLaunchKernelGGL((corr_split_kernel<MT, MB, NB, WM, WN, EPT, FORM>), dim3(blocks), dim3(kThreads), lds, s, a);
   return (int)hipGetLastError();
 }
 
+// The folded and the column forms: one instance per 128-column tile, for the largest patch; no rule leads a 1x1 kernel to
+// the 32-row tile.
 template <int MT, int MB, int NB, int WM, int WN>
 int launch_split_t(const CorrArgs& a, hipStream_t s) {
-  constexpr int BN = SplitCfg<MT, MB, NB, WM, WN>::BN;
-  if constexpr (BN <= 128)
+  constexpr int BM = SplitCfg<MT, MB, NB, WM, WN>::BM, BN = SplitCfg<MT, MB, NB, WM, WN>::BN;
+  if constexpr (BN <= 128 && BM >= 64) {
+    if (a.fold.subs) return launch_split_e<MT, MB, NB, WM, WN, 4, COLUMNS>(a, s);
+  }
+  if constexpr (BN <= 128) {
+    if (a.fold.ff > 1) return launch_split_e<MT, MB, NB, WM, WN, 4, FOLDED>(a, s);
     if (split_patch_units(a.PSZ, BN) == 2) return launch_split_e<MT, MB, NB, WM, WN, 2>(a, s);
+  }
+  if (a.fold.subs || a.fold.ff > 1) return (int)hipErrorInvalidValue;
   if (split_patch_units(a.PSZ, BN) == 3) return launch_split_e<MT, MB, NB, WM, WN, 3>(a, s);
   return launch_split_e<MT, MB, NB, WM, WN, 4>(a, s);
 }

@@ -116,6 +116,44 @@ __device__ __forceinline__ void mfma_split(const u32x4 (&a)[3], const u32x4 (&b)
   for (int j = 0; j < NB; ++j) mfma_bf16<MT>(a[0], b[j][0], hi[j]);
 }
 
+// Folded layers (SplitFold): where channel v of a grid position sits relative to the position's own pixel -- byte offset, and
+// row and column displacement in one word (15 and 16 bits; a channel past the last one fails every row test).
+struct FoldEntry {
+  uint32_t off, rc;
+};
+
+__device__ __forceinline__ int fold_row(const FoldEntry& f) { return (int)(f.rc >> 16) << (f.rc >> 31 ? 13 : 0); }
+__device__ __forceinline__ int fold_col(const FoldEntry& f) { return (int)(f.rc & 0xffffu); }
+
+__device__ __forceinline__ void fill_fold_table(FoldEntry* tab, int count, const SplitFold& f, int width, int plane, int t,
+                                                int threads) {
+  for (int v = t; v < count; v += threads) {
+    const uint32_t c = mdiv((uint32_t)v, f.mFF), rem = (uint32_t)v - c * (uint32_t)f.ff;
+    const uint32_t ir = mdiv(rem, f.mFw), jr = rem - ir * (uint32_t)f.fw;
+    FoldEntry e;
+    e.off = 4u * (c * (uint32_t)plane + ir * (uint32_t)(f.dh * width) + jr * (uint32_t)f.dw);
+    e.rc = v < f.V ? (ir * (uint32_t)f.dh) << 16 | jr * (uint32_t)f.dw : 0xffff0000u;
+    tab[v] = e;
+  }
+}
+
+// Eight channels of the grid position whose own pixel has byte offset `at` (modulo 2^32), row and column: two quads of four
+// pixels side by side that start on a column of a multiple of four, so only the right border of the image cuts a quad
+// (what lies behind the blob reads as zero element by element).
+__device__ __forceinline__ void load_folded(__amdgpu_buffer_rsrc_t rsrc, const FoldEntry* fe, uint32_t at, int row, int col,
+                                            int H, int W, float (&v)[8]) {
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const FoldEntry f = fe[4 * q];
+    const int c = col + fold_col(f);
+    const bool ok = ((uint32_t)(row + fold_row(f)) < (uint32_t)H) & ((uint32_t)c < (uint32_t)W);
+    const u32x4 x =
+        __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, ok ? at + f.off : 0x80000000u, 0, 0));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[4 * q + e] = c + e < W ? __builtin_bit_cast(float, (uint32_t)x[e]) : 0.f;
+  }
+}
+
 __device__ __forceinline__ bool not_finite(float v) {
   return (__builtin_bit_cast(uint32_t, v) & 0x7f800000u) == 0x7f800000u;
 }

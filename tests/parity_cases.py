@@ -193,26 +193,36 @@ VARIANT_CASES = [
 # The kernels on three-way split bf16 operands (problems of 0.4 / 1 GFLOP and more): every tile x patch size class of the
 # correlation and of the filter gradient, both passes, both epilogue forms with and without a split reduction, strides,
 # dilations, groups, one and two patch stages, odd tap counts, ragged channels, images whose pixel count is no multiple of
-# eight (test_split_parity_gpu.py checks on the CPU that together they select all of that).
+# eight, and the folded and column forms of the correlation on every tile that has them (test_split_parity_gpu.py checks on
+# the CPU that together they select all of that).
 SPLIT_CASES = [
-    P(27, 170, 27, 10, 158, 4, 4, 2, 1, 2, 3, 2, 2, 2),
-    P(27, 58, 34, 28, 84, 3, 3, 1, 1, 0, 1, 1, 1, 2),
-    P(39, 91, 32, 9, 68, 4, 4, 1, 1, 0, 1, 2, 2, 1),
-    P(8, 132, 26, 22, 110, 4, 4, 1, 1, 3, 0, 1, 1, 2),
-    P(2, 115, 40, 50, 127, 3, 3, 1, 1, 0, 2, 1, 1, 1),
-    P(21, 128, 21, 17, 70, 5, 5, 1, 1, 1, 4, 2, 2, 2),
-    P(27, 186, 15, 7, 169, 3, 5, 1, 1, 1, 0, 1, 1, 1),
-    P(33, 60, 37, 24, 25, 4, 3, 1, 1, 1, 2, 1, 1, 1),
-    P(12, 160, 36, 16, 86, 3, 5, 2, 1, 1, 0, 1, 1, 2),
-    P(12, 105, 24, 10, 123, 4, 4, 1, 1, 0, 0, 1, 1, 1),
-    P(5, 86, 40, 17, 172, 3, 5, 1, 1, 1, 0, 1, 1, 1),
+    P(23, 186, 28, 15, 78, 3, 5, 1, 1, 0, 1, 2, 2, 2),
+    P(13, 6, 150, 159, 248, 7, 8, 2, 4, 0, 4, 1, 1, 2),
+    P(19, 122, 7, 42, 71, 5, 3, 1, 1, 1, 1, 1, 1, 1),
+    P(17, 376, 29, 40, 405, 1, 1, 2, 1, 0, 0, 1, 1, 1),
+    P(24, 94, 33, 13, 194, 3, 3, 1, 1, 2, 1, 2, 2, 2),
+    P(4, 150, 37, 16, 113, 3, 5, 1, 1, 2, 1, 1, 1, 1),
+    P(13, 76, 19, 33, 58, 3, 5, 1, 1, 1, 4, 1, 1, 1),
+    P(17, 95, 19, 24, 55, 5, 5, 2, 1, 1, 3, 1, 1, 1),
+    P(4, 180, 9, 59, 125, 3, 5, 1, 1, 1, 3, 1, 1, 1),
+    P(33, 142, 37, 12, 56, 4, 3, 1, 1, 1, 0, 1, 1, 2),
+    P(6, 1312, 8, 26, 1532, 1, 1, 1, 1, 0, 1, 1, 1, 2),
+    P(18, 155, 35, 7, 95, 3, 5, 1, 1, 2, 0, 1, 1, 1),
+    P(9, 31, 17, 44, 187, 4, 3, 1, 1, 3, 3, 1, 1, 1),
     P(24, 64, 15, 40, 98, 3, 3, 1, 1, 0, 1, 1, 1, 1),
-    P(7, 127, 12, 10, 114, 5, 5, 1, 1, 2, 4, 2, 2, 1),
-    P(3, 95, 39, 26, 103, 7, 1, 1, 1, 4, 1, 1, 1, 1),
-    P(13, 175, 7, 14, 110, 3, 3, 1, 1, 2, 0, 1, 1, 1),
-    P(30, 138, 25, 8, 112, 3, 3, 2, 2, 0, 2, 1, 1, 1),
-    P(29, 46, 34, 8, 102, 7, 1, 1, 1, 4, 0, 1, 1, 1),
-    P(14, 48, 33, 31, 115, 7, 1, 1, 1, 1, 0, 1, 1, 1),
+    P(27, 2, 187, 135, 129, 12, 11, 4, 4, 2, 0, 1, 1, 1),
+    P(4, 180, 23, 13, 108, 3, 5, 1, 1, 1, 3, 1, 1, 2),
+    P(8, 26, 11, 47, 198, 4, 3, 1, 1, 0, 3, 1, 1, 1),
+    P(27, 32, 15, 16, 30, 7, 3, 1, 1, 5, 3, 1, 1, 1),
+    P(40, 16, 37, 15, 123, 5, 1, 1, 1, 1, 1, 1, 1, 1),
+    P(5, 58, 25, 48, 154, 3, 3, 1, 1, 0, 3, 1, 1, 2),
+    P(10, 79, 36, 9, 105, 7, 1, 1, 1, 4, 1, 1, 1, 1),
+    P(19, 11, 29, 46, 120, 7, 1, 1, 1, 5, 0, 1, 1, 1),
+    P(18, 2, 186, 192, 104, 12, 12, 4, 4, 3, 4, 1, 1, 2),
+    P(8, 705, 39, 21, 284, 1, 1, 1, 1, 0, 0, 1, 1, 1),
+    P(8, 359, 33, 31, 445, 1, 1, 1, 1, 1, 0, 1, 1, 1),
+    P(58, 2, 158, 50, 28, 20, 11, 2, 4),
+    P(8, 1523, 50, 38, 54, 1, 1),
 ]
 
 
