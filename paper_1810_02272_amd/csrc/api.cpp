@@ -190,12 +190,12 @@ void corr_variant_name(char* buf, size_t len, int32_t tile, const CorrArgs& a, i
     snprintf(buf, len, "%s[m%d,e%c](S=%d,L=%d)", corr_tile_name(tile), a.bounds_mode, e, a.ksplit, launches);
 }
 
-// "corrsplit_<tile>[p<patch units per thread>, fold<taps per channel> or cols<channel groups>,e<epilogue form>](S,L)"
+// "corrsplit_<tile>[p<patch units per thread>, fold<taps per channel>, cols or rows<channel groups>,e<epilogue form>](S,L)"
 void split_variant_name(char* buf, size_t len, int32_t tile, const CorrArgs& a, int zero_fill) {
   int32_t bm, bn, mt;
   split_tile_shape(tile, &bm, &bn, &mt);
   const char e = a.simple_epilogue ? 's' : ((uint32_t)a.out_elems < (1u << 29) ? 'r' : 'p');
-  snprintf(buf, len, "corrsplit_m%d_%dx%d[%s%d,e%c](S=%d,L=%d)", mt, bm, bn, a.fold.subs ? "cols" : a.fold.ff > 1 ? "fold" : "p",
+  snprintf(buf, len, "corrsplit_m%d_%dx%d[%s%d,e%c](S=%d,L=%d)", mt, bm, bn, a.fold.subs ? a.fold.pixels ? "rows" : "cols" : a.fold.ff > 1 ? "fold" : "p",
            a.fold.subs ? a.fold.subs : a.fold.ff > 1 ? a.fold.ff : split_patch_units(a.PSZ, bn), e,
            a.ksplit, 2 + (a.ksplit > 1) + (zero_fill != 0));
 }
@@ -554,9 +554,9 @@ size_t configure_split(const CorrArgs& base, const PackArgs& pbase, int64_t cg_i
   if (base.THW == 1) {
     // 256 -> 256 at 14x14, batch 64, 1.6 GFLOP: level; 344 -> 347 at 43x38, batch 23, 9 GFLOP: 94 -> 83 us.  Shorter reductions
     // want more tiles: 307 -> 314 at 98x98, 5.6 GFLOP: 60 -> 65; the filter gradient of a 128 x 9216 -> 4096 inner product,
-    // whose reduction are the 128 rows, 9.7 GFLOP: 106 -> 79
+    // whose reduction are the 128 rows, 9.7 GFLOP: 106 -> 79.  64 rows: 54 and 57, 4.8 GFLOP
     column_grid(cg_in, base.sh, base.sw, grid);
-    if (flops >= (base.Kred < 320 ? 6e9 : 2.5e9)) plan = plan_split(base, grid, out_elems);
+    if (base.Mrows > 64 && flops >= (base.Kred < 320 ? 6e9 : 2.5e9)) plan = plan_split(base, grid, out_elems);
   } else if (cg_in * 100 >= round_up(cg_in, 16) * 70) {
     plain_grid(cg_in, kh, kw, base.sh, base.sw, base.dh, base.dw, grid);
     if (base.THW >= 3 && base.Kred >= 256) plan = plan_split(base, grid, out_elems);
@@ -599,10 +599,12 @@ size_t configure_split(const CorrArgs& base, const PackArgs& pbase, int64_t cg_i
   a.NS = (int32_t)chunks;
   a.PH = base.P / base.PW;
   a.Nimg = (int32_t)n_img;
-  a.PWID = columns ? bn : (int32_t)plan.w.pitch;  // columns: from one group of 16 channels to the next
+  const bool pixels = columns && base.IHW == 1 && base.P == 1 && base.ph == 0 && base.pw == 0;
+  a.fold.pixels = pixels;
+  a.PWID = pixels ? bn + 1 : columns ? bn : (int32_t)plan.w.pitch;  // columns: from one group of 16 channels to the next
   a.share_w = (int32_t)plan.w.share;
   a.share_h = (int32_t)plan.h.share;
-  a.PSZ = (int32_t)plan.psz;
+  a.PSZ = pixels ? 4 * a.PWID : (int32_t)plan.psz;
   a.patch_stages = plan.psz <= 416 ? 2 : 1;  // two workgroups per compute unit either way
   a.mPWID = make_magic((uint32_t)a.PWID);
   a.mRSEG = make_magic((uint32_t)(columns ? 1 : plan.h.pitch));
@@ -842,6 +844,43 @@ int run_backward_data(const conv_desc* d, const float* w, const float* dy, float
     r.beta = beta;
     e = launch_reduce(r, hip_stream);
   }
+  return e ? record_hip_error(e) : CONV_OK;
+}
+
+size_t forward_transposed_workspace_bytes(const conv_desc* d) {
+  if (d->fwd_split < 0 || !d->fwd_sp.fold.pixels || !d->fwd_sp.simple_epilogue || d->p.group != 1) return 0;
+  return d->fwd_pack_bytes + (size_t)d->fwd_sp.ksplit * (size_t)d->fwd_sp.out_elems * 4;
+}
+
+int run_forward_transposed(const conv_desc* d, const float* x, const float* w, float* y, void* ws, size_t ws_bytes,
+                           void* hip_stream, const ReduceExtras& extras) {
+  if (!ws || ws_bytes < forward_transposed_workspace_bytes(d)) return CONV_EWORKSPACE;
+  PackArgs k = d->fwd_sp_pack;
+  k.w = w;
+  k.A = static_cast<float*>(ws);
+  int e = launch_pack_split(d->fwd_split, k, hip_stream);
+  if (e) return record_hip_error(e);
+  CorrArgs a = d->fwd_sp;
+  a.A = k.A;
+  a.in = x;
+  a.part = reinterpret_cast<float*>(static_cast<char*>(ws) + d->fwd_pack_bytes);
+  a.out = a.part;
+  a.OWd = d->p.n;  // a row of the output is one channel of all images
+  a.out_img_stride = 1;
+  e = launch_corr_split(d->fwd_split, a, hip_stream);
+  if (e) return record_hip_error(e);
+  ReduceArgs r = {};
+  r.part = a.part;
+  r.dst = y;
+  r.count = a.out_elems;
+  r.S = a.ksplit;
+  r.bias = extras.bias;
+  r.chan_elems = extras.chan_elems;
+  r.channels = extras.channels;
+  r.mChanElems = make_magic(r.chan_elems);
+  r.mChannels = make_magic(r.channels);
+  r.relu = extras.relu;
+  e = launch_reduce(r, hip_stream);
   return e ? record_hip_error(e) : CONV_OK;
 }
 

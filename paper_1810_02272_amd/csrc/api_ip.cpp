@@ -4,7 +4,9 @@
 //   forward          y[m][o]  = x w^T      = filter gradient  (dy' = x,  x' = w)      + bias/ReLU in its reduce
 //   backward data    dx[m][k] = dz w       = forward          (w' = dz,  x' = w)
 //   backward filter  dw[o][k] = dz^T x     = backward data    (w' = dz,  dy' = x)     + beta
-// so every operand is read along its contiguous axis and no transposed copy is made.
+// so every operand is read along its contiguous axis and no transposed copy is made.  A forward pass large enough for the
+// split kernel is that of a second problem instead, with its result transposed: num_output images of one pixel and k
+// channels (w), whose output channels are the m rows.
 #include <stdio.h>
 #include <string.h>
 
@@ -19,6 +21,7 @@ using namespace mi355conv;
 struct ip_desc {
   ip_params_t p;
   conv_desc_t* inner;  // null when m == 0
+  conv_desc_t* fwd;    // null: the forward pass is inner's filter gradient
   ColSumArgs cs;
   size_t cs_ws, ws_bytes;
   char names[320];
@@ -66,6 +69,21 @@ int ip_desc_create(ip_desc_t** out, const ip_params_t* pp) {
       return rc;
     }
     conv_desc_workspace_bytes(d->inner, &d->ws_bytes);
+    // Where it is ahead, m x k -> num_output: 128 x 9216 -> 4096 98 -> 82 us, 200 x 9216 -> 4096 179 -> 111, 2500 x 1300 ->
+    // 2500 185 -> 140, 1000 x 1500 -> 1500 56 -> 51; not on fewer rows (64 x 9216 -> 4096: 53 and 58), shorter reductions
+    // (8192 x 512 -> 512: 55 and 67) and smaller problems (150 x 9000 -> 1000, 2.7 GFLOP: 39 and 45).
+    if (2.0 * M * K * O >= 4e9 && M >= 96 && K >= 1024) {
+      c.n = p.num_output;
+      c.c = p.k;
+      c.w = 1;
+      size_t need = 0;
+      if (conv_desc_create(&d->fwd, &c) == CONV_OK) need = forward_transposed_workspace_bytes(d->fwd);
+      if (need == 0 && d->fwd) {
+        conv_desc_destroy(d->fwd);
+        d->fwd = nullptr;
+      }
+      if (need > d->ws_bytes) d->ws_bytes = need;
+    }
   }
   // bias gradient: column sums of dz[m][num_output], the rows split so that the grid has a few
   // hundred workgroups
@@ -82,8 +100,13 @@ int ip_desc_create(ip_desc_t** out, const ip_params_t* pp) {
   if (d->cs_ws > d->ws_bytes) d->ws_bytes = d->cs_ws;
   const char* in = d->inner ? conv_desc_kernel_names(d->inner) : "";
   const bool one_launch = M * O * 4 <= ((int64_t)4 << 20);  // see ip_backward_bias
+  std::string fwd = field(d->fwd ? conv_desc_kernel_names(d->fwd) : in, d->fwd ? "fwd=" : "bwd_filter=");
+  if (d->fwd) {  // inner's filter gradient on the split correlation; the reduce kernel runs for one slice as well
+    fwd.replace(fwd.rfind("L="), std::string::npos, "L=3)");
+    fwd.insert(0, "wgrad_on_");
+  }
   snprintf(d->names, sizeof(d->names), "fwd=%s;bwd_data=%s;bwd_filter=%s;bwd_bias=colsum(S=%d,L=%d)",
-           field(in, "bwd_filter=").c_str(), field(in, "fwd=").c_str(), field(in, "bwd_data=").c_str(),
+           fwd.c_str(), field(in, "fwd=").c_str(), field(in, "bwd_data=").c_str(),
            one_launch ? 1 : cs.S, one_launch ? 1 : 2);
   *out = d;
   return CONV_OK;
@@ -92,6 +115,7 @@ int ip_desc_create(ip_desc_t** out, const ip_params_t* pp) {
 int ip_desc_destroy(ip_desc_t* d) {
   if (!d) return CONV_EINVAL;
   if (d->inner) conv_desc_destroy(d->inner);
+  if (d->fwd) conv_desc_destroy(d->fwd);
   delete d;
   return CONV_OK;
 }
@@ -115,6 +139,7 @@ int ip_forward(const ip_desc_t* d, const float* x, const float* w, const float* 
   ex.chan_elems = 1;
   ex.channels = d->p.num_output;
   ex.relu = d->p.relu;
+  if (d->fwd) return run_forward_transposed(d->fwd, /*x'=*/w, /*w'=*/x, y, ws, ws_bytes, hip_stream, ex);
   return run_backward_filter(d->inner, /*x'=*/w, /*dy'=*/x, /*dw'=*/y, 0.f, ws, ws_bytes, hip_stream, ex);
 }
 

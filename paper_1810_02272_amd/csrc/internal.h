@@ -49,13 +49,15 @@ constexpr int kMaxPhases = 8;  // phase tables of the backward-data row space (l
 //    stands for the taps (it*fh + ir, jt*fw + jr).  The kernel's strides, dilations and tap counts are then those of the
 //    grid.  Channels 4q .. 4q+3 are four pixels of a row from a column of a multiple of four on.
 //  - The columns (1x1 kernels, subs = 4; Uh, Uw = the strides): the patch is no image but the tile's columns, once for each
-//    of four groups of 16 channels, which take the place of taps.
+//    of four groups of 16 channels, which take the place of taps.  The channels of images of one
+//    pixel are contiguous (pixels = 1: the column form's wide loads).
 struct SplitFold {
   int32_t fh, fw, ff;  // ff = fh * fw
   int32_t Uh, Uw;
   int32_t dh, dw;      // dilations of the layer
   int32_t V;           // channels: those of the group times ff
   int32_t subs;        // 0, or the groups of 16 channels of a chunk
+  int32_t pixels;      // column form of unpadded images of one pixel
   Magic mFF, mFw;
 };
 
@@ -386,6 +388,11 @@ struct ReduceExtras {
 // (it runs as the same three contractions with the operand roles exchanged).
 int run_forward(const conv_desc* d, const float* x, const float* w, const float* bias, float* y, void* ws,
                 size_t ws_bytes, void* stream);
+// The forward pass of 1x1 kernels over n images of one pixel with the result transposed, y[num_output][n], and the reduce
+// kernel's bias and ReLU; 0 bytes of workspace: this layer does not have it.
+size_t forward_transposed_workspace_bytes(const conv_desc* d);
+int run_forward_transposed(const conv_desc* d, const float* x, const float* w, float* y, void* ws, size_t ws_bytes,
+                           void* stream, const ReduceExtras& extras);
 int run_backward_data(const conv_desc* d, const float* w, const float* dy, float* dx, float beta, void* ws,
                       size_t ws_bytes, void* stream);
 // db non-null: also db = beta*db + row sums of dy, from the same read of dy

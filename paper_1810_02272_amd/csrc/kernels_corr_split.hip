@@ -49,7 +49,7 @@ struct SplitCfg {
   static_assert(WM * WN == 4, "four waves per workgroup");
 };
 
-enum SplitForm { IMAGE, FOLDED, COLUMNS };
+enum SplitForm { IMAGE, FOLDED, COLUMNS, PIXELS };  // PIXELS: COLUMNS over images of one pixel
 
 // EPT: patch units (one position x 8 channels) per thread, 2*PSZ <= 256*EPT.
 // FORM: what the patch holds (SplitFold in internal.h).
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
   using C = SplitCfg<MT, MB, NB, WM, WN>;
     using M = Mfma<MT>;
   constexpr int BM = C::BM, BN = C::BN;
-  constexpr bool FOLD = FORM == FOLDED, COLS = FORM == COLUMNS;
+  constexpr bool FOLD = FORM == FOLDED, PIX = FORM == PIXELS, COLS = FORM == COLUMNS || PIX;
 
   extern __shared__ __align__(16) float smem[];  // one or two patch stages; the epilogue's tables at the end
 
@@ -130,6 +130,11 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
   }
   // Unfolded: the byte offset of the unit's first channel in chunk 0.  Folded: that of its position, whose row and
   // column the channels are checked from.
+  // Of images of one pixel the channels are contiguous: a unit is two 16-byte loads, eight neighbouring lanes take the
+  // eight units of a column (256 contiguous bytes), and the groups' pitch of an odd number of 48-byte positions spreads
+  // their stores over the banks.
+  const uint32_t slot0 = PIX ? (t & 1u) * (uint32_t)a.PSZ + ((t >> 1) & 3u) * (uint32_t)a.PWID + (uint32_t)(t >> 3) : (uint32_t)t;
+  constexpr uint32_t kSlotStep = PIX ? kThreads / 8 : kThreads;  // a thread's units in the stage
   uint32_t psrc[EPT];
   int prow_in[FOLD ? EPT : 1], pcol_in[FOLD ? EPT : 1];
 #pragma unroll
@@ -139,7 +144,10 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
     const uint32_t e = u - hf * (uint32_t)a.PSZ;
     uint32_t src = 0x80000000u;  // beyond the blob (which is at most 2^30 bytes): reads as zero
     if (FOLD) prow_in[r] = -(1 << 28), pcol_in[r] = 0;  // fails every bounds test
-    if (e < patch_elems && u < 2u * (uint32_t)a.PSZ) {
+    if (PIX) {
+      const uint32_t col = col0 + (uint32_t)(t >> 3) + r * kSlotStep;
+      if (col <= col_last) src = 4u * (col * (uint32_t)a.in_img_stride + g * (uint32_t)a.in_grp_stride) + 32u * (t & 7u);
+    } else if (e < patch_elems && u < 2u * (uint32_t)a.PSZ) {
       const uint32_t prow = mdiv(e, a.mPWID);  // COLS: the group of 16 channels
       const uint32_t pcol = e - prow * a.PWID;
       uint32_t n = n0, rin = prow, alo = a0;
@@ -184,6 +192,15 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
         const FoldEntry* fe = fold_tab + (cc * 16 + (int)hf * 8);
         load_folded(in_rsrc, fe, src, prow_in[r], pcol_in[r], a.IH, a.IW, pr[r]);
         __builtin_amdgcn_sched_barrier(0);  // one unit's table entries in registers at a time
+      } else if (PIX) {
+        src += coff;
+        const u32x4 v0 = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(in_rsrc, src, 0, 0));
+        const u32x4 v1 = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(in_rsrc, src + 16u, 0, 0));
+#pragma unroll
+        for (int c4 = 0; c4 < 4; ++c4) {
+          pr[r][c4] = __builtin_bit_cast(float, (uint32_t)v0[c4]);
+          pr[r][4 + c4] = __builtin_bit_cast(float, (uint32_t)v1[c4]);
+        }
       } else {
         src += coff;
 #pragma unroll
@@ -198,8 +215,8 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
 #pragma unroll
     for (int r = 0; r < EPT; ++r) {
       const Split8 s = split8(pr[r], sel);
-      const uint32_t u = t + r * kThreads;
-      if (u < 2u * (uint32_t)a.PSZ) {
+      const uint32_t u = slot0 + r * kSlotStep;
+      if (PIX || u < 2u * (uint32_t)a.PSZ) {
         u32x4* dst = reinterpret_cast<u32x4*>(reinterpret_cast<char*>(smem) + (stage_off + 48u * u));
         dst[0] = s.h;
         dst[1] = s.m;
@@ -486,6 +503,7 @@ template <int MT, int MB, int NB, int WM, int WN>
 int launch_split_t(const CorrArgs& a, hipStream_t s) {
   constexpr int BM = SplitCfg<MT, MB, NB, WM, WN>::BM, BN = SplitCfg<MT, MB, NB, WM, WN>::BN;
   if constexpr (BN <= 128 && BM >= 64) {
+    if (a.fold.pixels) return launch_split_e<MT, MB, NB, WM, WN, 4, PIXELS>(a, s);
     if (a.fold.subs) return launch_split_e<MT, MB, NB, WM, WN, 4, COLUMNS>(a, s);
   }
   if constexpr (BN <= 128) {

@@ -222,7 +222,9 @@ SPLIT_CASES = [
     P(8, 705, 39, 21, 284, 1, 1, 1, 1, 0, 0, 1, 1, 1),
     P(8, 359, 33, 31, 445, 1, 1, 1, 1, 1, 0, 1, 1, 1),
     P(58, 2, 158, 50, 28, 20, 11, 2, 4),
-    P(8, 1523, 50, 38, 54, 1, 1),
+    P(300, 1231, 1, 1, 515, 1, 1, 1, 1, 1, 1),
+    P(767, 1336, 1, 1, 2450, 1, 1, 1, 1, 0, 0, 1, 1, 2),
+    P(2923, 1120, 1, 1, 412, 1, 1),
 ]
 
 

@@ -46,7 +46,8 @@ def test_cases_select_every_variant():
     want |= {(t, u) for t in tiles for u in ("34" if t.endswith("x256") else "234")}
     want |= {("fwd", "s", s) for s in (False, True)} | {("bwd_data", e, s) for e in "sr" for s in (False, True)}
     want |= {(f, t) for f in ("fold", "cols") for t in ("m32_128x128", "m32_64x128", "m32_96x128")} | {("fold", "m32_32x128")}
-    want |= {("fwd", "fold"), ("fwd", "cols"), ("bwd_data", "cols")}
+    want |= {("rows", t) for t in ("m32_128x128", "m32_64x128", "m32_96x128")}
+    want |= {("fwd", "rows"), ("bwd_data", "rows"), ("fwd", "fold"), ("fwd", "cols"), ("bwd_data", "cols")}
     assert want - corr == set()
     assert {(t, u) for t in ("128x9", "128x8", "64x16", "32x28", "32x12", "96x8") for u in "234"} | {"1", "2"} <= wgrad
 
@@ -130,10 +131,11 @@ def test_infinities_nans_and_the_largest_floats(pd, odd):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("beta", [0.0, 1.0])
-@pytest.mark.parametrize("m,k,o", [(333, 1503, 2570), (4100, 333, 965)])
+@pytest.mark.parametrize("m,k,o", [(333, 1503, 2570), (4100, 333, 965), (999, 1503, 1501), (2500, 1300, 2500)])
 def test_inner_product_on_the_column_form(m, k, o, beta):
-    """Ragged rows, columns and channels, the filter gradient in one slice and in several, added to dw or written."""
-    assert "cols" in conv.ip_desc_kernel_names(conv.ip_desc_create(conv.IpParams(m=m, k=k, num_output=o, relu=1)))
+    """Ragged rows, columns and channels, the forward pass in one slice (2500 rows) and in several, the filter gradient too,
+    added to dw or written."""
+    assert "corrsplit" in conv.ip_desc_kernel_names(conv.ip_desc_create(conv.IpParams(m=m, k=k, num_output=o, relu=1)))
     x, w, b, dy = workloads.ip_random_inputs(m, k, o, seed=8100 + m)
     dw0, db0 = workloads.draw((o, k), "normal", 8300 + m), workloads.draw((o,), "normal", 8301 + m)
     run_ip_case(m, k, o, True, 1, x, w, b, dy, beta=beta, dw0=dw0, db0=db0)
