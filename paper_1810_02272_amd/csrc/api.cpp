@@ -191,7 +191,7 @@ void corr_variant_name(char* buf, size_t len, int32_t tile, const CorrArgs& a, i
 }
 
 // "corrsplit_<tile>[p<patch units per thread>, fold<taps per channel>, cols or rows<channel groups>,e<epilogue form>](S,L)"
-void split_variant_name(char* buf, size_t len, int32_t tile, const CorrArgs& a, int zero_fill) {
+void split_variant_name(char* buf, size_t len, int32_t tile, const CorrSplitArgs& a, int zero_fill) {
   int32_t bm, bn, mt;
   split_tile_shape(tile, &bm, &bn, &mt);
   const char e = a.simple_epilogue ? 's' : ((uint32_t)a.out_elems < (1u << 29) ? 'r' : 'p');
@@ -539,7 +539,7 @@ SplitPlan plan_split(const CorrArgs& base, const SplitGrid& grid, int64_t out_el
 // Decides whether corr_split_kernel runs this correlation; fills a, k and the tile.  Returns the bytes of packed
 // weights, 0 if it does not.
 size_t configure_split(const CorrArgs& base, const PackArgs& pbase, int64_t cg_in, int64_t n_img, int64_t out_elems,
-                       CorrArgs& a, PackArgs& k, int32_t& tile) {
+                       CorrSplitArgs& a, PackSplitArgs& k, int32_t& tile) {
   tile = -1;
   const double flops = 2.0 * base.Mrows * base.Kred * (double)base.ncols * base.G;
   if (base.ncols < 1 || (int64_t)base.in_bytes > ((int64_t)1 << 30)) return 0;
@@ -585,8 +585,10 @@ size_t configure_split(const CorrArgs& base, const PackArgs& pbase, int64_t cg_i
   split_tile_shape(tile, &bm, &bn, &mt);
   const bool columns = grid.f.subs != 0;
   const int64_t chunks = ceil_div(grid.f.V, columns ? 64 : 16);
-  a = base;
-  k = pbase;
+  a = CorrSplitArgs();
+  k = PackSplitArgs();
+  static_cast<CorrArgs&>(a) = base;
+  static_cast<PackArgs&>(k) = pbase;
   a.use_patch = 0;
   a.fold = k.fold = grid.f;
   a.sh = (int32_t)grid.sh;
@@ -723,6 +725,23 @@ int32_t configure_wgrad_split(const WgradArgs& w, int64_t N, int64_t K, int64_t 
   return best;
 }
 
+// The split kernel's launches; its partial sums, if any, lie behind the packed weights.
+int launch_split(int32_t tile, const PackSplitArgs& pack, const CorrSplitArgs& plan, size_t pack_bytes, const float* in,
+                 const float* w, const float* bias, float* out, bool accumulate, void* ws, void* stream) {
+  PackSplitArgs k = pack;
+  k.w = w;
+  k.A = static_cast<float*>(ws);
+  if (const int e = launch_pack_split(tile, k, stream)) return e;
+  CorrSplitArgs a = plan;
+  a.A = k.A;
+  a.in = in;
+  a.bias = bias;
+  a.out = out;
+  a.accumulate = accumulate;
+  a.part = reinterpret_cast<float*>(static_cast<char*>(ws) + pack_bytes);
+  return launch_corr_split(tile, a, stream);
+}
+
 }  // namespace
 
 namespace mi355conv {
@@ -754,32 +773,38 @@ int run_forward(const conv_desc* d, const float* x, const float* w, const float*
     return ed ? record_hip_error(ed) : CONV_OK;
   }
   if (d->fwd_ws > 0 && (!ws || ws_bytes < d->fwd_ws)) return CONV_EWORKSPACE;
+  float* const part = reinterpret_cast<float*>(static_cast<char*>(ws) + d->fwd_pack_bytes);
   const bool split = d->fwd_split >= 0;
-  PackArgs k = split ? d->fwd_sp_pack : d->fwd_pack;
-  k.w = w;
-  k.A = static_cast<float*>(ws);
-  k.ktab = reinterpret_cast<KTabEntry*>(k.A + (size_t)k.G * k.KP * k.MP);
-  const bool in_place = d->fwd_thin && d->fwd.use_patch;  // that kernel reads the weight blob itself
-  int e = split ? launch_pack_split(d->fwd_split, k, hip_stream) : in_place ? 0 : launch_pack(k, hip_stream);
+  int e;
+  if (split) {
+    e = launch_split(d->fwd_split, d->fwd_sp_pack, d->fwd_sp, d->fwd_pack_bytes, x, w, bias, y, false, ws, hip_stream);
+  } else {
+    PackArgs k = d->fwd_pack;
+    k.w = w;
+    k.A = static_cast<float*>(ws);
+    k.ktab = reinterpret_cast<KTabEntry*>(k.A + (size_t)k.G * k.KP * k.MP);
+    const bool in_place = d->fwd_thin && d->fwd.use_patch;  // that kernel reads the weight blob itself
+    e = in_place ? 0 : launch_pack(k, hip_stream);
+    if (e) return record_hip_error(e);
+    CorrArgs a = d->fwd;
+    a.A = in_place ? w : k.A;
+    a.ktab = k.ktab;
+    a.in = x;
+    a.bias = bias;
+    a.out = y;
+    a.part = part;
+    e = d->fwd_thin  ? launch_corr_thin(a, hip_stream)
+        : a.use_patch ? launch_corr_patch(d->fwd_tile, a, hip_stream)
+                      : launch_corr(d->fwd_tile, a, hip_stream);
+  }
   if (e) return record_hip_error(e);
-  CorrArgs a = split ? d->fwd_sp : d->fwd;
-  a.A = in_place ? w : k.A;
-  a.ktab = k.ktab;
-  a.in = x;
-  a.bias = bias;
-  a.out = y;
-  a.part = reinterpret_cast<float*>(static_cast<char*>(ws) + d->fwd_pack_bytes);
-  e = split          ? launch_corr_split(d->fwd_split, a, hip_stream)
-      : d->fwd_thin ? launch_corr_thin(a, hip_stream)
-      : a.use_patch ? launch_corr_patch(d->fwd_tile, a, hip_stream)
-                    : launch_corr(d->fwd_tile, a, hip_stream);
-  if (e) return record_hip_error(e);
-  if (a.ksplit > 1) {  // add the split partials and the bias
+  const int32_t ksplit = split ? d->fwd_sp.ksplit : d->fwd.ksplit;
+  if (ksplit > 1) {  // add the split partials and the bias
     ReduceArgs r = {};
-    r.part = a.part;
+    r.part = part;
     r.dst = y;
-    r.count = a.out_elems;
-    r.S = a.ksplit;
+    r.count = d->fwd.out_elems;
+    r.S = ksplit;
     r.beta = 0.f;
     r.bias = bias;
     r.chan_elems = d->OH * d->OW;
@@ -807,40 +832,47 @@ int run_backward_data(const conv_desc* d, const float* w, const float* dy, float
     return ed ? record_hip_error(ed) : CONV_OK;
   }
   if (d->bwd_ws > 0 && (!ws || ws_bytes < d->bwd_ws)) return CONV_EWORKSPACE;
+  float* const part = reinterpret_cast<float*>(static_cast<char*>(ws) + d->bwd_pack_bytes);
   const bool split = d->bwd_split >= 0;
-  PackArgs k = split ? d->bwd_sp_pack : d->bwd_pack;
-  k.w = w;
-  k.A = static_cast<float*>(ws);
-  k.ktab = reinterpret_cast<KTabEntry*>(k.A + (size_t)k.G * k.KP * k.MP);
-  const bool in_place = d->bwd_thin && d->bwd.use_patch;  // that kernel reads the weight blob itself
-  int e = split ? launch_pack_split(d->bwd_split, k, hip_stream) : in_place ? 0 : launch_pack(k, hip_stream);
-  if (e) return record_hip_error(e);
-  CorrArgs a = split ? d->bwd_sp : d->bwd;
-  a.A = in_place ? w : k.A;
-  a.ktab = k.ktab;
-  a.in = dy;
-  a.bias = nullptr;
-  a.out = dx;
-  a.accumulate = beta != 0.f;
-  a.part = reinterpret_cast<float*>(static_cast<char*>(ws) + d->bwd_pack_bytes);
+  const int32_t ksplit = split ? d->bwd_sp.ksplit : d->bwd.ksplit, out_elems = d->bwd.out_elems;
+  int e = 0;
   if (d->bwd_zero_fill) {  // positions no tap reaches: zero the split partials, or dx itself when it is overwritten
-    if (a.ksplit > 1)
-      e = launch_fill_zero(a.part, (size_t)a.ksplit * a.out_elems * 4, hip_stream);
+    if (ksplit > 1)
+      e = launch_fill_zero(part, (size_t)ksplit * out_elems * 4, hip_stream);
     else if (beta == 0.f)
-      e = launch_fill_zero(dx, (size_t)a.out_elems * 4, hip_stream);
+      e = launch_fill_zero(dx, (size_t)out_elems * 4, hip_stream);
     if (e) return record_hip_error(e);
   }
-  e = split          ? launch_corr_split(d->bwd_split, a, hip_stream)
-      : d->bwd_thin ? launch_corr_thin(a, hip_stream)
-      : a.use_patch ? launch_corr_patch(d->bwd_tile, a, hip_stream)
-                    : launch_corr(d->bwd_tile, a, hip_stream);
+  if (split) {
+    e = launch_split(d->bwd_split, d->bwd_sp_pack, d->bwd_sp, d->bwd_pack_bytes, dy, w, nullptr, dx, beta != 0.f, ws,
+                     hip_stream);
+  } else {
+    PackArgs k = d->bwd_pack;
+    k.w = w;
+    k.A = static_cast<float*>(ws);
+    k.ktab = reinterpret_cast<KTabEntry*>(k.A + (size_t)k.G * k.KP * k.MP);
+    const bool in_place = d->bwd_thin && d->bwd.use_patch;  // that kernel reads the weight blob itself
+    e = in_place ? 0 : launch_pack(k, hip_stream);
+    if (e) return record_hip_error(e);
+    CorrArgs a = d->bwd;
+    a.A = in_place ? w : k.A;
+    a.ktab = k.ktab;
+    a.in = dy;
+    a.bias = nullptr;
+    a.out = dx;
+    a.accumulate = beta != 0.f;
+    a.part = part;
+    e = d->bwd_thin  ? launch_corr_thin(a, hip_stream)
+        : a.use_patch ? launch_corr_patch(d->bwd_tile, a, hip_stream)
+                      : launch_corr(d->bwd_tile, a, hip_stream);
+  }
   if (e) return record_hip_error(e);
-  if (a.ksplit > 1) {
+  if (ksplit > 1) {
     ReduceArgs r = {};
-    r.part = a.part;
+    r.part = part;
     r.dst = dx;
-    r.count = a.out_elems;
-    r.S = a.ksplit;
+    r.count = out_elems;
+    r.S = ksplit;
     r.beta = beta;
     e = launch_reduce(r, hip_stream);
   }
@@ -855,25 +887,17 @@ size_t forward_transposed_workspace_bytes(const conv_desc* d) {
 int run_forward_transposed(const conv_desc* d, const float* x, const float* w, float* y, void* ws, size_t ws_bytes,
                            void* hip_stream, const ReduceExtras& extras) {
   if (!ws || ws_bytes < forward_transposed_workspace_bytes(d)) return CONV_EWORKSPACE;
-  PackArgs k = d->fwd_sp_pack;
-  k.w = w;
-  k.A = static_cast<float*>(ws);
-  int e = launch_pack_split(d->fwd_split, k, hip_stream);
-  if (e) return record_hip_error(e);
-  CorrArgs a = d->fwd_sp;
-  a.A = k.A;
-  a.in = x;
-  a.part = reinterpret_cast<float*>(static_cast<char*>(ws) + d->fwd_pack_bytes);
-  a.out = a.part;
-  a.OWd = d->p.n;  // a row of the output is one channel of all images
-  a.out_img_stride = 1;
-  e = launch_corr_split(d->fwd_split, a, hip_stream);
+  float* const part = reinterpret_cast<float*>(static_cast<char*>(ws) + d->fwd_pack_bytes);
+  CorrSplitArgs plan = d->fwd_sp;
+  plan.OWd = d->p.n;  // a row of the output is one channel of all images
+  plan.out_img_stride = 1;
+  int e = launch_split(d->fwd_split, d->fwd_sp_pack, plan, d->fwd_pack_bytes, x, w, nullptr, part, false, ws, hip_stream);
   if (e) return record_hip_error(e);
   ReduceArgs r = {};
-  r.part = a.part;
+  r.part = part;
   r.dst = y;
-  r.count = a.out_elems;
-  r.S = a.ksplit;
+  r.count = plan.out_elems;
+  r.S = plan.ksplit;
   r.bias = extras.bias;
   r.chan_elems = extras.chan_elems;
   r.channels = extras.channels;
@@ -936,19 +960,23 @@ int run_backward_filter(const conv_desc* d, const float* x, const float* dy, flo
   r.mChanElems = make_magic(r.chan_elems);
   r.mChannels = make_magic(r.channels);
   r.relu = extras.relu;
-  if (d->wg_split >= 0 && !d->use_direct) {
-    r.taps = d->wg_sp.khw;
-    r.tap_channels = d->wg_sp.Cg;
-    r.mRow = make_magic((uint32_t)d->wg_sp.Kred);
-    r.mTapChannels = make_magic((uint32_t)d->wg_sp.Cg);
-  }
   if (db) {  // the same launch finishes db from the S * n_tiles shares of the row sums
     r.part2 = empty ? nullptr : a.bias_part;
     r.dst2 = db;
     r.count2 = d->p.num_output;
     r.S2 = empty ? 0 : a.S * a.n_tiles;
   }
-  e = launch_reduce(r, hip_stream);
+  if (d->wg_split >= 0 && !d->use_direct && d->wg_sp.khw > 1) {
+    ReduceTapsArgs rt;
+    static_cast<ReduceArgs&>(rt) = r;
+    rt.taps = d->wg_sp.khw;
+    rt.tap_channels = d->wg_sp.Cg;
+    rt.mRow = make_magic((uint32_t)d->wg_sp.Kred);
+    rt.mTapChannels = make_magic((uint32_t)d->wg_sp.Cg);
+    e = launch_reduce_taps(rt, hip_stream);
+  } else {
+    e = launch_reduce(r, hip_stream);
+  }
   return e ? record_hip_error(e) : CONV_OK;
 }
 

@@ -113,13 +113,17 @@ struct CorrArgs {
   int32_t Nimg;        // images
   int32_t PWID, PSZ;   // patch row length (PW + TW - 1); floats per channel of an LDS patch stage
   Magic mPWID, mRSEG;  // divisions by PWID and by the patch rows of a full image (PH + TH - 1)
-  SplitFold fold;            // corr_split_kernel: what the patch's grid and channels stand for
-  int32_t patch_stages;      // corr_split_kernel: patch stages in LDS (1 or 2)
-  int32_t share_w, share_h;  // corr_split_kernel: padding columns / rows that neighbouring patch rows / images share
   int32_t simple_epilogue;  // one phase per channel and an output of at most 2^30 bytes: offset-only epilogue
   // LDS-staged form of corr_thin_kernel: A is the weight blob itself (no pack kernel); element strides of
   // a GEMM row, a gathered channel and a group in it, and whether the taps run backwards (backward data)
   int32_t w_row_stride, w_chan_stride, w_grp_stride, w_reversed;
+};
+
+// The additions of corr_split_kernel: arguments of its own, or every other launch carries them too.
+struct CorrSplitArgs : CorrArgs {
+  SplitFold fold;            // what the patch's grid and channels stand for
+  int32_t patch_stages;      // patch stages in LDS (1 or 2)
+  int32_t share_w, share_h;  // padding columns / rows that neighbouring patch rows / images share
 };
 
 constexpr int kPatchEPT = 3;  // patch elements per thread and channel: PSZ <= 3 * 256
@@ -145,7 +149,10 @@ struct PackArgs {
   int32_t phase_h[kMaxPhases], phase_w[kMaxPhases];
   int32_t Kred, KP, Mrows, MP;
   int32_t kperm_T;  // 0, or the tap count T: k runs (8-channel chunk, tap, channel in chunk) instead of (c, tap)
-  int32_t split_chunks;  // corr_split_kernel: chunks of 16 channels
+};
+
+struct PackSplitArgs : PackArgs {
+  int32_t split_chunks;  // chunks of 16 channels
   SplitFold fold;
 };
 
@@ -213,10 +220,12 @@ struct ReduceArgs {
   int32_t chan_elems, channels;
   Magic mChanElems, mChannels;
   int32_t relu;  // clamp the finished value at zero from below
-  // partials in the order [row][tap][channel] of wgrad_split_kernel, dst in that of the weight blob, [row][channel][tap]
-  // (taps 0: the same order)
-  int32_t taps, tap_channels;
-  Magic mRow, mTapChannels;  // divisions by taps * tap_channels and tap_channels
+};
+
+// Partials in the order [row][tap][channel] of wgrad_split_kernel, dst in that of the weight blob, [row][channel][tap].
+struct ReduceTapsArgs : ReduceArgs {
+  int32_t taps, tap_channels;  // at least two taps
+  Magic mRow, mTapChannels;    // divisions by taps * tap_channels and tap_channels
 };
 
 // Element-wise and column-sum helpers of the InnerProduct layer.
@@ -337,14 +346,15 @@ int launch_corr_patch(int32_t tile, const CorrArgs& a, void* stream);
 // 256-column tiles have no instance for two: 256 columns and their halo need more.
 inline int32_t split_patch_units(int64_t psz, int32_t bn = 128) { return psz <= 256 && bn <= 128 ? 2 : psz <= 384 ? 3 : 4; }
 void split_tile_shape(int32_t tile, int32_t* bm, int32_t* bn, int32_t* mt);
-int launch_pack_split(int32_t tile, const PackArgs& a, void* stream);
-int launch_corr_split(int32_t tile, const CorrArgs& a, void* stream);
+int launch_pack_split(int32_t tile, const PackSplitArgs& a, void* stream);
+int launch_corr_split(int32_t tile, const CorrSplitArgs& a, void* stream);
 void wgrad_split_shape(int32_t tile, int32_t* rows, int32_t* taps);
 int32_t wgrad_split_chunk_runs();
 int launch_wgrad_split(int32_t tile, const WgradSplitArgs& a, void* stream);
 int launch_corr_thin(const CorrArgs& a, void* stream);  // Mrows <= 4, offset-only epilogue, no split
 int launch_wgrad(int32_t tile, const WgradArgs& a, void* stream);
 int launch_reduce(const ReduceArgs& a, void* stream);
+int launch_reduce_taps(const ReduceTapsArgs& a, void* stream);
 int launch_bias_grad(const BiasGradArgs& a, void* stream);
 int launch_fill_zero(void* dst, size_t bytes, void* stream);  // bytes a multiple of 4
 // pass: 0 forward, 1 backward data (dx overwritten), 2 filter-gradient partials
@@ -417,8 +427,8 @@ struct conv_desc {
   size_t fwd_ws, fwd_pack_bytes;
   // forward on the bf16 matrix instructions (fwd_split: its SplitTile, or -1: the fields above)
   int32_t fwd_split, bwd_split;
-  mi355conv::CorrArgs fwd_sp, bwd_sp;
-  mi355conv::PackArgs fwd_sp_pack, bwd_sp_pack;
+  mi355conv::CorrSplitArgs fwd_sp, bwd_sp;
+  mi355conv::PackSplitArgs fwd_sp_pack, bwd_sp_pack;
   // backward data
   int32_t bwd_tile;
   mi355conv::CorrArgs bwd;

@@ -54,7 +54,7 @@ enum SplitForm { IMAGE, FOLDED, COLUMNS, PIXELS };  // PIXELS: COLUMNS over imag
 // EPT: patch units (one position x 8 channels) per thread, 2*PSZ <= 256*EPT.
 // FORM: what the patch holds (SplitFold in internal.h).
 template <int MT, int MB, int NB, int WM, int WN, int EPT, SplitForm FORM>
-__global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) void corr_split_kernel(const CorrArgs a) {
+__global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) void corr_split_kernel(const CorrSplitArgs a) {
   using C = SplitCfg<MT, MB, NB, WM, WN>;
     using M = Mfma<MT>;
   constexpr int BM = C::BM, BN = C::BN;
@@ -433,7 +433,7 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
 
 // Packs the weights into A fragments: thread = (group, m tile, step, row block, lane), eight k values each.
 template <int MT>
-__global__ __launch_bounds__(256) void pack_split_kernel(const PackArgs a, int blocks, int m_tiles, uint32_t total) {
+__global__ __launch_bounds__(256) void pack_split_kernel(const PackSplitArgs a, int blocks, int m_tiles, uint32_t total) {
   const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
   if (idx >= total) return;
   const int lane = idx & 63;
@@ -485,7 +485,7 @@ __global__ __launch_bounds__(256) void pack_split_kernel(const PackArgs a, int b
 }
 
 template <int MT, int MB, int NB, int WM, int WN, int EPT, SplitForm FORM = IMAGE>
-int launch_split_e(const CorrArgs& a, hipStream_t s) {
+int launch_split_e(const CorrSplitArgs& a, hipStream_t s) {
   using C = SplitCfg<MT, MB, NB, WM, WN>;
   const size_t tables = 16 * (C::BM + C::BN);
   const size_t patch = 96 * (size_t)a.PSZ * a.patch_stages + (FORM == FOLDED ? a.NS * 16 * sizeof(FoldEntry) : 0);
@@ -500,7 +500,7 @@ int launch_split_e(const CorrArgs& a, hipStream_t s) {
 // The folded and the column forms: one instance per 128-column tile, for the largest patch; no rule leads a 1x1 kernel to
 // the 32-row tile.
 template <int MT, int MB, int NB, int WM, int WN>
-int launch_split_t(const CorrArgs& a, hipStream_t s) {
+int launch_split_t(const CorrSplitArgs& a, hipStream_t s) {
   constexpr int BM = SplitCfg<MT, MB, NB, WM, WN>::BM, BN = SplitCfg<MT, MB, NB, WM, WN>::BN;
   if constexpr (BN <= 128 && BM >= 64) {
     if (a.fold.pixels) return launch_split_e<MT, MB, NB, WM, WN, 4, PIXELS>(a, s);
@@ -525,7 +525,7 @@ void split_tile_shape(int32_t tile, int32_t* bm, int32_t* bn, int32_t* mt) {
   *mt = shapes[tile][2];
 }
 
-int launch_corr_split(int32_t tile, const CorrArgs& a, void* stream) {
+int launch_corr_split(int32_t tile, const CorrSplitArgs& a, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   switch (tile) {  //                             MT MB NB WM WN
     case SPLIT_128x128: return launch_split_t<32, 2, 2, 2, 2>(a, s);
@@ -539,7 +539,7 @@ int launch_corr_split(int32_t tile, const CorrArgs& a, void* stream) {
   }
 }
 
-int launch_pack_split(int32_t tile, const PackArgs& a, void* stream) {
+int launch_pack_split(int32_t tile, const PackSplitArgs& a, void* stream) {
   int32_t bm, bn, mt;
   split_tile_shape(tile, &bm, &bn, &mt);
   const int tps = mt == 32 ? 1 : 2, spc = (a.tTHW + tps - 1) / tps, blocks = bm / mt;

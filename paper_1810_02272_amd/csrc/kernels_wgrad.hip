@@ -19,6 +19,8 @@
 // store instructions, two chunks in flight, and a wait for the wave's own loads before each barrier.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "device_utils.h"
 #include "internal.h"
 
@@ -386,8 +388,8 @@ int launch_wgrad_t(const WgradArgs& a, hipStream_t s) {
 // else 1); its four waves each add a contiguous quarter of the splits (four independent chains per
 // lane), and the four quarter sums are combined in a fixed order, so the result does not depend on
 // scheduling.
-template <int V>
-__global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs a) {
+template <int V, typename Args>
+__global__ __launch_bounds__(256) void reduce_kernel(const Args a) {
   struct alignas(4 * V) Vec {
     float v[V];
   };
@@ -446,17 +448,20 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs a) {
     Vec out, old;
     float* const dst = (second ? a.dst2 : a.dst) + i;
     const bool first = !second;
-    if (a.taps > 1 && first) {  // [row][tap][channel] -> [row][channel][tap]
+    if constexpr (std::is_same_v<Args, ReduceTapsArgs>) {
+      if (first) {  // [row][tap][channel] -> [row][channel][tap]
 #pragma unroll
-      for (int e = 0; e < V; ++e) {
-        const uint32_t row = mdiv((uint32_t)(i + e), a.mRow), rem = (uint32_t)(i + e) - row * (uint32_t)(a.taps * a.tap_channels);
-        const uint32_t tap = mdiv(rem, a.mTapChannels), c = rem - tap * (uint32_t)a.tap_channels;
-        float* const to = a.dst + (size_t)(row * (uint32_t)a.tap_channels + c) * a.taps + tap;
-        float s = (quarter[0][lane].v[e] + quarter[1][lane].v[e]) + (quarter[2][lane].v[e] + quarter[3][lane].v[e]);
-        if (a.beta != 0.f) s += a.beta * *to;
-        *to = s;
+        for (int e = 0; e < V; ++e) {
+          const uint32_t row = mdiv((uint32_t)(i + e), a.mRow);
+          const uint32_t rem = (uint32_t)(i + e) - row * (uint32_t)(a.taps * a.tap_channels);
+          const uint32_t tap = mdiv(rem, a.mTapChannels), c = rem - tap * (uint32_t)a.tap_channels;
+          float* const to = a.dst + (size_t)(row * (uint32_t)a.tap_channels + c) * a.taps + tap;
+          float s = (quarter[0][lane].v[e] + quarter[1][lane].v[e]) + (quarter[2][lane].v[e] + quarter[3][lane].v[e]);
+          if (a.beta != 0.f) s += a.beta * *to;
+          *to = s;
+        }
+        return;
       }
-      return;
     }
     if (a.beta != 0.f) old = *reinterpret_cast<const Vec*>(dst);
 #pragma unroll
@@ -505,18 +510,22 @@ int launch_wgrad(int32_t tile, const WgradArgs& a, void* stream) {
   }
 }
 
-int launch_reduce(const ReduceArgs& a, void* stream) {
+template <typename Args>
+static int launch_reduce_t(const Args& a, void* stream) {
   // the four-element form needs enough elements to keep a thousand workgroups busy
   const bool vec = a.count >= (1 << 18) && a.count % 4 == 0 && a.count2 % 4 == 0 && a.stride % 4 == 0 &&
                    ((reinterpret_cast<uintptr_t>(a.part) | reinterpret_cast<uintptr_t>(a.dst) |
                      reinterpret_cast<uintptr_t>(a.part2) | reinterpret_cast<uintptr_t>(a.dst2)) & 15u) == 0;
   if (vec)
-    hipLaunchKernelGGL(reduce_kernel<4>, dim3((a.count / 4 + 63) / 64 + (a.count2 / 4 + 63) / 64), dim3(256), 0,
+    hipLaunchKernelGGL((reduce_kernel<4, Args>), dim3((a.count / 4 + 63) / 64 + (a.count2 / 4 + 63) / 64), dim3(256), 0,
                        (hipStream_t)stream, a);
   else
-    hipLaunchKernelGGL(reduce_kernel<1>, dim3((a.count + 63) / 64 + (a.count2 + 63) / 64), dim3(256), 0,
+    hipLaunchKernelGGL((reduce_kernel<1, Args>), dim3((a.count + 63) / 64 + (a.count2 + 63) / 64), dim3(256), 0,
                        (hipStream_t)stream, a);
   return (int)hipGetLastError();
 }
+
+int launch_reduce(const ReduceArgs& a, void* stream) { return launch_reduce_t(a, stream); }
+int launch_reduce_taps(const ReduceTapsArgs& a, void* stream) { return launch_reduce_t(a, stream); }
 
 }  // namespace mi355conv
