@@ -15,11 +15,17 @@
 // loads what its lanes feed with coalesced 16-byte loads straight from L2 into registers, one step ahead: A
 // never touches LDS, and the waves of a workgroup meet at a barrier once per chunk (T steps) only.
 //
-// Bound by the matrix unit (busy 74-80 % of the compute units' cycles, at the 1.9 GHz that the chip holds under this load),
-// then by the prologue on small problems.  With the pack kernel, against the fp32 kernels: 57.3 GFLOP (96 -> 256 in two
-// groups, 5x5 at 27x27, batch 128) forward 431 -> 247 us, backward data 459 -> 235; 38.3 GFLOP (256 -> 384, 3x3 at 13x13)
-// 292 -> 174 and 309 -> 200; 6.7 GFLOP (45 -> 77, 3x5 at 51x67, stride 2 x 1) 92 -> 54 and 87 -> 53; 1.3 GFLOP (32 -> 32,
-// 5x5 at 16x16, batch 100) 29 -> 24.  172 and 115 us are the matrix instructions of the first two at 2000 TFLOP/s.
+// Bound by the matrix unit (busy 67-78 % of the compute units' cycles on large layers, at the 1.9 GHz that the chip holds
+// under this load), then by the prologue on small problems.  With the pack kernel, against the fp32 kernels: 57.3 GFLOP (96 ->
+// 256 in two groups, 5x5 at 27x27, batch 128) forward 431 -> 247 us, backward data 459 -> 235; 38.3 GFLOP (256 -> 384, 3x3 at
+// 13x13) 292 -> 174 and 309 -> 200; 6.7 GFLOP (45 -> 77, 3x5 at 51x67, stride 2 x 1) 92 -> 52 and 87 -> 50; 1.3 GFLOP (32 ->
+// 32, 5x5 at 16x16, batch 100) 29 -> 21.  172 and 115 us are the matrix instructions of the first two at 2000 TFLOP/s.
+//
+// Forms (SplitFold).  Folded taps: 3 -> 96 channels, 11x11, stride 4 at 227x227, batch 128, forward 254 -> 195 us; busy 46 %,
+// the folded patch's loads and splits (3 vector instructions to a matrix one) and 30 % of padding take the rest.  Columns
+// of 1x1 kernels use a patch element once per row tile, so splitting weighs most there: inner product 128 x 9216 -> 4096, data
+// gradient 97 -> 64 us, filter gradient 106 -> 78 (151 MB written, 30 us), busy 36-51 %; one-pixel images: its forward pass
+// 90 -> 72.
 #include <hip/hip_runtime.h>
 
 #include "corr_epilogue.h"
@@ -56,7 +62,7 @@ enum SplitForm { IMAGE, FOLDED, COLUMNS, PIXELS };  // PIXELS: COLUMNS over imag
 template <int MT, int MB, int NB, int WM, int WN, int EPT, SplitForm FORM>
 __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) void corr_split_kernel(const CorrSplitArgs a) {
   using C = SplitCfg<MT, MB, NB, WM, WN>;
-    using M = Mfma<MT>;
+  using M = Mfma<MT>;
   constexpr int BM = C::BM, BN = C::BN;
   constexpr bool FOLD = FORM == FOLDED, PIX = FORM == PIXELS, COLS = FORM == COLUMNS || PIX;
 
@@ -432,8 +438,8 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
 }
 
 // Packs the weights into A fragments: thread = (group, m tile, step, row block, lane), eight k values each.  Few
-// workgroups whose time is one chain of index arithmetic, loads and stores: the divisions are per thread, not per k value (96 -> 256
-// in two groups, 5x5: 10.2 -> 7.4 us; 128 x 4096 rows: 7.2 -> 4.9).
+// workgroups whose time is one chain of index arithmetic, loads and stores: the divisions are per thread, not
+// per k value (96 -> 256 in two groups, 5x5: 10.2 -> 7.4 us; 128 x 4096 rows: 7.2 -> 4.9).
 template <int MT>
 __global__ __launch_bounds__(256) void pack_split_kernel(const PackSplitArgs a, int blocks, int m_tiles, uint32_t total) {
   const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
