@@ -367,7 +367,8 @@ int32_t configure_thin(CorrArgs& a, PackArgs& k, int64_t cg_in, int64_t n_img, b
 
 // One dimension of an LDS patch (corr_split_kernel, wgrad_split_kernel): `out` positions `stride` apart with windows of
 // `ext` positions over an image of `size` positions behind `pad` zeros.  `share` of the zeros behind the image, which
-// some window reads, are the same ones as those before the next row (image): `pitch` positions from row to row.
+// some window reads, are the same ones as those before the next row (image): `pitch` positions from row to row.  At most a
+// window's worth: a tile that starts in an image's last row owns ext - share rows of that image.
 struct PatchDim {
   int64_t pitch, share;
 };
@@ -376,6 +377,7 @@ PatchDim patch_dim(int64_t out, int64_t stride, int64_t ext, int64_t pad, int64_
   const int64_t reach = (out - 1) * stride + ext, behind = reach - pad - size;
   PatchDim r;
   r.share = behind <= 0 || pad <= 0 ? 0 : behind < pad ? behind : pad;
+  if (r.share > ext) r.share = ext;
   r.pitch = reach - r.share;
   return r;
 }

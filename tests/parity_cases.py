@@ -227,6 +227,16 @@ SPLIT_CASES = [
     P(2923, 1120, 1, 1, 412, 1, 1),
 ]
 
+# More rows of padding than a window has, on images so small that column tiles and chunks start in an image's last rows:
+# square, strided, dilated and one-row kernels.
+SPLIT_PAD_CASES = [
+    P(12, 128, 13, 13, 128, 3, 3, 1, 1, 5, 5),
+    P(56, 128, 5, 9, 144, 3, 5, 1, 1, 6, 2),
+    P(40, 64, 9, 11, 112, 5, 3, 2, 1, 14, 1, 1, 2),
+    P(16, 80, 12, 10, 128, 3, 3, 1, 1, 9, 6, 2, 2),
+    P(64, 128, 9, 13, 144, 1, 9, 1, 1, 3, 4),
+]
+
 
 def _valid(pd):
     return (oracle.out_size(pd["h"], pd["kernel_h"], pd["stride_h"], pd["pad_h"], pd["dilation_h"]) >= 1 and

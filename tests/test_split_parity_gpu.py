@@ -15,7 +15,7 @@ import oracle
 import paper_1810_02272_amd as conv
 from oracle import OracleParams
 from paper_1810_02272_amd import workloads
-from parity_cases import SPLIT_CASES, P
+from parity_cases import SPLIT_CASES, SPLIT_PAD_CASES, P
 from parity_metric import nerr
 from test_ip_parity_gpu import run_case as run_ip_case
 from test_parity_gpu import TOL, check_filter_and_bias_in_one_pass, run_all
@@ -58,9 +58,9 @@ def norm_error(g, r):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("i", range(len(SPLIT_CASES)))
+@pytest.mark.parametrize("i", range(len(SPLIT_CASES + SPLIT_PAD_CASES)))
 def test_split_full_compare(i):
-    pd = SPLIT_CASES[i]
+    pd = (SPLIT_CASES + SPLIT_PAD_CASES)[i]
     print("split case", i, pd, names(pd), flush=True)
     op = OracleParams(**pd)
     ys = oracle.output_shape(op)
