@@ -414,6 +414,8 @@ void plain_grid(int64_t cg, int64_t kh, int64_t kw, int64_t sh, int64_t sw, int6
   g.f.fh = g.f.fw = g.f.ff = g.f.Uh = g.f.Uw = 1;
   g.f.dh = (int32_t)dh;
   g.f.dw = (int32_t)dw;
+  g.f.kh = (int32_t)kh;
+  g.f.kw = (int32_t)kw;
   g.f.V = (int32_t)cg;
   g.f.mFF = g.f.mFw = make_magic(1);
   g.sh = sh;

@@ -55,6 +55,7 @@ struct SplitFold {
   int32_t fh, fw, ff;  // ff = fh * fw
   int32_t Uh, Uw;
   int32_t dh, dw;      // dilations of the layer
+  int32_t kh, kw;      // taps of the layer: folding rounds them up, with zero weights in the places beyond
   int32_t V;           // channels: those of the group times ff
   int32_t subs;        // 0, or the groups of 16 channels of a chunk
   int32_t pixels;      // column form of unpadded images of one pixel

@@ -408,9 +408,12 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
         for (int tp = 0; tp < (COLS ? 1 : T); ++tp) {
           int ih = ih0 + tp / a.TW * a.dh, iw = iw0 + tp % a.TW * a.dw, ci = c;
           if (FOLD || COLS) {
+            const int ir = c % a.fold.ff / a.fold.fw, jr = c % a.fold.ff % a.fold.fw;
+            // a place beyond the kernel's taps: its weight is zero, but the input there may be what spoilt the sum
+            if (FOLD && (tp / a.TW * a.fold.fh + ir >= a.fold.kh || tp % a.TW * a.fold.fw + jr >= a.fold.kw)) continue;
             ci = c / a.fold.ff;
-            ih = ih * a.fold.Uh + c % a.fold.ff / a.fold.fw * a.fold.dh;
-            iw = iw * a.fold.Uw + c % a.fold.ff % a.fold.fw * a.fold.dw;
+            ih = ih * a.fold.Uh + ir * a.fold.dh;
+            iw = iw * a.fold.Uw + jr * a.fold.dw;
           }
           ih -= a.ph;
           iw -= a.pw;

@@ -87,38 +87,65 @@ def test_split_full_compare(i):
     assert torch.equal(dw1, dw + dw) and torch.equal(dw2, dw)
 
 
+ODD = pytest.mark.parametrize("odd", [(float("inf"), float("-inf"), float("nan")), (3.4e38, -3.4028234e38)],
+                              ids=["not_finite", "largest"])
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("pd", [P(20, 48, 29, 30, 60, 5, 5), P(40, 48, 30, 31, 64, 3, 5)],
                          ids=["5x5", "3x5"])
-@pytest.mark.parametrize("odd", [(float("inf"), float("-inf"), float("nan")), (3.4e38, -3.4028234e38)],
-                         ids=["not_finite", "largest"])
+@ODD
 def test_infinities_nans_and_the_largest_floats(pd, odd):
     """An infinity or NaN spoils the split's differences and the largest floats round to a bf16 infinity: such sums are computed
     again, and must come out as plain fp32 arithmetic has them (no padding: a zero times an infinity is not the oracle's)."""
-    assert "split" in names(pd)["fwd"] and "split" in names(pd)["bwd_data"] and "split" in names(pd)["bwd_filter"], names(pd)
+    check_odd_values(pd, odd, ("fwd", "bwd_data", "bwd_filter"))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("pd,passes", [
+    (P(42, 3, 83, 87, 96, 11, 11, 4, 4), ("fwd",)), (P(8, 705, 39, 21, 284, 1, 1), ("fwd",)),
+    (P(1200, 700, 1, 1, 2100, 1, 1), ("fwd", "bwd_data")), (P(24, 90, 29, 30, 90, 3, 5, g=2), ("fwd", "bwd_data", "bwd_filter"))],
+    ids=["folded", "columns", "rows", "groups"])
+@ODD
+def test_odd_values_in_every_form(pd, passes, odd):
+    """The same for the forms whose patch is not the image -- the folded one rounds 11x11 taps up to 12x12: the odd values sit
+    right below and right of windows that do not have them -- and for channels of a chunk that are the next group's."""
+    check_odd_values(pd, odd, passes, (15, 19, 4))
+
+
+def check_odd_values(pd, odd, passes, at=None):
+    """`at`: row and column of the first odd value of x, and the step to the next one's."""
+    kernels = names(pd)
+    assert all("split" in kernels[p] for p in passes), kernels
     op = OracleParams(**pd)
     x, w, b, dy = workloads.random_inputs(oracle.x_shape(op), oracle.w_shape(op), oracle.output_shape(op), 77)
     x_plain = x.clone()
     for i, v in enumerate(odd):
-        x[i, 3 * i, 7 + i, 9] = v
-        dy[2 + i, 5 * i, 4, 6 + 2 * i] = v
+        r, c, step = at or (7 + i, 9, 0)
+        x[i, 3 * i % x.shape[1], (r + i * step) % x.shape[2], (c + i * step) % x.shape[3]] = v
+        dy[2 + i, 5 * i, 4 % dy.shape[2], (6 + 2 * i) % dy.shape[3]] = v
     d, ws, (_, _, bd, _), (y, dx, dw, db) = run_all(pd, x, w, b, dy)
     host = (x.numpy(), w.numpy(), b.numpy(), dy.numpy())
     # infinite and huge weights: forward only (the data gradient multiplies them with the zeros around dy, as any fp32
     # kernel does), on plain inputs
     w_inf = w.clone()
-    w_inf[9, 3, 0, 2] = float("inf")
-    w_inf[7, 2, 1, 1] = 3.4e38
+    w_inf[9, 3 % w.shape[1], 0, 2 % w.shape[3]] = float("inf")
+    w_inf[7, 2, 1 % w.shape[2], 1 % w.shape[3]] = 3.4e38
     y_inf = torch.empty_like(y)
     conv.conv_forward(d, x_plain.to(DEV), w_inf.to(DEV), bd, y_inf, ws)
     torch.cuda.synchronize()
+    mag = [np.abs(v) for v in host]
+    results = []
     with np.errstate(all="ignore"):
-        refs = (oracle.forward(op, *host[:3]), oracle.backward_data(op, host[1], host[3]),
-                oracle.backward_filter(op, host[0], host[3]), oracle.forward(op, x_plain.numpy(), w_inf.numpy(), host[2]))
-        mag = [np.abs(v) for v in host]
-        mags = (oracle.forward(op, *mag[:3]), oracle.backward_data(op, mag[1], mag[3]),
-                oracle.backward_filter(op, mag[0], mag[3]), oracle.forward(op, np.abs(x_plain.numpy()), np.abs(w_inf.numpy()), mag[2]))
-    for name, got, ref, size in zip(("y", "dx", "dw", "y, odd weights"), (y, dx, dw, y_inf), refs, mags):
+        if "fwd" in passes:
+            results += [("y", y, oracle.forward(op, *host[:3]), oracle.forward(op, *mag[:3])),
+                        ("y, odd weights", y_inf, oracle.forward(op, x_plain.numpy(), w_inf.numpy(), host[2]),
+                         oracle.forward(op, np.abs(x_plain.numpy()), np.abs(w_inf.numpy()), mag[2]))]
+        if "bwd_data" in passes:
+            results += [("dx", dx, oracle.backward_data(op, host[1], host[3]), oracle.backward_data(op, mag[1], mag[3]))]
+        if "bwd_filter" in passes:
+            results += [("dw", dw, oracle.backward_filter(op, host[0], host[3]), oracle.backward_filter(op, mag[0], mag[3]))]
+    for name, got, ref, size in results:
         g = got.cpu().double().numpy().reshape(ref.shape)
         r = np.where(np.abs(ref) > 3.4028235e38, np.sign(ref) * np.inf, ref)  # what fp32 cannot hold
         close = np.isfinite(size) & (size > 1e38)  # terms at the edge of the range: fp32 may or may not overflow on the way
