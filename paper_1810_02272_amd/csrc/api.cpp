@@ -681,7 +681,16 @@ int32_t configure_wgrad_split(const WgradArgs& w, int64_t N, int64_t K, int64_t 
   // at 12x12, 1.11 times: 38 -> 33 us).
   int32_t bm, bn, bk;
   wgrad_tile_shape(pick_wgrad_tile(w.Kg, w.Kred), &bm, &bn, &bk);
-  if (least_work > (flops < 2.5e9 ? 1.12 : flops < 4.5e9 ? 1.45 : 2.0) * (double)round_up(w.Kg, bm) * (double)round_up(w.Kred, bn)) return -1;
+  const double fp32_work = (double)round_up(w.Kg, bm) * (double)round_up(w.Kred, bn);
+  if (least_work > (flops < 2.5e9 ? 1.12 : flops < 4.5e9 ? 1.45 : 2.0) * fp32_work) return -1;
+  // A run holds pixels of one image: what an image's last run is short of eight is padding as well.  Half of it (four
+  // pixels: 512 -> 512, 3x3, batch 2048, 368 us fp32, 404 split; one pixel: 134 and 390) is too much, and with the blocks'
+  // padding 2.2 times the work (20 -> 320, 5x5 on six pixels, 2.33 times: 127 and 142; 24 -> 200, 3x3 on seventeen, 1.82
+  // times: 184 and 118).  Nine pixels (1.78 times) gain on some layers (512 x 128 -> 128: 38 and 30) and lose on others (256 x 256 ->
+  // 384: 59 and 64): by modelled times, the fp32 kernel's from the same measurements.
+  const double fill = 8.0 * (double)runs / (double)w.P;
+  if (fill >= 2 || fill * least_work > 2.2 * fp32_work) return -1;
+  if (fill > 1.7 && best_cost + 8 > 25 + flops / 106e6 * fp32_work / ((double)w.Kg * w.Kred)) return -1;
   int32_t rows, taps;
   wgrad_split_shape(best, &rows, &taps);
   a = WgradSplitArgs();

@@ -225,6 +225,11 @@ SPLIT_CASES = [
     P(300, 1231, 1, 1, 515, 1, 1, 1, 1, 1, 1),
     P(767, 1336, 1, 1, 2450, 1, 1, 1, 1, 0, 0, 1, 1, 2),
     P(2923, 1120, 1, 1, 412, 1, 1),
+    # filter gradients of images of 5, 6, 7 and 9 pixels: chunks that span up to sixteen images
+    P(1300, 48, 1, 5, 120, 3, 3, 1, 1, 1, 1),
+    P(4700, 90, 2, 3, 77, 3, 3, 1, 1, 1, 1),
+    P(901, 61, 3, 9, 96, 3, 5, 3, 1, 1, 1, 1, 1),
+    P(1603, 45, 3, 3, 77, 3, 5, 1, 1, 1, 2),
 ]
 
 # More rows of padding than a window has, on images so small that column tiles and chunks start in an image's last rows:
