@@ -377,7 +377,7 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
 #pragma unroll
     for (int j = 0; j < NB; ++j)
 #pragma unroll
-      for (int r = 0; r < M::NR; ++r) acc[i][j][r] += lo[i][j][r];
+      for (int r = 0; r < M::NR; ++r) acc[i][j][r] = (acc[i][j][r] + lo[i][j][r]) * kSplitUnscale;
 
   // ---- sums that are not finite once more with fp32 multiply-adds (the weights put back together exactly):
   // an infinity or NaN among the operands makes the split's differences NaN where the plain sum may be

@@ -293,7 +293,7 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
 #pragma unroll
     for (int j = 0; j < NB; ++j)
 #pragma unroll
-      for (int r = 0; r < M::NR; ++r) acc[i][j][r] += lo[i][j][r];
+      for (int r = 0; r < M::NR; ++r) acc[i][j][r] = (acc[i][j][r] + lo[i][j][r]) * kSplitUnscale;
 
   const int c = c16 * 16 + (lane & 15);
   // ---- sums that are not finite once more with fp32 multiply-adds (see corr_split_kernel) ----

@@ -170,6 +170,32 @@ def check_odd_values(pd, odd, passes, at=None):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("pd", [P(20, 48, 29, 30, 60, 5, 5), P(40, 48, 30, 31, 64, 3, 5), P(42, 3, 83, 87, 96, 11, 11, 4, 4),
+                                P(8, 705, 39, 21, 284, 1, 1), P(1200, 700, 1, 1, 2100, 1, 1)],
+                         ids=["5x5", "3x5", "folded", "columns", "rows"])
+@pytest.mark.parametrize("ex,ew,edy", [(-118, 70, 70), (70, -118, 70), (70, 70, -118), (-136, 70, 70), (70, -136, 70), (70, 70, -136)])
+def test_tiny_operands_keep_their_bits(pd, ex, ew, edy):
+    """Operands down to fp32's denormals against large ones: the bound of ordinary operands holds, it does not
+    know their size.  The filter gradient of two large blobs (2^140) and products of two tiny ones are left out."""
+    op = OracleParams(**pd)
+    x, w, b, dy = workloads.random_inputs(oracle.x_shape(op), oracle.w_shape(op), oracle.output_shape(op), 78)
+    x, w, b, dy = x * 2.0 ** ex, w * 2.0 ** ew, b * 0, dy * 2.0 ** edy
+    d, ws, _, (y, dx, dw, db) = run_all(pd, x, w, b, dy)
+    kernels, ys = names(pd), oracle.output_shape(op)
+    taps = pd["kernel_h"] * pd["kernel_w"]
+    checked = 0
+    for which, got, e, ref, terms in (
+            ("fwd", y, ex + ew, lambda: oracle.forward(op, x.numpy(), w.numpy(), b.numpy()), pd["c"] * taps),
+            ("bwd_data", dx, edy + ew, lambda: oracle.backward_data(op, w.numpy(), dy.numpy()), pd["num_output"] * taps),
+            ("bwd_filter", dw, ex + edy, lambda: oracle.backward_filter(op, x.numpy(), dy.numpy()), ys[0] * ys[2] * ys[3])):
+        if "split" in kernels[which] and -80 < e < 80:
+            r = ref()
+            assert norm_error(got, r) <= 2.0 ** -24 * np.sqrt(terms / 16 + 32), (which, norm_error(got, r))
+            checked += 1
+    assert checked or ew > 0
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("beta", [0.0, 1.0])
 @pytest.mark.parametrize("m,k,o", [(333, 1503, 2570), (4100, 333, 965), (999, 1503, 1501), (2500, 1300, 2500)])
 def test_inner_product_on_the_column_form(m, k, o, beta):
