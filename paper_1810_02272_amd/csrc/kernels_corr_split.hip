@@ -379,9 +379,11 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
 #pragma unroll
       for (int r = 0; r < M::NR; ++r) acc[i][j][r] = (acc[i][j][r] + lo[i][j][r]) * kSplitUnscale;
 
-  // ---- sums that are not finite once more with fp32 multiply-adds (the weights put back together exactly):
-  // an infinity or NaN among the operands makes the split's differences NaN where the plain sum may be
-  // infinite.  Every wave for itself. ----
+  // ---- sums that are not finite once more on the fp32 matrix instructions (the weights put back together exactly, the
+  // inputs as they are in memory): an infinity or NaN among the operands makes the split's differences NaN where the plain
+  // sum may be infinite.  Every wave for itself, over the steps of the main loop: lane for lane an fp32 instruction takes the
+  // e-th of the eight k values that the lane feeds to the bf16 one.  256 -> 384, 3x3 at 13x13, batch 128, forward: one NaN
+  // 190 -> 490 us, all NaN 600 (with scalar multiply-adds 16 and 18 ms). ----
   bool bad = false;
 #pragma unroll
   for (int i = 0; i < MB; ++i)
@@ -390,51 +392,79 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
 #pragma unroll
       for (int r = 0; r < M::NR; ++r) bad |= not_finite(acc[i][j][r]);
   if (__any(bad)) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));  // what depends on it is computed here again, not kept in registers over the main loop
+    const uint32_t kg = (uint32_t)ln / MT, hf = kg & 1;
+    int row0[NB], col0s[NB];  // the column's window on the image (or the grid), and its image
+    uint32_t img[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
 #pragma unroll
       for (int i = 0; i < MB; ++i)
 #pragma unroll
         for (int r = 0; r < M::NR; ++r) acc[i][j][r] = 0.f;
-      uint32_t col = col0 + (wn * NB + j) * MT + lane % MT;
+      uint32_t col = col0 + (wn * NB + j) * MT + (uint32_t)ln % MT;
       if (col > col_last) col = col_last;
       const uint32_t n = mdiv(col, a.mP);
       const uint32_t pix = col - n * a.P;
       const uint32_t pa = mdiv(pix, a.mPW);
-      const int ih0 = (int)pa * a.sh, iw0 = (int)(pix - pa * a.PW) * a.sw;
-      const uint32_t base = n * (uint32_t)a.in_img_stride + g * (uint32_t)a.in_grp_stride;
-      constexpr int kChan = COLS ? 64 : 16;  // channels of a chunk
-      for (int c = cc_first * kChan; c < cc_end * kChan && c < (FOLD || COLS ? a.fold.V : a.Cg_in); ++c)
-        for (int tp = 0; tp < (COLS ? 1 : T); ++tp) {
-          int ih = ih0 + tp / a.TW * a.dh, iw = iw0 + tp % a.TW * a.dw, ci = c;
-          if (FOLD || COLS) {
-            const int ir = c % a.fold.ff / a.fold.fw, jr = c % a.fold.ff % a.fold.fw;
-            // a place beyond the kernel's taps: its weight is zero, but the input there may be what spoilt the sum
-            if (FOLD && (tp / a.TW * a.fold.fh + ir >= a.fold.kh || tp % a.TW * a.fold.fw + jr >= a.fold.kw)) continue;
-            ci = c / a.fold.ff;
-            ih = ih * a.fold.Uh + ir * a.fold.dh;
-            iw = iw * a.fold.Uw + jr * a.fold.dw;
-          }
-          ih -= a.ph;
-          iw -= a.pw;
-          const bool in = (uint32_t)ih < (uint32_t)a.IH && (uint32_t)iw < (uint32_t)a.IW;
-          const float b = in ? a.in[base + (uint32_t)ci * (uint32_t)a.IHW + (uint32_t)ih * a.IW + iw] : 0.f;
-          const int tq = COLS ? c % 64 / 16 : tp;  // the tap, or the group of 16 channels in its place
-          const int st = (c / kChan - cc_first) * SPC + tq / C::TPS;
-          const uint32_t grp = (uint32_t)((c % 16) / 8 + 2 * (tq % C::TPS));
-          const char* frag = Ag + (size_t)(uint32_t)st * C::STEP + (uint32_t)(wm * MB) * 3u * C::FRAG + (grp * MT * 16u + (uint32_t)(c % 8) * 2u);
-#pragma unroll
-          for (int i = 0; i < MB; ++i)
-#pragma unroll
-            for (int r = 0; r < M::NR; ++r) {
-              const char* p = frag + (uint32_t)i * 3u * C::FRAG + (uint32_t)M::row(r, lane) * 16u;
-              const float w = join_bf16(*reinterpret_cast<const uint16_t*>(p),
-                                        *reinterpret_cast<const uint16_t*>(p + C::FRAG),
-                                        *reinterpret_cast<const uint16_t*>(p + 2 * C::FRAG));
-              acc[i][j][r] = fmaf(w, b, acc[i][j][r]);
-            }
-        }
+      const uint32_t pb = pix - pa * a.PW;
+      row0[j] = (int)pa * a.sh;
+      col0s[j] = (int)pb * a.sw;
+      img[j] = n * (uint32_t)a.in_img_stride + g * (uint32_t)a.in_grp_stride;
     }
+    const int channels = FOLD || COLS ? a.fold.V : a.Cg_in;
+    uint32_t off = 0;
+    for (int ch = cc_first; ch < cc_end; ++ch)
+      for (int st = 0; st < SPC; ++st, off += C::STEP) {
+        const int tp = st * C::TPS + (int)(kg >> 1);  // (kg >> 1) is 0 for the 32-row instruction
+        const int c0 = (COLS ? ch * 64 + tp * 16 : ch * 16) + (int)hf * 8;
+        const int ti = COLS ? 0 : tp / a.TW, tj = COLS ? 0 : tp - ti * a.TW;
+        float b[NB][8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          int ci = c0 + e, ir = 0, jr = 0;
+          // Zero: channels past the group's last, the 16-row instruction's tap past the last, and places beyond the
+          // kernel's taps (there the weight is zero, but the input may be what spoilt the sum).
+          bool in = tp < T && ci < channels;
+          if (FOLD) {
+            const int v = ci;
+            ci = v / a.fold.ff;
+            ir = (v - ci * a.fold.ff) / a.fold.fw;
+            jr = v - ci * a.fold.ff - ir * a.fold.fw;
+            in = in && ti * a.fold.fh + ir < a.fold.kh && tj * a.fold.fw + jr < a.fold.kw;
+          }
+#pragma unroll
+          for (int j = 0; j < NB; ++j) {
+            int ih = row0[j] + ti * a.dh, iw = col0s[j] + tj * a.dw;
+            if (FOLD || COLS) {
+              ih = ih * a.fold.Uh + ir * a.fold.dh;
+              iw = iw * a.fold.Uw + jr * a.fold.dw;
+            }
+            ih -= a.ph;
+            iw -= a.pw;
+            const bool ok = in && (uint32_t)ih < (uint32_t)a.IH && (uint32_t)iw < (uint32_t)a.IW;
+            const uint32_t at = 4u * (img[j] + (uint32_t)ci * (uint32_t)a.IHW + (uint32_t)ih * (uint32_t)a.IW + (uint32_t)iw);
+            b[j][e] = __builtin_bit_cast(
+                float, __builtin_amdgcn_raw_buffer_load_b32(in_rsrc, ok ? at : 0x80000000u, 0, 0));
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < MB; ++i) {
+          u32x4 w[3];
+#pragma unroll
+          for (int q = 0; q < 3; ++q)
+            w[q] = __builtin_bit_cast(
+                u32x4, __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, 16u * (uint32_t)ln + ((uint32_t)(wm * MB + i) * 3u + q) * C::FRAG, (int)off, 0));
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int sh = 16 * (e & 1);
+            const float v = join_bf16((uint16_t)(w[0][e >> 1] >> sh), (uint16_t)(w[1][e >> 1] >> sh), (uint16_t)(w[2][e >> 1] >> sh));
+#pragma unroll
+            for (int j = 0; j < NB; ++j) M::run(v, b[j][e], acc[i][j]);
+          }
+        }
+      }
   }
 
   corr_epilogue<MT, MB, NB, BM, BN>(a, smem, acc, m_tile, col_tile, g, wm, wn, split);

@@ -296,7 +296,8 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
       for (int r = 0; r < M::NR; ++r) acc[i][j][r] = (acc[i][j][r] + lo[i][j][r]) * kSplitUnscale;
 
   const int c = c16 * 16 + (lane & 15);
-  // ---- sums that are not finite once more with fp32 multiply-adds (see corr_split_kernel) ----
+  // ---- sums that are not finite once more on the fp32 matrix instructions (see corr_split_kernel); channels past the
+  // group's last are the next group's and never stored ----
   bool bad = false;
 #pragma unroll
   for (int i = 0; i < MB; ++i)
@@ -304,33 +305,43 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
     for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int r = 0; r < M::NR; ++r) bad |= not_finite(acc[i][j][r]);
-  if (__any(bad)) {
+  if (__any(bad && c < a.Cg)) {
+    int th[NB], tw[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
 #pragma unroll
       for (int i = 0; i < MB; ++i)
 #pragma unroll
         for (int r = 0; r < M::NR; ++r) acc[i][j][r] = 0.f;
-      const int tp = tap0 + j;
-      const int ti = tp / a.kw, tj = tp - ti * a.kw;
-      if (tp < a.khw) {
-        for (uint32_t q = (uint32_t)chunk_first * kChunkRuns; q < (uint32_t)chunk_end * kChunkRuns && q < run_end; ++q) {
-          uint32_t n, p;
-          run_pos(q, n, p);
-          for (int e = 0; e < 8 && (int)p + e < a.P; ++e) {
-            const uint32_t pix = p + e, pa = mdiv(pix, a.mPW), pb = pix - pa * a.PW;
-            const int ih = (int)pa * a.sh - a.ph + ti * a.dh, iw = (int)pb * a.sw - a.pw + tj * a.dw;
-            const bool in = c < a.Cg && (uint32_t)ih < (uint32_t)a.H && (uint32_t)iw < (uint32_t)a.W;
-            const float xv = in ? a.x[((size_t)n * a.C + g * a.Cg + c) * (size_t)(a.H * a.W) + (size_t)ih * a.W + iw] : 0.f;
+      int tp = tap0 + j;
+      if (tp > a.khw - 1) tp = a.khw - 1;
+      th[j] = __builtin_amdgcn_readfirstlane(tp / a.kw * a.dh);
+      tw[j] = __builtin_amdgcn_readfirstlane(tp % a.kw * a.dw);
+    }
+#pragma unroll 1
+    for (int step = chunk_first * kChunkSteps; step <= last_step; ++step) {
+      load_dy(step);
+      uint32_t n, p;
+      run_pos((uint32_t)step * kStepRuns + (uint32_t)(lane >> 4), n, p);
+      const uint32_t image = n * (uint32_t)(a.C * a.H * a.W) + (g * (uint32_t)a.Cg + (uint32_t)c) * (uint32_t)(a.H * a.W);
 #pragma unroll
-            for (int i = 0; i < MB; ++i)
+      for (int e = 0; e < 8; ++e) {
+        const bool real = e < valid && c < a.Cg;
+        const uint32_t pix = p + e, pa = mdiv(pix, a.mPW), pb = pix - pa * a.PW;
+        const int ih0 = (int)pa * a.sh - a.ph, iw0 = (int)pb * a.sw - a.pw;
+        float b[NB];
 #pragma unroll
-              for (int r = 0; r < M::NR; ++r) {
-                uint32_t m = m_tile * BM + (uint32_t)((wm * MB + i) * 16 + M::row(r, lane));
-                if (m > (uint32_t)a.Kg - 1) m = (uint32_t)a.Kg - 1;
-                acc[i][j][r] = fmaf(a.dy[((size_t)n * a.Ktot + g * a.Kg + m) * (size_t)a.P + pix], xv, acc[i][j][r]);
-              }
-          }
+        for (int j = 0; j < NB; ++j) {
+          const int ih = ih0 + th[j], iw = iw0 + tw[j];
+          const bool ok = real && (uint32_t)ih < (uint32_t)a.H && (uint32_t)iw < (uint32_t)a.W;
+          b[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                               x_rsrc, ok ? 4u * (image + (uint32_t)ih * (uint32_t)a.W + (uint32_t)iw) : 0x80000000u, 0, 0));
+        }
+#pragma unroll
+        for (int i = 0; i < MB; ++i) {
+          const float v = e < valid ? raw[i][e] : 0.f;
+#pragma unroll
+          for (int j = 0; j < NB; ++j) M::run(v, b[j], acc[i][j]);
         }
       }
     }

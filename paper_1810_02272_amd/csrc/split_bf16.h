@@ -15,7 +15,7 @@
 // 814 -> 823 us).
 //
 // An operand that is not finite or from 2^111 on, or a sum from 2^96 on, makes the differences or the sums infinite or NaN; the
-// kernels look for non-finite sums at their end and compute those again with fp32 multiply-adds.
+// kernels look for non-finite sums at their end and compute those again on the fp32 matrix instructions.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -170,6 +170,37 @@ def check_odd_values(pd, odd, passes, at=None):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("pd", [P(64, 256, 13, 13, 384, 3, 3, 1, 1, 1, 1), P(42, 3, 83, 87, 96, 11, 11, 4, 4),
+                                P(1200, 700, 1, 1, 2100, 1, 1)], ids=["image", "folded", "rows"])
+def test_recomputed_sums_cost_no_order_of_magnitude(pd):
+    """All sums computed again take 1.1 to 3.9 times a pass (one value after the other: 40 to 95 times)."""
+    d = conv.conv_desc_create(conv.ConvParams(**pd))
+    op, kernels = OracleParams(**pd), names(pd)
+    x, w, b, dy = (t.to(DEV) for t in workloads.random_inputs(oracle.x_shape(op), oracle.w_shape(op), oracle.output_shape(op), 79))
+    y, dx, dw, db = torch.empty_like(dy), torch.empty_like(x), torch.empty_like(w), torch.empty_like(b)
+    ws = torch.empty((conv.conv_desc_workspace_bytes(d) + 7) // 8, device=DEV, dtype=torch.float64)
+    nan = float("nan")
+
+    def ms(call):
+        call()
+        start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        start.record()
+        for _ in range(5):
+            call()
+        end.record()
+        torch.cuda.synchronize()
+        return start.elapsed_time(end) / 5
+
+    for which, call in (("fwd", lambda x, dy: conv.conv_forward(d, x, w, b, y, ws)),
+                        ("bwd_data", lambda x, dy: conv.conv_backward_data(d, w, dy, dx, ws)),
+                        ("bwd_filter", lambda x, dy: conv.conv_backward_filter_bias(d, x, dy, dw, db, 0.0, ws))):
+        if "split" in kernels[which]:
+            plain = ms(lambda: call(x, dy))
+            spoilt = ms(lambda: call(torch.full_like(x, nan), torch.full_like(dy, nan)))
+            assert spoilt < 10 * plain, (which, plain, spoilt)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("pd", [P(20, 48, 29, 30, 60, 5, 5), P(40, 48, 30, 31, 64, 3, 5), P(42, 3, 83, 87, 96, 11, 11, 4, 4),
                                 P(8, 705, 39, 21, 284, 1, 1), P(1200, 700, 1, 1, 2100, 1, 1)],
                          ids=["5x5", "3x5", "folded", "columns", "rows"])
