@@ -621,7 +621,13 @@ size_t configure_split(const CorrArgs& base, const PackArgs& pbase, int64_t cg_i
   a.chunks_per_split = (int32_t)ceil_div(chunks, plan.S);
   a.ksplit = (int32_t)ceil_div(chunks, a.chunks_per_split);
   k.split_chunks = a.NS;
-  return (size_t)a.G * a.m_tiles * chunks * ceil_div(a.THW, mt == 32 ? 1 : 2) * (bm / mt) * 3072;
+  // Six bytes a packed weight and the slices: a workspace beyond the boundary's 2^30 elements stays with the fp32 kernel (four).
+  const int64_t bytes = (int64_t)a.G * a.m_tiles * chunks * ceil_div(a.THW, mt == 32 ? 1 : 2) * (bm / mt) * 3072;
+  if (bytes + (a.ksplit > 1 ? 4 * a.ksplit * out_elems : 0) >= 4 * kMaxElems) {
+    tile = -1;
+    return 0;
+  }
+  return (size_t)bytes;
 }
 
 // Decides whether wgrad_split_kernel runs the backward filter; fills a and returns its tile, -1 if it does not.

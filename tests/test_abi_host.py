@@ -47,6 +47,13 @@ def test_benchmark_layers_shapes_and_workspace():
         assert "fwd=" in names and "bwd_data=" in names and "bwd_filter=" in names
 
 
+@pytest.mark.parametrize("pd", [dict(n=64, c=30000, h=1, w=1, num_output=32000, kernel_h=1, kernel_w=1),
+                                dict(n=4, c=1000, h=9, w=9, num_output=100000, kernel_h=3, kernel_w=3)])
+def test_workspace_stays_below_the_boundary_s_limit(pd):
+    """2^30 elements: layers of 0.9e9 weights, which the split kernels would pack into six bytes each."""
+    assert conv.conv_desc_workspace_bytes(conv.conv_desc_create(conv.ConvParams(**pd))) < 4 << 30
+
+
 def test_thin_groups_select_the_direct_kernels():
     """Depthwise and near-depthwise descriptors take the direct kernels (forward and backward data then
     need no workspace); wide groups and ungrouped layers stay on the matrix-unit tiles."""
