@@ -630,8 +630,9 @@ size_t configure_split(const CorrArgs& base, const PackArgs& pbase, int64_t cg_i
   return (size_t)bytes;
 }
 
-// Decides whether wgrad_split_kernel runs the backward filter; fills a and returns its tile, -1 if it does not.
-int32_t configure_wgrad_split(const WgradArgs& w, int64_t N, int64_t K, int64_t w_elems, WgradSplitArgs& a) {
+// Decides whether wgrad_split_kernel runs the backward filter instead of the fp32 kernel on its tile and split; fills a and
+// returns its own tile, -1 if it does not.
+int32_t configure_wgrad_split(const WgradArgs& w, int32_t fp32_tile, int64_t N, int64_t K, int64_t w_elems, WgradSplitArgs& a) {
   const double flops = 2.0 * w.Kg * w.Kred * (double)w.ncols * w.G;
   if (w.ncols < 1 || flops < 4e8 || w.x_bytes > (1u << 30) || w.dy_bytes > (1u << 31) - 32) return -1;
   if (4 * (int64_t)w.Kg * w.Kred > ((int64_t)1 << 30)) return -1;
@@ -687,16 +688,20 @@ int32_t configure_wgrad_split(const WgradArgs& w, int64_t N, int64_t K, int64_t 
   // at 12x12, 1.11 times: 38 -> 33 us).
   int32_t bm, bn, bk;
   wgrad_tile_shape(pick_wgrad_tile(w.Kg, w.Kred), &bm, &bn, &bk);
-  const double fp32_work = (double)round_up(w.Kg, bm) * (double)round_up(w.Kred, bn);
-  if (least_work > (flops < 2.5e9 ? 1.12 : flops < 4.5e9 ? 1.45 : 2.0) * fp32_work) return -1;
-  // A run holds pixels of one image: what an image's last run is short of eight is padding as well.  Half of it (four
-  // pixels: 512 -> 512, 3x3, batch 2048, 368 us fp32, 404 split; one pixel: 134 and 390) is too much, and with the blocks'
-  // padding 2.2 times the work (20 -> 320, 5x5 on six pixels, 2.33 times: 127 and 142; 24 -> 200, 3x3 on seventeen, 1.82
-  // times: 184 and 118).  Nine pixels (1.78 times) gain on some layers (512 x 128 -> 128: 38 and 30) and lose on others (256 x 256 ->
-  // 384: 59 and 64): by modelled times, the fp32 kernel's from the same measurements.
-  const double fill = 8.0 * (double)runs / (double)w.P;
-  if (fill >= 2 || fill * least_work > 2.2 * fp32_work) return -1;
-  if (fill > 1.7 && best_cost + 8 > 25 + flops / 106e6 * fp32_work / ((double)w.Kg * w.Kred)) return -1;
+  if (least_work > (flops < 2.5e9 ? 1.12 : flops < 4.5e9 ? 1.45 : 2.0) * (double)round_up(w.Kg, bm) * (double)round_up(w.Kred, bn)) return -1;
+  wgrad_tile_shape(fp32_tile, &bm, &bn, &bk);
+  // The rest by modelled times (us).  The fp32 kernel's: workgroups of a compute unit times the 32-column steps of one, by
+  // tile and by what the bounds test costs it, and its slices; a fit to 825 filter gradients of 0.4 to 20 GFLOP (rms error
+  // 5 %; 7 % on 1288, the split kernel's 8 %).  A run holds pixels of one image, so best_cost counts the zeros that fill an
+  // image's last run.  Of those 1288 the lines above let through, 139 were more than 3 % slower than fp32 (one pixel, 512 -> 512,
+  // 3x3, batch 2048: 134 us fp32, 390 split; 48 x 249 -> 266, 2x2 taps on tiles of eight: 62 and 78), with this line 16, at
+  // worst 11 %; 26 that gained more than 3 % stay behind with them, at best 434 -> 293 us.
+  static const double kFp32Step[WGRAD_TILE_COUNT] = {1.74, 1.45, 1.04, 0.634, 0.978};
+  const double bounds = (double)(bm * bn) / 16384.0 * (w.bounds_mode == 1 ? 0.51 : w.bounds_mode == 2 ? 0.29 : 0.0);
+  const int64_t per_cu = ceil_div((int64_t)w.G * w.m_tiles * w.n_tiles * w.S, 256);
+  const double fp32 = 13.2 + 0.375 * (double)w.S * w_mb +
+                      (double)(per_cu * ceil_div(w.cols_per_split, 32)) * (kFp32Step[fp32_tile] + bounds);
+  if (8.4 + 0.99 * best_cost > fp32) return -1;
   int32_t rows, taps;
   wgrad_split_shape(best, &rows, &taps);
   a = WgradSplitArgs();
@@ -1328,7 +1333,7 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
       delete d;
       return CONV_ESHAPE;
     }
-    d->wg_split = configure_wgrad_split(a, N, K, w_elems, d->wg_sp);
+    d->wg_split = configure_wgrad_split(a, d->wg_tile, N, K, w_elems, d->wg_sp);
     if (d->wg_split >= 0) {
       d->wg_ws = (size_t)d->wg_sp.S * (size_t)w_elems * 4;
       d->wgb_ws = (size_t)d->wg_sp.S * (size_t)(w_elems + d->wg_sp.n_tiles * K) * 4;
