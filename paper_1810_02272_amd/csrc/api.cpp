@@ -583,6 +583,12 @@ size_t configure_split(const CorrArgs& base, const PackArgs& pbase, int64_t cg_i
     here += (base.THW <= 3 ? 2.5 : 1.5) * (double)per_cu + (plan.S > 1 ? 4 : 0) + (base.simple_epilogue ? 0 : 6);
     fp32 = flops16 / 90e6 + 8;
   }
+  // The model leaves out what packing six bytes a weight costs.  With many taps and few columns that decides (forward, one
+  // image of 14x14, 3x3, 1024 -> 1024, 38 MB of weights: 67 us fp32, 97 split; 2048 -> 1024 on 200 columns: 119 and 182; on 784:
+  // 329 and 293; data gradient, 2048 -> 1024 on 98 columns: 97 and 139); 1x1 weights are packed as they lie.
+  const double weight_mb = 4e-6 * (double)base.G * base.Mrows * base.Kred;
+  if (base.THW > 1 && pbase.mode == 0 && weight_mb > 6) here += 1.5 * (weight_mb - 6);
+  if (base.THW > 1 && pbase.mode != 0 && weight_mb > 16) here += weight_mb - 16;
   if (here > fp32 || (!base.simple_epilogue && flops < 3e9)) return 0;
   tile = plan.tile;
   int32_t bm, bn, mt;

@@ -71,6 +71,14 @@ def test_filter_gradients_that_the_fp32_kernel_is_faster_on():
         assert names(pd)["bwd_filter"].startswith("wgrad"), pd
 
 
+def test_many_weights_and_few_columns_stay():
+    for pd in (P(1, 1024, 14, 14, 1024, 3, 3, 1, 1, 1, 1), P(2, 2048, 10, 10, 1024, 3, 3, 1, 1, 1, 1), P(1, 963, 14, 14, 878, 3, 3, 1, 1, 0, 1)):
+        assert "split" not in names(pd)["fwd"], pd
+    assert "split" not in names(P(2, 2048, 7, 7, 1024, 3, 3, 1, 1, 1, 1))["bwd_data"]
+    # more columns for the same weights: 329 us fp32, 293 split
+    assert "split" in names(P(4, 2048, 14, 14, 1024, 3, 3, 1, 1, 1, 1))["fwd"]
+
+
 def norm_error(g, r):
     g = g.cpu().double().numpy().reshape(r.shape)
     return float(np.linalg.norm(g - r) / np.linalg.norm(r))
