@@ -71,8 +71,9 @@ int ip_desc_create(ip_desc_t** out, const ip_params_t* pp) {
     conv_desc_workspace_bytes(d->inner, &d->ws_bytes);
     // Where it is ahead, m x k -> num_output: 128 x 9216 -> 4096 98 -> 82 us, 200 x 9216 -> 4096 179 -> 111, 2500 x 1300 ->
     // 2500 185 -> 140, 1000 x 1500 -> 1500 56 -> 51; not on fewer rows (64 x 9216 -> 4096: 53 and 58), shorter reductions
-    // (8192 x 512 -> 512: 55 and 67) and smaller problems (150 x 9000 -> 1000, 2.7 GFLOP: 39 and 45).
-    if (2.0 * M * K * O >= 4e9 && M >= 96 && K >= 1024) {
+    // (8192 x 512 -> 512: 55 and 67), smaller problems (150 x 9000 -> 1000, 2.7 GFLOP: 39 and 45) and few outputs, the columns of
+    // that problem (512 x 9216 -> 512: 51 and 58, 640 outputs: 62 and 66, 900: 86 and 76).
+    if (2.0 * M * K * O >= 4e9 && M >= 96 && K >= 1024 && O > 640) {
       c.n = p.num_output;
       c.c = p.k;
       c.w = 1;

@@ -79,6 +79,12 @@ def test_many_weights_and_few_columns_stay():
     assert "split" in names(P(4, 2048, 14, 14, 1024, 3, 3, 1, 1, 1, 1))["fwd"]
 
 
+@pytest.mark.parametrize("m,k,o,split", [(512, 9216, 512, False), (1000, 4096, 500, False), (512, 9216, 900, True)])
+def test_inner_products_of_few_outputs_stay(m, k, o, split):
+    kernels = conv.ip_desc_kernel_names(conv.ip_desc_create(conv.IpParams(m=m, k=k, num_output=o, relu=1)))
+    assert kernels.startswith("fwd=wgrad_on_corrsplit") == split, kernels
+
+
 def norm_error(g, r):
     g = g.cpu().double().numpy().reshape(r.shape)
     return float(np.linalg.norm(g - r) / np.linalg.norm(r))
