@@ -617,7 +617,8 @@ size_t configure_split(const CorrArgs& base, const PackArgs& pbase, int64_t cg_i
   a.share_w = (int32_t)plan.w.share;
   a.share_h = (int32_t)plan.h.share;
   a.PSZ = pixels ? 4 * a.PWID : (int32_t)plan.psz;
-  a.patch_stages = plan.psz <= 416 ? 2 : 1;  // two workgroups per compute unit either way
+  const int64_t table = grid.f.ff > 1 ? 128 * chunks : 0;  // the folded form's, behind the stages
+  a.patch_stages = plan.psz <= 416 && 192 * plan.psz + table <= 80 * 1024 ? 2 : 1;  // two workgroups per compute unit either way
   a.mPWID = make_magic((uint32_t)a.PWID);
   a.mRSEG = make_magic((uint32_t)(columns ? 1 : plan.h.pitch));
   a.m_tiles = (int32_t)ceil_div(a.Mrows, bm);
