@@ -36,10 +36,10 @@
  * synchronising.  Passes that use the workspace must not run concurrently on different
  * streams with the same workspace.  A pass is one to three kernel launches (helper kernels
  * pack the weights, clear or add partial results around the main kernel).  The first call
- * of a pass in a process may also perform a one-time, thread-safe kernel attribute set-up
- * (the opt-in to more than 64 KB of LDS), which is a host-side runtime call and not an
- * enqueue: make that first call outside HIP stream capture; every later call only enqueues
- * kernels and can be captured into a HIP graph.
+ * of a pass with a layer may also perform a one-time, thread-safe kernel attribute set-up
+ * (the opt-in of its kernels to more than 64 KB of LDS), which is a host-side runtime call
+ * and not an enqueue: make that first call outside HIP stream capture; every later call only
+ * enqueues kernels and can be captured into a HIP graph.
  *
  * Errors: every function returns a conv_status_t (0 = success, negative = error); no
  * exception, abort or printing crosses this boundary.  Argument, shape and workspace

@@ -9,7 +9,9 @@
 // [h, m, l][8 channels], 48 bytes per position and half.  An element is loaded and split once per tile and
 // chunk however many taps use it, the MFMA B operand of a tap is a 16-byte read at the column's base
 // plus a uniform offset, and padding, ragged borders and columns past the batch are resolved by the range
-// check of the patch's loads.  48 is an odd multiple of 16: 32 consecutive positions hit every bank evenly.
+// check of the patch's loads.  48 is an odd multiple of 16: a run of consecutive positions spreads over the banks.  Where a
+// tile's columns go on in the next image row the runs break, and with the stores 5 to 15 M conflict cycles a launch
+// remain on the large layers below (11 % of the cycles of the 48x256 tile, 4 to 10 % of the others').
 //
 // The A operand is packed in fragment order -- [m tile][step][row block][h, m, l][lane][8 k] -- so a wave
 // loads what its lanes feed with coalesced 16-byte loads straight from L2 into registers, one step ahead: A

@@ -247,6 +247,40 @@ def test_tiny_operands_keep_their_bits(pd, ex, ew, edy):
 
 
 @pytest.mark.gpu
+def test_split_passes_in_a_hip_graph():
+    """Captured once after an eager step, replayed on other inputs: the eager step's bits each time."""
+    pd = P(20, 48, 29, 30, 60, 5, 5)
+    assert names(pd)["fwd"].endswith("L=3)") and "split" in names(pd)["bwd_data"] and "split" in names(pd)["bwd_filter"]
+    op, d = OracleParams(**pd), conv.conv_desc_create(conv.ConvParams(**pd))
+    shapes = (oracle.x_shape(op), oracle.w_shape(op), oracle.output_shape(op))
+    x, w, b, dy = (t.to(DEV) for t in workloads.random_inputs(*shapes, 80))
+    y, dx, dw, db = torch.empty_like(dy), torch.empty_like(x), torch.empty_like(w), torch.empty_like(b)
+    ws = torch.empty((conv.conv_desc_workspace_bytes(d) + 7) // 8, device=DEV, dtype=torch.float64)
+
+    def step():
+        conv.conv_forward(d, x, w, b, y, ws)
+        conv.conv_backward_data(d, w, dy, dx, ws)
+        conv.conv_backward_filter_bias(d, x, dy, dw, db, 0.0, ws)
+
+    step()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    for rep in range(3):
+        for to, t in zip((x, w, b, dy), workloads.random_inputs(*shapes, 81 + rep)):
+            to.copy_(t)
+        for t in (y, dx, dw, db):
+            t.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [t.clone() for t in (y, dx, dw, db)]
+        step()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, e) for a, e in zip(got, (y, dx, dw, db)))
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("beta", [0.0, 1.0])
 @pytest.mark.parametrize("m,k,o", [(333, 1503, 2570), (4100, 333, 965), (999, 1503, 1501), (2500, 1300, 2500)])
 def test_inner_product_on_the_column_form(m, k, o, beta):
