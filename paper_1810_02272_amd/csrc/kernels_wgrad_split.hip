@@ -211,13 +211,18 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
     const bool my_turn = row_sums && (uint32_t)(ch - chunk_first) % turns == turn;
 #pragma unroll 1
     for (int s = 0; s < kChunkSteps; ++s) {
-      // this step's dy operands: masked, summed, split; then the next step's loads
+      // this step's dy operands: masked, summed, split; then the next step's loads.  Only an image's last run has anything to
+      // mask: a test for the wave instead of a select per value, which the two multiplications of a split pair cost.
       u32x4 av[MB][3];
+      if (__any(valid < 8)) {
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) raw[i][e] = e < valid ? raw[i][e] : 0.f;
+      }
 #pragma unroll
       for (int i = 0; i < MB; ++i) {
-        float v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = e < valid ? raw[i][e] : 0.f;
+        const float(&v)[8] = raw[i];
         if (my_turn) bsum[i] += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
         const Split8 sp = split8(v, sel);
         av[i][0] = sp.h;
