@@ -574,7 +574,9 @@ size_t configure_split(const CorrArgs& base, const PackArgs& pbase, int64_t cg_i
   // under 800 that the fp32 kernel need not slice are closer: it has no reduce launch there, and what the modelled steps
   // leave out of a split workgroup (prologue, epilogue, patch of a kernel of 1 to 3 taps) weighs more.  Of 329 passes drawn
   // over 1 to 30 GFLOP, 305 take the split form, at worst 3 % slower, 48 % faster in the mean; without the second line of
-  // constants 15 were up to 16 % slower (1x1, 141 -> 279 at 103x119: 57 and 67 us; 3x3, 80 -> 229 at 78x84: 31 and 36).
+  // constants 15 were up to 16 % slower (1x1, 141 -> 279 at 103x119: 57 and 67 us; 3x3, 80 -> 229 at 78x84: 31 and 36).  Of
+  // 2640 that take it in a wider draw (0.4 to 20 GFLOP, images from 1x1 on) 24 are more than 3 % slower, at worst 21 %, with
+  // the lines on weights below, 53 % faster in the mean.
   // Small strided backward passes stay: their scattered stores cost the gain (17 channels at 43x43, stride 2: 29 and 38).
   const double flops16 = 2.0 * (double)round_up(base.Mrows, 16) * base.Kred * (double)base.ncols * base.G;
   double here = plan.cost + 10, fp32 = flops16 / 85e6 + 12;
