@@ -22,10 +22,8 @@ extern "C" int replay_corr(const conv_desc* d, int backward, int64_t* out) {
   const int32_t tile = backward ? d->bwd_split : d->fwd_split;
   if (tile < 0) return 0;
   const CorrSplitArgs& a = backward ? d->bwd_sp : d->fwd_sp;
-  int32_t bm, bn, mt;
-  static const int32_t widths[SPLIT_TILE_COUNT] = {128, 256, 128, 128, 256, 128, 256};
-  bn = widths[tile];
-  (void)bm, (void)mt;
+  static const int32_t widths[SPLIT_TILE_COUNT] = {128, 256, 128, 128, 256, 128, 256};  // columns, by SplitTile
+  const int32_t bn = widths[tile];
   const bool cols = a.fold.subs != 0, fold = a.fold.ff > 1;
   if (a.fold.pixels) return 2;
   out[0] = out[1] = out[2] = 0;
