@@ -128,12 +128,13 @@ __device__ __forceinline__ void mfma_split(const u32x4 (&a)[3], const u32x4 (&b)
 }
 
 // Folded layers (SplitFold): where channel v of a grid position sits relative to the position's own pixel -- byte offset, and
-// row and column displacement in one word (15 and 16 bits; a channel past the last one fails every row test).
+// row and column displacement in one word (15 and 16 bits).  A channel past the last one sits beyond any blob (which is at
+// most 2^30 bytes): its loads read as zero.
 struct FoldEntry {
   uint32_t off, rc;
 };
 
-__device__ __forceinline__ int fold_row(const FoldEntry& f) { return (int)(f.rc >> 16) << (f.rc >> 31 ? 13 : 0); }
+__device__ __forceinline__ int fold_row(const FoldEntry& f) { return (int)(f.rc >> 16); }
 __device__ __forceinline__ int fold_col(const FoldEntry& f) { return (int)(f.rc & 0xffffu); }
 
 __device__ __forceinline__ void fill_fold_table(FoldEntry* tab, int count, const SplitFold& f, int width, int plane, int t,
@@ -142,8 +143,9 @@ __device__ __forceinline__ void fill_fold_table(FoldEntry* tab, int count, const
     const uint32_t c = mdiv((uint32_t)v, f.mFF), rem = (uint32_t)v - c * (uint32_t)f.ff;
     const uint32_t ir = mdiv(rem, f.mFw), jr = rem - ir * (uint32_t)f.fw;
     FoldEntry e;
-    e.off = 4u * (c * (uint32_t)plane + ir * (uint32_t)(f.dh * width) + jr * (uint32_t)f.dw);
-    e.rc = v < f.V ? (ir * (uint32_t)f.dh) << 16 | jr * (uint32_t)f.dw : 0xffff0000u;
+    const bool real = v < f.V;
+    e.off = real ? 4u * (c * (uint32_t)plane + ir * (uint32_t)(f.dh * width) + jr * (uint32_t)f.dw) : 0x80000000u;
+    e.rc = real ? (ir * (uint32_t)f.dh) << 16 | jr * (uint32_t)f.dw : 0u;
     tab[v] = e;
   }
 }
