@@ -12,7 +12,7 @@
 // before they are split and the sums by 2^-32 at the end: every fp32 value below 2^111, denormals included, keeps its bits.
 // Without the factors operands under 2^-109 lost some (2^-118: results off by 8.8e-6; fp32 denormals: all of them).  They
 // cost two vector instructions to the split's seven, up to 0.3 % of a layer's step (96 -> 256 in two groups, 5x5 at 27x27,
-// batch 128: 817 -> 819 us).
+// batch 128: 817 -> 819 us) and 0.7 % on the folded form, whose loads are busiest (3 -> 96, 11x11, stride 4: 448 -> 451).
 //
 // An operand that is not finite or from 2^111 on, or a sum from 2^96 on, makes the differences or the sums infinite or NaN; the
 // kernels look for non-finite sums at their end and compute those again on the fp32 matrix instructions.
