@@ -200,6 +200,23 @@ void split_variant_name(char* buf, size_t len, int32_t tile, const CorrSplitArgs
            a.ksplit, 2 + (a.ksplit > 1) + (zero_fill != 0));
 }
 
+// "<kernel>_<rows>x<columns>x<waves>[w<how the weights are read>, or v<16-byte loads of x>](S,L)"
+void small_variant_name(char* buf, size_t len, const char* kernel, const SmallTile& t, int32_t mode, int32_t S, int32_t launches) {
+  snprintf(buf, len, "%s_%dx%dx%d[%c%d](S=%d,L=%d)", kernel, 16 * t.mb, 16 * t.nb, t.waves, kernel[0] == 'c' ? 'w' : 'v', mode, S, launches);
+}
+
+// Puts the names of the passes that the one-launch kernels take in place of the others' (which: 0 floats, 1 doubles).
+void small_names(const conv_desc* d, int which, char* fwd, char* bwd, char* wg, size_t len) {
+  const char* const corr = which ? "corrsmall64" : "corrsmall";
+  if (d->fwd_small[which] >= 0)
+    small_variant_name(fwd, len, corr, kCorrSmallTiles[d->fwd_small[which]], d->fwd_sm[which].wmode, 1, 1);
+  if (d->bwd_small[which] >= 0)
+    small_variant_name(bwd, len, corr, kCorrSmallTiles[d->bwd_small[which]], d->bwd_sm[which].wmode, 1, 1 + (d->bwd_zero_fill != 0));
+  if (d->wg_small[which] >= 0)
+    small_variant_name(wg, len, which ? "smallwgrad64" : "smallwgrad", kWgradSmallTiles[d->wg_small[which]], d->wg_sm[which].xvec,
+                       d->wg_sm[which].S, 1 + (d->wg_sm[which].S > 1));
+}
+
 uint32_t koff_invalid(int32_t mode) { return mode == 0 ? 0x7FFFFFFCu : mode == 2 ? 0x40000000u : 0u; }
 
 // Decides whether the patch-staged kernel runs this correlation and, if so, fills its fields.
@@ -758,6 +775,170 @@ int32_t configure_wgrad_split(const WgradArgs& w, int32_t fp32_tile, int64_t N, 
   return best;
 }
 
+// Modelled times (us) of the one-launch kernels: a launch; then per tile the wave's chain of reduction groups (blocks of 64
+// places in the filter gradient), the groups that a compute unit's workgroups share, and those workgroups.
+struct SmallCost {
+  double chain, shared, workgroup;
+};
+
+// Sizes at which the tiled kernels stay although they are slower there (4 to 8 us a pass against 3.5 to 6): fewer columns
+// than two blocks, and reductions under three groups over 512 columns or more.  They are where every variant of a
+// tiled kernel can be compared with the oracle in milliseconds, which larger layers need as much as before.
+bool small_keeps_tiles(int64_t ncols, int64_t kred, int32_t elem_bytes) {
+  return ncols < 32 || (kred < 48 && (ncols >= 512 || elem_bytes == 8));
+}
+
+// Decides whether corr_small_kernel runs this correlation instead of the launches of `base` (tiles of bm x bn); fills a and
+// returns its tile, -1 if it does not.
+int32_t configure_corr_small(const CorrArgs& base, const PackArgs& k, int64_t w_elems, int64_t out_elems, int32_t elem_bytes,
+                             int32_t bm, int32_t bn, CorrSmallArgs& a) {
+  const int64_t limit = (int64_t)1 << 30, TH = base.THW / base.TW;
+  // Not measured: layers with a stride and a dilation, and what the patch-staged kernel takes.
+  if (base.use_patch || (base.sh * base.sw > 1 && base.dh * base.dw > 1)) return -1;
+  if (small_keeps_tiles(base.ncols, base.Kred, elem_bytes)) return -1;
+  if (base.ncols < 1 || (int64_t)base.in_bytes > limit || elem_bytes * w_elems > limit || elem_bytes * out_elems > limit) return -1;
+  // the kernel's packed displacements, and the row that stands for "past the reduction"
+  if (base.IH > 16384 || base.IW > 16384 || base.ph > 4096 || base.pw > 4096) return -1;
+  if ((TH - 1) * base.dh > 8192 || (int64_t)(base.TW - 1) * base.dw > 8192 || k.kh > 8192 || k.kw > 8192) return -1;
+  a = CorrSmallArgs();
+  static_cast<CorrArgs&>(a) = base;
+  a.w_bytes = (uint32_t)(elem_bytes * w_elems);
+  a.use_patch = 0;
+  a.ksplit = 1;
+  a.tap_pitch = a.THW;
+  a.Qh = (int32_t)TH;
+  a.kh = k.kh;
+  a.kw = k.kw;
+  const int32_t T = k.kh * k.kw;
+  a.w_grp_stride = k.Kg * k.Cg * T;
+  if (k.mode == 0) {
+    a.wmode = 0;
+    a.w_row_stride = k.Cg * T;
+    a.w_chan_stride = T;
+  } else {
+    a.w_row_stride = T;
+    a.w_chan_stride = k.Cg * T;
+    // tap slot q of a row phase r stands for the tap (stride*q + r) / dilation (see phase_dim): the same tap for every row
+    // where the stride divides the dilation, stride*q + r in an undilated layer, and not linear in q otherwise
+    const bool same_h = k.dh % k.sh == 0, same_w = k.dw % k.sw == 0;
+    if ((!same_h && k.dh != 1) || (!same_w && k.dw != 1)) return -1;
+    a.step_h = same_h ? 1 : k.sh;
+    a.step_w = same_w ? 1 : k.sw;
+    a.wmode = !same_h || !same_w ? 2 : T < 3 ? 1 : 3;
+    a.Cg_in = k.Kg;
+    if (a.wmode == 3) a.tap_pitch = (int32_t)round_up(T, 4);
+  }
+  const int64_t KT = round_up((int64_t)a.Kred / a.THW * a.tap_pitch, 16);
+  if (KT * (a.wmode == 3 ? 9 : 4 * (2 + a.wmode)) > 56 * 1024) return -1;  // the tables
+  a.KT = (int32_t)KT;
+  a.mPitch = make_magic((uint32_t)a.tap_pitch);
+  // [doubles][weights by single loads][tile]: fits to every tile on 203 (doubles: 123) passes of up to 3 (1) GFLOP, rms errors
+  // 10 to 19 %; the choice is 2 % behind the best tile on average, 1.5 times at worst
+  static const SmallCost kCost[2][2][CORR_SMALL_COUNT] = {
+      {{{0.129, 0.035, 0.32}, {0.110, 0.037, 0.58}, {0.123, 0.048, 0.53}, {0.216, 0.054, 0.67}, {0.228, 0.082, 1.05}, {0.148, 0.060, 0.80}, {0.274, 0.103, 1.22}},
+       {{0.151, 0.047, 0.32}, {0.193, 0.050, 0.43}, {0.224, 0.061, 0.54}, {0.224, 0.062, 0.73}, {0.259, 0.094, 1.18}, {0.309, 0.081, 0.72}, {0.390, 0.117, 1.45}}},
+      {{{0.072, 0.059, 0.42}, {0.000, 0.066, 0.72}, {0.091, 0.089, 0.68}, {0.139, 0.092, 0.78}, {0.149, 0.153, 1.21}, {0.119, 0.114, 1.01}, {}},
+       {{0.151, 0.063, 0.39}, {0.000, 0.079, 0.69}, {0.156, 0.107, 0.59}, {0.214, 0.102, 0.65}, {0.242, 0.175, 0.99}, {0.151, 0.159, 0.88}, {}}}};
+  // a forward gather that strides over columns takes more cache lines a load
+  const double strided = base.sw == 1 ? 1.0 : base.sw < 4 ? 1.1 : 1.3;
+  const int64_t groups = KT / 16;
+  int32_t best = -1;
+  double here = 0;
+  for (int32_t t = 0; t < CORR_SMALL_COUNT; ++t) {
+    const SmallCost& c = kCost[elem_bytes == 8][a.wmode == 1 || a.wmode == 2][t];
+    const SmallTile& s = kCorrSmallTiles[t];
+    if (c.shared == 0) continue;  // no instance
+    const int64_t units = (int64_t)a.G * ceil_div(a.Mrows, 16 * s.mb) * ceil_div(a.ncols, 16 * s.nb), per_cu = ceil_div(units, 256);
+    const double cost =
+        3.0 + strided * (c.chain * (double)ceil_div(groups, s.waves) + (c.shared * (double)groups + c.workgroup) * (double)per_cu);
+    if (best < 0 || cost < here) {
+      best = t;
+      here = cost;
+    }
+  }
+  // The launches of `base`, a fit to such passes (rms errors 9 and 6 %): pack, main and reduce kernel, the chunks of one
+  // workgroup and those of a compute unit by tile, partial sums and output.  Beyond 0.7 GFLOP a miss costs more than a launch
+  // gains, hence the second margin.  Of 203 passes of floats that were not in the fit none is more than 3 % slower, 1.46 times
+  // as fast in the geometric mean over all; doubles (123) 1.42 times, two more than 3 % slower.
+  static const double kOld[2][8] = {{5.7, 2.3, 0.73, 0.18, 0.117, 0.027, 0.199, 0.30}, {5.7, 2.3, 0.64, 0.17, 0.413, 0.090, 0.198, 0.31}};
+  const double* const o = kOld[elem_bytes == 8];
+  const int64_t chunks = ceil_div(ceil_div(base.Kred, 16), base.ksplit);
+  const int64_t per_cu = ceil_div((int64_t)base.G * base.m_tiles * base.col_tiles * base.ksplit, 256);
+  const double area = (double)(bm * bn) / 4096.0, out_mb = 1e-6 * (double)elem_bytes * (double)out_elems;
+  const double old = o[0] + (base.ksplit > 1 ? o[1] + o[2] * base.ksplit * out_mb : 0.0) + (double)chunks * (o[3] + o[4] * area) +
+                     (double)(per_cu * chunks) * (o[5] + o[6] * area + (elem_bytes == 4 && base.bounds_mode == 1 ? 0.018 : 0.0)) + o[7] * out_mb;
+  const double flops = 2.0 * base.Mrows * base.Kred * (double)base.ncols * base.G;
+  if (flops > (elem_bytes == 8 ? 1e9 : 1.5e9) || here > (flops < 0.7e9 ? 0.9 : 0.75) * old) return -1;
+  a.m_tiles = (int32_t)ceil_div(a.Mrows, 16 * kCorrSmallTiles[best].mb);
+  a.col_tiles = (int32_t)ceil_div(a.ncols, 16 * kCorrSmallTiles[best].nb);
+  if ((int64_t)a.G * a.m_tiles * a.col_tiles >= ((int64_t)1 << 31)) return -1;
+  return best;
+}
+
+// Decides whether wgrad_small_kernel runs the backward filter instead of the launches of `w` (tiles of bm x bn, steps of
+// 32 columns); fills a and returns its tile, -1 if it does not.
+int32_t configure_wgrad_small(const WgradArgs& w, int64_t N, int32_t elem_bytes, int32_t bm, int32_t bn, WgradSmallArgs& a) {
+  const int64_t limit = (int64_t)1 << 30, TH = w.khw / w.kw;
+  // Not measured: layers with a stride and a dilation.  Fewer places than one block: see small_keeps_tiles (128x128 tile).
+  if ((w.sh * w.sw > 1 && w.dh * w.dw > 1) || w.ncols < 64) return -1;
+  if (w.ncols < 1 || (int64_t)w.x_bytes > limit || (int64_t)w.dy_bytes > limit) return -1;
+  if (w.H > 16384 || w.W > 16384 || w.ph > 4096 || w.pw > 4096) return -1;  // packed into 16 bits
+  if ((TH - 1) * w.dh > 8192 || (int64_t)(w.kw - 1) * w.dw > 8192) return -1;
+  a = WgradSmallArgs();
+  static_cast<WgradArgs&>(a) = w;
+  a.N = (int32_t)N;
+  a.runs = (int32_t)ceil_div(w.P, 4);
+  a.mRuns = make_magic((uint32_t)a.runs);
+  a.xvec = w.khw == 1 && w.sh == 1 && w.sw == 1 && w.ph == 0 && w.pw == 0;
+  a.blocks = (int32_t)ceil_div(N * a.runs, 16);
+  // [doubles][16-byte loads of x][tile], and what a reduce launch costs: fits to every tile and 1 to 128 slices on 180
+  // (doubles: 64) filter gradients, rms errors 10 to 22 %; the choice is 2 % behind the best on average
+  static const SmallCost kCost[2][2][WGRAD_SMALL_COUNT] = {
+      {{{0.48, 0.196, 0.36}, {0.66, 0.321, 1.02}, {0.70, 0.263, 1.03}, {0.98, 0.412, 1.85}, {1.80, 0.325, 1.12}},
+       {{0.00, 0.169, 0.30}, {0.14, 0.213, 1.04}, {0.36, 0.249, 0.55}, {0.70, 0.310, 1.58}, {1.11, 0.247, 1.31}}},
+      {{{0.00, 0.329, 0.93}, {0.00, 0.488, 2.37}, {0.00, 0.494, 2.18}, {}, {0.78, 0.682, 2.28}},
+       {{0.00, 0.438, 0.00}, {0.00, 0.681, 0.00}, {0.00, 0.635, 0.00}, {}, {1.19, 0.801, 0.00}}}};
+  const double w_mb = 1e-6 * elem_bytes * (double)w.part_stride;
+  int32_t best = -1;
+  int64_t best_bps = 0;
+  double here = 0;
+  for (int32_t t = 0; t < WGRAD_SMALL_COUNT; ++t) {
+    const SmallCost& c = kCost[elem_bytes == 8][a.xvec != 0][t];
+    const SmallTile& s = kWgradSmallTiles[t];
+    if (c.shared == 0) continue;  // no instance
+    const int64_t tiles = (int64_t)w.G * ceil_div(w.Kg, 16 * s.mb) * ceil_div(w.Kred, 16 * s.nb);
+    for (int64_t S = 1; S <= w.S; S *= 2) {  // at most the slices that the workspace has room for
+      const int64_t bps = ceil_div(a.blocks, S), slices = ceil_div(a.blocks, bps), per_cu = ceil_div(tiles * slices, 256);
+      // a running sum no longer than on the tiled kernel: one that took all of 1.2 million places was off by 5e-6
+      if (bps * 64 / s.waves > (w.cols_per_split > 2048 ? w.cols_per_split : 2048)) continue;
+      const double cost = 3.3 + c.chain * (double)ceil_div(bps, s.waves) + (c.shared * (double)bps + c.workgroup) * (double)per_cu +
+                          (slices > 1 ? 2.0 + (elem_bytes == 8 ? 1.0 : 1.6) * (double)slices * w_mb : 0.0);
+      if (best < 0 || cost < here) {
+        best = t;
+        best_bps = bps;
+        here = cost;
+      }
+    }
+  }
+  if (best < 0) return -1;
+  // The launches of `w`, a fit to the same layers (rms errors 7 and 16 %).  With a margin of 0.9 142 of 175 layers of floats are
+  // taken, 1.43 times as fast in the geometric mean over all, eight more than 3 % slower; doubles 36 of 64, 1.11 times, one.
+  static const double kOld[2][7] = {{3.2, 0.74, 0.236, 0.374, 0.115, 0.242, 2.9}, {4.7, 0.63, 1.46, 1.91, 0.0, 0.222, 1.9}};
+  const double* const o = kOld[elem_bytes == 8];
+  const double area = (double)(bm * bn) / 4096.0;
+  const int64_t steps = ceil_div(w.cols_per_split, 32), per_cu = ceil_div((int64_t)w.G * w.m_tiles * w.n_tiles * w.S, 256);
+  const double old = o[0] + o[1] * w.S * w_mb + (double)steps * (o[2] + o[3] * area) +
+                     (double)(per_cu * steps) * (o[4] + o[5] * area + (elem_bytes == 4 && w.bounds_mode == 1 ? 0.32 : 0.0)) + o[6] * (double)per_cu;
+  const double flops = 2.0 * w.Kg * w.Kred * (double)w.ncols * w.G;
+  if (flops > 1e9 || here > (flops < 0.5e9 ? 0.9 : 0.75) * old) return -1;
+  a.m_tiles = (int32_t)ceil_div(a.Kg, 16 * kWgradSmallTiles[best].mb);
+  a.n_tiles = (int32_t)ceil_div(a.Kred, 16 * kWgradSmallTiles[best].nb);
+  a.blocks_per_split = (int32_t)best_bps;
+  a.S = (int32_t)ceil_div(a.blocks, best_bps);
+  if ((int64_t)a.S * a.G * a.m_tiles * a.n_tiles >= ((int64_t)1 << 31)) return -1;
+  return best;
+}
+
 // The split kernel's launches; its partial sums, if any, lie behind the packed weights.
 int launch_split(int32_t tile, const PackSplitArgs& pack, const CorrSplitArgs& plan, size_t pack_bytes, const float* in,
                  const float* w, const float* bias, float* out, bool accumulate, void* ws, void* stream) {
@@ -806,6 +987,15 @@ int run_forward(const conv_desc* d, const float* x, const float* w, const float*
     return ed ? record_hip_error(ed) : CONV_OK;
   }
   if (d->fwd_ws > 0 && (!ws || ws_bytes < d->fwd_ws)) return CONV_EWORKSPACE;
+  if (d->fwd_small[0] >= 0) {
+    CorrSmallArgs a = d->fwd_sm[0];
+    a.A = w;
+    a.in = x;
+    a.bias = bias;
+    a.out = y;
+    const int es = launch_corr_small(d->fwd_small[0], a, false, hip_stream);
+    return es ? record_hip_error(es) : CONV_OK;
+  }
   float* const part = reinterpret_cast<float*>(static_cast<char*>(ws) + d->fwd_pack_bytes);
   const bool split = d->fwd_split >= 0;
   int e;
@@ -865,6 +1055,17 @@ int run_backward_data(const conv_desc* d, const float* w, const float* dy, float
     return ed ? record_hip_error(ed) : CONV_OK;
   }
   if (d->bwd_ws > 0 && (!ws || ws_bytes < d->bwd_ws)) return CONV_EWORKSPACE;
+  if (d->bwd_small[0] >= 0) {
+    int es = d->bwd_zero_fill && beta == 0.f ? launch_fill_zero(dx, (size_t)d->bwd.out_elems * 4, hip_stream) : 0;
+    if (es) return record_hip_error(es);
+    CorrSmallArgs a = d->bwd_sm[0];
+    a.A = w;
+    a.in = dy;
+    a.out = dx;
+    a.accumulate = beta != 0.f;
+    es = launch_corr_small(d->bwd_small[0], a, false, hip_stream);
+    return es ? record_hip_error(es) : CONV_OK;
+  }
   float* const part = reinterpret_cast<float*>(static_cast<char*>(ws) + d->bwd_pack_bytes);
   const bool split = d->bwd_split >= 0;
   const int32_t ksplit = split ? d->bwd_sp.ksplit : d->bwd.ksplit, out_elems = d->bwd.out_elems;
@@ -966,6 +1167,22 @@ int run_backward_filter(const conv_desc* d, const float* x, const float* dy, flo
     a.n_tiles = 1;
     if (db) da.bias_part = a.bias_part = a.part + (size_t)da.S * w_elems;
     if (!empty) e = launch_direct(2, da, false, hip_stream);
+  } else if (d->wg_small[0] >= 0 && !empty) {
+    WgradSmallArgs sa = d->wg_sm[0];
+    a.S = sa.S;
+    a.n_tiles = 1;  // one share of the row sums per slice
+    sa.dy = dy;
+    sa.x = x;
+    sa.part = a.part;
+    sa.dw_out = dw;
+    sa.beta = beta;
+    if (db) sa.bias_part = a.bias_part = sa.S == 1 ? db : a.part + (size_t)sa.S * w_elems;
+    if (sa.S == 1) {
+      if (extras.bias) sa.col_bias = extras.bias;
+      sa.relu = extras.relu;
+    }
+    e = launch_wgrad_small(d->wg_small[0], sa, false, hip_stream);
+    if (e || sa.S == 1) return e ? record_hip_error(e) : CONV_OK;
   } else if (d->wg_split >= 0) {
     WgradSplitArgs sa = d->wg_sp;
     a.S = sa.S;
@@ -1133,6 +1350,7 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
     d->fwd_split = -1;
     const size_t sp = d->fwd_thin ? 0 : configure_split(a, k, Cg, N, y_elems, d->fwd_sp, d->fwd_sp_pack, d->fwd_split);
     if (sp) d->fwd_pack_bytes = sp;
+    d->fwd_small[0] = d->fwd_thin || sp ? -1 : configure_corr_small(a, k, w_elems, y_elems, 4, bm, bn, d->fwd_sm[0]);
     const int32_t S = sp ? d->fwd_sp.ksplit : a.ksplit;
     d->fwd_ws = d->fwd_pack_bytes + (S > 1 ? (size_t)S * y_elems * 4 : 0);
   }
@@ -1253,6 +1471,7 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
     d->bwd_split = -1;
     const size_t sp = d->bwd_thin ? 0 : configure_split(a, k, Kg, N, x_elems, d->bwd_sp, d->bwd_sp_pack, d->bwd_split);
     if (sp) d->bwd_pack_bytes = sp;
+    d->bwd_small[0] = d->bwd_thin || sp ? -1 : configure_corr_small(a, k, w_elems, x_elems, 4, bm, bn, d->bwd_sm[0]);
     const int32_t S = sp ? d->bwd_sp.ksplit : a.ksplit;
     d->bwd_ws = d->bwd_pack_bytes + (S > 1 ? (size_t)S * x_elems * 4 : 0);
   }
@@ -1343,6 +1562,7 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
       return CONV_ESHAPE;
     }
     d->wg_split = configure_wgrad_split(a, d->wg_tile, N, K, w_elems, d->wg_sp);
+    d->wg_small[0] = d->wg_split >= 0 ? -1 : configure_wgrad_small(a, N, 4, bm, bn, d->wg_sm[0]);
     if (d->wg_split >= 0) {
       d->wg_ws = (size_t)d->wg_sp.S * (size_t)w_elems * 4;
       d->wgb_ws = (size_t)d->wg_sp.S * (size_t)(w_elems + d->wg_sp.n_tiles * K) * 4;
@@ -1398,6 +1618,8 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
     };
     corr64(d->fwd, d->fwd_pack, d->fwd64, d->fwd64_pack, x_elems, d->fwd64_ws, d->fwd64_rows);
     corr64(d->bwd, d->bwd_pack, d->bwd64, d->bwd64_pack, y_elems, d->bwd64_ws, d->bwd64_rows);
+    d->fwd_small[1] = configure_corr_small(d->fwd64, d->fwd_pack, w_elems, y_elems, 8, d->fwd64_rows, bn64, d->fwd_sm[1]);
+    d->bwd_small[1] = configure_corr_small(d->bwd64, d->bwd_pack, w_elems, x_elems, 8, d->bwd64_rows, bn64, d->bwd_sm[1]);
     const int32_t bm64 = d->wg64_rows = f64_pick_rows(Kg, true);
     WgradArgs& a = d->wg64;
     a = d->wg;
@@ -1418,6 +1640,7 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
     a.S = (int32_t)ceil_div((int64_t)a.ncols > 0 ? a.ncols : 1, a.cols_per_split);
     if (a.S * w_elems >= max64 || tiles * a.S >= ((int64_t)1 << 31)) d->f64_ok = 0;
     d->wg64_ws = (size_t)a.S * (size_t)w_elems * 8;
+    d->wg_small[1] = configure_wgrad_small(a, N, 8, bm64, bn64, d->wg_sm[1]);
     d->bg64_ws = 2 * d->bg_ws;
     auto e64 = [](const CorrArgs& c) { return c.simple_epilogue ? 's' : 'p'; };
     snprintf(d->names64, sizeof(d->names64),
@@ -1426,6 +1649,15 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
              d->fwd64_rows, e64(d->fwd64), d->fwd64.ksplit, 2 + (d->fwd64.ksplit > 1), d->bwd64_rows, e64(d->bwd64),
              d->bwd64.ksplit, 2 + (d->bwd64.ksplit > 1) + (d->bwd_zero_fill != 0), d->wg64_rows, a.S,
              d->bg.S);
+    if (d->fwd_small[1] >= 0 || d->bwd_small[1] >= 0 || d->wg_small[1] >= 0) {
+      char f[64], b[64], wg[64];
+      snprintf(f, sizeof(f), "corr64_%dx64x16[e%c](S=%d,L=%d)", d->fwd64_rows, e64(d->fwd64), d->fwd64.ksplit, 2 + (d->fwd64.ksplit > 1));
+      snprintf(b, sizeof(b), "corr64_%dx64x16[e%c](S=%d,L=%d)", d->bwd64_rows, e64(d->bwd64), d->bwd64.ksplit,
+               2 + (d->bwd64.ksplit > 1) + (d->bwd_zero_fill != 0));
+      snprintf(wg, sizeof(wg), "wgrad64_%dx64x16(S=%d,L=2)", d->wg64_rows, a.S);
+      small_names(d, 1, f, b, wg, sizeof(f));
+      snprintf(d->names64, sizeof(d->names64), "fwd=%s;bwd_data=%s;bwd_filter=%s;bwd_bias=bias_grad64(S=%d,L=2)", f, b, wg, d->bg.S);
+    }
     d->ws_bytes64 = d->fwd64_ws;
     if (d->bwd64_ws > d->ws_bytes64) d->ws_bytes64 = d->bwd64_ws;
     if (d->wg64_ws > d->ws_bytes64) d->ws_bytes64 = d->wg64_ws;
@@ -1528,6 +1760,7 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
       snprintf(wg, sizeof(wg), "splitwgrad_%dx%dx16[p%d,st%d](S=%d,L=2)", rows, taps, split_patch_units(psz),
                d->wg_sp.patch_stages, d->wg_sp.S);
     }
+    small_names(d, 0, f, b, wg, sizeof(f));
     if (d->use_direct) {
       char df[3][32];
       for (int pass = 0; pass < 3; ++pass) direct_form_name(pass, d->dir, df[pass], sizeof(df[pass]));
@@ -1627,11 +1860,22 @@ int conv_desc_workspace_bytes_f64(const conv_desc_t* d, size_t* bytes) {
   return CONV_OK;
 }
 
-static int run_corr64(const conv_desc_t* d, int32_t tile_rows, const CorrArgs& args, const PackArgs& pack, size_t need,
+static int run_corr64(const conv_desc_t* d, int32_t small, const CorrSmallArgs& small_args, int32_t tile_rows, const CorrArgs& args, const PackArgs& pack, size_t need,
                       const double* w, const double* in, const double* bias, double* out, size_t zero_out_bytes,
                       void* ws, size_t ws_bytes, void* hip_stream) {
   if (!d->f64_ok) return CONV_ESHAPE;
   if (!ws || ws_bytes < need) return CONV_EWORKSPACE;
+  if (small >= 0) {
+    int es = zero_out_bytes ? launch_fill_zero(out, zero_out_bytes, hip_stream) : 0;
+    if (es) return record_hip_error(es);
+    CorrSmallArgs sa = small_args;
+    sa.A = reinterpret_cast<const float*>(w);
+    sa.in = reinterpret_cast<const float*>(in);
+    sa.bias = reinterpret_cast<const float*>(bias);
+    sa.out = reinterpret_cast<float*>(out);
+    es = launch_corr_small(small, sa, true, hip_stream);
+    return es ? record_hip_error(es) : CONV_OK;
+  }
   PackArgs k = pack;
   const size_t pack_bytes = (size_t)k.G * k.KP * k.MP * 8 + (size_t)k.KP * sizeof(KTabEntry);
   double* const part = reinterpret_cast<double*>(static_cast<char*>(ws) + pack_bytes);
@@ -1686,7 +1930,7 @@ int conv_forward_f64(const conv_desc_t* d, const double* x, const double* w, con
     const int ed = launch_direct(0, da, true, hip_stream);
     return ed ? record_hip_error(ed) : CONV_OK;
   }
-  return run_corr64(d, d->fwd64_rows, d->fwd64, d->fwd64_pack, d->fwd64_ws, w, x, bias, y, 0, ws, ws_bytes,
+  return run_corr64(d, d->fwd_small[1], d->fwd_sm[1], d->fwd64_rows, d->fwd64, d->fwd64_pack, d->fwd64_ws, w, x, bias, y, 0, ws, ws_bytes,
                     hip_stream);
 }
 
@@ -1704,7 +1948,7 @@ int conv_backward_data_f64(const conv_desc_t* d, const double* w, const double* 
     return ed ? record_hip_error(ed) : CONV_OK;
   }
   const size_t zero = d->bwd_zero_fill ? (size_t)d->bwd64.out_elems * 8 : 0;
-  return run_corr64(d, d->bwd64_rows, d->bwd64, d->bwd64_pack, d->bwd64_ws, w, dy, nullptr, dx, zero, ws, ws_bytes,
+  return run_corr64(d, d->bwd_small[1], d->bwd_sm[1], d->bwd64_rows, d->bwd64, d->bwd64_pack, d->bwd64_ws, w, dy, nullptr, dx, zero, ws, ws_bytes,
                     hip_stream);
 }
 
@@ -1728,6 +1972,16 @@ int conv_backward_filter_f64(const conv_desc_t* d, const double* x, const double
     da.part = ws;
     a.S = da.S;
     if (!empty) e = launch_direct(2, da, true, hip_stream);
+  } else if (!empty && d->wg_small[1] >= 0) {
+    WgradSmallArgs sa = d->wg_sm[1];
+    a.S = sa.S;
+    sa.dy = a.dy;
+    sa.x = a.x;
+    sa.part = a.part;
+    sa.dw_out = reinterpret_cast<float*>(dw);
+    sa.beta = (float)beta;
+    e = launch_wgrad_small(d->wg_small[1], sa, true, hip_stream);
+    if (e || sa.S == 1) return e ? record_hip_error(e) : CONV_OK;
   } else if (!empty) {
     e = launch_wgrad64(d->wg64_rows, a, hip_stream);
   }

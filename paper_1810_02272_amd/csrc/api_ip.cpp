@@ -106,6 +106,7 @@ int ip_desc_create(ip_desc_t** out, const ip_params_t* pp) {
     fwd.replace(fwd.rfind("L="), std::string::npos, "L=3)");
     fwd.insert(0, "wgrad_on_");
   }
+  if (fwd.compare(0, 5, "small") == 0) fwd.insert(0, "wgrad_on_");
   snprintf(d->names, sizeof(d->names), "fwd=%s;bwd_data=%s;bwd_filter=%s;bwd_bias=colsum(S=%d,L=%d)",
            fwd.c_str(), field(in, "fwd=").c_str(), field(in, "bwd_data=").c_str(),
            one_launch ? 1 : cs.S, one_launch ? 1 : 2);

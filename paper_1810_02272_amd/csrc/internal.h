@@ -205,6 +205,34 @@ struct WgradSplitArgs {
   Magic mPWID, mRSEG;
 };
 
+// One-launch kernels of small layers (kernels_small.hip); the pointer members address floats or doubles.
+struct CorrSmallArgs : CorrArgs {  // A = the weight blob itself, with the strides of the staged thin-row form
+  uint32_t w_bytes;
+  int32_t KT;                    // reduction indices, a multiple of the kernel's groups of 16
+  int32_t wmode;                 // how the weights are read (WMODE of the kernel)
+  int32_t tap_pitch;             // reduction indices per channel
+  Magic mPitch;
+  int32_t Qh, kh, kw;            // tap rows of the gather; taps of the layer
+  int32_t step_h, step_w;        // taps of the layer between two of the gather
+};
+
+struct WgradSmallArgs : WgradArgs {
+  int32_t N, runs;  // images, runs of four pixels per image
+  Magic mRuns;
+  int32_t blocks, blocks_per_split;  // of sixteen runs
+  int32_t xvec;     // four pixels of x are one 16-byte load
+  // S == 1: the kernel finishes dw (and db, through bias_part)
+  float* dw_out;
+  float beta;
+  const float* col_bias;  // added to every row of dw, one value per column
+  int32_t relu;
+};
+
+struct SmallTile {
+  int32_t mb, nb, waves;  // 16-row blocks, 16-column blocks, waves that share the reduction
+};
+constexpr int32_t CORR_SMALL_COUNT = 7, WGRAD_SMALL_COUNT = 5;
+
 struct ReduceArgs {
   const float* part;  // [S][stride]: elements [0, count) of a slice go to dst
   float* dst;         // [count]
@@ -352,6 +380,9 @@ int launch_corr_split(int32_t tile, const CorrSplitArgs& a, void* stream);
 void wgrad_split_shape(int32_t tile, int32_t* rows, int32_t* taps);
 int32_t wgrad_split_chunk_runs();
 int launch_wgrad_split(int32_t tile, const WgradSplitArgs& a, void* stream);
+extern const SmallTile kCorrSmallTiles[CORR_SMALL_COUNT], kWgradSmallTiles[WGRAD_SMALL_COUNT];
+int launch_corr_small(int32_t tile, const CorrSmallArgs& a, bool f64, void* stream);
+int launch_wgrad_small(int32_t tile, const WgradSmallArgs& a, bool f64, void* stream);
 int launch_corr_thin(const CorrArgs& a, void* stream);  // Mrows <= 4, offset-only epilogue, no split
 int launch_wgrad(int32_t tile, const WgradArgs& a, void* stream);
 int launch_reduce(const ReduceArgs& a, void* stream);
@@ -430,6 +461,10 @@ struct conv_desc {
   int32_t fwd_split, bwd_split;
   mi355conv::CorrSplitArgs fwd_sp, bwd_sp;
   mi355conv::PackSplitArgs fwd_sp_pack, bwd_sp_pack;
+  // one launch, small layers (index into kCorrSmallTiles / kWgradSmallTiles, or -1); [0] floats, [1] doubles
+  int32_t fwd_small[2], bwd_small[2], wg_small[2];
+  mi355conv::CorrSmallArgs fwd_sm[2], bwd_sm[2];
+  mi355conv::WgradSmallArgs wg_sm[2];
   // backward data
   int32_t bwd_tile;
   mi355conv::CorrArgs bwd;

@@ -187,6 +187,14 @@ VARIANT_CASES = [
     (P(3, 1, 33, 31, 6, 5, 5, 1, 1, 2, 2), "bwd_data", "corr_thin_r1_lds5"),
     (P(7, 2, 12, 11, 6, 5, 5, 1, 1, 2, 2), "bwd_data", "corr_thin_r2_lds5"),
     (P(3, 3, 20, 31, 9, 5, 5, 1, 1, 4, 4), "bwd_data", "corr_thin_r3_lds5"),
+    # variants whose other cases run on the one-launch kernels of small layers
+    (P(1, 1, 5, 6, 33, 2, 2, 2, 2), "fwd", "corr_m16_48x128x16[m0"),
+    (P(1, 1, 5, 6, 64, 2, 2, 2, 2), "fwd", "corr_m32_64x64x16[m0"),
+    (P(1, 1, 5, 6, 96, 2, 2, 2, 2), "fwd", "corr_m32_96x128x16[m0"),
+    (P(1, 16, 5, 6, 1, 6, 6, 1, 1, 2, 2), "bwd_data", "corr_m16_16x64x16[m1"),
+    (P(1, 128, 5, 6, 1, 1, 1), "bwd_data", "corr_m32_128x64x16[m2"),
+    (P(1, 24, 5, 6, 1, 2, 2, 2, 2), "bwd_data", "corr_m32_96x128x16[m2"),  # in doubles the 96-row tile's scattered stores
+    (P(1, 8, 5, 6, 96, 3, 3, 1, 1, 1, 1), "bwd_filter", "wgrad_m32_96x128x32[m2"),
     (P(6, 8, 15, 16, 8, 5, 5, 1, 1, 2, 2, 1, 1, 2), "bwd_data", "corr_thin_r4_lds5"),
 ]
 
