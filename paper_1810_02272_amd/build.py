@@ -8,6 +8,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_HERE)
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "libmi355conv.so")
+MARSHAL = os.path.join(_HERE, "_marshal.so")  # Python extension over LIB (csrc/marshal.cpp)
 SOURCES = ["api.cpp", "api_ip.cpp", "kernels_corr.hip", "kernels_corr_patch.hip", "kernels_corr_thin.hip",
            "kernels_small.hip", "kernels_corr_split.hip", "kernels_wgrad_split.hip", "kernels_wgrad.hip", "kernels_bias.hip",
            "kernels_ip.hip", "kernels_pg.hip", "kernels_f64.hip", "kernels_direct.hip", "static_workspace.hip"]
@@ -32,12 +33,44 @@ def _hipcc() -> str:
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(MARSHAL):
         return True
-    t = os.path.getmtime(LIB)
-    deps = [os.path.join(CSRC, s) for s in SOURCES + HEADERS] + [
+    t = min(os.path.getmtime(LIB), os.path.getmtime(MARSHAL))
+    deps = [os.path.join(CSRC, s) for s in SOURCES + HEADERS + ["marshal.cpp"]] + [
         os.path.join(_ROOT, "include", h) for h in ("mi355conv.h", "mi355ip.h", "mi355pg.h")]
     return any(os.path.getmtime(d) > t for d in deps)
+
+
+def _torch_dir() -> str:
+    import torch
+    return os.path.dirname(torch.__file__)
+
+
+def _compile_marshal(obj_dir: str) -> str:
+    """Host code only: the extension calls the C entry points of LIB."""
+    import sysconfig
+
+    torch_include = os.path.join(_torch_dir(), "include")
+    obj = os.path.join(obj_dir, "marshal.o")
+    rocm = os.path.dirname(os.path.dirname(_hipcc())) if os.path.isabs(_hipcc()) else "/opt/rocm"
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM", "-w",
+           "-I", os.path.join(_ROOT, "include"), "-isystem", torch_include,
+           "-isystem", os.path.join(torch_include, "torch", "csrc", "api", "include"),
+           "-isystem", os.path.join(rocm, "include"), "-isystem", sysconfig.get_paths()["include"],
+           "-c", os.path.join(CSRC, "marshal.cpp"), "-o", obj]
+    res = subprocess.run(cmd, cwd=CSRC, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + " ".join(cmd) + "\n" + res.stdout + res.stderr)
+    return obj
+
+
+def _link_marshal(obj: str) -> None:
+    torch_lib = os.path.join(_torch_dir(), "lib")
+    cmd = ["g++", "-shared", "-o", MARSHAL, obj, "-L", _HERE, "-l:libmi355conv.so", "-Wl,-rpath,$ORIGIN",
+           "-L", torch_lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    res = subprocess.run(cmd, cwd=_HERE, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ link failed:\n" + " ".join(cmd) + "\n" + res.stdout + res.stderr)
 
 
 def build(force: bool = True, verbose: bool = False) -> str:
@@ -63,11 +96,14 @@ def build(force: bool = True, verbose: bool = False) -> str:
         return obj
 
     with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as pool:
+        marshal = pool.submit(_compile_marshal, obj_dir)
         objs = list(pool.map(compile_one, SOURCES))
+        marshal_obj = marshal.result()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     res = subprocess.run(cmd, cwd=CSRC, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("hipcc link failed:\n" + " ".join(cmd) + "\n" + res.stdout + res.stderr)
+    _link_marshal(marshal_obj)
     return LIB
 
 

@@ -1,5 +1,6 @@
-"""ctypes binding for the InnerProduct entry points of libmi355conv.so: the same names as
-include/mi355ip.h, marshalling only (every compute step runs in the HIP kernels)."""
+"""Binding for the InnerProduct entry points of libmi355conv.so: the same names as
+include/mi355ip.h, marshalling only (every compute step runs in the HIP kernels; see
+binding.py for the extension that the compute calls go through)."""
 from __future__ import annotations
 
 import ctypes
@@ -52,6 +53,7 @@ class IpDesc:
     def __init__(self, handle: int, params: IpParams):
         self.handle = handle
         self.params = params
+        self._plan = None
 
     def __del__(self):
         try:
@@ -64,11 +66,14 @@ def ip_desc_create(params: IpParams) -> IpDesc:
     c = _CParams(*[int(getattr(params, f.name)) for f in fields(IpParams)])
     out = ctypes.c_void_p()
     _b._check(_load().ip_desc_create(ctypes.byref(out), ctypes.byref(c)), "ip_desc_create")
-    return IpDesc(out.value, params)
+    desc = IpDesc(out.value, params)
+    desc._plan = _b._marshal.ip_plan(desc.handle, c.m, c.k, c.num_output)
+    return desc
 
 
 def ip_desc_destroy(desc: IpDesc) -> None:
     if desc.handle:
+        desc._plan = None
         _load().ip_desc_destroy(desc.handle)
         desc.handle = None
 
@@ -84,6 +89,9 @@ def ip_desc_kernel_names(desc: IpDesc) -> str:
 
 
 def ip_forward(desc, x, w, bias, y, ws=None, stream=None) -> None:
+    status = _b._marshal.ip_forward(desc._plan, x, w, bias, y, ws, stream)
+    if status is not None:
+        return _b._check(status, "ip_forward")
     p = desc.params
     wp, wb = _b._ws(ws)
     _b._check(_load().ip_forward(desc.handle, _b._ptr(x, (p.m, p.k), "x"), _b._ptr(w, (p.num_output, p.k), "w"),
@@ -92,6 +100,9 @@ def ip_forward(desc, x, w, bias, y, ws=None, stream=None) -> None:
 
 
 def ip_relu_backward(desc, y, dy, dz, stream=None) -> None:
+    status = _b._marshal.ip_relu_backward(desc._plan, y, dy, dz, stream)
+    if status is not None:
+        return _b._check(status, "ip_relu_backward")
     p = desc.params
     _b._check(_load().ip_relu_backward(desc.handle, _b._ptr(y, (p.m, p.num_output), "y"),
                                        _b._ptr(dy, (p.m, p.num_output), "dy"), _b._ptr(dz, (p.m, p.num_output), "dz"),
@@ -99,6 +110,9 @@ def ip_relu_backward(desc, y, dy, dz, stream=None) -> None:
 
 
 def ip_backward_data(desc, w, dz, dx, ws=None, stream=None) -> None:
+    status = _b._marshal.ip_backward_data(desc._plan, w, dz, dx, ws, stream)
+    if status is not None:
+        return _b._check(status, "ip_backward_data")
     p = desc.params
     wp, wb = _b._ws(ws)
     _b._check(_load().ip_backward_data(desc.handle, _b._ptr(w, (p.num_output, p.k), "w"),
@@ -107,6 +121,9 @@ def ip_backward_data(desc, w, dz, dx, ws=None, stream=None) -> None:
 
 
 def ip_backward_filter(desc, x, dz, dw, beta=0.0, ws=None, stream=None) -> None:
+    status = _b._marshal.ip_backward_filter(desc._plan, x, dz, dw, beta, ws, stream)
+    if status is not None:
+        return _b._check(status, "ip_backward_filter")
     p = desc.params
     wp, wb = _b._ws(ws)
     _b._check(_load().ip_backward_filter(desc.handle, _b._ptr(x, (p.m, p.k), "x"),
@@ -115,6 +132,9 @@ def ip_backward_filter(desc, x, dz, dw, beta=0.0, ws=None, stream=None) -> None:
 
 
 def ip_backward_bias(desc, dz, db, beta=0.0, ws=None, stream=None) -> None:
+    status = _b._marshal.ip_backward_bias(desc._plan, dz, db, beta, ws, stream)
+    if status is not None:
+        return _b._check(status, "ip_backward_bias")
     p = desc.params
     wp, wb = _b._ws(ws)
     _b._check(_load().ip_backward_bias(desc.handle, _b._ptr(dz, (p.m, p.num_output), "dz"),

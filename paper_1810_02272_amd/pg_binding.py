@@ -1,5 +1,6 @@
-"""ctypes binding for the policy-gradient entry points of libmi355conv.so: the same names as
-include/mi355pg.h, marshalling only (every compute step runs in the HIP kernels)."""
+"""Binding for the policy-gradient entry points of libmi355conv.so: the same names as
+include/mi355pg.h, marshalling only (every compute step runs in the HIP kernels; see binding.py for the
+extension that the calls go through)."""
 from __future__ import annotations
 
 import ctypes
@@ -27,6 +28,12 @@ def _load():
     return lib
 
 
+def _native():
+    if _b._marshal is None:  # no descriptor has loaded it
+        _load()
+    return _b._marshal
+
+
 def _iptr(t, shape, name):
     if t is None:
         return None
@@ -40,6 +47,9 @@ def _iptr(t, shape, name):
 
 
 def pg_sigmoid_sample_action(aprob, random, action, stream=None) -> None:
+    status = _native().pg_sigmoid_sample_action(aprob, random, action, stream)
+    if status is not None:
+        return _b._check(status, "pg_sigmoid_sample_action")
     steps = aprob.numel()
     _b._check(_load().pg_sigmoid_sample_action(_b._ptr(aprob, (steps,), "aprob"), _b._ptr(random, (steps,), "random"),
                                                _iptr(action, (steps,), "action"), steps, _b._stream(stream)),
@@ -47,6 +57,9 @@ def pg_sigmoid_sample_action(aprob, random, action, stream=None) -> None:
 
 
 def pg_discount_rewards(reward, episode_offsets, gamma, discounted, stream=None) -> None:
+    status = _native().pg_discount_rewards(reward, episode_offsets, gamma, discounted, stream)
+    if status is not None:
+        return _b._check(status, "pg_discount_rewards")
     steps, episodes = reward.numel(), episode_offsets.numel() - 1
     _b._check(_load().pg_discount_rewards(_b._ptr(reward, (steps,), "reward"),
                                           _iptr(episode_offsets, (episodes + 1,), "episode_offsets"), episodes, steps,
@@ -55,6 +68,9 @@ def pg_discount_rewards(reward, episode_offsets, gamma, discounted, stream=None)
 
 
 def pg_sigmoid_bottom_diff(aprob, action, discounted, dlogps, bottom_diff, stream=None) -> None:
+    status = _native().pg_sigmoid_bottom_diff(aprob, action, discounted, dlogps, bottom_diff, stream)
+    if status is not None:
+        return _b._check(status, "pg_sigmoid_bottom_diff")
     steps = aprob.numel()
     _b._check(_load().pg_sigmoid_bottom_diff(_b._ptr(aprob, (steps,), "aprob"), _iptr(action, (steps,), "action"),
                                              _b._ptr(discounted, (steps,), "discounted"),
@@ -64,6 +80,9 @@ def pg_sigmoid_bottom_diff(aprob, action, discounted, dlogps, bottom_diff, strea
 
 
 def pg_softmax_bottom_diff(logits, action, discounted, probs, bottom_diff, stream=None) -> None:
+    status = _native().pg_softmax_bottom_diff(logits, action, discounted, probs, bottom_diff, stream)
+    if status is not None:
+        return _b._check(status, "pg_softmax_bottom_diff")
     steps, actions = logits.shape
     _b._check(_load().pg_softmax_bottom_diff(_b._ptr(logits, (steps, actions), "logits"),
                                              _iptr(action, (steps,), "action"),
