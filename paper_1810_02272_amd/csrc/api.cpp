@@ -775,11 +775,79 @@ int32_t configure_wgrad_split(const WgradArgs& w, int32_t fp32_tile, int64_t N, 
   return best;
 }
 
+// Modelled time (us) of a forward or backward-data pass on the tiled fp32 kernels: the launches, packed weights (MB), partial
+// sums and output (MB), then per tile the chunks of 16 reduction indices that one workgroup walks alone and those that the
+// workgroups of a compute unit share, dearer where the gather compares or masks.  A fit to 8653 timings -- every tile, 1 to 16
+// slices, 240 passes of 0.15 to 20 GFLOP (rms error 14 to 16 %, most of it in configurations far from the best).
+double corr_model(const CorrArgs& a, int32_t tile, int64_t S, int64_t out_elems, bool zero_fill) {
+  static const double kCost[CORR_TILE_COUNT][4] = {  // alone, shared, with compares, with masks
+      {0.243, 0.802, 0.151, 0.075}, {0.208, 0.386, 0.081, 0.045}, {0.263, 0.564, 0.191, 0.099}, {0.296, 0.327, 0.152, 0.078},
+      {0.250, 0.168, 0.074, 0.035}, {0.317, 0.379, 0.233, 0.104}, {0.281, 0.184, 0.107, 0.043}, {0.253, 0.615, 0.280, 0.136},
+      {0.238, 0.263, 0.137, 0.065}, {0.250, 0.307, 0.134, 0.028}, {0.208, 0.080, 0.021, 0.003}};
+  int32_t bm, bn, bk;
+  corr_tile_shape(tile, &bm, &bn, &bk);
+  const double* const c = kCost[tile];
+  const int64_t units = (int64_t)a.G * ceil_div(a.Mrows, bm) * ceil_div(a.ncols, bn), all = ceil_div(a.Kred, 16);
+  const int64_t chunks = ceil_div(all, S), slices = ceil_div(all, chunks), per_cu = ceil_div(units * slices, 256);
+  const double out_mb = 4e-6 * (double)out_elems, pack_mb = 4e-6 * (double)a.G * (double)round_up(a.Mrows, bm) * (double)(16 * all);
+  const double shared = c[1] + (a.bounds_mode == 1 ? c[2] : a.bounds_mode == 2 ? c[3] : 0.0) + (tile == CORR_16x64 ? 0.09 / (double)chunks : 0.0);
+  return 5.5 + 0.3 * pack_mb + 0.25 * out_mb + (zero_fill ? 2.4 : 0.0) + (slices > 1 ? 2.2 + 0.7 * (double)slices * out_mb : 0.0) +
+         (double)chunks * (c[0] + (double)per_cu * shared);
+}
+
+// Tile and slices of a pass on the tiled fp32 kernels by that model, for passes of 0.2 GFLOP and more: the row count that pads
+// least says little about the time.  73 -> 2 channels 8x8, stride 2, at 26x32, batch 73, backward data: 16x64 unsplit 128 us, in
+// 12 slices 61; 236 -> 300 in four groups, 3x5, stride 2: 16x64 162, 32x128 94.  Of 152 passes of the fit that these kernels
+// took, none was on the tiles of at most 48 rows by 256 columns that the patch-staged kernel takes (left alone); the
+// choice is 11 % faster than the rules' in the geometric mean, up to twice, and 2 % behind the best.  Smaller passes keep the
+// rules (pick_corr_tile, configure_ksplit): their times differ little, and each variant has its parity case there.
+void plan_corr(CorrArgs& a, PackArgs& k, int64_t out_elems, bool zero_fill, int32_t& tile) {
+  const double flops = 2.0 * a.Mrows * a.Kred * (double)a.ncols * a.G;
+  if (a.use_patch || a.ncols < 1 || flops < 2e8) return;
+  static const int32_t kSlices[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
+  const int64_t all = ceil_div(a.Kred, 16);
+  int32_t best = tile;
+  int64_t best_S = a.ksplit;
+  double cost = 0.92 * corr_model(a, tile, a.ksplit, out_elems, zero_fill);  // nearer than that is within the model's error
+  for (int32_t t = 0; t < CORR_TILE_COUNT; ++t) {
+    int32_t bm, bn, bk;
+    corr_tile_shape(t, &bm, &bn, &bk);
+    if ((int64_t)a.G * a.KP * round_up(a.Mrows, bm) >= kMaxElems) continue;
+    for (const int64_t S : kSlices) {
+      if (S > 1 && (2 * S > all || S * out_elems > ((int64_t)16 << 20))) break;  // slices of two chunks, 64 MiB of partial sums
+      const double c = corr_model(a, t, S, out_elems, zero_fill);
+      if (c < cost) {
+        best = t;
+        best_S = S;
+        cost = c;
+      }
+    }
+  }
+  if (best == tile && best_S == a.ksplit) return;
+  int32_t bm, bn, bk;
+  corr_tile_shape(best, &bm, &bn, &bk);
+  tile = best;
+  a.MP = k.MP = (int32_t)round_up(a.Mrows, bm);
+  a.m_tiles = a.MP / bm;
+  a.col_tiles = (int32_t)ceil_div(a.ncols, bn);
+  a.chunks_per_split = (int32_t)ceil_div(all, best_S);
+  a.ksplit = (int32_t)ceil_div(all, a.chunks_per_split);
+}
+
 // Modelled times (us) of the one-launch kernels: a launch; then per tile the wave's chain of reduction groups (blocks of 64
 // places in the filter gradient), the groups that a compute unit's workgroups share, and those workgroups.
 struct SmallCost {
   double chain, shared, workgroup;
 };
+
+// The same for a pass on the tiled kernels of doubles (tiles of bm x bn), a fit to 123 passes (rms error 6 %).
+double corr64_model(const CorrArgs& a, int32_t bm, int32_t bn, int64_t out_elems) {
+  const int64_t chunks = ceil_div(ceil_div(a.Kred, 16), a.ksplit);
+  const int64_t per_cu = ceil_div((int64_t)a.G * a.m_tiles * a.col_tiles * a.ksplit, 256);
+  const double area = (double)(bm * bn) / 4096.0, out_mb = 8e-6 * (double)out_elems;
+  return 5.7 + (a.ksplit > 1 ? 2.3 + 0.64 * a.ksplit * out_mb : 0.0) + (double)chunks * (0.17 + 0.413 * area) +
+         (double)(per_cu * chunks) * (0.090 + 0.198 * area) + 0.31 * out_mb;
+}
 
 // Sizes at which the tiled kernels stay although they are slower there (4 to 8 us a pass against 3.5 to 6): fewer columns
 // than two blocks, and reductions under three groups over 512 columns or more.  They are where every variant of a
@@ -788,10 +856,10 @@ bool small_keeps_tiles(int64_t ncols, int64_t kred, int32_t elem_bytes) {
   return ncols < 32 || (kred < 48 && (ncols >= 512 || elem_bytes == 8));
 }
 
-// Decides whether corr_small_kernel runs this correlation instead of the launches of `base` (tiles of bm x bn); fills a and
-// returns its tile, -1 if it does not.
+// Decides whether corr_small_kernel runs this correlation instead of the launches of `base`, which are modelled to take `old`
+// us; fills a and returns its tile, -1 if it does not.
 int32_t configure_corr_small(const CorrArgs& base, const PackArgs& k, int64_t w_elems, int64_t out_elems, int32_t elem_bytes,
-                             int32_t bm, int32_t bn, CorrSmallArgs& a) {
+                             double old, CorrSmallArgs& a) {
   const int64_t limit = (int64_t)1 << 30, TH = base.THW / base.TW;
   // Not measured: layers with a stride and a dilation, and what the patch-staged kernel takes.
   if (base.use_patch || (base.sh * base.sw > 1 && base.dh * base.dw > 1)) return -1;
@@ -856,23 +924,63 @@ int32_t configure_corr_small(const CorrArgs& base, const PackArgs& k, int64_t w_
       here = cost;
     }
   }
-  // The launches of `base`, a fit to such passes (rms errors 9 and 6 %): pack, main and reduce kernel, the chunks of one
-  // workgroup and those of a compute unit by tile, partial sums and output.  Beyond 0.7 GFLOP a miss costs more than a launch
-  // gains, hence the second margin.  Of 203 passes of floats that were not in the fit none is more than 3 % slower, 1.46 times
-  // as fast in the geometric mean over all; doubles (123) 1.42 times, two more than 3 % slower.
-  static const double kOld[2][8] = {{5.7, 2.3, 0.73, 0.18, 0.117, 0.027, 0.199, 0.30}, {5.7, 2.3, 0.64, 0.17, 0.413, 0.090, 0.198, 0.31}};
-  const double* const o = kOld[elem_bytes == 8];
-  const int64_t chunks = ceil_div(ceil_div(base.Kred, 16), base.ksplit);
-  const int64_t per_cu = ceil_div((int64_t)base.G * base.m_tiles * base.col_tiles * base.ksplit, 256);
-  const double area = (double)(bm * bn) / 4096.0, out_mb = 1e-6 * (double)elem_bytes * (double)out_elems;
-  const double old = o[0] + (base.ksplit > 1 ? o[1] + o[2] * base.ksplit * out_mb : 0.0) + (double)chunks * (o[3] + o[4] * area) +
-                     (double)(per_cu * chunks) * (o[5] + o[6] * area + (elem_bytes == 4 && base.bounds_mode == 1 ? 0.018 : 0.0)) + o[7] * out_mb;
+  // Beyond 0.7 GFLOP a miss costs more than a launch gains, hence the second margin.  Of 203 passes of floats that were not in
+  // the fit none is more than 3 % slower, 1.46 times as fast in the geometric mean over all; doubles (123) 1.42 times, two
+  // more than 3 % slower.
   const double flops = 2.0 * base.Mrows * base.Kred * (double)base.ncols * base.G;
   if (flops > (elem_bytes == 8 ? 1e9 : 1.5e9) || here > (flops < 0.7e9 ? 0.9 : 0.75) * old) return -1;
   a.m_tiles = (int32_t)ceil_div(a.Mrows, 16 * kCorrSmallTiles[best].mb);
   a.col_tiles = (int32_t)ceil_div(a.ncols, 16 * kCorrSmallTiles[best].nb);
   if ((int64_t)a.G * a.m_tiles * a.col_tiles >= ((int64_t)1 << 31)) return -1;
   return best;
+}
+
+// The kernel of a forward or backward-data pass of floats: thin rows, split bf16, one launch, or the tiles.
+struct CorrChoice {
+  int32_t thin, split, small;
+  size_t pack_bytes;  // 0: a blob too large for the boundary
+};
+
+CorrChoice choose_corr(CorrArgs& a, PackArgs& k, int32_t& tile, int64_t cg_in, int64_t n_img, bool backward, int64_t out_elems,
+                       int64_t w_elems, bool zero_fill, CorrSplitArgs& sp, PackSplitArgs& sp_pack, CorrSmallArgs& small) {
+  CorrChoice c = {0, -1, -1, 0};
+  CorrArgs tiled = a;
+  PackArgs tiled_pack = k;
+  c.thin = configure_thin(a, k, cg_in, n_img, backward);
+  const int64_t pack_elems = (int64_t)a.G * a.KP * a.MP;
+  if (pack_elems >= kMaxElems || (int64_t)a.G * a.m_tiles * a.col_tiles >= ((int64_t)1 << 31)) return c;
+  const int64_t steps = ceil_div(2 * ceil_div(a.Kred, 16), 4);
+  if (c.thin && !a.use_patch && steps >= 12) {
+    // Without LDS staging a thin-row workgroup walks its reduction in dependent steps of eight indices a wave: 4 -> 384
+    // channels, 5x3 at 15x15, batch 4, 118 us, in one launch 15; 2 -> 30, 11x11 at 24x24, 128 and 14; 1 -> 82, 7x7, batch 8,
+    // 127 and 32 on 16-row tiles in 16 slices.  Modelled by a fit to 54 passes (rms error 10 %); of the 33 with reductions
+    // of 128 and more the choice is 2.1 times as fast in the geometric mean, none slower.  Reductions under a dozen steps
+    // take 5 to 9 us here and 4 to 6 there: they stay, with the parity cases of every row count and bounds mode.
+    int32_t t = tile;
+    plan_corr(tiled, tiled_pack, out_elems, zero_fill, t);
+    const int64_t per_cu = ceil_div((int64_t)a.G * ceil_div(a.ncols, 64), 256);
+    const bool compares = a.bounds_mode == 1;
+    const double thin = 4.2 + (double)steps * (compares ? 0.86 : 0.37) +
+                        (double)per_cu * (0.56 + (double)steps * (0.0385 * a.Mrows + (compares ? 0.045 : 0.0)));
+    const double here = corr_model(tiled, t, tiled.ksplit, out_elems, zero_fill);
+    c.small = configure_corr_small(tiled, tiled_pack, w_elems, out_elems, 4, here < thin ? here : thin, small);
+    if (c.small >= 0 || here < 0.9 * thin) {
+      c.thin = 0;
+      a = tiled;
+      k = tiled_pack;
+      tile = t;
+    }
+  }
+  c.pack_bytes = (size_t)pack_elems * 4 + (size_t)a.KP * sizeof(KTabEntry);
+  if (c.thin || c.small >= 0) return c;
+  if (const size_t bytes = configure_split(a, k, cg_in, n_img, out_elems, sp, sp_pack, c.split)) {
+    c.pack_bytes = bytes;
+    return c;
+  }
+  plan_corr(a, k, out_elems, zero_fill, tile);
+  c.pack_bytes = (size_t)a.G * (size_t)a.KP * (size_t)a.MP * 4 + (size_t)a.KP * sizeof(KTabEntry);
+  c.small = configure_corr_small(a, k, w_elems, out_elems, 4, corr_model(a, tile, a.ksplit, out_elems, zero_fill), small);
+  return c;
 }
 
 // Decides whether wgrad_small_kernel runs the backward filter instead of the launches of `w` (tiles of bm x bn, steps of
@@ -1340,18 +1448,16 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
     k.koff_invalid = koff_invalid(a.bounds_mode);
     configure_patch(a, k, Cg, N, bm, bn);
     configure_ksplit(a, y_elems, bm, bn);
-    d->fwd_thin = configure_thin(a, k, Cg, N, false);
-    const int64_t pack_elems = G * (int64_t)a.KP * a.MP;
-    if (pack_elems >= kMaxElems || (int64_t)G * a.m_tiles * a.col_tiles >= ((int64_t)1 << 31)) {
+    const CorrChoice c = choose_corr(a, k, d->fwd_tile, Cg, N, false, y_elems, w_elems, false, d->fwd_sp, d->fwd_sp_pack, d->fwd_sm[0]);
+    if (c.pack_bytes == 0) {
       delete d;
       return CONV_ESHAPE;
     }
-    d->fwd_pack_bytes = (size_t)pack_elems * 4 + (size_t)a.KP * sizeof(KTabEntry);
-    d->fwd_split = -1;
-    const size_t sp = d->fwd_thin ? 0 : configure_split(a, k, Cg, N, y_elems, d->fwd_sp, d->fwd_sp_pack, d->fwd_split);
-    if (sp) d->fwd_pack_bytes = sp;
-    d->fwd_small[0] = d->fwd_thin || sp ? -1 : configure_corr_small(a, k, w_elems, y_elems, 4, bm, bn, d->fwd_sm[0]);
-    const int32_t S = sp ? d->fwd_sp.ksplit : a.ksplit;
+    d->fwd_thin = c.thin;
+    d->fwd_split = c.split;
+    d->fwd_small[0] = c.small;
+    d->fwd_pack_bytes = c.pack_bytes;
+    const int32_t S = c.split >= 0 ? d->fwd_sp.ksplit : a.ksplit;
     d->fwd_ws = d->fwd_pack_bytes + (S > 1 ? (size_t)S * y_elems * 4 : 0);
   }
 
@@ -1461,18 +1567,17 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
     k.koff_invalid = koff_invalid(a.bounds_mode);
     configure_patch(a, k, Kg, N, bm, bn);
     configure_ksplit(a, x_elems, bm, bn);
-    d->bwd_thin = configure_thin(a, k, Kg, N, true);
-    const int64_t pack_elems = G * (int64_t)a.KP * a.MP;
-    if (pack_elems >= kMaxElems || (int64_t)G * a.m_tiles * a.col_tiles >= ((int64_t)1 << 31)) {
+    const CorrChoice c = choose_corr(a, k, d->bwd_tile, Kg, N, true, x_elems, w_elems, d->bwd_zero_fill != 0, d->bwd_sp, d->bwd_sp_pack,
+                                     d->bwd_sm[0]);
+    if (c.pack_bytes == 0) {
       delete d;
       return CONV_ESHAPE;
     }
-    d->bwd_pack_bytes = (size_t)pack_elems * 4 + (size_t)a.KP * sizeof(KTabEntry);
-    d->bwd_split = -1;
-    const size_t sp = d->bwd_thin ? 0 : configure_split(a, k, Kg, N, x_elems, d->bwd_sp, d->bwd_sp_pack, d->bwd_split);
-    if (sp) d->bwd_pack_bytes = sp;
-    d->bwd_small[0] = d->bwd_thin || sp ? -1 : configure_corr_small(a, k, w_elems, x_elems, 4, bm, bn, d->bwd_sm[0]);
-    const int32_t S = sp ? d->bwd_sp.ksplit : a.ksplit;
+    d->bwd_thin = c.thin;
+    d->bwd_split = c.split;
+    d->bwd_small[0] = c.small;
+    d->bwd_pack_bytes = c.pack_bytes;
+    const int32_t S = c.split >= 0 ? d->bwd_sp.ksplit : a.ksplit;
     d->bwd_ws = d->bwd_pack_bytes + (S > 1 ? (size_t)S * x_elems * 4 : 0);
   }
 
@@ -1618,8 +1723,10 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
     };
     corr64(d->fwd, d->fwd_pack, d->fwd64, d->fwd64_pack, x_elems, d->fwd64_ws, d->fwd64_rows);
     corr64(d->bwd, d->bwd_pack, d->bwd64, d->bwd64_pack, y_elems, d->bwd64_ws, d->bwd64_rows);
-    d->fwd_small[1] = configure_corr_small(d->fwd64, d->fwd_pack, w_elems, y_elems, 8, d->fwd64_rows, bn64, d->fwd_sm[1]);
-    d->bwd_small[1] = configure_corr_small(d->bwd64, d->bwd_pack, w_elems, x_elems, 8, d->bwd64_rows, bn64, d->bwd_sm[1]);
+    d->fwd_small[1] = configure_corr_small(d->fwd64, d->fwd_pack, w_elems, y_elems, 8,
+                                           corr64_model(d->fwd64, d->fwd64_rows, bn64, y_elems), d->fwd_sm[1]);
+    d->bwd_small[1] = configure_corr_small(d->bwd64, d->bwd_pack, w_elems, x_elems, 8,
+                                           corr64_model(d->bwd64, d->bwd64_rows, bn64, x_elems), d->bwd_sm[1]);
     const int32_t bm64 = d->wg64_rows = f64_pick_rows(Kg, true);
     WgradArgs& a = d->wg64;
     a = d->wg;

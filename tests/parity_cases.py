@@ -189,6 +189,7 @@ VARIANT_CASES = [
     (P(3, 3, 20, 31, 9, 5, 5, 1, 1, 4, 4), "bwd_data", "corr_thin_r3_lds5"),
     # variants whose other cases run on the one-launch kernels of small layers
     (P(1, 1, 5, 6, 33, 2, 2, 2, 2), "fwd", "corr_m16_48x128x16[m0"),
+    (P(3, 2, 24, 25, 1, 6, 6, 2, 2, 1, 1, 2, 2), "fwd", "corr_thin_r1[m1"),
     (P(1, 1, 5, 6, 64, 2, 2, 2, 2), "fwd", "corr_m32_64x64x16[m0"),
     (P(1, 1, 5, 6, 96, 2, 2, 2, 2), "fwd", "corr_m32_96x128x16[m0"),
     (P(1, 16, 5, 6, 1, 6, 6, 1, 1, 2, 2), "bwd_data", "corr_m16_16x64x16[m1"),
