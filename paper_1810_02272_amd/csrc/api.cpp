@@ -878,6 +878,9 @@ int32_t configure_corr_small(const CorrArgs& base, const PackArgs& k, int64_t w_
   a.kh = k.kh;
   a.kw = k.kw;
   const int32_t T = k.kh * k.kw;
+  a.pad = base.ph > 0 || base.pw > 0 ||
+          ((int64_t)base.P / base.PW - 1) * base.sh - base.ph + (TH - 1) * base.dh >= base.IH ||
+          ((int64_t)base.PW - 1) * base.sw - base.pw + (int64_t)(base.TW - 1) * base.dw >= base.IW;
   a.w_grp_stride = k.Kg * k.Cg * T;
   if (k.mode == 0) {
     a.wmode = 0;
@@ -908,7 +911,7 @@ int32_t configure_corr_small(const CorrArgs& base, const PackArgs& k, int64_t w_
       {{{0.072, 0.059, 0.42}, {0.000, 0.066, 0.72}, {0.091, 0.089, 0.68}, {0.139, 0.092, 0.78}, {0.149, 0.153, 1.21}, {0.119, 0.114, 1.01}, {}},
        {{0.151, 0.063, 0.39}, {0.000, 0.079, 0.69}, {0.156, 0.107, 0.59}, {0.214, 0.102, 0.65}, {0.242, 0.175, 0.99}, {0.151, 0.159, 0.88}, {}}}};
   // a forward gather that strides over columns takes more cache lines a load
-  const double strided = base.sw == 1 ? 1.0 : base.sw < 4 ? 1.1 : 1.3;
+  const double strided = (base.sw == 1 ? 1.0 : base.sw < 4 ? 1.1 : 1.3) * (a.pad ? 1.0 : elem_bytes == 8 ? 0.95 : 0.88);
   const int64_t groups = KT / 16;
   int32_t best = -1;
   double here = 0;
@@ -995,40 +998,56 @@ int32_t configure_wgrad_small(const WgradArgs& w, int64_t N, int32_t elem_bytes,
   a = WgradSmallArgs();
   static_cast<WgradArgs&>(a) = w;
   a.N = (int32_t)N;
-  a.runs = (int32_t)ceil_div(w.P, 4);
-  a.mRuns = make_magic((uint32_t)a.runs);
   a.xvec = w.khw == 1 && w.sh == 1 && w.sw == 1 && w.ph == 0 && w.pw == 0;
-  a.blocks = (int32_t)ceil_div(N * a.runs, 16);
-  // [doubles][16-byte loads of x][tile], and what a reduce launch costs: fits to every tile and 1 to 128 slices on 180
-  // (doubles: 64) filter gradients, rms errors 10 to 22 %; the choice is 2 % behind the best on average
-  static const SmallCost kCost[2][2][WGRAD_SMALL_COUNT] = {
-      {{{0.48, 0.196, 0.36}, {0.66, 0.321, 1.02}, {0.70, 0.263, 1.03}, {0.98, 0.412, 1.85}, {1.80, 0.325, 1.12}},
-       {{0.00, 0.169, 0.30}, {0.14, 0.213, 1.04}, {0.36, 0.249, 0.55}, {0.70, 0.310, 1.58}, {1.11, 0.247, 1.31}}},
-      {{{0.00, 0.329, 0.93}, {0.00, 0.488, 2.37}, {0.00, 0.494, 2.18}, {}, {0.78, 0.682, 2.28}},
-       {{0.00, 0.438, 0.00}, {0.00, 0.681, 0.00}, {0.00, 0.635, 0.00}, {}, {1.19, 0.801, 0.00}}}};
+  auto set_runs = [&](WgradSmallArgs& r) {
+    r.row_runs = (int32_t)ceil_div(w.PW, 4);
+    r.runs = r.xvec == 2 ? (int32_t)(w.P / w.PW) * r.row_runs : (int32_t)ceil_div(w.P, 4);
+    r.mRuns = make_magic((uint32_t)r.runs);
+    r.mRowRuns = make_magic((uint32_t)r.row_runs);
+    r.blocks = (int32_t)ceil_div(N * r.runs, 16);
+  };
+  a.pad = w.ph > 0 || w.pw > 0;
+  // [doubles][xvec][tile], and what a reduce launch costs: fits to every tile and 1 to 128 slices on 182 (doubles: 106) filter
+  // gradients, rms errors 11 to 25 %; the choice is 3 (doubles: 5) % behind the best on average.  Runs within rows of doubles
+  // are two loads each and took 1.09 times as long as single ones: no instance.
+  static const SmallCost kCost[2][3][WGRAD_SMALL_COUNT] = {
+      {{{0.453, 0.190, 0.41}, {0.476, 0.321, 0.97}, {0.598, 0.268, 0.91}, {0.883, 0.412, 1.30}, {1.422, 0.365, 0.36}},
+       {{0.000, 0.154, 0.36}, {0.093, 0.211, 0.86}, {0.129, 0.227, 0.59}, {0.599, 0.289, 1.21}, {0.986, 0.221, 0.60}},
+       {{0.341, 0.124, 0.75}, {0.585, 0.200, 1.13}, {0.653, 0.194, 1.04}, {1.058, 0.311, 1.45}, {1.593, 0.268, 0.47}}},
+      {{{0.000, 0.329, 0.93}, {0.000, 0.488, 2.37}, {0.000, 0.494, 2.18}, {}, {0.780, 0.682, 2.28}},
+       {{0.000, 0.438, 0.00}, {0.000, 0.681, 0.00}, {0.000, 0.635, 0.00}, {}, {1.190, 0.801, 0.00}},
+       {}}};
   const double w_mb = 1e-6 * elem_bytes * (double)w.part_stride;
-  int32_t best = -1;
+  const int32_t first = a.xvec, last = elem_bytes == 4 && w.sw == 1 && first == 0 ? 2 : first;
+  int32_t best = -1, best_xvec = 0;
   int64_t best_bps = 0;
   double here = 0;
-  for (int32_t t = 0; t < WGRAD_SMALL_COUNT; ++t) {
-    const SmallCost& c = kCost[elem_bytes == 8][a.xvec != 0][t];
-    const SmallTile& s = kWgradSmallTiles[t];
-    if (c.shared == 0) continue;  // no instance
-    const int64_t tiles = (int64_t)w.G * ceil_div(w.Kg, 16 * s.mb) * ceil_div(w.Kred, 16 * s.nb);
-    for (int64_t S = 1; S <= w.S; S *= 2) {  // at most the slices that the workspace has room for
-      const int64_t bps = ceil_div(a.blocks, S), slices = ceil_div(a.blocks, bps), per_cu = ceil_div(tiles * slices, 256);
-      // a running sum no longer than on the tiled kernel: one that took all of 1.2 million places was off by 5e-6
-      if (bps * 64 / s.waves > (w.cols_per_split > 2048 ? w.cols_per_split : 2048)) continue;
-      const double cost = 3.3 + c.chain * (double)ceil_div(bps, s.waves) + (c.shared * (double)bps + c.workgroup) * (double)per_cu +
-                          (slices > 1 ? 2.0 + (elem_bytes == 8 ? 1.0 : 1.6) * (double)slices * w_mb : 0.0);
-      if (best < 0 || cost < here) {
-        best = t;
-        best_bps = bps;
-        here = cost;
+  for (a.xvec = first; a.xvec <= last; a.xvec += 2) {
+    set_runs(a);
+    for (int32_t t = 0; t < WGRAD_SMALL_COUNT; ++t) {
+      const SmallCost& c = kCost[elem_bytes == 8][a.xvec][t];
+      const SmallTile& s = kWgradSmallTiles[t];
+      if (c.shared == 0) continue;  // no instance
+      const int64_t tiles = (int64_t)w.G * ceil_div(w.Kg, 16 * s.mb) * ceil_div(w.Kred, 16 * s.nb);
+      for (int64_t S = 1; S <= w.S; S *= 2) {  // at most the slices that the workspace has room for
+        const int64_t bps = ceil_div(a.blocks, S), slices = ceil_div(a.blocks, bps), per_cu = ceil_div(tiles * slices, 256);
+        // a running sum hardly longer than on the tiled kernel: one of 256 was up to 1.3 times as far off as the slices there
+        const int64_t sums = s.waves * (elem_bytes == 8 ? 1 : 4 / (s.mb * s.nb)), free = elem_bytes == 8 ? 2048 : 192;
+        if (bps * 64 / sums > (w.cols_per_split > free ? w.cols_per_split : free)) continue;
+        const double cost = 3.3 + c.chain * (double)ceil_div(bps, s.waves) + (c.shared * (double)bps + c.workgroup) * (double)per_cu +
+                            (slices > 1 ? 2.0 + (elem_bytes == 8 ? 1.0 : 1.6) * (double)slices * w_mb : 0.0);
+        if (best < 0 || cost < here) {
+          best = t;
+          best_xvec = a.xvec;
+          best_bps = bps;
+          here = cost;
+        }
       }
     }
   }
   if (best < 0) return -1;
+  a.xvec = best_xvec;
+  set_runs(a);
   // The launches of `w`, a fit to the same layers (rms errors 7 and 16 %).  With a margin of 0.9 142 of 175 layers of floats are
   // taken, 1.43 times as fast in the geometric mean over all, eight more than 3 % slower; doubles 36 of 64, 1.11 times, one.
   static const double kOld[2][7] = {{3.2, 0.74, 0.236, 0.374, 0.115, 0.242, 2.9}, {4.7, 0.63, 1.46, 1.91, 0.0, 0.222, 1.9}};

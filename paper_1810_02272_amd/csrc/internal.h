@@ -211,16 +211,19 @@ struct CorrSmallArgs : CorrArgs {  // A = the weight blob itself, with the strid
   int32_t KT;                    // reduction indices, a multiple of the kernel's groups of 16
   int32_t wmode;                 // how the weights are read (WMODE of the kernel)
   int32_t tap_pitch;             // reduction indices per channel
+  int32_t pad;                   // some place of the gather may lie outside the image
   Magic mPitch;
   int32_t Qh, kh, kw;            // tap rows of the gather; taps of the layer
   int32_t step_h, step_w;        // taps of the layer between two of the gather
 };
 
 struct WgradSmallArgs : WgradArgs {
-  int32_t N, runs;  // images, runs of four pixels per image
-  Magic mRuns;
+  int32_t N, runs;   // images, runs of four pixels per image
+  int32_t row_runs;  // xvec 2: per row of the output
+  Magic mRuns, mRowRuns;
   int32_t blocks, blocks_per_split;  // of sixteen runs
-  int32_t xvec;     // four pixels of x are one 16-byte load
+  int32_t xvec;      // how x is read (XV of the kernel)
+  int32_t pad;       // some tap may lie outside the image
   // S == 1: the kernel finishes dw (and db, through bias_part)
   float* dw_out;
   float beta;

@@ -76,7 +76,10 @@ constexpr uint32_t kOutside = 0x80000000u;  // byte offset beyond any blob of at
 // offsets (backward data: kk runs over the output channels); 2: the same, and a row phase lacks some taps (stride > 1); 3:
 // backward data at unit stride, a channel's taps as 16-byte loads.  With single loads the sixteen rows of the weights, a
 // channel's taps apart, are sixteen cache lines in each of four loads: 20 -> 50 channels, 5x5 at 12x12, batch 64, 27.2 against 18.3 us.
-template <typename T, int MB, int NB, int WAVES, int WMODE>
+// PAD: some place of the gather may lie outside the image.  Its row and column compares are most of the eight vector
+// instructions a value takes; without them 1x1 layers take 0.87 of the time (3160 -> 64 at 330 places 24.5 -> 16.2 us).
+// One bit per tap and column instead (the tiled kernels' way) was 3 % faster on the mean, 15 % slower where reductions are short.
+template <typename T, int MB, int NB, int WAVES, int WMODE, bool PAD>
 __global__ __launch_bounds__(64 * WAVES) void corr_small_kernel(const CorrSmallArgs a) {
   using S = Small<T>;
   constexpr int BM = 16 * MB, BN = 16 * NB, kThreads = 64 * WAVES, kRing = 3;
@@ -111,8 +114,10 @@ __global__ __launch_bounds__(64 * WAVES) void corr_small_kernel(const CorrSmallA
       j = in ? (uint32_t)a.TW - 1 - j : 0;
     }
     tab_off[kk] = (uint32_t)sizeof(T) * (c * (uint32_t)a.IHW + i * (uint32_t)(a.dh * a.IW) + j * (uint32_t)a.dw);
-    // past the reduction: a row that fails every bounds test (rows are below 2^14, padding at most 2^12)
-    tab_rc[kk] = in ? (i * (uint32_t)a.dh) << 16 | j * (uint32_t)a.dw : kNoTap;
+    // past the reduction: an offset beyond any blob with every column's, or a row that fails every bounds test (rows are below
+    // 2^14, padding at most 2^12)
+    if (!PAD && !in) tab_off[kk] = 0x40000000u;
+    if (PAD) tab_rc[kk] = in ? (i * (uint32_t)a.dh) << 16 | j * (uint32_t)a.dw : kNoTap;
     if (WMODE == 3) {
       if ((kk & 3) == 0) tab_w[kk >> 2] = in ? (uint32_t)sizeof(T) * (c * (uint32_t)a.w_chan_stride + r) : kOutside;
     } else if (WMODE > 0) {
@@ -157,7 +162,7 @@ __global__ __launch_bounds__(64 * WAVES) void corr_small_kernel(const CorrSmallA
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
     const uint32_t col = col_tile * BN + j * 16 + (lane & 15);
-    cbase[j] = 0;
+    cbase[j] = PAD ? 0u : kOutside;
     ih0[j] = -(1 << 29);
     iw0[j] = 0;
     if (col < (uint32_t)a.ncols) {
@@ -210,11 +215,17 @@ __global__ __launch_bounds__(64 * WAVES) void corr_small_kernel(const CorrSmallA
   int next = wv;  // the group loaded next; past the last one that one again, never multiplied
   auto load = [&](T(&A)[MB][4], T(&B)[NB][4]) {
     const int kk = next * 16 + 4 * (lane >> 4);
-    const u32x4 off = *reinterpret_cast<const u32x4*>(tab_off + kk), rc = *reinterpret_cast<const u32x4*>(tab_rc + kk);
+    const u32x4 off = *reinterpret_cast<const u32x4*>(tab_off + kk);
+    u32x4 rc;
+    if (PAD) rc = *reinterpret_cast<const u32x4*>(tab_rc + kk);
 #pragma unroll
     for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
+        if (!PAD) {
+          B[j][e] = S::load(in_rsrc, cbase[j] + off[e]);
+          continue;
+        }
         const int ih = ih0[j] + (int)(rc[e] >> 16), iw = iw0[j] + (int)(rc[e] & 0xffffu);
         const bool ok = ((uint32_t)ih < (uint32_t)a.IH) & ((uint32_t)iw < (uint32_t)a.IW);
         B[j][e] = S::load(in_rsrc, ok ? cbase[j] + off[e] : kOutside);
@@ -305,15 +316,22 @@ __global__ __launch_bounds__(64 * WAVES) void corr_small_kernel(const CorrSmallA
   }
 }
 
-template <typename T, int MB, int NB, int WAVES, int WMODE>
-int launch_corr_small_m(const CorrSmallArgs& a, hipStream_t s) {
+template <typename T, int MB, int NB, int WAVES, int WMODE, bool PAD>
+int launch_corr_small_b(const CorrSmallArgs& a, hipStream_t s) {
   constexpr size_t fixed = 16 * (16 * MB + 16 * NB) + 16 * MB * sizeof(T);
   constexpr size_t red = (size_t)WAVES * 16 * MB * (16 * NB + 4) * sizeof(T);
   static_assert(fixed + red <= 64 * 1024, "LDS without an opt-in");
   const size_t tab = (size_t)a.KT * (WMODE == 3 ? 9 : 4 * (2 + WMODE));
-  hipLaunchKernelGGL((corr_small_kernel<T, MB, NB, WAVES, WMODE>), dim3((uint32_t)(a.G * a.m_tiles * a.col_tiles)),
+  hipLaunchKernelGGL((corr_small_kernel<T, MB, NB, WAVES, WMODE, PAD>), dim3((uint32_t)(a.G * a.m_tiles * a.col_tiles)),
                      dim3(64 * WAVES), fixed + (tab > red ? tab : red), s, a);
   return (int)hipGetLastError();
+}
+
+template <typename T, int MB, int NB, int WAVES, int WMODE>
+int launch_corr_small_m(const CorrSmallArgs& a, hipStream_t s) {
+  if constexpr (WMODE <= 1)  // backward data of more than one tap always reaches outside
+    if (!a.pad) return launch_corr_small_b<T, MB, NB, WAVES, WMODE, false>(a, s);
+  return launch_corr_small_b<T, MB, NB, WAVES, WMODE, true>(a, s);
 }
 
 template <typename T, int MB, int NB, int WAVES>
@@ -331,12 +349,16 @@ int launch_corr_small_t(const CorrSmallArgs& a, hipStream_t s) {
 // (c, i, j) (see WgradArgs).  The reduction runs in blocks of 64 places: sixteen runs of four pixels of one image, the last
 // run of an image padded.  A wave writes the places' offsets to LDS for itself (lane = place), so they are worked out once
 // and not once per row or column.  With one slice the workgroup finishes dw (and db) itself.
-// XVEC: 1x1 kernels at unit stride without padding -- four places are one 16-byte load of x as well.
-template <typename T, int MB, int NB, int WAVES, bool XVEC>
+// XV 1: 1x1 kernels at unit stride without padding -- four places are one 16-byte load of x as well.  2 (floats): unit column
+// stride -- the runs are cut at the ends of the output's rows, so that they are: 374 -> 35, 3x3 at 74x74, two images, 103 -> 51
+// us; 1.18 times as fast as 0 in the geometric mean of the gradients over 8 us, slower where rows end in short runs.
+// PAD: some tap may lie outside the image; else the places' and columns' offsets alone tell what reads as zero (5 to 15 %).
+template <typename T, int MB, int NB, int WAVES, int XV, bool PAD>
 __global__ __launch_bounds__(64 * WAVES) void wgrad_small_kernel(const WgradSmallArgs a) {
   using S = Small<T>;
   constexpr int BM = 16 * MB, BN = 16 * NB, kThreads = 64 * WAVES;
   constexpr int kPitch = BN + 4;
+  constexpr bool XVEC = XV == 1;
   extern __shared__ __align__(16) uint32_t lds[];
   const int t = threadIdx.x, lane = t & 63;
   const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -372,7 +394,7 @@ __global__ __launch_bounds__(64 * WAVES) void wgrad_small_kernel(const WgradSmal
       idh[j] = (int)i * a.dh;
       jdw[j] = (int)jj * a.dw;
       cbase[j] = (uint32_t)sizeof(T) * (c * (uint32_t)a.HW + (uint32_t)(idh[j] * a.W + jdw[j]));
-    } else if (XVEC) {
+    } else if (XVEC || !PAD) {
       cbase[j] = 0x40000000u;
     }
   }
@@ -381,21 +403,30 @@ __global__ __launch_bounds__(64 * WAVES) void wgrad_small_kernel(const WgradSmal
   const __amdgpu_buffer_rsrc_t x_rsrc =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.x), 0, (int)a.x_bytes, 0x00020000);
 
-  typename S::Acc acc[MB][NB];
+  constexpr int kSums = sizeof(T) == 8 ? 1 : 4 / (MB * NB);  // running sums of floats in parts, as in corr_small_kernel
+  typename S::Acc acc[kSums][MB][NB];
   T rowsum[MB];
 #pragma unroll
   for (int i = 0; i < MB; ++i) {
     rowsum[i] = 0;
 #pragma unroll
-    for (int j = 0; j < NB; ++j) acc[i][j] = typename S::Acc{0, 0, 0, 0};
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int q = 0; q < kSums; ++q) acc[q][i][j] = typename S::Acc{0, 0, 0, 0};
   }
-  const bool ragged = (a.P & 3) != 0;
+  const bool ragged = ((XV == 2 ? a.PW : a.P) & 3) != 0;
   constexpr uint32_t kNoPlace = 0x80000000u;  // row -32768: no tap reaches the image
   auto fill = [&](int block, int buf) {
     const uint32_t run = (uint32_t)block * 16 + (uint32_t)(lane >> 2);
-    const uint32_t n = mdiv(run, a.mRuns), p = (run - n * (uint32_t)a.runs) * 4 + (uint32_t)(lane & 3);
-    const bool in = block < b1 && n < (uint32_t)a.N && p < (uint32_t)a.P;
-    const uint32_t pa = mdiv(p, a.mPW), pb = p - pa * (uint32_t)a.PW;
+    const uint32_t n = mdiv(run, a.mRuns), in_image = run - n * (uint32_t)a.runs;
+    uint32_t p = in_image * 4 + (uint32_t)(lane & 3), pa = mdiv(p, a.mPW), pb = p - pa * (uint32_t)a.PW;
+    bool in = block < b1 && n < (uint32_t)a.N && p < (uint32_t)a.P;
+    if (XV == 2) {
+      pa = mdiv(in_image, a.mRowRuns);
+      pb = (in_image - pa * (uint32_t)a.row_runs) * 4 + (uint32_t)(lane & 3);
+      p = pa * (uint32_t)a.PW + pb;
+      in = block < b1 && n < (uint32_t)a.N && pb < (uint32_t)a.PW;
+    }
     const int ih = (int)pa * a.sh - a.ph, iw = (int)pb * a.sw - a.pw;
     uint32_t* const dst = places + buf * (3 * 64) + lane;
     dst[0] = in ? (uint32_t)sizeof(T) * ((n * (uint32_t)a.C + g * (uint32_t)a.Cg) * (uint32_t)a.HW + (uint32_t)(ih * a.W + iw)) : kOutside;
@@ -421,6 +452,23 @@ __global__ __launch_bounds__(64 * WAVES) void wgrad_small_kernel(const WgradSmal
         if (ragged)
 #pragma unroll
           for (int e = 1; e < 4; ++e) B[j][e] = rc[e] == kNoPlace ? (T)0 : B[j][e];
+      } else if (XV == 2) {
+        const int ih = ((int)rc[0] >> 16) + idh[j], iw = (int)(int16_t)(rc[0] & 0xffffu) + jdw[j];
+        const bool row = !PAD || (uint32_t)ih < (uint32_t)a.H;
+        const uint32_t at = xo[0] + cbase[j];
+        if (PAD && __any(row && (int)at < 0)) {  // left of the blob's first pixel: the address must not wrap
+#pragma unroll
+          for (int e = 0; e < 4; ++e) B[j][e] = S::load(x_rsrc, row && iw + e >= 0 ? at + (uint32_t)sizeof(T) * e : kOutside);
+        } else {
+          S::load4(x_rsrc, row ? at : kOutside, B[j]);
+        }
+        if (PAD || ragged)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            B[j][e] = (!PAD || (uint32_t)(iw + e) < (uint32_t)a.W) && rc[e] != kNoPlace ? B[j][e] : (T)0;
+      } else if (!PAD) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) B[j][e] = S::load(x_rsrc, xo[e] + cbase[j]);
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -449,7 +497,7 @@ __global__ __launch_bounds__(64 * WAVES) void wgrad_small_kernel(const WgradSmal
 #pragma unroll
           for (int i = 0; i < MB; ++i)
 #pragma unroll
-            for (int j = 0; j < NB; ++j) S::run(av[gi][i][e], bv[gi][j][e], acc[i][j]);
+            for (int j = 0; j < NB; ++j) S::run(av[gi][i][e], bv[gi][j][e], acc[e % kSums][i][j]);
         if (sum_rows)
 #pragma unroll
           for (int i = 0; i < MB; ++i) rowsum[i] += (av[gi][i][0] + av[gi][i][1]) + (av[gi][i][2] + av[gi][i][3]);
@@ -464,8 +512,12 @@ __global__ __launch_bounds__(64 * WAVES) void wgrad_small_kernel(const WgradSmal
 #pragma unroll
     for (int j = 0; j < NB; ++j)
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        red[(wv * BM + i * 16 + S::row(r, lane)) * kPitch + j * 16 + (lane & 15)] = acc[i][j][r];
+      for (int r = 0; r < 4; ++r) {
+        T s = acc[0][i][j][r];
+        if (kSums == 2) s += acc[1 % kSums][i][j][r];
+        if (kSums == 4) s = (s + acc[1 % kSums][i][j][r]) + (acc[2 % kSums][i][j][r] + acc[3 % kSums][i][j][r]);
+        red[(wv * BM + i * 16 + S::row(r, lane)) * kPitch + j * 16 + (lane & 15)] = s;
+      }
   T* const sums = red + WAVES * BM * kPitch;  // [wave][quarter][row]
   if (sum_rows)
 #pragma unroll
@@ -510,10 +562,20 @@ int launch_wgrad_small_t(const WgradSmallArgs& a, hipStream_t s) {
   constexpr size_t lds = places > red ? places : red;
   static_assert(lds <= 64 * 1024, "LDS without an opt-in");
   const dim3 grid((uint32_t)a.S * a.G * a.m_tiles * a.n_tiles);
-  if (a.xvec)
-    hipLaunchKernelGGL((wgrad_small_kernel<T, MB, NB, WAVES, true>), grid, dim3(64 * WAVES), lds, s, a);
+  if constexpr (sizeof(T) == 4)
+    if (a.xvec == 2) {
+      if (a.pad)
+        hipLaunchKernelGGL((wgrad_small_kernel<T, MB, NB, WAVES, 2, true>), grid, dim3(64 * WAVES), lds, s, a);
+      else
+        hipLaunchKernelGGL((wgrad_small_kernel<T, MB, NB, WAVES, 2, false>), grid, dim3(64 * WAVES), lds, s, a);
+      return (int)hipGetLastError();
+    }
+  if (a.xvec == 1)
+    hipLaunchKernelGGL((wgrad_small_kernel<T, MB, NB, WAVES, 1, false>), grid, dim3(64 * WAVES), lds, s, a);
+  else if (a.pad)
+    hipLaunchKernelGGL((wgrad_small_kernel<T, MB, NB, WAVES, 0, true>), grid, dim3(64 * WAVES), lds, s, a);
   else
-    hipLaunchKernelGGL((wgrad_small_kernel<T, MB, NB, WAVES, false>), grid, dim3(64 * WAVES), lds, s, a);
+    hipLaunchKernelGGL((wgrad_small_kernel<T, MB, NB, WAVES, 0, false>), grid, dim3(64 * WAVES), lds, s, a);
   return (int)hipGetLastError();
 }
 

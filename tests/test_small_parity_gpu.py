@@ -2,6 +2,8 @@
 that end inside a tile, a group of reduction indices, a run of four pixels and a slice, with every way of reading the weights.
 
 Tolerances are those of the sweeps (test_parity_gpu.py, test_f64_parity_gpu.py): the same sums in another order."""
+import re
+
 import pytest
 import torch
 
@@ -53,6 +55,43 @@ CASES = [
     P(4, 3, 8, 4, 1, 4, 4, 1, 1, 1, 2, 2, 2, 1),
     P(1, 7, 5, 8, 1, 1, 2, 1, 1, 1, 0, 1, 1, 1),
     P(2, 1, 8, 4, 1, 1, 1, 1, 1, 0, 0, 1, 1, 1),
+    # without padding, and runs cut at the ends of rows
+    P(38, 144, 27, 26, 118, 1, 1, 1, 1, 0, 0, 1, 1, 2),
+    P(12, 5, 69, 69, 39, 3, 3, 1, 1, 0, 0, 1, 1, 1),
+    P(7, 18, 40, 44, 249, 1, 5, 1, 1, 0, 0, 2, 2, 3),
+    P(13, 76, 15, 17, 42, 7, 7, 2, 2, 0, 0, 1, 1, 1),
+    P(13, 66, 7, 11, 142, 5, 5, 1, 1, 0, 0, 1, 1, 2),
+    P(18, 210, 28, 25, 195, 1, 1, 3, 2, 0, 0, 1, 1, 3),
+    P(3, 156, 28, 23, 80, 1, 2, 1, 1, 1, 1, 1, 1, 2),
+    P(25, 134, 8, 9, 80, 4, 4, 3, 1, 0, 0, 1, 1, 2),
+    P(31, 174, 5, 4, 57, 5, 5, 1, 1, 0, 5, 1, 1, 3),
+    P(8, 54, 55, 55, 51, 1, 1, 1, 1, 1, 0, 1, 1, 3),
+    P(2, 27, 26, 31, 123, 7, 7, 3, 3, 0, 0, 1, 1, 1),
+    P(23, 177, 6, 5, 288, 2, 1, 1, 1, 0, 0, 1, 1, 3),
+    P(16, 98, 23, 20, 52, 1, 1, 1, 1, 0, 0, 1, 1, 2),
+    P(2, 26, 67, 68, 19, 5, 5, 3, 2, 0, 0, 1, 1, 1),
+    P(51, 1, 50, 46, 61, 2, 1, 1, 1, 0, 0, 1, 1, 1),
+    P(1, 68, 16, 20, 84, 5, 2, 1, 1, 0, 0, 1, 1, 1),
+    P(3, 180, 6, 5, 57, 5, 5, 1, 1, 2, 3, 1, 1, 3),
+    P(3, 69, 23, 24, 36, 1, 2, 1, 1, 1, 1, 2, 2, 1),
+    P(5, 150, 13, 11, 78, 3, 3, 2, 2, 0, 0, 1, 1, 2),
+    P(9, 234, 7, 11, 21, 5, 5, 1, 1, 0, 0, 1, 1, 3),
+    P(3, 7, 46, 43, 95, 1, 2, 1, 1, 0, 0, 1, 1, 1),
+    P(20, 18, 48, 46, 6, 1, 3, 2, 1, 0, 0, 1, 1, 1),
+    P(1, 68, 38, 33, 34, 1, 2, 1, 1, 1, 1, 2, 2, 1),
+    P(18, 42, 11, 8, 36, 7, 7, 2, 2, 3, 0, 1, 1, 2),
+    P(2, 26, 53, 51, 3, 5, 2, 1, 1, 0, 0, 1, 1, 1),
+    P(5, 201, 43, 44, 6, 2, 2, 2, 2, 0, 0, 1, 1, 3),
+    P(5, 65, 53, 55, 1, 2, 2, 1, 1, 0, 0, 1, 1, 1),
+    P(17, 3, 61, 62, 90, 1, 2, 2, 2, 0, 0, 1, 1, 3),
+    P(32, 13, 20, 15, 1, 7, 7, 1, 2, 0, 5, 1, 1, 1),
+    P(14, 1, 65, 64, 47, 1, 1, 1, 1, 1, 0, 1, 1, 1),
+    P(1, 112, 9, 10, 4, 7, 7, 1, 1, 6, 6, 1, 1, 2),
+    P(2, 1, 6, 4, 134, 1, 1, 1, 1, 0, 1, 1, 1, 1),
+    P(2, 1, 4, 4, 63, 2, 1, 1, 1, 0, 1, 1, 1, 1),
+    P(4, 73, 10, 5, 1, 1, 1, 3, 3, 0, 0, 1, 1, 1),
+    P(1, 5, 4, 9, 4, 1, 1, 1, 1, 0, 1, 2, 2, 1),
+    P(5, 1, 5, 10, 1, 1, 1, 2, 2, 0, 0, 1, 1, 1),
 ]
 
 
@@ -78,7 +117,22 @@ def test_cases_reach_every_variant():
     for b, tiles in (("", ["16x16x8", "16x32x8", "32x16x8", "32x32x8", "32x32x4"]), ("64", ["16x16x8", "16x32x8", "32x16x8", "32x32x4"])):
         want |= {(f"smallwgrad{b}_{t}[v0]", s) for t in tiles for s in (False, True)}
         want |= {(f"smallwgrad{b}_16x16x8[v1]", s) for s in (False, True)} | {(f"smallwgrad{b}_{t}[v1]", True) for t in tiles if (b, t) != ("", "32x32x4")}
+    want |= {(f"smallwgrad_{t}[v2]", s) for t in ("16x16x8", "16x32x8", "32x16x8", "32x32x8", "32x32x4") for s in (False, True)}
     assert want <= have, sorted(want - have)
+
+
+def test_cases_reach_both_sides_of_padding():
+    """Instances without bounds tests and with them (backward data of one tap has none, of two always)."""
+    padded, plain = set(), set()
+    for pd in CASES:
+        for v in small_variants(pd):
+            if "[w1]" in v[0]:
+                (padded if pd["kernel_h"] * pd["kernel_w"] > 1 else plain).add(v)
+            elif re.search(r"\[(w0|v0|v2)\]", v[0]):
+                (padded if pd["pad_h"] or pd["pad_w"] else plain).add(v)
+    # one tap a channel and eight waves a tile do not meet in backward data of floats; the same for one slice of this tile
+    assert padded - plain <= {("corrsmall_16x16x8[w1]", False), ("smallwgrad_32x32x4[v2]", False)}, sorted(padded - plain)
+    assert plain <= padded, sorted(plain - padded)
 
 
 @pytest.mark.gpu
@@ -94,17 +148,19 @@ def test_small_layers_against_the_oracle(i):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("pad", [1, 0])
 @pytest.mark.parametrize("f64", [False, True])
-def test_what_lies_behind_a_row_does_not_leak(f64):
+def test_what_lies_behind_a_row_does_not_leak(f64, pad):
     """NaN in one output channel's weights, one input channel's, one channel of dy and of x: the wide loads run past a row's
     reduction, a channel's taps and an image's last pixels, and only the results that own a NaN may show it."""
-    pd = P(3, 6, 9, 9, 40, 3, 3, 1, 1, 1, 1)  # 54 indices forward (14 past them), nine taps, 81 pixels
+    pd = P(3, 6, 15, 15, 40, 3, 3, 1, 1, pad, pad)  # 54 indices forward (10 past them), nine taps, rows of 15 or 13 pixels
+    o = 13 + 2 * pad
     d = conv.conv_desc_create(conv.ConvParams(**pd))
-    assert len(small_variants(pd)) >= 3, small_variants(pd)
+    assert len(small_variants(pd)) >= 5 and ("smallwgrad_16x16x8[v2]", False) in small_variants(pd), small_variants(pd)
     dt = torch.float64 if f64 else torch.float32
     size = conv.conv_desc_workspace_bytes_f64(d) if f64 else conv.conv_desc_workspace_bytes(d)
     gen = torch.Generator().manual_seed(5)
-    x, w, b, dy = (torch.randn(s, generator=gen, dtype=torch.float64).to(DEV, dt) for s in ((3, 6, 9, 9), (40, 6, 3, 3), (40,), (3, 40, 9, 9)))
+    x, w, b, dy = (torch.randn(s, generator=gen, dtype=torch.float64).to(DEV, dt) for s in ((3, 6, 15, 15), (40, 6, 3, 3), (40,), (3, 40, o, o)))
     ws = torch.full((size // 8 + 1,), NAN, device=DEV, dtype=torch.float64)
     f, bd, bf = ((conv.conv_forward_f64, conv.conv_backward_data_f64, conv.conv_backward_filter_f64) if f64 else
                  (conv.conv_forward, conv.conv_backward_data, conv.conv_backward_filter))
