@@ -840,13 +840,58 @@ struct SmallCost {
   double chain, shared, workgroup;
 };
 
-// The same for a pass on the tiled kernels of doubles (tiles of bm x bn), a fit to 123 passes (rms error 6 %).
+// The same for a pass on the tiled kernels of doubles as configure_ksplit slices them (tiles of bm x bn), a fit to 123 passes
+// (rms error 6 %).
 double corr64_model(const CorrArgs& a, int32_t bm, int32_t bn, int64_t out_elems) {
   const int64_t chunks = ceil_div(ceil_div(a.Kred, 16), a.ksplit);
   const int64_t per_cu = ceil_div((int64_t)a.G * a.m_tiles * a.col_tiles * a.ksplit, 256);
   const double area = (double)(bm * bn) / 4096.0, out_mb = 8e-6 * (double)out_elems;
   return 5.7 + (a.ksplit > 1 ? 2.3 + 0.64 * a.ksplit * out_mb : 0.0) + (double)chunks * (0.17 + 0.413 * area) +
          (double)(per_cu * chunks) * (0.090 + 0.198 * area) + 0.31 * out_mb;
+}
+
+// Tile and slices of the fp64 kernel where another choice is modelled at least 8 % ahead, from 0.05 to 6 GFLOP.  The model is a fit
+// to 130 layers of those sizes on every tile and slice count (260 passes, rms error 8 %).  Of the 260, 55 change, 1.26 times as
+// fast in the geometric mean, two 6 % slower; one of 0.18 GFLOP took 268 us unsplit on the 16-row tile and 86 in sixteen
+// slices, one of 4.5 GFLOP 335 on it and 124 on 48 rows.
+void plan_corr64(CorrArgs& a, int64_t out_elems, int32_t& rows) {
+  const double flops = 2.0 * a.Mrows * a.Kred * (double)a.ncols * a.G;
+  if (a.ncols < 1 || flops < 5e7 || flops > 6e9) return;
+  static const int32_t kSlices[] = {1, 2, 3, 4, 6, 8, 12, 16};
+  static const struct {
+    int32_t rows;
+    double chain, chunk, workgroup;
+  } kTiles[] = {{16, 0.270, 0.146, 0.44}, {32, 0.285, 0.239, 0.54}, {48, 0.325, 0.349, 0.70}, {64, 0.363, 0.471, 0.88}, {96, 0.446, 0.724, 1.47}};
+  const int64_t all = ceil_div(a.Kred, kF64TileK);
+  const double out_mb = 8e-6 * (double)out_elems;
+  int32_t best = rows;
+  int64_t best_S = a.ksplit;
+  double cost = 0, here = 0;
+  for (const auto& t : kTiles) {
+    const int64_t m_tiles = ceil_div(a.Mrows, t.rows);
+    auto model = [&](int64_t S) {
+      const int64_t chunks = ceil_div(all, S), per_cu = ceil_div((int64_t)a.G * m_tiles * a.col_tiles * ceil_div(all, chunks), 256);
+      return 5.0 + 0.21 * out_mb + 0.27 * 8e-6 * (double)(a.G * m_tiles * t.rows) * (double)a.KP +
+             (S > 1 ? 4.0 + 0.288 * (double)S * out_mb : 0.0) + (double)chunks * (t.chain + t.chunk * (double)per_cu) +
+             t.workgroup * (double)per_cu;
+    };
+    if (t.rows == rows) here = 0.92 * model(a.ksplit);  // nearer than that is within the model's error
+    for (const int64_t S : kSlices) {
+      if (S > 1 && (2 * S > all || S * out_elems > ((int64_t)8 << 20))) break;  // slices of two chunks, 64 MiB of partial sums
+      const double c = model(S);
+      if (cost == 0 || c < cost) {
+        best = t.rows;
+        best_S = S;
+        cost = c;
+      }
+    }
+  }
+  if (cost >= here) return;
+  rows = best;
+  a.MP = (int32_t)round_up(a.Mrows, best);
+  a.m_tiles = a.MP / best;
+  a.chunks_per_split = (int32_t)ceil_div(all, best_S);
+  a.ksplit = (int32_t)ceil_div(all, a.chunks_per_split);
 }
 
 // Sizes at which the tiled kernels stay although they are slower there (4 to 8 us a pass against 3.5 to 6): fewer columns
@@ -1057,7 +1102,10 @@ int32_t configure_wgrad_small(const WgradArgs& w, int64_t N, int32_t elem_bytes,
   const double old = o[0] + o[1] * w.S * w_mb + (double)steps * (o[2] + o[3] * area) +
                      (double)(per_cu * steps) * (o[4] + o[5] * area + (elem_bytes == 4 && w.bounds_mode == 1 ? 0.32 : 0.0)) + o[6] * (double)per_cu;
   const double flops = 2.0 * w.Kg * w.Kred * (double)w.ncols * w.G;
-  if (flops > 1e9 || here > (flops < 0.5e9 ? 0.9 : 0.75) * old) return -1;
+  // 1x1 layers and fully connected ones need another 1.2: rows of x far apart cost more than the fit knows (28 x 3090 -> 3506
+  // outputs took 26.9 us here, 21.7 on the tiles).
+  const double least = (flops < 0.5e9 ? 0.9 : 0.75) / (a.xvec == 1 && elem_bytes == 4 ? 1.2 : 1.0);
+  if (flops > 1e9 || here > least * old) return -1;
   a.m_tiles = (int32_t)ceil_div(a.Kg, 16 * kWgradSmallTiles[best].mb);
   a.n_tiles = (int32_t)ceil_div(a.Kred, 16 * kWgradSmallTiles[best].nb);
   a.blocks_per_split = (int32_t)best_bps;
@@ -1717,7 +1765,7 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
     const int64_t max64 = (int64_t)1 << 29;  // 32-bit byte offsets of 8-byte elements
     d->f64_ok = x_elems < max64 && y_elems < max64 && w_elems < max64;
     auto corr64 = [&](const CorrArgs& src, const PackArgs& psrc, CorrArgs& a, PackArgs& k, int64_t in_elems,
-                      size_t& ws, int32_t& tile_rows) {
+                      size_t& ws, int32_t& tile_rows, int32_t& small, CorrSmallArgs& sm) {
       a = src;
       const int32_t bm64 = tile_rows = f64_pick_rows(src.Mrows, false);
       a.in_bytes = (uint32_t)(8 * in_elems);
@@ -1729,6 +1777,8 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
       a.use_patch = 0;
       a.accumulate = 0;
       configure_ksplit(a, src.out_elems, bm64, bn64, 8);  // the same rule on this tile's grid (chunks are 16 k rows here too)
+      small = configure_corr_small(a, psrc, w_elems, src.out_elems, 8, corr64_model(a, bm64, bn64, src.out_elems), sm);
+      if (small < 0) plan_corr64(a, src.out_elems, tile_rows);
       a.simple_epilogue = src.simple_epilogue && 8 * (int64_t)src.out_elems <= ((int64_t)1 << 30);
       k = psrc;
       k.KP = a.KP;
@@ -1740,12 +1790,8 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
       ws = (size_t)pack_elems * 8 + (size_t)a.KP * sizeof(KTabEntry) +
            (a.ksplit > 1 ? (size_t)a.ksplit * (size_t)src.out_elems * 8 : 0);
     };
-    corr64(d->fwd, d->fwd_pack, d->fwd64, d->fwd64_pack, x_elems, d->fwd64_ws, d->fwd64_rows);
-    corr64(d->bwd, d->bwd_pack, d->bwd64, d->bwd64_pack, y_elems, d->bwd64_ws, d->bwd64_rows);
-    d->fwd_small[1] = configure_corr_small(d->fwd64, d->fwd_pack, w_elems, y_elems, 8,
-                                           corr64_model(d->fwd64, d->fwd64_rows, bn64, y_elems), d->fwd_sm[1]);
-    d->bwd_small[1] = configure_corr_small(d->bwd64, d->bwd_pack, w_elems, x_elems, 8,
-                                           corr64_model(d->bwd64, d->bwd64_rows, bn64, x_elems), d->bwd_sm[1]);
+    corr64(d->fwd, d->fwd_pack, d->fwd64, d->fwd64_pack, x_elems, d->fwd64_ws, d->fwd64_rows, d->fwd_small[1], d->fwd_sm[1]);
+    corr64(d->bwd, d->bwd_pack, d->bwd64, d->bwd64_pack, y_elems, d->bwd64_ws, d->bwd64_rows, d->bwd_small[1], d->bwd_sm[1]);
     const int32_t bm64 = d->wg64_rows = f64_pick_rows(Kg, true);
     WgradArgs& a = d->wg64;
     a = d->wg;

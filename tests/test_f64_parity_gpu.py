@@ -193,3 +193,28 @@ def test_f64_benchmark_layers_config_4_full(name):
     print("f64 layer", name, "full compare", flush=True)
     x, w, b, dy = (t.double() for t in workloads.layer_inputs(l, bias="random"))
     check_full64(l.params_dict(), x, w, b, dy)
+
+
+# layer, the tile rows and whether slices follow from the modelled time and not from the least padding, forward or backward data
+MODELLED = [
+    (P(12, 112, 21, 16, 52, 2, 2, 2, 1, 0, 2, 2, 2, 2), "fwd", 16, False),
+    (P(3, 250, 6, 11, 139, 4, 4, 2, 2, 1, 1, 1, 1, 1), "fwd", 16, True),
+    (P(25, 7, 54, 57, 52, 3, 3, 3, 3, 2, 0, 2, 2, 1), "fwd", 32, False),
+    (P(5, 19, 20, 23, 108, 7, 7, 2, 2, 1, 4, 2, 2, 1), "fwd", 32, True),
+    (P(5, 9, 22, 26, 261, 5, 3, 1, 1, 0, 0, 1, 1, 3), "fwd", 48, False),
+    (P(13, 162, 8, 6, 282, 3, 3, 1, 2, 2, 1, 2, 2, 3), "fwd", 48, True),
+    (P(25, 4, 25, 22, 104, 4, 1, 1, 1, 3, 0, 1, 1, 1), "fwd", 64, False),
+    (P(24, 94, 13, 13, 41, 7, 7, 1, 1, 0, 2, 2, 2, 1), "bwd_data", 48, True),
+    (P(1, 214, 63, 60, 8, 4, 2, 1, 1, 1, 1, 1, 1, 2), "bwd_data", 64, False),
+]
+
+
+@pytest.mark.parametrize("i", range(len(MODELLED)))
+def test_f64_modelled_tiles_against_the_oracle(i):
+    pd, which, rows, sliced = MODELLED[i]
+    names = dict(f.split("=", 1) for f in conv.conv_desc_kernel_names_f64(conv.conv_desc_create(conv.ConvParams(**pd))).split(";"))
+    assert names[which].startswith(f"corr64_{rows}x64x16[") and ("(S=1," not in names[which]) == sliced, (pd, names)
+    op = OracleParams(**pd)
+    x, w, b, dy = (widen(t, 95000 + 10 * i + j) for j, t in enumerate(
+        workloads.random_inputs(oracle.x_shape(op), oracle.w_shape(op), oracle.output_shape(op), 94000 + 10 * i)))
+    check_full64(pd, x, w, b, dy)
