@@ -217,6 +217,10 @@ void small_names(const conv_desc* d, int which, char* fwd, char* bwd, char* wg, 
                        d->wg_sm[which].S, 1 + (d->wg_sm[which].S > 1));
 }
 
+// Places of a channel up to which one workgroup sums them and finishes db of doubles: 2.6 to 3.5 us up to 6000 places where the
+// two launches took 4.1 to 9.2, 5.1 to 12.8 against 5.8 to 17.2 at 21632, no longer ahead at 25088 (5.6 and 5.3, 32 channels).
+constexpr int64_t kBias64Direct = 24576;
+
 uint32_t koff_invalid(int32_t mode) { return mode == 0 ? 0x7FFFFFFCu : mode == 2 ? 0x40000000u : 0u; }
 
 // Decides whether the patch-staged kernel runs this correlation and, if so, fills its fields.
@@ -1742,6 +1746,7 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
   }
 
   // ---- backward bias ----
+  char bias64[32];
   {
     BiasGradArgs& a = d->bg;
     a.N = p.n;
@@ -1757,6 +1762,10 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
     a.n_per_split = (int32_t)ceil_div(N > 0 ? N : 1, S);
     a.S = (int32_t)ceil_div(N > 0 ? N : 1, a.n_per_split);
     d->bg_ws = p.bias_term ? (size_t)a.S * K * 4 : 0;
+    a.mP = make_magic((uint32_t)a.P);
+    d->bg64_direct = N * a.P <= kBias64Direct;
+    snprintf(bias64, sizeof(bias64), "bias_grad64[%s](S=%d,L=%d)", d->bg64_direct ? "one" : "two", d->bg64_direct ? 1 : a.S,
+             d->bg64_direct ? 1 : 2);
   }
 
   // ---- double base type: the same geometry on the fp64 tiles, compare-style bounds checks ----
@@ -1817,10 +1826,9 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
     auto e64 = [](const CorrArgs& c) { return c.simple_epilogue ? 's' : 'p'; };
     snprintf(d->names64, sizeof(d->names64),
              "fwd=corr64_%dx64x16[e%c](S=%d,L=%d);bwd_data=corr64_%dx64x16[e%c](S=%d,L=%d);"
-             "bwd_filter=wgrad64_%dx64x16(S=%d,L=2);bwd_bias=bias_grad64(S=%d,L=2)",
+             "bwd_filter=wgrad64_%dx64x16(S=%d,L=2);bwd_bias=%s",
              d->fwd64_rows, e64(d->fwd64), d->fwd64.ksplit, 2 + (d->fwd64.ksplit > 1), d->bwd64_rows, e64(d->bwd64),
-             d->bwd64.ksplit, 2 + (d->bwd64.ksplit > 1) + (d->bwd_zero_fill != 0), d->wg64_rows, a.S,
-             d->bg.S);
+             d->bwd64.ksplit, 2 + (d->bwd64.ksplit > 1) + (d->bwd_zero_fill != 0), d->wg64_rows, a.S, bias64);
     if (d->fwd_small[1] >= 0 || d->bwd_small[1] >= 0 || d->wg_small[1] >= 0) {
       char f[64], b[64], wg[64];
       snprintf(f, sizeof(f), "corr64_%dx64x16[e%c](S=%d,L=%d)", d->fwd64_rows, e64(d->fwd64), d->fwd64.ksplit, 2 + (d->fwd64.ksplit > 1));
@@ -1828,7 +1836,7 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
                2 + (d->bwd64.ksplit > 1) + (d->bwd_zero_fill != 0));
       snprintf(wg, sizeof(wg), "wgrad64_%dx64x16(S=%d,L=2)", d->wg64_rows, a.S);
       small_names(d, 1, f, b, wg, sizeof(f));
-      snprintf(d->names64, sizeof(d->names64), "fwd=%s;bwd_data=%s;bwd_filter=%s;bwd_bias=bias_grad64(S=%d,L=2)", f, b, wg, d->bg.S);
+      snprintf(d->names64, sizeof(d->names64), "fwd=%s;bwd_data=%s;bwd_filter=%s;bwd_bias=%s", f, b, wg, bias64);
     }
     d->ws_bytes64 = d->fwd64_ws;
     if (d->bwd64_ws > d->ws_bytes64) d->ws_bytes64 = d->bwd64_ws;
@@ -1903,8 +1911,8 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
       for (int pass = 0; pass < 3; ++pass) direct_form_name(pass, a, df[pass], sizeof(df[pass]));
       snprintf(d->names64, sizeof(d->names64),
                "fwd=direct64[%s](S=1,L=1);bwd_data=direct64[%s](S=1,L=1);bwd_filter=direct64[%s](S=%d,L=2);"
-               "bwd_bias=bias_grad64(S=%d,L=2)",
-               df[0], df[1], df[2], a.S, d->bg.S);
+               "bwd_bias=%s",
+               df[0], df[1], df[2], a.S, bias64);
     }
   }
 
@@ -2180,6 +2188,14 @@ int conv_backward_bias_f64(const conv_desc_t* d, const double* dy, double* db, d
   BiasGradArgs a = d->bg;
   a.dy = reinterpret_cast<const float*>(dy);
   a.part = static_cast<float*>(ws);
+  if (!empty && d->bg64_direct) {  // one launch writes db
+    a.S = 1;
+    a.n_per_split = d->p.n;
+    a.db = reinterpret_cast<float*>(db);
+    a.beta = (float)beta;
+    const int e1 = launch_bias_grad64(a, hip_stream);
+    return e1 ? record_hip_error(e1) : CONV_OK;
+  }
   int e = empty ? 0 : launch_bias_grad64(a, hip_stream);
   if (e) return record_hip_error(e);
   ReduceArgs r = {};

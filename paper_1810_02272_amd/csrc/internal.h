@@ -283,6 +283,7 @@ struct BiasGradArgs {
   int32_t N, K, P;
   int32_t S;        // splits over the images
   int32_t n_per_split;
+  Magic mP;         // double base type
   // S == 1 on a small blob: the kernel finishes db itself (db = beta*db + sum) and no reduce
   // kernel follows; db is null otherwise
   float* db;
@@ -484,7 +485,8 @@ struct conv_desc {
   // backward bias
   mi355conv::BiasGradArgs bg;
   size_t bg_ws;
-  int32_t bg_direct;  // fp32: the bias-gradient kernel writes db itself (small blobs)
+  int32_t bg_direct;    // fp32: the bias-gradient kernel writes db itself (small blobs)
+  int32_t bg64_direct;  // the same, double base type
   size_t ws_bytes;
   // thin groups: all three passes run the direct kernels (both base types)
   int32_t use_direct;

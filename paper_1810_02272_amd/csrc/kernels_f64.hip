@@ -473,32 +473,39 @@ __global__ __launch_bounds__(256) void reduce64_kernel(const ReduceArgs a) {
   dst[i] = v;
 }
 
-// part[s][k] = sum of dy[n][k][:] over the images of split s: one wave per image at a time.
-__global__ __launch_bounds__(256) void bias_grad64_kernel(const BiasGradArgs a) {
-  __shared__ double wsum[4];
+// part[s][k] = sum of dy[n][k][:] over the images of split s, or db[k] where db is set (one split).  The workgroup walks the
+// images' planes as one run of places, four loads a lane in flight: one wave per image left two, and most lanes idle where
+// planes are small.
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void bias_grad64_kernel(const BiasGradArgs a) {
+  constexpr uint32_t kThreads = 64 * WAVES;
+  __shared__ double wsum[WAVES];
   const int k = blockIdx.x, s = blockIdx.y;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int n0 = s * a.n_per_split;
   int n1 = n0 + a.n_per_split;
   if (n1 > a.N) n1 = a.N;
-  const double* dy = reinterpret_cast<const double*>(a.dy);
-  double acc0 = 0., acc1 = 0.;
-  for (int n = n0 + wv; n < n1; n += 4) {
-    const double* src = dy + ((size_t)n * a.K + k) * a.P;
-    int p = lane;
-    for (; p + 64 < a.P; p += 128) {
-      acc0 += src[p];
-      acc1 += src[p + 64];
-    }
-    for (; p < a.P; p += 64) acc0 += src[p];
-  }
-  double v = acc0 + acc1;
+  const double* const dy = reinterpret_cast<const double*>(a.dy) + ((size_t)n0 * a.K + k) * a.P;
+  const uint32_t count = (uint32_t)(n1 - n0) * (uint32_t)a.P;
+  const size_t skip = (size_t)(a.K - 1) * a.P;  // elements of the other channels between two planes
+  double acc[4] = {0., 0., 0., 0.};
+  uint32_t i = threadIdx.x;
+  for (; i + 3 * kThreads < count; i += 4 * kThreads)
+#pragma unroll
+    for (uint32_t e = 0; e < 4; ++e) acc[e] += dy[i + kThreads * e + mdiv(i + kThreads * e, a.mP) * skip];
+  for (; i < count; i += kThreads) acc[0] += dy[i + mdiv(i, a.mP) * skip];
+  double v = (acc[0] + acc[1]) + (acc[2] + acc[3]);
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-  if (lane == 0) wsum[wv] = v;
+  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = v;
   __syncthreads();
-  if (threadIdx.x == 0)
-    reinterpret_cast<double*>(a.part)[(size_t)s * a.K + k] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+  if (threadIdx.x == 0) {
+    double sum = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+    if constexpr (WAVES == 8) sum += (wsum[4] + wsum[5]) + (wsum[6] + wsum[7]);
+    if (double* const db = reinterpret_cast<double*>(a.db))
+      db[k] = a.beta != 0.f ? a.beta * db[k] + sum : sum;
+    else
+      reinterpret_cast<double*>(a.part)[(size_t)s * a.K + k] = sum;
+  }
 }
 
 }  // namespace
@@ -554,7 +561,10 @@ int launch_reduce64(const ReduceArgs& a, void* stream) {
 }
 
 int launch_bias_grad64(const BiasGradArgs& a, void* stream) {
-  hipLaunchKernelGGL(bias_grad64_kernel, dim3(a.K, a.S), dim3(256), 0, (hipStream_t)stream, a);
+  if (a.db)
+    hipLaunchKernelGGL(bias_grad64_kernel<8>, dim3(a.K, a.S), dim3(512), 0, (hipStream_t)stream, a);
+  else
+    hipLaunchKernelGGL(bias_grad64_kernel<4>, dim3(a.K, a.S), dim3(256), 0, (hipStream_t)stream, a);
   return (int)hipGetLastError();
 }
 

@@ -218,3 +218,20 @@ def test_f64_modelled_tiles_against_the_oracle(i):
     x, w, b, dy = (widen(t, 95000 + 10 * i + j) for j, t in enumerate(
         workloads.random_inputs(oracle.x_shape(op), oracle.w_shape(op), oracle.output_shape(op), 94000 + 10 * i)))
     check_full64(pd, x, w, b, dy)
+
+
+@pytest.mark.parametrize("n,k,h,w", [(1, 1, 1, 1), (3, 5, 7, 9), (64, 3, 8, 1), (7, 2, 293, 1), (1, 4, 2048, 1), (6, 3, 64, 64), (8, 2, 3073, 1), (200, 16, 11, 13)])
+def test_f64_bias_gradient_in_one_launch_and_two(n, k, h, w):
+    """Places a channel around one and four loads a lane and around the limit of the one-launch form (24576); whole numbers, so
+    that the sums are exact in any order."""
+    d = conv.conv_desc_create(conv.ConvParams(n=n, c=1, h=h, w=w, num_output=k, kernel_h=1, kernel_w=1))
+    names = dict(f.split("=", 1) for f in conv.conv_desc_kernel_names_f64(d).split(";"))
+    assert names["bwd_bias"].startswith("bias_grad64[one](S=1,L=1)" if n * h * w <= 24576 else "bias_grad64[two]"), names
+    gen = torch.Generator().manual_seed(n + k + h)
+    dy = torch.randint(-8, 9, (n, k, h, w), generator=gen).double()
+    ws = torch.full((conv.conv_desc_workspace_bytes_f64(d) // 8 + 1,), NAN, device=DEV, dtype=torch.float64)
+    db = torch.full((k,), NAN, device=DEV, dtype=torch.float64)
+    conv.conv_backward_bias_f64(d, dy.to(DEV), db, 0.0, ws)
+    assert torch.equal(db.cpu(), dy.sum((0, 2, 3)))
+    conv.conv_backward_bias_f64(d, dy.to(DEV), db, 1.0, ws)
+    assert torch.equal(db.cpu(), 2 * dy.sum((0, 2, 3)))
