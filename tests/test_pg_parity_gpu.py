@@ -131,3 +131,36 @@ def test_pg_full_size():
     """The benchmark's batch at full size (the oracle finishes it in seconds), same checks."""
     episodes, lo, hi, actions = workloads.PG_BENCH
     check_batch(workloads.pg_batch(episodes, lo, hi, actions, workloads.PG_SEED), 0.99, perturb_seed=None)
+
+
+@pytest.mark.parametrize("lo,hi,episodes", [(0, 1, 9000), (0, 3, 9001), (1, 9, 8333), (3, 33, 8777), (12, 12, 8192), (60, 70, 8200), (0, 250, 8195),
+                                            (0, 1, 400), (250, 262, 30), (0, 5000, 7)])
+def test_pg_episodes_that_share_a_wave(lo, hi, episodes):
+    """Many short episodes (8192 and more of under 128 steps: groups of them a wave; else a wave each): empty ones, ends on every position of a lane's four steps, of a row of lanes and of a chunk; steps before
+    the first and behind the last episode stay as they were; an infinite reward stays in its episode."""
+    gen = torch.Generator().manual_seed(lo + 7 * hi + episodes)
+    lengths = torch.randint(lo, hi + 1, (episodes,), generator=gen)
+    offsets = torch.zeros(episodes + 1, dtype=torch.int64)
+    offsets[1:] = torch.cumsum(lengths, 0)
+    offsets += 5
+    steps = int(offsets[-1]) + 6
+    reward = torch.randn(steps, generator=gen)
+    R = torch.full((steps,), 77.0, device=DEV)
+    lib.pg_discount_rewards(reward.to(DEV), offsets.to(torch.int32).to(DEV), 0.97, R)
+    want = np.full(steps, 77.0)
+    for e in range(episodes):
+        run = 0.0
+        for t in range(int(offsets[e + 1]) - 1, int(offsets[e]) - 1, -1):
+            run = float(reward[t]) + 0.97 * run
+            want[t] = run
+    assert nerr(R, want) <= TOL
+    assert bool((R[:5] == 77).all()) and bool((R[-6:] == 77).all())
+    inner = [e for e in range(episodes) if int(lengths[e]) > 0]
+    if not inner:
+        return
+    e = inner[len(inner) // 2]
+    reward[int(offsets[e + 1]) - 1] = float("inf")
+    lib.pg_discount_rewards(reward.to(DEV), offsets.to(torch.int32).to(DEV), 0.97, R)
+    bad = torch.zeros(steps, dtype=torch.bool)
+    bad[int(offsets[e]):int(offsets[e + 1])] = True
+    assert torch.equal(~torch.isfinite(R.cpu()), bad)
