@@ -959,7 +959,7 @@ int32_t configure_corr_small(const CorrArgs& base, const PackArgs& k, int64_t w_
        {{0.151, 0.047, 0.32}, {0.193, 0.050, 0.43}, {0.224, 0.061, 0.54}, {0.224, 0.062, 0.73}, {0.259, 0.094, 1.18}, {0.309, 0.081, 0.72}, {0.390, 0.117, 1.45}}},
       {{{0.072, 0.059, 0.42}, {0.000, 0.066, 0.72}, {0.091, 0.089, 0.68}, {0.139, 0.092, 0.78}, {0.149, 0.153, 1.21}, {0.119, 0.114, 1.01}, {}},
        {{0.151, 0.063, 0.39}, {0.000, 0.079, 0.69}, {0.156, 0.107, 0.59}, {0.214, 0.102, 0.65}, {0.242, 0.175, 0.99}, {0.151, 0.159, 0.88}, {}}}};
-  // a forward gather that strides over columns takes more cache lines a load
+  // a forward gather that strides over columns takes more cache lines a load; one that stays in the image no bounds tests
   const double strided = (base.sw == 1 ? 1.0 : base.sw < 4 ? 1.1 : 1.3) * (a.pad ? 1.0 : elem_bytes == 8 ? 0.95 : 0.88);
   const int64_t groups = KT / 16;
   int32_t best = -1;
@@ -1056,8 +1056,8 @@ int32_t configure_wgrad_small(const WgradArgs& w, int64_t N, int32_t elem_bytes,
     r.blocks = (int32_t)ceil_div(N * r.runs, 16);
   };
   a.pad = w.ph > 0 || w.pw > 0;
-  // [doubles][xvec][tile], and what a reduce launch costs: fits to every tile and 1 to 128 slices on 182 (doubles: 106) filter
-  // gradients, rms errors 11 to 25 %; the choice is 3 (doubles: 5) % behind the best on average.  Runs within rows of doubles
+  // [doubles][xvec][tile], and what a reduce launch costs: fits to every tile and 1 to 128 slices on 182 (doubles: 64) filter
+  // gradients, rms errors 10 to 25 %; the choice is 3 (doubles: 5) % behind the best on average.  Runs within rows of doubles
   // are two loads each and took 1.09 times as long as single ones: no instance.
   static const SmallCost kCost[2][3][WGRAD_SMALL_COUNT] = {
       {{{0.453, 0.190, 0.41}, {0.476, 0.321, 0.97}, {0.598, 0.268, 0.91}, {0.883, 0.412, 1.30}, {1.422, 0.365, 0.36}},
@@ -1097,8 +1097,8 @@ int32_t configure_wgrad_small(const WgradArgs& w, int64_t N, int32_t elem_bytes,
   if (best < 0) return -1;
   a.xvec = best_xvec;
   set_runs(a);
-  // The launches of `w`, a fit to the same layers (rms errors 7 and 16 %).  With a margin of 0.9 142 of 175 layers of floats are
-  // taken, 1.43 times as fast in the geometric mean over all, eight more than 3 % slower; doubles 36 of 64, 1.11 times, one.
+  // The launches of `w`, a fit to as many layers (rms errors 7 and 16 %).  With the margins below 136 of 190 layers of floats up to 4
+  // GFLOP are taken, 1.42 times as fast in the geometric mean over all, three more than 3 % slower; doubles 90 of 110, 1.20 times, six.
   static const double kOld[2][7] = {{3.2, 0.74, 0.236, 0.374, 0.115, 0.242, 2.9}, {4.7, 0.63, 1.46, 1.91, 0.0, 0.222, 1.9}};
   const double* const o = kOld[elem_bytes == 8];
   const double area = (double)(bm * bn) / 4096.0;
