@@ -210,6 +210,17 @@ __global__ __launch_bounds__(256) void pg_discount_kernel(const float* __restric
 // Left out and not weighted by zero: the next episode's values may be infinite.  Bound by the latency of a load, the scan and a
 // store; groups of 200 steps were up to 1.9 times as slow beyond 50 steps an episode.
 constexpr int kGroupSteps = 384;  // a group of average length fits the chunks in flight
+// A group's episodes follow from the mean length alone, so long ones that stand together would all fall to one wave, 1.1 us a round of
+// 512 steps.  Groups of more than kGroupMost steps beside their longest episode are therefore left to further waves: each looks
+// through a share of the groups and takes one part of every such group that it finds, parts of equal steps, as many as a group has
+// episodes where that makes kPartWaves waves or fewer.  64 neighbours of 10000 steps among 60000 episodes of one step 706 -> 23 us
+// (30 in the form above), 64 of 1000 among 65536 of four 112 -> 8.3 (21); evenly drawn lengths 1 to 4 % slower, 300000 episodes 13 %.
+// Cut by steps and not by count, which needs a search in the offsets before the loads, those took 1.1 to 2 times as long.
+constexpr int kGroupMost = 2048, kPartWaves = 1024, kLeastParts = 4;
+constexpr int kShareGroups = 256;  // groups in a share: four loads a lane, all in flight
+// Their place: behind all groups of a grid that is resident as a whole (2048 blocks), where nothing waits for their blocks; near the start of a
+// larger one, at whose end they are waited for (300000 episodes of 3 to 33 steps: 10.3 us without them, 14.2 there, 11.6 early).
+constexpr int kResidentBlocks = 2048, kEarly = 256;
 // Taken from the number of episodes on at which a wave of the other form walks several, and up to an average length: 44013
 // episodes of 3 to 33 steps 4.9 us, there 16.8; 60000 of 8 to 120 10.2 and 22.9; 16000 of 8 to 200 6.9 and 8.8; 8000 of 5 to 60
 // 4.8 and 5.8; but 65536 of 8 to 500 32.0 and 25.6, 4000 of 5 to 60 4.8 and 4.5.
@@ -244,21 +255,10 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__global__ __launch_bounds__(256) void pg_discount_short_kernel(const float* __restrict__ reward,
-                                                          const int32_t* __restrict__ offsets, int episodes,
-                                                          int steps, int per_wave, float gamma, float* __restrict__ discounted) {
-  __shared__ uint32_t marks[4][kChunksInFlight][64];  // per wave, chunk and lane: which of its four steps end an episode
-  const int lane = threadIdx.x & 63;
-  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int e0 = ((int)blockIdx.x * 4 + wv) * per_wave;
-  if (e0 >= episodes) return;
-  const int n = episodes - e0 < per_wave ? episodes - e0 : per_wave;
-  auto clamped = [&](int v) { return v < 0 ? 0 : v > steps ? steps : v; };
-  const int my_end = lane < n ? clamped(offsets[e0 + lane + 1]) : 0;  // lane l: one past the last step of episode l
-  const int b = __builtin_amdgcn_readfirstlane(clamped(offsets[e0]));
-  const int end = __builtin_amdgcn_readlane(my_end, n - 1);
-  const float g2 = gamma * gamma, g3 = g2 * gamma, g4 = g2 * g2;
-  const ScanWeights w = scan_weights(g4, lane);
+// Episodes of the steps [b, end), n of them, lane l holding one past the last step of episode l.
+__device__ __forceinline__ void discount_run(const float* __restrict__ reward, float* __restrict__ discounted, int b, int end, int my_end,
+                                             int n, int lane, float gamma, const ScanWeights& w, uint32_t (&marks)[kChunksInFlight][64]) {
+  const float g2 = gamma * gamma, g3 = g2 * gamma;
   const int row = lane >> 4;
 
   float carry = 0.f;  // R of the first step of the later chunk
@@ -278,16 +278,16 @@ __global__ __launch_bounds__(256) void pg_discount_short_kernel(const float* __r
     }
     uint32_t mark[kChunksInFlight];
 #pragma unroll
-    for (int c = 0; c < kChunksInFlight; ++c) marks[wv][c][lane] = 0;
+    for (int c = 0; c < kChunksInFlight; ++c) marks[c][lane] = 0;
     wave_sync();
     const int back = hi - my_end;  // steps between the end of my episode and the end of the chunks
     if (lane < n && my_end > b && back >= 0 && back < kChunkSteps * kChunksInFlight) {
       const int place = kChunkSteps - 1 - (back & (kChunkSteps - 1));
-      atomicOr(&marks[wv][back / kChunkSteps][place >> 2], 1u << (place & 3));
+      atomicOr(&marks[back / kChunkSteps][place >> 2], 1u << (place & 3));
     }
     wave_sync();
 #pragma unroll
-    for (int c = 0; c < kChunksInFlight; ++c) mark[c] = marks[wv][c][lane];
+    for (int c = 0; c < kChunksInFlight; ++c) mark[c] = marks[c][lane];
     wave_sync();
     float s[kChunksInFlight][4], total[kChunksInFlight], t1[kChunksInFlight], t2[kChunksInFlight], t3[kChunksInFlight];
     uint64_t ends[kChunksInFlight];
@@ -330,6 +330,76 @@ __global__ __launch_bounds__(256) void pg_discount_short_kernel(const float* __r
           if (t + j >= b && t + j < end) discounted[t + j] = out.v[j];
       }
       carry = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, with_carry)));
+    }
+  }
+}
+
+__global__ __launch_bounds__(256) void pg_discount_short_kernel(const float* __restrict__ reward,
+                                                                const int32_t* __restrict__ offsets, int episodes, int steps, int per_wave,
+                                                                int groups, int shares, int parts, int lead, int part_blocks, float gamma,
+                                                                float* __restrict__ discounted) {
+  __shared__ uint32_t marks[4][kChunksInFlight][64];  // per wave, chunk and lane: which of its four steps end an episode
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  auto clamped = [&](int v) { return v < 0 ? 0 : v > steps ? steps : v; };
+  auto size = [&](int group) { return episodes - group * per_wave < per_wave ? episodes - group * per_wave : per_wave; };
+  const float g2 = gamma * gamma;
+  const ScanWeights w = scan_weights(g2 * g2, lane);
+  const int place = (int)blockIdx.x - lead;  // the parts' blocks stand behind the first `lead` of the groups'
+  if (place < 0 || place >= part_blocks) {
+    const int group = (place < 0 ? (int)blockIdx.x : (int)blockIdx.x - part_blocks) * 4 + wv;
+    if (group >= groups) return;
+    const int e0 = group * per_wave, n = size(group);
+    const int my_end = lane < n ? clamped(offsets[e0 + lane + 1]) : 0;  // lane l: one past the last step of episode l
+    const int b = __builtin_amdgcn_readfirstlane(clamped(offsets[e0])), end = __builtin_amdgcn_readlane(my_end, n - 1);
+    if (end - b > kGroupMost) {
+      const int before = __shfl_up(my_end, 1, 64);
+      int longest = lane < n ? my_end - (lane ? before : b) : 0;
+#pragma unroll
+      for (int d = 32; d >= 1; d >>= 1) longest = max(longest, __shfl_xor(longest, d, 64));
+      if (end - b - longest > kGroupMost) return;
+    }
+    discount_run(reward, discounted, b, end, my_end, n, lane, gamma, w, marks[wv]);
+    return;
+  }
+  // part `part` of the groups share, share + shares, ...
+  const int wave = place * 4 + wv, part = wave % parts, share = wave / parts;
+  if (share >= shares) return;
+  int from[4], to[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int64_t group = share + (int64_t)(lane + 64 * j) * shares;
+    from[j] = to[j] = 0;
+    if (group < groups) {
+      from[j] = clamped(offsets[(int)group * per_wave]);
+      to[j] = clamped(offsets[(int)group * per_wave + size((int)group)]);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    bool is_long = to[j] - from[j] > kGroupMost;
+    if (is_long) {
+      const int group = share + (lane + 64 * j) * shares, n = size(group);
+      int longest = 0, start = from[j];
+#pragma unroll 4
+      for (int i = 1; i <= n; ++i) {
+        const int stop = clamped(offsets[group * per_wave + i]);
+        longest = max(longest, stop - start);
+        start = stop;
+      }
+      is_long = to[j] - from[j] - longest > kGroupMost;
+    }
+    for (uint64_t left = __ballot(is_long); left; left &= left - 1) {
+      const int l = (int)__builtin_ctzll(left), group = share + (l + 64 * j) * shares, n = size(group), e0 = group * per_wave;
+      const int start = __builtin_amdgcn_readlane(from[j], l), total = __builtin_amdgcn_readlane(to[j], l) - start;
+      const int begin = lane < n ? clamped(offsets[e0 + lane]) : 0, stop = lane < n ? clamped(offsets[e0 + lane + 1]) : 0;
+      // the part's episodes: neighbours, as their starts ascend
+      const uint64_t lanes = __ballot(lane < n && (int64_t)(begin - start) * parts / total == part);
+      if (lanes == 0) continue;
+      const int first = (int)__builtin_ctzll(lanes), count = (int)__builtin_popcountll(lanes);
+      const int my_end = __shfl(stop, first + lane, 64);
+      discount_run(reward, discounted, __builtin_amdgcn_readlane(begin, first), __builtin_amdgcn_readlane(my_end, count - 1), my_end, count, lane,
+                   gamma, w, marks[wv]);
     }
   }
 }
@@ -523,9 +593,12 @@ int pg_discount_rewards(const float* reward, const int32_t* episode_offsets, int
   if (!reward || !episode_offsets || !discounted) return CONV_EINVAL;
   if (episodes >= kShortEpisodes && steps / episodes < kShortSteps) {
     const int per_wave = (int)std::min<int64_t>(64, std::max<int64_t>(1, (int64_t)kGroupSteps * episodes / steps));
-    const int waves = (episodes + per_wave - 1) / per_wave;
-    hipLaunchKernelGGL(pg_discount_short_kernel, dim3((waves + 3) / 4), dim3(256), 0, (hipStream_t)hip_stream, reward,
-                       episode_offsets, episodes, steps, per_wave, gamma, discounted);
+    const int groups = (int)(((int64_t)episodes + per_wave - 1) / per_wave);
+    const int shares = std::max(std::min(groups, kPartWaves / per_wave), (groups + kShareGroups - 1) / kShareGroups);
+    const int parts = std::min(per_wave, std::max(kLeastParts, kPartWaves / shares));
+    const int group_blocks = (groups + 3) / 4, part_blocks = per_wave == 1 ? 0 : (shares * parts + 3) / 4;
+    hipLaunchKernelGGL(pg_discount_short_kernel, dim3(group_blocks + part_blocks), dim3(256), 0, (hipStream_t)hip_stream, reward,
+                       episode_offsets, episodes, steps, per_wave, groups, shares, parts, group_blocks <= kResidentBlocks ? group_blocks : kEarly, part_blocks, gamma, discounted);
     return done();
   }
   int blocks = (episodes + 3) / 4;

@@ -164,3 +164,57 @@ def test_pg_episodes_that_share_a_wave(lo, hi, episodes):
     bad = torch.zeros(steps, dtype=torch.bool)
     bad[int(offsets[e]):int(offsets[e + 1])] = True
     assert torch.equal(~torch.isfinite(R.cpu()), bad)
+
+
+def _skewed(kind, episodes):
+    """Lengths whose mean says little: short episodes in which 64 long ones stand together (in the middle, at an end) or lie apart, sorted
+    by length, with a stretch of empty ones longer than any probe."""
+    gen = torch.Generator().manual_seed(episodes)
+    lengths = torch.randint(0, 4, (episodes,), generator=gen)
+    if kind == "sorted":
+        return torch.randint(0, 250, (episodes,), generator=gen).sort().values
+    if kind == "empty_middle":
+        lengths = torch.randint(20, 60, (episodes,), generator=gen)
+        lengths[episodes // 4:3 * episodes // 4] = 0
+        return lengths
+    where = {"middle": slice(episodes // 2, episodes // 2 + 64), "last": slice(episodes - 64, episodes), "first": slice(0, 64),
+             "apart": slice(5, None, episodes // 64)}[kind]
+    lengths[where] = 1500 + torch.arange(lengths[where].numel())
+    return lengths
+
+
+@pytest.mark.parametrize("kind", ["middle", "last", "first", "apart", "sorted", "empty_middle"])
+@pytest.mark.parametrize("episodes", [8192, 20011])
+def test_pg_long_episodes_among_many_short_ones(kind, episodes):
+    lengths = _skewed(kind, episodes)
+    offsets = torch.zeros(episodes + 1, dtype=torch.int64)
+    offsets[1:] = torch.cumsum(lengths, 0)
+    steps = int(offsets[-1])
+    reward = torch.randn(steps, generator=torch.Generator().manual_seed(steps))
+    R = torch.full((steps,), NAN, device=DEV)
+    lib.pg_discount_rewards(reward.to(DEV), offsets.to(torch.int32).to(DEV), 0.97, R)
+    assert nerr(R, pgo.discount_rewards(reward.numpy(), offsets.numpy(), 0.97)) <= TOL
+
+
+def test_pg_neighbouring_long_episodes_cost_no_more_than_distant_ones():
+    """64 episodes of 10000 steps among 60000 of one step.  Where they stand together a wave must not walk them all: by count of
+    episodes it took 20 times the time of the same lengths spread out (the bound leaves room for clocks and other load)."""
+    times = {}
+    for kind in ("together", "apart"):
+        lengths = torch.ones(60000, dtype=torch.int64)
+        lengths[torch.arange(64) * (1 if kind == "together" else 900) + 1000] = 10000
+        offsets = torch.zeros(60001, dtype=torch.int64)
+        offsets[1:] = torch.cumsum(lengths, 0)
+        reward, offsets = torch.ones(int(offsets[-1]), device=DEV), offsets.to(torch.int32).to(DEV)
+        R = torch.empty_like(reward)
+        best = float("inf")
+        for _ in range(6):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(10):
+                lib.pg_discount_rewards(reward, offsets, 0.99, R)
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, start.elapsed_time(end))
+        times[kind] = best
+    assert times["together"] <= 3 * times["apart"], times
