@@ -7,12 +7,14 @@ their ``data_ptr()`` and the current stream handle are passed through.
 The compute calls go through the extension ``_marshal`` (csrc/marshal.cpp), which checks plain tensors in C++ and calls the C
 entry point.  It returns None, having called nothing, for whatever is not plainly in order; the checks below then run, which
 raise, or accept what only they know how to (subclasses, numbers of other types).  A call's host time was 8 us here beside
-2 us a launch; through the extension it is under 1.
+2 us a launch; through the extension it is under 1.  The extension is built for one PyTorch and one Python; under others, where it
+cannot be built again, every call takes the checks below.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from dataclasses import dataclass, fields
 
 import torch  # imported before the library on purpose: both must share one HIP runtime
@@ -63,7 +65,7 @@ def _load():
     global _lib
     if _lib is not None:
         return _lib
-    if not os.path.exists(_build.LIB) or not os.path.exists(_build.MARSHAL):
+    if not os.path.exists(_build.LIB):
         _build.build()  # nothing built yet: build once (raises if a compiler fails)
     lib = ctypes.CDLL(_build.LIB)
     vp, sz, fp = ctypes.c_void_p, ctypes.c_size_t, ctypes.c_float
@@ -101,10 +103,27 @@ def _load():
                  "conv_backward_filter_f64", "conv_backward_bias_f64"):
         getattr(lib, name).restype = ctypes.c_int
     global _marshal
-    from . import _marshal as native
-
-    _lib, _marshal = lib, native
+    _marshal = _load_marshal()  # first: another thread that finds the library finds this too
+    _lib = lib
     return lib
+
+
+class _NoMarshal:
+    """Stands for an extension that cannot be had: declines every call, so that the checks in Python take it."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _load_marshal():
+    try:
+        if not _build.marshal_fits():
+            _build.build_marshal()
+        from . import _marshal as native
+        return native
+    except (ImportError, OSError, RuntimeError) as e:
+        warnings.warn(f"the binding's extension for {_build.marshal_target()} could not be loaded; calls take about 8 us more ({e})")
+        return _NoMarshal()
 
 
 def conv_status_string(status: int) -> str:

@@ -3,12 +3,13 @@ from __future__ import annotations
 
 import os
 import subprocess
+import sys
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_HERE)
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "libmi355conv.so")
-MARSHAL = os.path.join(_HERE, "_marshal.so")  # Python extension over LIB (csrc/marshal.cpp)
+MARSHAL = os.path.join(_HERE, "_marshal.so")  # Python extension over LIB (csrc/marshal.cpp), built for one PyTorch and one Python
 SOURCES = ["api.cpp", "api_ip.cpp", "kernels_corr.hip", "kernels_corr_patch.hip", "kernels_corr_thin.hip",
            "kernels_small.hip", "kernels_corr_split.hip", "kernels_wgrad_split.hip", "kernels_wgrad.hip", "kernels_bias.hip",
            "kernels_ip.hip", "kernels_pg.hip", "kernels_f64.hip", "kernels_direct.hip", "static_workspace.hip"]
@@ -32,8 +33,23 @@ def _hipcc() -> str:
     return "hipcc"
 
 
+def marshal_target() -> str:
+    """What MARSHAL is built for: neither PyTorch's C++ interface nor Python's is the same from one version to the next."""
+    import torch
+    return f"for torch {torch.__version__} and Python {sys.version_info.major}.{sys.version_info.minor}."
+
+
+def marshal_fits() -> bool:
+    """Whether MARSHAL is there and was built for what is running (it holds the text that marshal_target gave then)."""
+    try:
+        with open(MARSHAL, "rb") as f:
+            return marshal_target().encode() in f.read()
+    except OSError:
+        return False
+
+
 def is_stale() -> bool:
-    if not os.path.exists(LIB) or not os.path.exists(MARSHAL):
+    if not os.path.exists(LIB) or not marshal_fits():
         return True
     t = min(os.path.getmtime(LIB), os.path.getmtime(MARSHAL))
     deps = [os.path.join(CSRC, s) for s in SOURCES + HEADERS + ["marshal.cpp"]] + [
@@ -54,6 +70,7 @@ def _compile_marshal(obj_dir: str) -> str:
     obj = os.path.join(obj_dir, "marshal.o")
     rocm = os.path.dirname(os.path.dirname(_hipcc())) if os.path.isabs(_hipcc()) else "/opt/rocm"
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM", "-w",
+           f'-DMARSHAL_TARGET="{marshal_target()}"',
            "-I", os.path.join(_ROOT, "include"), "-isystem", torch_include,
            "-isystem", os.path.join(torch_include, "torch", "csrc", "api", "include"),
            "-isystem", os.path.join(rocm, "include"), "-isystem", sysconfig.get_paths()["include"],
@@ -71,6 +88,13 @@ def _link_marshal(obj: str) -> None:
     res = subprocess.run(cmd, cwd=_HERE, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("g++ link failed:\n" + " ".join(cmd) + "\n" + res.stdout + res.stderr)
+
+
+def build_marshal() -> None:
+    """The extension alone, over the library that is there."""
+    obj_dir = os.path.join(_HERE, "_build")
+    os.makedirs(obj_dir, exist_ok=True)
+    _link_marshal(_compile_marshal(obj_dir))
 
 
 def build(force: bool = True, verbose: bool = False) -> str:

@@ -21,6 +21,8 @@
 
 namespace {
 
+const char kTarget[] __attribute__((used)) = MARSHAL_TARGET;  // looked up in the built file, before it is loaded
+
 struct Shape {
   int dims;
   int64_t d[4];

@@ -36,6 +36,45 @@ def test_arguments_out_of_order_on_the_cpu():
         conv.conv_forward(d, t)
 
 
+def test_an_extension_that_cannot_be_had_leaves_the_python_checks(monkeypatch):
+    """Built for another PyTorch or Python and not to be built again: a warning, and descriptors and checks as ever."""
+    from paper_1810_02272_amd import build
+
+    assert build.marshal_fits()
+
+    def fails():
+        raise RuntimeError("no compiler")
+
+    monkeypatch.setattr(build, "marshal_target", lambda: "for torch 0.1 and Python 2.7.")
+    assert not build.marshal_fits() and build.is_stale()
+    monkeypatch.setattr(build, "build_marshal", fails)
+    with pytest.warns(UserWarning, match="no compiler"):
+        without = binding._load_marshal()
+    monkeypatch.setattr(binding, "_marshal", without)
+    d = conv.conv_desc_create(conv.ConvParams(2, 3, 9, 9, 5, 3, 3))
+    conv.ip_desc_create(conv.IpParams(2, 3, 4))
+    t = torch.zeros(2, 3, 9, 9)
+    with pytest.raises(TypeError, match="x: expected a CUDA/HIP tensor"):
+        conv.conv_forward(d, t, t, t, t)
+    with pytest.raises(TypeError, match="aprob"):
+        conv.pg_sigmoid_sample_action(t, t, t)
+
+
+@pytest.mark.gpu
+def test_calls_without_the_extension(monkeypatch):
+    d, x, w, b, y, ws = layer()
+    conv.conv_forward(d, x, w, b, y, ws)
+    torch.cuda.synchronize()
+    ref = y.clone()
+    y.fill_(float("nan"))
+    monkeypatch.setattr(binding, "_marshal", binding._NoMarshal())
+    conv.conv_forward(d, x, w, b, y, ws)
+    again = layer()  # a descriptor made without it
+    conv.conv_forward(*again)
+    torch.cuda.synchronize()
+    assert torch.equal(y, ref) and torch.equal(again[4], ref)
+
+
 @pytest.mark.gpu
 def test_what_is_refused_and_what_is_accepted():
     d, x, w, b, y, ws = layer()
