@@ -994,7 +994,7 @@ struct CorrChoice {
 };
 
 CorrChoice choose_corr(CorrArgs& a, PackArgs& k, int32_t& tile, int64_t cg_in, int64_t n_img, bool backward, int64_t out_elems,
-                       int64_t w_elems, bool zero_fill, CorrSplitArgs& sp, PackSplitArgs& sp_pack, CorrSmallArgs& small) {
+                       int64_t w_elems, bool zero_fill, bool one_launch, CorrSplitArgs& sp, PackSplitArgs& sp_pack, CorrSmallArgs& small) {
   CorrChoice c = {0, -1, -1, 0};
   CorrArgs tiled = a;
   PackArgs tiled_pack = k;
@@ -1002,7 +1002,7 @@ CorrChoice choose_corr(CorrArgs& a, PackArgs& k, int32_t& tile, int64_t cg_in, i
   const int64_t pack_elems = (int64_t)a.G * a.KP * a.MP;
   if (pack_elems >= kMaxElems || (int64_t)a.G * a.m_tiles * a.col_tiles >= ((int64_t)1 << 31)) return c;
   const int64_t steps = ceil_div(2 * ceil_div(a.Kred, 16), 4);
-  if (c.thin && !a.use_patch && steps >= 12) {
+  if (c.thin && !a.use_patch && one_launch && steps >= 12) {
     // Without LDS staging a thin-row workgroup walks its reduction in dependent steps of eight indices a wave: 4 -> 384
     // channels, 5x3 at 15x15, batch 4, 118 us, in one launch 15; 2 -> 30, 11x11 at 24x24, 128 and 14; 1 -> 82, 7x7, batch 8,
     // 127 and 32 on 16-row tiles in 16 slices.  Modelled by a fit to 54 passes (rms error 10 %); of the 33 with reductions
@@ -1031,7 +1031,7 @@ CorrChoice choose_corr(CorrArgs& a, PackArgs& k, int32_t& tile, int64_t cg_in, i
   }
   plan_corr(a, k, out_elems, zero_fill, tile);
   c.pack_bytes = (size_t)a.G * (size_t)a.KP * (size_t)a.MP * 4 + (size_t)a.KP * sizeof(KTabEntry);
-  c.small = configure_corr_small(a, k, w_elems, out_elems, 4, corr_model(a, tile, a.ksplit, out_elems, zero_fill), small);
+  if (one_launch) c.small = configure_corr_small(a, k, w_elems, out_elems, 4, corr_model(a, tile, a.ksplit, out_elems, zero_fill), small);
   return c;
 }
 
@@ -1413,7 +1413,8 @@ int run_backward_filter(const conv_desc* d, const float* x, const float* dy, flo
 
 extern "C" {
 
-int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
+// one_launch: the kernels of small layers may be taken (conv_desc_create_tiled leaves them out)
+static int create_desc(conv_desc_t** out, const conv_params_t* pp, bool one_launch) {
   if (!out || !pp) return CONV_EINVAL;
   const conv_params_t p = *pp;
   if (p.n < 0 || p.c < 1 || p.h < 1 || p.w < 1 || p.num_output < 1) return CONV_EINVAL;
@@ -1519,7 +1520,7 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
     k.koff_invalid = koff_invalid(a.bounds_mode);
     configure_patch(a, k, Cg, N, bm, bn);
     configure_ksplit(a, y_elems, bm, bn);
-    const CorrChoice c = choose_corr(a, k, d->fwd_tile, Cg, N, false, y_elems, w_elems, false, d->fwd_sp, d->fwd_sp_pack, d->fwd_sm[0]);
+    const CorrChoice c = choose_corr(a, k, d->fwd_tile, Cg, N, false, y_elems, w_elems, false, one_launch, d->fwd_sp, d->fwd_sp_pack, d->fwd_sm[0]);
     if (c.pack_bytes == 0) {
       delete d;
       return CONV_ESHAPE;
@@ -1638,7 +1639,7 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
     k.koff_invalid = koff_invalid(a.bounds_mode);
     configure_patch(a, k, Kg, N, bm, bn);
     configure_ksplit(a, x_elems, bm, bn);
-    const CorrChoice c = choose_corr(a, k, d->bwd_tile, Kg, N, true, x_elems, w_elems, d->bwd_zero_fill != 0, d->bwd_sp, d->bwd_sp_pack,
+    const CorrChoice c = choose_corr(a, k, d->bwd_tile, Kg, N, true, x_elems, w_elems, d->bwd_zero_fill != 0, one_launch, d->bwd_sp, d->bwd_sp_pack,
                                      d->bwd_sm[0]);
     if (c.pack_bytes == 0) {
       delete d;
@@ -1738,7 +1739,7 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
       return CONV_ESHAPE;
     }
     d->wg_split = configure_wgrad_split(a, d->wg_tile, N, K, w_elems, d->wg_sp);
-    d->wg_small[0] = d->wg_split >= 0 ? -1 : configure_wgrad_small(a, N, 4, bm, bn, d->wg_sm[0]);
+    d->wg_small[0] = d->wg_split >= 0 || !one_launch ? -1 : configure_wgrad_small(a, N, 4, bm, bn, d->wg_sm[0]);
     if (d->wg_split >= 0) {
       d->wg_ws = (size_t)d->wg_sp.S * (size_t)w_elems * 4;
       d->wgb_ws = (size_t)d->wg_sp.S * (size_t)(w_elems + d->wg_sp.n_tiles * K) * 4;
@@ -1786,7 +1787,7 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
       a.use_patch = 0;
       a.accumulate = 0;
       configure_ksplit(a, src.out_elems, bm64, bn64, 8);  // the same rule on this tile's grid (chunks are 16 k rows here too)
-      small = configure_corr_small(a, psrc, w_elems, src.out_elems, 8, corr64_model(a, bm64, bn64, src.out_elems), sm);
+      small = !one_launch ? -1 : configure_corr_small(a, psrc, w_elems, src.out_elems, 8, corr64_model(a, bm64, bn64, src.out_elems), sm);
       if (small < 0) plan_corr64(a, src.out_elems, tile_rows);
       a.simple_epilogue = src.simple_epilogue && 8 * (int64_t)src.out_elems <= ((int64_t)1 << 30);
       k = psrc;
@@ -1821,7 +1822,7 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
     a.S = (int32_t)ceil_div((int64_t)a.ncols > 0 ? a.ncols : 1, a.cols_per_split);
     if (a.S * w_elems >= max64 || tiles * a.S >= ((int64_t)1 << 31)) d->f64_ok = 0;
     d->wg64_ws = (size_t)a.S * (size_t)w_elems * 8;
-    d->wg_small[1] = configure_wgrad_small(a, N, 8, bm64, bn64, d->wg_sm[1]);
+    d->wg_small[1] = !one_launch ? -1 : configure_wgrad_small(a, N, 8, bm64, bn64, d->wg_sm[1]);
     d->bg64_ws = 2 * d->bg_ws;
     auto e64 = [](const CorrArgs& c) { return c.simple_epilogue ? 's' : 'p'; };
     snprintf(d->names64, sizeof(d->names64),
@@ -1954,6 +1955,10 @@ int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) {
   *out = d;
   return CONV_OK;
 }
+
+int conv_desc_create(conv_desc_t** out, const conv_params_t* pp) { return create_desc(out, pp, true); }
+
+int conv_desc_create_tiled(conv_desc_t** out, const conv_params_t* pp) { return create_desc(out, pp, false); }
 
 int conv_desc_destroy(conv_desc_t* d) {
   if (!d) return CONV_EINVAL;

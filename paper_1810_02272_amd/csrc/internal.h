@@ -503,3 +503,7 @@ struct conv_desc {
   mi355conv::WgradArgs wg64;
   size_t wg64_ws, bg64_ws, ws_bytes64;
 };
+
+// As conv_desc_create, with every pass on the kernels of larger layers, whatever the size: each variant of those can so be compared
+// with the oracle on a layer of a few milliseconds.  No part of the boundary: nothing but the tests calls it.
+extern "C" int conv_desc_create_tiled(conv_desc_t** out, const conv_params_t* params);

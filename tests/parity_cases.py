@@ -1,9 +1,33 @@
 """The parameter sets of the GPU parity tests, kept apart from the tests themselves so that a CPU-only
 test (test_variant_coverage.py) can ask the library which kernel variant each of them selects and
 check that every variant the library can select is run by some GPU test."""
+import ctypes
+
 import numpy as np
 
 import oracle
+import paper_1810_02272_amd as conv
+from paper_1810_02272_amd import binding
+
+
+def public_desc(pd):
+    return conv.conv_desc_create(conv.ConvParams(**pd))
+
+
+def tiled_desc(pd):
+    """A descriptor whose passes run the kernels of larger layers, whatever the size (conv_desc_create_tiled in
+    internal.h): the lists below reach the variants of those on layers so small that users get the one-launch kernels."""
+    lib, params = binding._load(), conv.ConvParams(**pd)
+    lib.conv_desc_create_tiled.argtypes, lib.conv_desc_create_tiled.restype = lib.conv_desc_create.argtypes, ctypes.c_int
+    c, out = binding._CParams(**pd), ctypes.c_void_p()
+    binding._check(lib.conv_desc_create_tiled(ctypes.byref(out), ctypes.byref(c)), "conv_desc_create_tiled")
+    return binding.ConvDesc(out.value, params)
+
+
+def descs(pd, names=conv.conv_desc_kernel_names):
+    """How a layer's parity is checked: as users get it and, where that differs, on the kernels of larger layers."""
+    public, tiled = public_desc(pd), tiled_desc(pd)
+    return [public] if names(public) == names(tiled) else [public, tiled]
 
 
 def P(n, c, h, w, k, kh, kw, sh=1, sw=1, ph=0, pw=0, dh=1, dw=1, g=1, bias=1):

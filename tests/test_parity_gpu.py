@@ -14,7 +14,7 @@ import oracle
 import paper_1810_02272_amd as conv
 from oracle import OracleParams
 from paper_1810_02272_amd import workloads
-from parity_cases import DIRECT_CASES, PATCH_CASES, SWEEP, VARIANT_CASES, P
+from parity_cases import DIRECT_CASES, PATCH_CASES, SWEEP, VARIANT_CASES, P, descs, public_desc, tiled_desc
 from parity_metric import gated_error, nerr
 
 pytestmark = pytest.mark.gpu
@@ -22,10 +22,10 @@ TOL = 1e-4
 DEV = "cuda:0"
 
 
-def run_all(pd: dict, x, w, b, dy, beta_check=True, poison=True):
+def run_all(pd: dict, x, w, b, dy, beta_check=True, poison=True, d=None):
     """Run the four passes on the GPU; returns (y, dx, dw, db) device tensors."""
     p = conv.ConvParams(**pd)
-    d = conv.conv_desc_create(p)
+    d = d or public_desc(pd)
     ws_bytes = conv.conv_desc_workspace_bytes(d)
     fill = float("nan") if poison else 0.0
     ws = torch.full((max(ws_bytes // 4, 1),), fill, device=DEV)
@@ -52,20 +52,24 @@ def check_full(pd: dict, seed: int, bias=True):
     op = OracleParams(**pd)
     xs, wsh, ys = oracle.x_shape(op), oracle.w_shape(op), oracle.output_shape(op)
     x, w, b, dy = workloads.random_inputs(xs, wsh, ys, seed, bias=bias)
-    d, ws, dev_in, (y, dx, dw, db) = run_all(pd, x, w, b, dy)
-    assert conv.conv_desc_output_shape(d) == ys
     xn, wn, dyn = x.numpy(), w.numpy(), dy.numpy()
     bn = b.numpy() if b is not None else None
-    refs = {"y": (y, oracle.forward(op, xn, wn, bn)), "dx": (dx, oracle.backward_data(op, wn, dyn)),
-            "dw": (dw, oracle.backward_filter(op, xn, dyn))}
+    refs = {"y": oracle.forward(op, xn, wn, bn), "dx": oracle.backward_data(op, wn, dyn),
+            "dw": oracle.backward_filter(op, xn, dyn)}
     if b is not None:
-        refs["db"] = (db, oracle.backward_bias(op, dyn))
-    errs = {k: gated_error(op, k, g, r, TOL, xn, wn, bn, dyn, case=pd) for k, (g, r) in refs.items()}
-    for k, v in errs.items():
-        assert np.isfinite(v) and v <= TOL, (pd, k, v, conv.conv_desc_kernel_names(d))
-    if b is not None:
-        check_filter_and_bias_in_one_pass(pd, op, d, ws, dev_in, dw, refs["db"][1], (xn, wn, bn, dyn))
-    return errs
+        refs["db"] = oracle.backward_bias(op, dyn)
+    first = None
+    for d in descs(pd):
+        d, ws, dev_in, out = run_all(pd, x, w, b, dy, d=d)
+        assert conv.conv_desc_output_shape(d) == ys
+        got = dict(zip(("y", "dx", "dw", "db"), out))
+        errs = {k: gated_error(op, k, got[k], r, TOL, xn, wn, bn, dyn, case=pd) for k, r in refs.items()}
+        for k, v in errs.items():
+            assert np.isfinite(v) and v <= TOL, (pd, k, v, conv.conv_desc_kernel_names(d))
+        if b is not None:
+            check_filter_and_bias_in_one_pass(pd, op, d, ws, dev_in, got["dw"], refs["db"], (xn, wn, bn, dyn))
+        first = first or errs
+    return first
 
 
 def check_filter_and_bias_in_one_pass(pd, op, d, ws, dev_in, dw, db_ref, host, beta=0.0, dw0=None, db0=None):
@@ -129,8 +133,7 @@ def test_thin_groups_blobs_not_16_byte_aligned():
 
 
 def selected(pd):
-    d = conv.conv_desc_create(conv.ConvParams(**pd))
-    return dict(kv.split("=", 1) for kv in conv.conv_desc_kernel_names(d).split(";"))
+    return dict(kv.split("=", 1) for kv in conv.conv_desc_kernel_names(tiled_desc(pd)).split(";"))
 
 
 @pytest.mark.parametrize("i", range(len(PATCH_CASES)))

@@ -44,10 +44,10 @@ def selected():
     for key, cases, names in (("fp32", pc.fp32_conv_cases(), conv.conv_desc_kernel_names),
                               ("fp64", pc.fp64_conv_cases(), conv.conv_desc_kernel_names_f64)):
         for pd in cases:
-            d = conv.conv_desc_create(conv.ConvParams(**pd))
-            for which, v in fields(names(d)).items():
-                variant, splits = split_variant(v)
-                out[key].setdefault(which, {}).setdefault(variant, set()).add(splits > 1)
+            for d in pc.descs(pd, names):  # both are compared with the oracle
+                for which, v in fields(names(d)).items():
+                    variant, splits = split_variant(v)
+                    out[key].setdefault(which, {}).setdefault(variant, set()).add(splits > 1)
     return out
 
 
