@@ -779,6 +779,9 @@ int32_t configure_wgrad_split(const WgradArgs& w, int32_t fp32_tile, int64_t N, 
   return best;
 }
 
+// The launch that clears dx where no tap reaches some of it, whatever kernel runs the rest (us; dx in MB): a fit to 1300 such passes.
+double zero_fill_model(bool zero_fill, double out_mb) { return zero_fill ? 2.7 + 0.15 * out_mb : 0.0; }
+
 // Modelled time (us) of a forward or backward-data pass on the tiled fp32 kernels: the launches, packed weights (MB), partial
 // sums and output (MB), then per tile the chunks of 16 reduction indices that one workgroup walks alone and those that the
 // workgroups of a compute unit share, dearer where the gather compares or masks.  A fit to 8653 timings -- every tile, 1 to 16
@@ -795,7 +798,7 @@ double corr_model(const CorrArgs& a, int32_t tile, int64_t S, int64_t out_elems,
   const int64_t chunks = ceil_div(all, S), slices = ceil_div(all, chunks), per_cu = ceil_div(units * slices, 256);
   const double out_mb = 4e-6 * (double)out_elems, pack_mb = 4e-6 * (double)a.G * (double)round_up(a.Mrows, bm) * (double)(16 * all);
   const double shared = c[1] + (a.bounds_mode == 1 ? c[2] : a.bounds_mode == 2 ? c[3] : 0.0) + (tile == CORR_16x64 ? 0.09 / (double)chunks : 0.0);
-  return 5.5 + 0.3 * pack_mb + 0.25 * out_mb + (zero_fill ? 2.4 : 0.0) + (slices > 1 ? 2.2 + 0.7 * (double)slices * out_mb : 0.0) +
+  return 5.5 + 0.3 * pack_mb + 0.25 * out_mb + zero_fill_model(zero_fill, out_mb) + (slices > 1 ? 2.2 + 0.7 * (double)slices * out_mb : 0.0) +
          (double)chunks * (c[0] + (double)per_cu * shared);
 }
 
@@ -846,12 +849,12 @@ struct SmallCost {
 
 // The same for a pass on the tiled kernels of doubles as configure_ksplit slices them (tiles of bm x bn), a fit to 123 passes
 // (rms error 6 %).
-double corr64_model(const CorrArgs& a, int32_t bm, int32_t bn, int64_t out_elems) {
+double corr64_model(const CorrArgs& a, int32_t bm, int32_t bn, int64_t out_elems, bool zero_fill) {
   const int64_t chunks = ceil_div(ceil_div(a.Kred, 16), a.ksplit);
   const int64_t per_cu = ceil_div((int64_t)a.G * a.m_tiles * a.col_tiles * a.ksplit, 256);
   const double area = (double)(bm * bn) / 4096.0, out_mb = 8e-6 * (double)out_elems;
   return 5.7 + (a.ksplit > 1 ? 2.3 + 0.64 * a.ksplit * out_mb : 0.0) + (double)chunks * (0.17 + 0.413 * area) +
-         (double)(per_cu * chunks) * (0.090 + 0.198 * area) + 0.31 * out_mb;
+         (double)(per_cu * chunks) * (0.090 + 0.198 * area) + 0.31 * out_mb + zero_fill_model(zero_fill, out_mb);
 }
 
 // Tile and slices of the fp64 kernel where another choice is modelled at least 8 % ahead, from 0.05 to 6 GFLOP.  The model is a fit
@@ -907,8 +910,8 @@ bool small_keeps_tiles(int64_t ncols, int64_t kred, int32_t elem_bytes) {
 
 // Decides whether corr_small_kernel runs this correlation instead of the launches of `base`, which are modelled to take `old`
 // us; fills a and returns its tile, -1 if it does not.
-int32_t configure_corr_small(const CorrArgs& base, const PackArgs& k, int64_t w_elems, int64_t out_elems, int32_t elem_bytes,
-                             double old, CorrSmallArgs& a) {
+int32_t configure_corr_small(const CorrArgs& base, const PackArgs& k, int64_t w_elems, int64_t out_elems, bool zero_fill,
+                             int32_t elem_bytes, double old, CorrSmallArgs& a) {
   const int64_t limit = (int64_t)1 << 30, TH = base.THW / base.TW;
   // Not measured: layers with a stride and a dilation, and what the patch-staged kernel takes.
   if (base.use_patch || (base.sh * base.sw > 1 && base.dh * base.dw > 1)) return -1;
@@ -970,7 +973,7 @@ int32_t configure_corr_small(const CorrArgs& base, const PackArgs& k, int64_t w_
     if (c.shared == 0) continue;  // no instance
     const int64_t units = (int64_t)a.G * ceil_div(a.Mrows, 16 * s.mb) * ceil_div(a.ncols, 16 * s.nb), per_cu = ceil_div(units, 256);
     const double cost =
-        3.0 + strided * (c.chain * (double)ceil_div(groups, s.waves) + (c.shared * (double)groups + c.workgroup) * (double)per_cu);
+        3.0 + zero_fill_model(zero_fill, 1e-6 * elem_bytes * (double)out_elems) + strided * (c.chain * (double)ceil_div(groups, s.waves) + (c.shared * (double)groups + c.workgroup) * (double)per_cu);
     if (best < 0 || cost < here) {
       best = t;
       here = cost;
@@ -1015,7 +1018,7 @@ CorrChoice choose_corr(CorrArgs& a, PackArgs& k, int32_t& tile, int64_t cg_in, i
     const double thin = 4.2 + (double)steps * (compares ? 0.86 : 0.37) +
                         (double)per_cu * (0.56 + (double)steps * (0.0385 * a.Mrows + (compares ? 0.045 : 0.0)));
     const double here = corr_model(tiled, t, tiled.ksplit, out_elems, zero_fill);
-    c.small = configure_corr_small(tiled, tiled_pack, w_elems, out_elems, 4, here < thin ? here : thin, small);
+    c.small = configure_corr_small(tiled, tiled_pack, w_elems, out_elems, zero_fill, 4, here < thin ? here : thin, small);
     if (c.small >= 0 || here < 0.9 * thin) {
       c.thin = 0;
       a = tiled;
@@ -1031,7 +1034,7 @@ CorrChoice choose_corr(CorrArgs& a, PackArgs& k, int32_t& tile, int64_t cg_in, i
   }
   plan_corr(a, k, out_elems, zero_fill, tile);
   c.pack_bytes = (size_t)a.G * (size_t)a.KP * (size_t)a.MP * 4 + (size_t)a.KP * sizeof(KTabEntry);
-  if (one_launch) c.small = configure_corr_small(a, k, w_elems, out_elems, 4, corr_model(a, tile, a.ksplit, out_elems, zero_fill), small);
+  if (one_launch) c.small = configure_corr_small(a, k, w_elems, out_elems, zero_fill, 4, corr_model(a, tile, a.ksplit, out_elems, zero_fill), small);
   return c;
 }
 
@@ -1775,7 +1778,7 @@ static int create_desc(conv_desc_t** out, const conv_params_t* pp, bool one_laun
     const int64_t max64 = (int64_t)1 << 29;  // 32-bit byte offsets of 8-byte elements
     d->f64_ok = x_elems < max64 && y_elems < max64 && w_elems < max64;
     auto corr64 = [&](const CorrArgs& src, const PackArgs& psrc, CorrArgs& a, PackArgs& k, int64_t in_elems,
-                      size_t& ws, int32_t& tile_rows, int32_t& small, CorrSmallArgs& sm) {
+                      bool zero_fill, size_t& ws, int32_t& tile_rows, int32_t& small, CorrSmallArgs& sm) {
       a = src;
       const int32_t bm64 = tile_rows = f64_pick_rows(src.Mrows, false);
       a.in_bytes = (uint32_t)(8 * in_elems);
@@ -1787,7 +1790,8 @@ static int create_desc(conv_desc_t** out, const conv_params_t* pp, bool one_laun
       a.use_patch = 0;
       a.accumulate = 0;
       configure_ksplit(a, src.out_elems, bm64, bn64, 8);  // the same rule on this tile's grid (chunks are 16 k rows here too)
-      small = !one_launch ? -1 : configure_corr_small(a, psrc, w_elems, src.out_elems, 8, corr64_model(a, bm64, bn64, src.out_elems), sm);
+      small = !one_launch ? -1 : configure_corr_small(a, psrc, w_elems, src.out_elems, zero_fill, 8,
+                                                        corr64_model(a, bm64, bn64, src.out_elems, zero_fill), sm);
       if (small < 0) plan_corr64(a, src.out_elems, tile_rows);
       a.simple_epilogue = src.simple_epilogue && 8 * (int64_t)src.out_elems <= ((int64_t)1 << 30);
       k = psrc;
@@ -1800,8 +1804,8 @@ static int create_desc(conv_desc_t** out, const conv_params_t* pp, bool one_laun
       ws = (size_t)pack_elems * 8 + (size_t)a.KP * sizeof(KTabEntry) +
            (a.ksplit > 1 ? (size_t)a.ksplit * (size_t)src.out_elems * 8 : 0);
     };
-    corr64(d->fwd, d->fwd_pack, d->fwd64, d->fwd64_pack, x_elems, d->fwd64_ws, d->fwd64_rows, d->fwd_small[1], d->fwd_sm[1]);
-    corr64(d->bwd, d->bwd_pack, d->bwd64, d->bwd64_pack, y_elems, d->bwd64_ws, d->bwd64_rows, d->bwd_small[1], d->bwd_sm[1]);
+    corr64(d->fwd, d->fwd_pack, d->fwd64, d->fwd64_pack, x_elems, false, d->fwd64_ws, d->fwd64_rows, d->fwd_small[1], d->fwd_sm[1]);
+    corr64(d->bwd, d->bwd_pack, d->bwd64, d->bwd64_pack, y_elems, d->bwd_zero_fill != 0, d->bwd64_ws, d->bwd64_rows, d->bwd_small[1], d->bwd_sm[1]);
     const int32_t bm64 = d->wg64_rows = f64_pick_rows(Kg, true);
     WgradArgs& a = d->wg64;
     a = d->wg;

@@ -1,0 +1,22 @@
+"""Layers on which a rule once chose the slower kernel.  Each with the pass, what it has to run on and both times (us); on the CPU, as
+descriptors name their kernels without a device."""
+import pytest
+
+import paper_1810_02272_amd as conv
+from parity_cases import P
+
+CASES = {
+    # the launch that clears dx belongs to either kernel's time
+    "zero_fill_counts_on_both_sides": [
+        (P(12, 125, 56, 56, 27, 1, 7, 3, 3), "f32", "bwd_data", "corr_m", (18.6, 23.0)),
+    ],
+}
+
+
+@pytest.mark.parametrize("rule", list(CASES))
+def test_the_faster_kernel_is_chosen(rule):
+    for pd, base, which, prefix, times in CASES[rule]:
+        d = conv.conv_desc_create(conv.ConvParams(**pd))
+        names = conv.conv_desc_kernel_names(d) if base == "f32" else conv.conv_desc_kernel_names_f64(d)
+        got = dict(kv.split("=", 1) for kv in names.split(";"))[which]
+        assert got.startswith(prefix), (pd, base, which, got, "should take %.1f us, not %.1f" % times)
