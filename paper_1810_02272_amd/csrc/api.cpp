@@ -847,14 +847,22 @@ struct SmallCost {
   double chain, shared, workgroup;
 };
 
-// The same for a pass on the tiled kernels of doubles as configure_ksplit slices them (tiles of bm x bn), a fit to 123 passes
-// (rms error 6 %).
-double corr64_model(const CorrArgs& a, int32_t bm, int32_t bn, int64_t out_elems, bool zero_fill) {
-  const int64_t chunks = ceil_div(ceil_div(a.Kred, 16), a.ksplit);
-  const int64_t per_cu = ceil_div((int64_t)a.G * a.m_tiles * a.col_tiles * a.ksplit, 256);
-  const double area = (double)(bm * bn) / 4096.0, out_mb = 8e-6 * (double)out_elems;
-  return 5.7 + (a.ksplit > 1 ? 2.3 + 0.64 * a.ksplit * out_mb : 0.0) + (double)chunks * (0.17 + 0.413 * area) +
-         (double)(per_cu * chunks) * (0.090 + 0.198 * area) + 0.31 * out_mb + zero_fill_model(zero_fill, out_mb);
+// The same for a pass on the tiled kernels of doubles, as planned, on tiles of `rows`: launches, packed weights, partial sums and output
+// (MB), then per tile the chunks that one workgroup walks alone, those that the workgroups of a compute unit share, and these
+// workgroups; a forward pass 3 % less, backward data 4 % more.  A fit to 12665 timings of up to 6 GFLOP -- every tile, 1 to 16 slices; 6
+// to 8 % off (rms) from the smallest to the largest, on 16796 others as well.
+double corr64_model(const CorrArgs& a, int32_t rows, int64_t out_elems, bool backward, bool zero_fill) {
+  static const struct {
+    int32_t rows;
+    double alone, shared, workgroup;
+  } kCost[] = {{16, 0.266, 0.138, 0.494}, {32, 0.318, 0.222, 0.666}, {48, 0.360, 0.326, 0.866}, {64, 0.405, 0.444, 1.062}, {96, 0.497, 0.679, 1.683}};
+  int t = 0;
+  while (kCost[t].rows != rows) ++t;
+  const double per_cu = (double)ceil_div((int64_t)a.G * a.m_tiles * a.col_tiles * a.ksplit, 256);
+  const double out_mb = 8e-6 * (double)out_elems, pack_mb = 8e-6 * (double)a.G * (double)a.MP * (double)a.KP;
+  const double rest = 5.97 + 0.544 * pack_mb + 0.073 * out_mb + (a.ksplit > 1 ? 2.27 + 0.363 * a.ksplit * out_mb : 0.0) +
+                      (double)a.chunks_per_split * (kCost[t].alone + kCost[t].shared * per_cu) + kCost[t].workgroup * per_cu;
+  return (backward ? 1.04 : 0.97) * rest + zero_fill_model(zero_fill, out_mb);
 }
 
 // Tile and slices of the fp64 kernel where another choice is modelled at least 8 % ahead, from 0.05 to 6 GFLOP.  The model is a fit
@@ -983,7 +991,15 @@ int32_t configure_corr_small(const CorrArgs& base, const PackArgs& k, int64_t w_
   // the fit none is more than 3 % slower, 1.46 times as fast in the geometric mean over all; doubles (123) 1.42 times, two
   // more than 3 % slower.
   const double flops = 2.0 * base.Mrows * base.Kred * (double)base.ncols * base.G;
-  if (flops > (elem_bytes == 8 ? 1e9 : 1.5e9) || here > (flops < 0.7e9 ? 0.9 : 0.75) * old) return -1;
+  double margin = flops < 0.7e9 ? 0.9 : 0.75;
+  if (elem_bytes == 8) {
+    // Nearer to the time of the tile chosen: rows past the last load no weights (rms error 8 to 11 %, 10 to 16 % without)
+    const int32_t rows = 16 * kCorrSmallTiles[best].mb;
+    const double fill = (double)a.Mrows / (double)round_up(a.Mrows, rows), launches = 3.0 + zero_fill_model(zero_fill, 8e-6 * (double)out_elems);
+    here = launches + 0.15 + (here - launches) * (a.wmode == 0 ? 0.79 + 0.28 * fill : 0.92 + 0.16 * fill);
+    margin = 0.95;
+  }
+  if (flops > (elem_bytes == 8 ? 1e9 : 1.5e9) || here > margin * old) return -1;
   a.m_tiles = (int32_t)ceil_div(a.Mrows, 16 * kCorrSmallTiles[best].mb);
   a.col_tiles = (int32_t)ceil_div(a.ncols, 16 * kCorrSmallTiles[best].nb);
   if ((int64_t)a.G * a.m_tiles * a.col_tiles >= ((int64_t)1 << 31)) return -1;
@@ -1790,9 +1806,10 @@ static int create_desc(conv_desc_t** out, const conv_params_t* pp, bool one_laun
       a.use_patch = 0;
       a.accumulate = 0;
       configure_ksplit(a, src.out_elems, bm64, bn64, 8);  // the same rule on this tile's grid (chunks are 16 k rows here too)
-      small = !one_launch ? -1 : configure_corr_small(a, psrc, w_elems, src.out_elems, zero_fill, 8,
-                                                        corr64_model(a, bm64, bn64, src.out_elems, zero_fill), sm);
-      if (small < 0) plan_corr64(a, src.out_elems, tile_rows);
+      plan_corr64(a, src.out_elems, tile_rows);
+      small = -1;
+      if (one_launch)
+        small = configure_corr_small(a, psrc, w_elems, src.out_elems, zero_fill, 8, corr64_model(a, tile_rows, src.out_elems, psrc.mode != 0, zero_fill), sm);
       a.simple_epilogue = src.simple_epilogue && 8 * (int64_t)src.out_elems <= ((int64_t)1 << 30);
       k = psrc;
       k.KP = a.KP;

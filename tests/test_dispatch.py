@@ -10,6 +10,12 @@ CASES = {
     "zero_fill_counts_on_both_sides": [
         (P(12, 125, 56, 56, 27, 1, 7, 3, 3), "f32", "bwd_data", "corr_m", (18.6, 23.0)),
     ],
+    # doubles: one launch against the tiles as they are planned, not as the rules would have them (95.6 and 28.5 us)
+    "doubles_are_planned_before_they_are_compared": [
+        (P(127, 2, 12, 12, 324, 3, 3, 1, 1, 1, 0), "f64", "bwd_data", "corr64_16x64x16[es](S=8,", (52.6, 77.9)),
+        (P(9, 54, 19, 24, 91, 8, 8, 4, 4, 0, 1), "f64", "fwd", "corr64_16x64x16[es](S=12,", (19.3, 27.6)),
+        (P(12, 111, 12, 12, 88, 7, 7, 2, 2), "f64", "fwd", "corr64_16x64x16[es](S=16,", (20.1, 27.2)),
+    ],
 }
 
 
