@@ -841,6 +841,25 @@ void plan_corr(CorrArgs& a, PackArgs& k, int64_t out_elems, bool zero_fill, int3
   a.ksplit = (int32_t)ceil_div(all, a.chunks_per_split);
 }
 
+// The time of a pass on the tiled fp32 kernels, as planned, against which the one-launch kernel is held.  Below 0.7 GFLOP corr_model is 8
+// to 17 % short of it; a fit of its own to 51740 timings -- every tile, 1 to 16 slices -- is 5 to 10 % off (rms) on 19000 others.  20 -> 50
+// channels, 5x5 at 12x12, batch 64, backward data: 23.7 us on the tiles, 23.6 here, 21.7 by corr_model; 19.5 in one launch.
+double tiled_time(const CorrArgs& a, int32_t tile, int64_t out_elems, bool backward, bool zero_fill) {
+  static const double kCost[CORR_TILE_COUNT][5] = {  // alone, shared, with compares, with masks, workgroup
+      {0.397, 0.599, 0.186, 0.145, 2.023}, {0.294, 0.263, 0.108, 0.111, 1.164}, {0.448, 0.334, 0.234, 0.167, 2.082},
+      {0.338, 0.261, 0.155, 0.114, 1.092}, {0.286, 0.105, 0.104, 0.093, 0.532}, {0.426, 0.151, 0.357, 0.219, 1.605},
+      {0.319, 0.078, 0.186, 0.135, 0.617}, {0.311, 0.458, 0.355, 0.229, 2.052}, {0.262, 0.142, 0.217, 0.154, 0.946},
+      {0.267, 0.142, 0.286, 0.165, 1.037}, {0.236, 0.012, 0.067, 0.056, 0.255}};
+  if (2.0 * a.Mrows * a.Kred * (double)a.ncols * a.G >= 0.7e9) return corr_model(a, tile, a.ksplit, out_elems, zero_fill);
+  const double* const c = kCost[tile];
+  const double per_cu = (double)ceil_div((int64_t)a.G * a.m_tiles * a.col_tiles * a.ksplit, 256);
+  const double out_mb = 4e-6 * (double)out_elems, pack_mb = 4e-6 * (double)a.G * (double)a.MP * (double)a.KP;
+  const double shared = c[1] + (a.bounds_mode == 1 ? c[2] : a.bounds_mode == 2 ? c[3] : 0.0);
+  const double rest = 6.07 + 0.787 * pack_mb + 0.096 * out_mb + (a.ksplit > 1 ? 2.33 + 0.608 * a.ksplit * out_mb : 0.0) +
+                      (double)a.chunks_per_split * (c[0] + per_cu * shared) + per_cu * c[4];
+  return (backward ? 1.05 : 0.98) * rest + zero_fill_model(zero_fill, out_mb);
+}
+
 // Modelled times (us) of the one-launch kernels: a launch; then per tile the wave's chain of reduction groups (blocks of 64
 // places in the filter gradient), the groups that a compute unit's workgroups share, and those workgroups.
 struct SmallCost {
@@ -987,18 +1006,16 @@ int32_t configure_corr_small(const CorrArgs& base, const PackArgs& k, int64_t w_
       here = cost;
     }
   }
-  // Beyond 0.7 GFLOP a miss costs more than a launch gains, hence the second margin.  Of 203 passes of floats that were not in
-  // the fit none is more than 3 % slower, 1.46 times as fast in the geometric mean over all; doubles (123) 1.42 times, two
-  // more than 3 % slower.
   const double flops = 2.0 * base.Mrows * base.Kred * (double)base.ncols * base.G;
-  double margin = flops < 0.7e9 ? 0.9 : 0.75;
-  if (elem_bytes == 8) {
-    // Nearer to the time of the tile chosen: rows past the last load no weights (rms error 8 to 11 %, 10 to 16 % without)
-    const int32_t rows = 16 * kCorrSmallTiles[best].mb;
-    const double fill = (double)a.Mrows / (double)round_up(a.Mrows, rows), launches = 3.0 + zero_fill_model(zero_fill, 8e-6 * (double)out_elems);
-    here = launches + 0.15 + (here - launches) * (a.wmode == 0 ? 0.79 + 0.28 * fill : 0.92 + 0.16 * fill);
-    margin = 0.95;
-  }
+  // Nearer to the time of the tile chosen: rows past the last load no weights, and rows of 64 taps, or 16, meet in the caches where they are
+  // read by single loads (rms errors 9 to 11 %, floats with such loads 14; without this 10 to 17).
+  static const double kNear[2][4][2] = {{{0.86, 0.22}, {0.71, 0.17}, {0.88, 0.27}, {0.93, 0.07}}, {{0.79, 0.28}, {0.90, 0.17}, {0.90, 0.17}, {0.94, 0.15}}};
+  const double* const near = kNear[elem_bytes == 8][a.wmode];
+  const double fill = (double)a.Mrows / (double)round_up(a.Mrows, 16 * kCorrSmallTiles[best].mb);
+  const double meet = elem_bytes == 4 && a.wmode == 2 ? (T % 64 == 0 ? 0.19 : T % 16 == 0 ? 0.07 : 0.0) : 0.0;
+  const double launches = 3.0 + zero_fill_model(zero_fill, 1e-6 * elem_bytes * (double)out_elems);
+  here = launches + 0.15 + (here - launches) * (near[0] + near[1] * fill + meet);
+  const double margin = elem_bytes == 4 && flops >= 0.7e9 ? 0.9 : 0.95;
   if (flops > (elem_bytes == 8 ? 1e9 : 1.5e9) || here > margin * old) return -1;
   a.m_tiles = (int32_t)ceil_div(a.Mrows, 16 * kCorrSmallTiles[best].mb);
   a.col_tiles = (int32_t)ceil_div(a.ncols, 16 * kCorrSmallTiles[best].nb);
@@ -1050,7 +1067,7 @@ CorrChoice choose_corr(CorrArgs& a, PackArgs& k, int32_t& tile, int64_t cg_in, i
   }
   plan_corr(a, k, out_elems, zero_fill, tile);
   c.pack_bytes = (size_t)a.G * (size_t)a.KP * (size_t)a.MP * 4 + (size_t)a.KP * sizeof(KTabEntry);
-  if (one_launch) c.small = configure_corr_small(a, k, w_elems, out_elems, zero_fill, 4, corr_model(a, tile, a.ksplit, out_elems, zero_fill), small);
+  if (one_launch) c.small = configure_corr_small(a, k, w_elems, out_elems, zero_fill, 4, tiled_time(a, tile, out_elems, backward, zero_fill), small);
   return c;
 }
 

@@ -14,7 +14,11 @@ CASES = {
     "doubles_are_planned_before_they_are_compared": [
         (P(127, 2, 12, 12, 324, 3, 3, 1, 1, 1, 0), "f64", "bwd_data", "corr64_16x64x16[es](S=8,", (52.6, 77.9)),
         (P(9, 54, 19, 24, 91, 8, 8, 4, 4, 0, 1), "f64", "fwd", "corr64_16x64x16[es](S=12,", (19.3, 27.6)),
-        (P(12, 111, 12, 12, 88, 7, 7, 2, 2), "f64", "fwd", "corr64_16x64x16[es](S=16,", (20.1, 27.2)),
+    ],
+    # below 0.7 GFLOP the tiled kernels' time is modelled in their own range: packing and reducing are most of such a pass
+    "small_passes_are_modelled_in_their_range": [
+        (P(64, 20, 12, 12, 50, 5, 5), "f32", "bwd_data", "corrsmall_32x16x4[w3]", (19.5, 23.7)),
+        (P(64, 20, 12, 12, 50, 5, 5), "f32", "fwd", "corrsmall_32x16x4[w0]", (7.0, 14.0)),
     ],
 }
 
