@@ -807,7 +807,7 @@ double corr_model(const CorrArgs& a, int32_t tile, int64_t S, int64_t out_elems,
 // 12 slices 61; 236 -> 300 in four groups, 3x5, stride 2: 16x64 162, 32x128 94.  Of 152 passes of the fit that these kernels
 // took, none was on the tiles of at most 48 rows by 256 columns that the patch-staged kernel takes (left alone); the
 // choice is 11 % faster than the rules' in the geometric mean, up to twice, and 2 % behind the best.  Smaller passes keep the
-// rules (pick_corr_tile, configure_ksplit): their times differ little, and each variant has its parity case there.
+// rules (pick_corr_tile, configure_ksplit): where the tiles run them at all, the times of the choice differ by 3 % (4 from 0.05 GFLOP on).
 void plan_corr(CorrArgs& a, PackArgs& k, int64_t out_elems, bool zero_fill, int32_t& tile) {
   const double flops = 2.0 * a.Mrows * a.Kred * (double)a.ncols * a.G;
   if (a.use_patch || a.ncols < 1 || flops < 2e8) return;
@@ -928,21 +928,13 @@ void plan_corr64(CorrArgs& a, int64_t out_elems, int32_t& rows) {
   a.ksplit = (int32_t)ceil_div(all, a.chunks_per_split);
 }
 
-// Sizes at which the tiled kernels stay although they are slower there (4 to 8 us a pass against 3.5 to 6): fewer columns
-// than two blocks, and reductions under three groups over 512 columns or more.  They are where every variant of a
-// tiled kernel can be compared with the oracle in milliseconds, which larger layers need as much as before.
-bool small_keeps_tiles(int64_t ncols, int64_t kred, int32_t elem_bytes) {
-  return ncols < 32 || (kred < 48 && (ncols >= 512 || elem_bytes == 8));
-}
-
 // Decides whether corr_small_kernel runs this correlation instead of the launches of `base`, which are modelled to take `old`
 // us; fills a and returns its tile, -1 if it does not.
 int32_t configure_corr_small(const CorrArgs& base, const PackArgs& k, int64_t w_elems, int64_t out_elems, bool zero_fill,
                              int32_t elem_bytes, double old, CorrSmallArgs& a) {
   const int64_t limit = (int64_t)1 << 30, TH = base.THW / base.TW;
-  // Not measured: layers with a stride and a dilation, and what the patch-staged kernel takes.
+  // Not measured: forward passes of layers with a stride and a dilation, and what the patch-staged kernel takes.
   if (base.use_patch || (base.sh * base.sw > 1 && base.dh * base.dw > 1)) return -1;
-  if (small_keeps_tiles(base.ncols, base.Kred, elem_bytes)) return -1;
   if (base.ncols < 1 || (int64_t)base.in_bytes > limit || elem_bytes * w_elems > limit || elem_bytes * out_elems > limit) return -1;
   // the kernel's packed displacements, and the row that stands for "past the reduction"
   if (base.IH > 16384 || base.IW > 16384 || base.ph > 4096 || base.pw > 4096) return -1;
@@ -1037,20 +1029,17 @@ CorrChoice choose_corr(CorrArgs& a, PackArgs& k, int32_t& tile, int64_t cg_in, i
   c.thin = configure_thin(a, k, cg_in, n_img, backward);
   const int64_t pack_elems = (int64_t)a.G * a.KP * a.MP;
   if (pack_elems >= kMaxElems || (int64_t)a.G * a.m_tiles * a.col_tiles >= ((int64_t)1 << 31)) return c;
-  const int64_t steps = ceil_div(2 * ceil_div(a.Kred, 16), 4);
-  if (c.thin && !a.use_patch && one_launch && steps >= 12) {
+  if (c.thin && !a.use_patch && one_launch) {
     // Without LDS staging a thin-row workgroup walks its reduction in dependent steps of eight indices a wave: 4 -> 384
     // channels, 5x3 at 15x15, batch 4, 118 us, in one launch 15; 2 -> 30, 11x11 at 24x24, 128 and 14; 1 -> 82, 7x7, batch 8,
-    // 127 and 32 on 16-row tiles in 16 slices.  Modelled by a fit to 54 passes (rms error 10 %); of the 33 with reductions
-    // of 128 and more the choice is 2.1 times as fast in the geometric mean, none slower.  Reductions under a dozen steps
-    // take 5 to 9 us here and 4 to 6 there: they stay, with the parity cases of every row count and bounds mode.
+    // 127 and 32 on 16-row tiles in 16 slices.  And its weights are packed by a launch of their own: of 1600 passes under 5 MFLOP nearly
+    // all are ahead in one launch, 1.8 times in the geometric mean.  A fit to 4800 passes (rms error 13 to 16 %).
+    const int64_t steps = ceil_div(2 * ceil_div(a.Kred, 16), 4), per_cu = ceil_div((int64_t)a.G * ceil_div(a.ncols, 64), 256);
     int32_t t = tile;
     plan_corr(tiled, tiled_pack, out_elems, zero_fill, t);
-    const int64_t per_cu = ceil_div((int64_t)a.G * ceil_div(a.ncols, 64), 256);
-    const bool compares = a.bounds_mode == 1;
-    const double thin = 4.2 + (double)steps * (compares ? 0.86 : 0.37) +
-                        (double)per_cu * (0.56 + (double)steps * (0.0385 * a.Mrows + (compares ? 0.045 : 0.0)));
-    const double here = corr_model(tiled, t, tiled.ksplit, out_elems, zero_fill);
+    const double thin = 5.7 + 4e-6 * 0.75 * (double)out_elems +
+                        (double)steps * (0.383 + (a.bounds_mode == 1 ? 0.619 : 0.0) + 0.0389 * (double)per_cu * a.Mrows);
+    const double here = tiled_time(tiled, t, out_elems, backward, zero_fill);
     c.small = configure_corr_small(tiled, tiled_pack, w_elems, out_elems, zero_fill, 4, here < thin ? here : thin, small);
     if (c.small >= 0 || here < 0.9 * thin) {
       c.thin = 0;
@@ -1075,8 +1064,7 @@ CorrChoice choose_corr(CorrArgs& a, PackArgs& k, int32_t& tile, int64_t cg_in, i
 // 32 columns); fills a and returns its tile, -1 if it does not.
 int32_t configure_wgrad_small(const WgradArgs& w, int64_t N, int32_t elem_bytes, int32_t bm, int32_t bn, WgradSmallArgs& a) {
   const int64_t limit = (int64_t)1 << 30, TH = w.khw / w.kw;
-  // Not measured: layers with a stride and a dilation.  Fewer places than one block: see small_keeps_tiles (128x128 tile).
-  if ((w.sh * w.sw > 1 && w.dh * w.dw > 1) || w.ncols < 64) return -1;
+  if (w.sh * w.sw > 1 && w.dh * w.dw > 1) return -1;  // not measured: layers with a stride and a dilation
   if (w.ncols < 1 || (int64_t)w.x_bytes > limit || (int64_t)w.dy_bytes > limit) return -1;
   if (w.H > 16384 || w.W > 16384 || w.ph > 4096 || w.pw > 4096) return -1;  // packed into 16 bits
   if ((TH - 1) * w.dh > 8192 || (int64_t)(w.kw - 1) * w.dw > 8192) return -1;

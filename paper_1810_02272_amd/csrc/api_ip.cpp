@@ -43,7 +43,7 @@ std::string field(const char* names, const char* key) {
 
 extern "C" {
 
-int ip_desc_create(ip_desc_t** out, const ip_params_t* pp) {
+static int create_desc(ip_desc_t** out, const ip_params_t* pp, int (*conv_create)(conv_desc_t**, const conv_params_t*)) {
   if (!out || !pp) return CONV_EINVAL;
   const ip_params_t p = *pp;
   if (p.m < 0 || p.k < 1 || p.num_output < 1) return CONV_EINVAL;
@@ -63,7 +63,7 @@ int ip_desc_create(ip_desc_t** out, const ip_params_t* pp) {
     c.num_output = p.m;
     c.kernel_h = c.kernel_w = c.stride_h = c.stride_w = c.dilation_h = c.dilation_w = c.group = 1;
     c.bias_term = 0;
-    const int rc = conv_desc_create(&d->inner, &c);
+    const int rc = conv_create(&d->inner, &c);
     if (rc != CONV_OK) {
       delete d;
       return rc;
@@ -78,7 +78,7 @@ int ip_desc_create(ip_desc_t** out, const ip_params_t* pp) {
       c.c = p.k;
       c.w = 1;
       size_t need = 0;
-      if (conv_desc_create(&d->fwd, &c) == CONV_OK) need = forward_transposed_workspace_bytes(d->fwd);
+      if (conv_create(&d->fwd, &c) == CONV_OK) need = forward_transposed_workspace_bytes(d->fwd);
       if (need == 0 && d->fwd) {
         conv_desc_destroy(d->fwd);
         d->fwd = nullptr;
@@ -113,6 +113,10 @@ int ip_desc_create(ip_desc_t** out, const ip_params_t* pp) {
   *out = d;
   return CONV_OK;
 }
+
+int ip_desc_create(ip_desc_t** out, const ip_params_t* pp) { return create_desc(out, pp, &conv_desc_create); }
+
+int ip_desc_create_tiled(ip_desc_t** out, const ip_params_t* pp) { return create_desc(out, pp, &conv_desc_create_tiled); }
 
 int ip_desc_destroy(ip_desc_t* d) {
   if (!d) return CONV_EINVAL;

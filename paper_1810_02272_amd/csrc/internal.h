@@ -504,6 +504,6 @@ struct conv_desc {
   size_t wg64_ws, bg64_ws, ws_bytes64;
 };
 
-// As conv_desc_create, with every pass on the kernels of larger layers, whatever the size: each variant of those can so be compared
-// with the oracle on a layer of a few milliseconds.  No part of the boundary: nothing but the tests calls it.
+// As conv_desc_create (and ip_desc_create, in api_ip.cpp), with every pass on the kernels of larger layers, whatever the size: each variant of those can so be
+// compared with the oracle on a layer of a few milliseconds.  No part of the boundary: nothing but the tests calls them.
 extern "C" int conv_desc_create_tiled(conv_desc_t** out, const conv_params_t* params);

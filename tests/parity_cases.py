@@ -7,7 +7,7 @@ import numpy as np
 
 import oracle
 import paper_1810_02272_amd as conv
-from paper_1810_02272_amd import binding
+from paper_1810_02272_amd import binding, ip_binding
 
 
 def public_desc(pd):
@@ -22,6 +22,16 @@ def tiled_desc(pd):
     c, out = binding._CParams(**pd), ctypes.c_void_p()
     binding._check(lib.conv_desc_create_tiled(ctypes.byref(out), ctypes.byref(c)), "conv_desc_create_tiled")
     return binding.ConvDesc(out.value, params)
+
+
+def ip_descs(pd):
+    """The same for an InnerProduct layer: as users get it and, where that differs, on the kernels of larger layers."""
+    lib, params = ip_binding._load(), conv.IpParams(**pd)
+    lib.ip_desc_create_tiled.argtypes, lib.ip_desc_create_tiled.restype = lib.ip_desc_create.argtypes, ctypes.c_int
+    c, out = ip_binding._CParams(*[int(getattr(params, f[0])) for f in ip_binding._CParams._fields_]), ctypes.c_void_p()
+    binding._check(lib.ip_desc_create_tiled(ctypes.byref(out), ctypes.byref(c)), "ip_desc_create_tiled")
+    public, tiled = conv.ip_desc_create(params), ip_binding.IpDesc(out.value, params)
+    return [public] if conv.ip_desc_kernel_names(public) == conv.ip_desc_kernel_names(tiled) else [public, tiled]
 
 
 def descs(pd, names=conv.conv_desc_kernel_names):

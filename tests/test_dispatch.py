@@ -20,6 +20,18 @@ CASES = {
         (P(64, 20, 12, 12, 50, 5, 5), "f32", "bwd_data", "corrsmall_32x16x4[w3]", (19.5, 23.7)),
         (P(64, 20, 12, 12, 50, 5, 5), "f32", "fwd", "corrsmall_32x16x4[w0]", (7.0, 14.0)),
     ],
+    # nothing but the modelled time keeps a size on the tiled kernels: short reductions, few columns, thin rows, few places
+    "no_size_is_kept_for_the_tests": [
+        (P(64, 1, 28, 28, 20, 5, 5), "f32", "fwd", "corrsmall", (8.0, 8.6)),
+        (P(2, 6, 6, 6, 343, 5, 5, 2, 2, 1, 2), "f32", "fwd", "corrsmall", (5.0, 10.4)),
+        (P(6, 256, 1, 1, 1, 3, 3, 1, 1, 1, 1), "f32", "bwd_data", "corrsmall", (3.7, 8.3)),
+        (P(8, 2, 12, 12, 2, 6, 6, 1, 1, 2, 2), "f32", "fwd", "corrsmall", (4.2, 9.6)),
+        (P(21, 4, 1, 25, 1, 3, 7, 1, 1, 1, 2), "f32", "bwd_data", "corrsmall", (3.8, 7.4)),
+        (P(4, 47, 3, 3, 3, 3, 3), "f32", "bwd_filter", "smallwgrad", (3.5, 6.2)),
+        (P(2, 4, 4, 4, 153, 3, 7, 3, 3, 1, 3), "f64", "fwd", "corrsmall64", (4.2, 9.6)),
+        (P(45, 24, 8, 8, 2, 1, 1), "f64", "bwd_data", "corrsmall64", (3.5, 7.4)),
+        (P(12, 177, 3, 3, 2, 2, 2), "f64", "bwd_filter", "smallwgrad64", (3.4, 5.7)),
+    ],
 }
 
 

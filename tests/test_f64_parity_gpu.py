@@ -13,7 +13,7 @@ import paper_1810_02272_amd as conv
 from oracle import OracleParams
 from paper_1810_02272_amd import workloads
 from parity_metric import gated_error
-from parity_cases import DIRECT_CASES, SWEEP, VARIANT_CASES, P, descs, public_desc
+from parity_cases import DIRECT_CASES, SWEEP, VARIANT_CASES, P, descs, public_desc, tiled_desc
 
 pytestmark = pytest.mark.gpu
 TOL = 1e-12
@@ -215,7 +215,7 @@ MODELLED = [
 @pytest.mark.parametrize("i", range(len(MODELLED)))
 def test_f64_modelled_tiles_against_the_oracle(i):
     pd, which, rows, sliced = MODELLED[i]
-    names = dict(f.split("=", 1) for f in conv.conv_desc_kernel_names_f64(conv.conv_desc_create(conv.ConvParams(**pd))).split(";"))
+    names = dict(f.split("=", 1) for f in conv.conv_desc_kernel_names_f64(tiled_desc(pd)).split(";"))
     assert names[which].startswith(f"corr64_{rows}x64x16[") and ("(S=1," not in names[which]) == sliced, (pd, names)
     op = OracleParams(**pd)
     x, w, b, dy = (widen(t, 95000 + 10 * i + j) for j, t in enumerate(

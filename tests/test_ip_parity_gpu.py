@@ -15,7 +15,7 @@ import paper_1810_02272_amd as conv
 from oracle import inner_product as ipo
 from oracle.inner_product import IpOracleParams
 from paper_1810_02272_amd import workloads
-from parity_cases import IP_BETA_SHAPES, IP_SHAPES
+from parity_cases import IP_BETA_SHAPES, IP_SHAPES, ip_descs
 from parity_metric import small_tensor_error
 
 pytestmark = pytest.mark.gpu
@@ -33,7 +33,11 @@ def nerr(gpu, ref):
 
 def run_case(m, k, o, bias, relu, x, w, b, dy, beta=0.0, dw0=None, db0=None):
     pd = dict(m=m, k=k, num_output=o, bias_term=int(bias), relu=int(relu))
-    d = conv.ip_desc_create(conv.IpParams(**pd))
+    return [run_on(d, pd, bias, relu, x, w, b, dy, beta, dw0, db0) for d in ip_descs(pd)][0]
+
+
+def run_on(d, pd, bias, relu, x, w, b, dy, beta, dw0, db0):
+    m, k, o = pd["m"], pd["k"], pd["num_output"]
     op = IpOracleParams(**pd)
     ws = torch.full((max(conv.ip_desc_workspace_bytes(d) // 4, 1),), NAN, device=DEV)
     xd, wd, dyd = x.to(DEV), w.to(DEV), dy.to(DEV)

@@ -14,7 +14,7 @@ import oracle
 import paper_1810_02272_amd as conv
 from oracle import OracleParams
 from paper_1810_02272_amd import workloads
-from parity_cases import (IP_RANDOM, MANY_CHANNEL, MULTI_TILE, RANDOM_BLOCKS, THIN_BLOCKS, THIN_ROW, draw_block,
+from parity_cases import (IP_RANDOM, MANY_CHANNEL, MULTI_TILE, RANDOM_BLOCKS, THIN_BLOCKS, THIN_ROW, draw_block, tiled_desc,
                           random_ip_case, random_multi_tile_params, random_params, random_thin_group_params,
                           random_thin_row_params)
 from test_f64_parity_gpu import check_full64
@@ -64,7 +64,7 @@ def test_random_thin_row_parameters_reach_the_thin_row_kernel_and_its_staged_for
     """Random stride-1 layers with at most four input channels or outputs per group: GEMMs of at most four rows."""
     plain = staged = 0
     for i, pd in enumerate(draw_block(*THIN_ROW)):
-        names = conv.conv_desc_kernel_names(conv.conv_desc_create(conv.ConvParams(**pd)))
+        names = conv.conv_desc_kernel_names(tiled_desc(pd))  # one of the two ways that check_both_types runs it
         print("random thin-row case", i, pd, names, flush=True)
         plain += re.search(r"corr_thin_r\d\[", names) is not None
         staged += re.search(r"corr_thin_r\d_lds", names) is not None
@@ -83,7 +83,7 @@ def test_random_many_channel_parameters_reach_the_square_filter_gradient_tile():
     backward-filter tile (loads that write LDS directly) with ragged rows and columns, every bounds mode."""
     square = 0
     for i, pd in enumerate(draw_block(*MANY_CHANNEL)):
-        names = conv.conv_desc_kernel_names(conv.conv_desc_create(conv.ConvParams(**pd)))
+        names = conv.conv_desc_kernel_names(tiled_desc(pd))  # one of the two ways that check_both_types runs it
         print("random many-channel case", i, pd, names, flush=True)
         square += "wgrad_m32_128x128x32" in names
         check_both_types(pd, 71000 + i)

@@ -160,18 +160,18 @@ def test_inner_product_shapes_cover_the_three_contractions():
     shapes += [pc.random_ip_case(rng)[:3] for _ in range(pc.IP_RANDOM[1])]
     seen = {"fwd": set(), "bwd_data": set(), "bwd_filter": set()}
     for m, k, o in shapes:
-        d = conv.ip_desc_create(conv.IpParams(m, k, o, 1, 1))
-        for which, v in fields(conv.ip_desc_kernel_names(d)).items():
-            if which in seen:
-                seen[which].add(split_variant(v)[0])
+        for d in pc.ip_descs(dict(m=m, k=k, num_output=o, bias_term=1, relu=1)):
+            for which, v in fields(conv.ip_desc_kernel_names(d)).items():
+                if which in seen:
+                    seen[which].add(split_variant(v)[0])
     assert all(v.startswith("wgrad") for v in seen["fwd"]) and len(seen["fwd"]) >= 3, seen["fwd"]
     assert all(v.startswith("corr") for v in seen["bwd_data"] | seen["bwd_filter"])
     # beta = 1: the filter gradient is added in the epilogue of the gather kernels and of the kernel for GEMMs of at
     # most four rows (test_ip_beta_one_accumulates)
     beta_kernels = set()
     for m, k, o in pc.IP_BETA_SHAPES:
-        d = conv.ip_desc_create(conv.IpParams(m, k, o, 1, 1))
-        beta_kernels.add(split_variant(fields(conv.ip_desc_kernel_names(d))["bwd_filter"])[0].split("[")[0])
+        for d in pc.ip_descs(dict(m=m, k=k, num_output=o, bias_term=1, relu=1)):
+            beta_kernels.add(split_variant(fields(conv.ip_desc_kernel_names(d))["bwd_filter"])[0].split("[")[0])
     assert any(v.startswith("corr_thin_r") for v in beta_kernels), beta_kernels
     assert any(v.startswith("corr_m") for v in beta_kernels), beta_kernels
     # a forward output of more than 2^30 bytes takes the plain-pointer store of the filter-gradient kernel
