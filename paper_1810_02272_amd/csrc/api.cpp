@@ -25,6 +25,8 @@ int64_t floor_div(int64_t a, int64_t b) {
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
+// For the loops over tiles and slices, which a descriptor runs by the hundred: a 64-bit division takes several times as long.
+uint32_t parts_of(int64_t a, uint32_t b) { return ((uint32_t)a + b - 1) / b; }
 
 // Row tile: the smallest padded row count wins; a taller tile is taken over a shorter one when it
 // pads at most 3 % more rows (the 32-row MFMA tiles it brings are worth that).  Column tile, among
@@ -786,21 +788,34 @@ double zero_fill_model(bool zero_fill, double out_mb) { return zero_fill ? 2.7 +
 // sums and output (MB), then per tile the chunks of 16 reduction indices that one workgroup walks alone and those that the
 // workgroups of a compute unit share, dearer where the gather compares or masks.  A fit to 8653 timings -- every tile, 1 to 16
 // slices, 240 passes of 0.15 to 20 GFLOP (rms error 14 to 16 %, most of it in configurations far from the best).
-double corr_model(const CorrArgs& a, int32_t tile, int64_t S, int64_t out_elems, bool zero_fill) {
-  static const double kCost[CORR_TILE_COUNT][4] = {  // alone, shared, with compares, with masks
-      {0.243, 0.802, 0.151, 0.075}, {0.208, 0.386, 0.081, 0.045}, {0.263, 0.564, 0.191, 0.099}, {0.296, 0.327, 0.152, 0.078},
-      {0.250, 0.168, 0.074, 0.035}, {0.317, 0.379, 0.233, 0.104}, {0.281, 0.184, 0.107, 0.043}, {0.253, 0.615, 0.280, 0.136},
-      {0.238, 0.263, 0.137, 0.065}, {0.250, 0.307, 0.134, 0.028}, {0.208, 0.080, 0.021, 0.003}};
-  int32_t bm, bn, bk;
-  corr_tile_shape(tile, &bm, &bn, &bk);
-  const double* const c = kCost[tile];
-  const int64_t units = (int64_t)a.G * ceil_div(a.Mrows, bm) * ceil_div(a.ncols, bn), all = ceil_div(a.Kred, 16);
-  const int64_t chunks = ceil_div(all, S), slices = ceil_div(all, chunks), per_cu = ceil_div(units * slices, 256);
-  const double out_mb = 4e-6 * (double)out_elems, pack_mb = 4e-6 * (double)a.G * (double)round_up(a.Mrows, bm) * (double)(16 * all);
-  const double shared = c[1] + (a.bounds_mode == 1 ? c[2] : a.bounds_mode == 2 ? c[3] : 0.0) + (tile == CORR_16x64 ? 0.09 / (double)chunks : 0.0);
-  return 5.5 + 0.3 * pack_mb + 0.25 * out_mb + zero_fill_model(zero_fill, out_mb) + (slices > 1 ? 2.2 + 0.7 * (double)slices * out_mb : 0.0) +
-         (double)chunks * (c[0] + (double)per_cu * shared);
-}
+struct CorrModel {
+  CorrModel(const CorrArgs& a, int32_t tile, int64_t out_elems, bool zero_fill) {
+    static const double kCost[CORR_TILE_COUNT][4] = {  // alone, shared, with compares, with masks
+        {0.243, 0.802, 0.151, 0.075}, {0.208, 0.386, 0.081, 0.045}, {0.263, 0.564, 0.191, 0.099}, {0.296, 0.327, 0.152, 0.078},
+        {0.250, 0.168, 0.074, 0.035}, {0.317, 0.379, 0.233, 0.104}, {0.281, 0.184, 0.107, 0.043}, {0.253, 0.615, 0.280, 0.136},
+        {0.238, 0.263, 0.137, 0.065}, {0.250, 0.307, 0.134, 0.028}, {0.208, 0.080, 0.021, 0.003}};
+    int32_t bm, bn, bk;
+    corr_tile_shape(tile, &bm, &bn, &bk);
+    const double* const c = kCost[tile];
+    all = (uint32_t)ceil_div(a.Kred, 16);
+    const int64_t m_tiles = parts_of(a.Mrows, (uint32_t)bm);
+    units = (int64_t)a.G * m_tiles * parts_of(a.ncols, (uint32_t)bn);
+    out_mb = 4e-6 * (double)out_elems;
+    const double pack_mb = 4e-6 * (double)a.G * (double)(m_tiles * bm) * (double)(16 * (int64_t)all);
+    launches = 5.5 + 0.3 * pack_mb + 0.25 * out_mb + zero_fill_model(zero_fill, out_mb);
+    alone = c[0];
+    shared = c[1] + (a.bounds_mode == 1 ? c[2] : a.bounds_mode == 2 ? c[3] : 0.0);
+    workgroup = tile == CORR_16x64 ? 0.09 : 0.0;
+  }
+  double time(int64_t S) const {  // in S slices
+    const uint32_t chunks = parts_of(all, (uint32_t)S), slices = parts_of(all, chunks);
+    const double per_cu = (double)((units * slices + 255) >> 8);
+    return launches + (slices > 1 ? 2.2 + 0.7 * (double)slices * out_mb : 0.0) + (double)chunks * (alone + per_cu * shared) + per_cu * workgroup;
+  }
+  uint32_t all;
+  int64_t units;
+  double out_mb, launches, alone, shared, workgroup;
+};
 
 // Tile and slices of a pass on the tiled fp32 kernels by that model, for passes of 0.2 GFLOP and more: the row count that pads
 // least says little about the time.  73 -> 2 channels 8x8, stride 2, at 26x32, batch 73, backward data: 16x64 unsplit 128 us, in
@@ -815,14 +830,15 @@ void plan_corr(CorrArgs& a, PackArgs& k, int64_t out_elems, bool zero_fill, int3
   const int64_t all = ceil_div(a.Kred, 16);
   int32_t best = tile;
   int64_t best_S = a.ksplit;
-  double cost = 0.92 * corr_model(a, tile, a.ksplit, out_elems, zero_fill);  // nearer than that is within the model's error
+  double cost = 0.92 * CorrModel(a, tile, out_elems, zero_fill).time(a.ksplit);  // nearer than that is within the model's error
   for (int32_t t = 0; t < CORR_TILE_COUNT; ++t) {
     int32_t bm, bn, bk;
     corr_tile_shape(t, &bm, &bn, &bk);
     if ((int64_t)a.G * a.KP * round_up(a.Mrows, bm) >= kMaxElems) continue;
+    const CorrModel model(a, t, out_elems, zero_fill);
     for (const int64_t S : kSlices) {
       if (S > 1 && (2 * S > all || S * out_elems > ((int64_t)16 << 20))) break;  // slices of two chunks, 64 MiB of partial sums
-      const double c = corr_model(a, t, S, out_elems, zero_fill);
+      const double c = model.time(S);
       if (c < cost) {
         best = t;
         best_S = S;
@@ -841,16 +857,16 @@ void plan_corr(CorrArgs& a, PackArgs& k, int64_t out_elems, bool zero_fill, int3
   a.ksplit = (int32_t)ceil_div(all, a.chunks_per_split);
 }
 
-// The time of a pass on the tiled fp32 kernels, as planned, against which the one-launch kernel is held.  Below 0.7 GFLOP corr_model is 8
+// The time of a pass on the tiled fp32 kernels, as planned, against which the one-launch kernel is held.  Below 0.7 GFLOP CorrModel is 8
 // to 17 % short of it; a fit of its own to 51740 timings -- every tile, 1 to 16 slices -- is 5 to 10 % off (rms) on 19000 others.  20 -> 50
-// channels, 5x5 at 12x12, batch 64, backward data: 23.7 us on the tiles, 23.6 here, 21.7 by corr_model; 19.5 in one launch.
+// channels, 5x5 at 12x12, batch 64, backward data: 23.7 us on the tiles, 23.6 here, 21.7 by CorrModel; 19.5 in one launch.
 double tiled_time(const CorrArgs& a, int32_t tile, int64_t out_elems, bool backward, bool zero_fill) {
   static const double kCost[CORR_TILE_COUNT][5] = {  // alone, shared, with compares, with masks, workgroup
       {0.397, 0.599, 0.186, 0.145, 2.023}, {0.294, 0.263, 0.108, 0.111, 1.164}, {0.448, 0.334, 0.234, 0.167, 2.082},
       {0.338, 0.261, 0.155, 0.114, 1.092}, {0.286, 0.105, 0.104, 0.093, 0.532}, {0.426, 0.151, 0.357, 0.219, 1.605},
       {0.319, 0.078, 0.186, 0.135, 0.617}, {0.311, 0.458, 0.355, 0.229, 2.052}, {0.262, 0.142, 0.217, 0.154, 0.946},
       {0.267, 0.142, 0.286, 0.165, 1.037}, {0.236, 0.012, 0.067, 0.056, 0.255}};
-  if (2.0 * a.Mrows * a.Kred * (double)a.ncols * a.G >= 0.7e9) return corr_model(a, tile, a.ksplit, out_elems, zero_fill);
+  if (2.0 * a.Mrows * a.Kred * (double)a.ncols * a.G >= 0.7e9) return CorrModel(a, tile, out_elems, zero_fill).time(a.ksplit);
   const double* const c = kCost[tile];
   const double per_cu = (double)ceil_div((int64_t)a.G * a.m_tiles * a.col_tiles * a.ksplit, 256);
   const double out_mb = 4e-6 * (double)out_elems, pack_mb = 4e-6 * (double)a.G * (double)a.MP * (double)a.KP;
@@ -902,12 +918,12 @@ void plan_corr64(CorrArgs& a, int64_t out_elems, int32_t& rows) {
   int64_t best_S = a.ksplit;
   double cost = 0, here = 0;
   for (const auto& t : kTiles) {
-    const int64_t m_tiles = ceil_div(a.Mrows, t.rows);
+    const int64_t m_tiles = parts_of(a.Mrows, (uint32_t)t.rows), units = (int64_t)a.G * m_tiles * a.col_tiles;
+    const double launches = 5.0 + 0.21 * out_mb + 0.27 * 8e-6 * (double)(a.G * m_tiles * t.rows) * (double)a.KP;
     auto model = [&](int64_t S) {
-      const int64_t chunks = ceil_div(all, S), per_cu = ceil_div((int64_t)a.G * m_tiles * a.col_tiles * ceil_div(all, chunks), 256);
-      return 5.0 + 0.21 * out_mb + 0.27 * 8e-6 * (double)(a.G * m_tiles * t.rows) * (double)a.KP +
-             (S > 1 ? 4.0 + 0.288 * (double)S * out_mb : 0.0) + (double)chunks * (t.chain + t.chunk * (double)per_cu) +
-             t.workgroup * (double)per_cu;
+      const uint32_t chunks = parts_of(all, (uint32_t)S), slices = parts_of(all, chunks);
+      const double per_cu = (double)((units * slices + 255) >> 8);
+      return launches + (S > 1 ? 4.0 + 0.288 * (double)S * out_mb : 0.0) + (double)chunks * (t.chain + t.chunk * per_cu) + t.workgroup * per_cu;
     };
     if (t.rows == rows) here = 0.92 * model(a.ksplit);  // nearer than that is within the model's error
     for (const int64_t S : kSlices) {
@@ -935,6 +951,8 @@ int32_t configure_corr_small(const CorrArgs& base, const PackArgs& k, int64_t w_
   const int64_t limit = (int64_t)1 << 30, TH = base.THW / base.TW;
   // Not measured: forward passes of layers with a stride and a dilation, and what the patch-staged kernel takes.
   if (base.use_patch || (base.sh * base.sw > 1 && base.dh * base.dw > 1)) return -1;
+  const double flops = 2.0 * base.Mrows * base.Kred * (double)base.ncols * base.G;
+  if (flops > (elem_bytes == 8 ? 1e9 : 1.5e9)) return -1;
   if (base.ncols < 1 || (int64_t)base.in_bytes > limit || elem_bytes * w_elems > limit || elem_bytes * out_elems > limit) return -1;
   // the kernel's packed displacements, and the row that stands for "past the reduction"
   if (base.IH > 16384 || base.IW > 16384 || base.ph > 4096 || base.pw > 4096) return -1;
@@ -983,6 +1001,7 @@ int32_t configure_corr_small(const CorrArgs& base, const PackArgs& k, int64_t w_
        {{0.151, 0.063, 0.39}, {0.000, 0.079, 0.69}, {0.156, 0.107, 0.59}, {0.214, 0.102, 0.65}, {0.242, 0.175, 0.99}, {0.151, 0.159, 0.88}, {}}}};
   // a forward gather that strides over columns takes more cache lines a load; one that stays in the image no bounds tests
   const double strided = (base.sw == 1 ? 1.0 : base.sw < 4 ? 1.1 : 1.3) * (a.pad ? 1.0 : elem_bytes == 8 ? 0.95 : 0.88);
+  const double launches = 3.0 + zero_fill_model(zero_fill, 1e-6 * elem_bytes * (double)out_elems);
   const int64_t groups = KT / 16;
   int32_t best = -1;
   double here = 0;
@@ -990,25 +1009,23 @@ int32_t configure_corr_small(const CorrArgs& base, const PackArgs& k, int64_t w_
     const SmallCost& c = kCost[elem_bytes == 8][a.wmode == 1 || a.wmode == 2][t];
     const SmallTile& s = kCorrSmallTiles[t];
     if (c.shared == 0) continue;  // no instance
-    const int64_t units = (int64_t)a.G * ceil_div(a.Mrows, 16 * s.mb) * ceil_div(a.ncols, 16 * s.nb), per_cu = ceil_div(units, 256);
-    const double cost =
-        3.0 + zero_fill_model(zero_fill, 1e-6 * elem_bytes * (double)out_elems) + strided * (c.chain * (double)ceil_div(groups, s.waves) + (c.shared * (double)groups + c.workgroup) * (double)per_cu);
+    const int64_t units = (int64_t)a.G * parts_of(a.Mrows, 16 * (uint32_t)s.mb) * parts_of(a.ncols, 16 * (uint32_t)s.nb);
+    const double per_cu = (double)((units + 255) >> 8);
+    const double cost = launches + strided * (c.chain * (double)parts_of(groups, (uint32_t)s.waves) + (c.shared * (double)groups + c.workgroup) * per_cu);
     if (best < 0 || cost < here) {
       best = t;
       here = cost;
     }
   }
-  const double flops = 2.0 * base.Mrows * base.Kred * (double)base.ncols * base.G;
   // Nearer to the time of the tile chosen: rows past the last load no weights, and rows of 64 taps, or 16, meet in the caches where they are
   // read by single loads (rms errors 9 to 11 %, floats with such loads 14; without this 10 to 17).
   static const double kNear[2][4][2] = {{{0.86, 0.22}, {0.71, 0.17}, {0.88, 0.27}, {0.93, 0.07}}, {{0.79, 0.28}, {0.90, 0.17}, {0.90, 0.17}, {0.94, 0.15}}};
   const double* const near = kNear[elem_bytes == 8][a.wmode];
   const double fill = (double)a.Mrows / (double)round_up(a.Mrows, 16 * kCorrSmallTiles[best].mb);
   const double meet = elem_bytes == 4 && a.wmode == 2 ? (T % 64 == 0 ? 0.19 : T % 16 == 0 ? 0.07 : 0.0) : 0.0;
-  const double launches = 3.0 + zero_fill_model(zero_fill, 1e-6 * elem_bytes * (double)out_elems);
   here = launches + 0.15 + (here - launches) * (near[0] + near[1] * fill + meet);
   const double margin = elem_bytes == 4 && flops >= 0.7e9 ? 0.9 : 0.95;
-  if (flops > (elem_bytes == 8 ? 1e9 : 1.5e9) || here > margin * old) return -1;
+  if (here > margin * old) return -1;
   a.m_tiles = (int32_t)ceil_div(a.Mrows, 16 * kCorrSmallTiles[best].mb);
   a.col_tiles = (int32_t)ceil_div(a.ncols, 16 * kCorrSmallTiles[best].nb);
   if ((int64_t)a.G * a.m_tiles * a.col_tiles >= ((int64_t)1 << 31)) return -1;
@@ -1065,6 +1082,8 @@ CorrChoice choose_corr(CorrArgs& a, PackArgs& k, int32_t& tile, int64_t cg_in, i
 int32_t configure_wgrad_small(const WgradArgs& w, int64_t N, int32_t elem_bytes, int32_t bm, int32_t bn, WgradSmallArgs& a) {
   const int64_t limit = (int64_t)1 << 30, TH = w.khw / w.kw;
   if (w.sh * w.sw > 1 && w.dh * w.dw > 1) return -1;  // not measured: layers with a stride and a dilation
+  const double flops = 2.0 * w.Kg * w.Kred * (double)w.ncols * w.G;
+  if (flops > 1e9) return -1;
   if (w.ncols < 1 || (int64_t)w.x_bytes > limit || (int64_t)w.dy_bytes > limit) return -1;
   if (w.H > 16384 || w.W > 16384 || w.ph > 4096 || w.pw > 4096) return -1;  // packed into 16 bits
   if ((TH - 1) * w.dh > 8192 || (int64_t)(w.kw - 1) * w.dw > 8192) return -1;
@@ -1101,13 +1120,15 @@ int32_t configure_wgrad_small(const WgradArgs& w, int64_t N, int32_t elem_bytes,
       const SmallCost& c = kCost[elem_bytes == 8][a.xvec][t];
       const SmallTile& s = kWgradSmallTiles[t];
       if (c.shared == 0) continue;  // no instance
-      const int64_t tiles = (int64_t)w.G * ceil_div(w.Kg, 16 * s.mb) * ceil_div(w.Kred, 16 * s.nb);
-      for (int64_t S = 1; S <= w.S; S *= 2) {  // at most the slices that the workspace has room for
-        const int64_t bps = ceil_div(a.blocks, S), slices = ceil_div(a.blocks, bps), per_cu = ceil_div(tiles * slices, 256);
-        // a running sum hardly longer than on the tiled kernel: one of 256 was up to 1.3 times as far off as the slices there
-        const int64_t sums = s.waves * (elem_bytes == 8 ? 1 : 4 / (s.mb * s.nb)), free = elem_bytes == 8 ? 2048 : 192;
-        if (bps * 64 / sums > (w.cols_per_split > free ? w.cols_per_split : free)) continue;
-        const double cost = 3.3 + c.chain * (double)ceil_div(bps, s.waves) + (c.shared * (double)bps + c.workgroup) * (double)per_cu +
+      const int64_t tiles = (int64_t)w.G * parts_of(w.Kg, 16 * (uint32_t)s.mb) * parts_of(w.Kred, 16 * (uint32_t)s.nb);
+      // a running sum hardly longer than on the tiled kernel: one of 256 was up to 1.3 times as far off as the slices there
+      const int64_t sums = s.waves * (elem_bytes == 8 ? 1 : 4 / (s.mb * s.nb)), free = elem_bytes == 8 ? 2048 : 192;
+      const int64_t longest = sums * ((w.cols_per_split > free ? w.cols_per_split : free) + 1);
+      for (uint32_t S = 1; S <= (uint32_t)w.S; S *= 2) {  // at most the slices that the workspace has room for
+        const uint32_t bps = parts_of(a.blocks, S), slices = parts_of(a.blocks, bps);
+        const int64_t per_cu = (tiles * slices + 255) >> 8;
+        if ((int64_t)bps * 64 >= longest) continue;
+        const double cost = 3.3 + c.chain * (double)parts_of(bps, (uint32_t)s.waves) + (c.shared * (double)bps + c.workgroup) * (double)per_cu +
                             (slices > 1 ? 2.0 + (elem_bytes == 8 ? 1.0 : 1.6) * (double)slices * w_mb : 0.0);
         if (best < 0 || cost < here) {
           best = t;
@@ -1129,11 +1150,10 @@ int32_t configure_wgrad_small(const WgradArgs& w, int64_t N, int32_t elem_bytes,
   const int64_t steps = ceil_div(w.cols_per_split, 32), per_cu = ceil_div((int64_t)w.G * w.m_tiles * w.n_tiles * w.S, 256);
   const double old = o[0] + o[1] * w.S * w_mb + (double)steps * (o[2] + o[3] * area) +
                      (double)(per_cu * steps) * (o[4] + o[5] * area + (elem_bytes == 4 && w.bounds_mode == 1 ? 0.32 : 0.0)) + o[6] * (double)per_cu;
-  const double flops = 2.0 * w.Kg * w.Kred * (double)w.ncols * w.G;
   // 1x1 layers and fully connected ones need another 1.2: rows of x far apart cost more than the fit knows (28 x 3090 -> 3506
   // outputs took 26.9 us here, 21.7 on the tiles).
   const double least = (flops < 0.5e9 ? 0.9 : 0.75) / (a.xvec == 1 && elem_bytes == 4 ? 1.2 : 1.0);
-  if (flops > 1e9 || here > least * old) return -1;
+  if (here > least * old) return -1;
   a.m_tiles = (int32_t)ceil_div(a.Kg, 16 * kWgradSmallTiles[best].mb);
   a.n_tiles = (int32_t)ceil_div(a.Kred, 16 * kWgradSmallTiles[best].nb);
   a.blocks_per_split = (int32_t)best_bps;
@@ -1850,21 +1870,15 @@ static int create_desc(conv_desc_t** out, const conv_params_t* pp, bool one_laun
     d->wg64_ws = (size_t)a.S * (size_t)w_elems * 8;
     d->wg_small[1] = !one_launch ? -1 : configure_wgrad_small(a, N, 8, bm64, bn64, d->wg_sm[1]);
     d->bg64_ws = 2 * d->bg_ws;
-    auto e64 = [](const CorrArgs& c) { return c.simple_epilogue ? 's' : 'p'; };
-    snprintf(d->names64, sizeof(d->names64),
-             "fwd=corr64_%dx64x16[e%c](S=%d,L=%d);bwd_data=corr64_%dx64x16[e%c](S=%d,L=%d);"
-             "bwd_filter=wgrad64_%dx64x16(S=%d,L=2);bwd_bias=%s",
-             d->fwd64_rows, e64(d->fwd64), d->fwd64.ksplit, 2 + (d->fwd64.ksplit > 1), d->bwd64_rows, e64(d->bwd64),
-             d->bwd64.ksplit, 2 + (d->bwd64.ksplit > 1) + (d->bwd_zero_fill != 0), d->wg64_rows, a.S, bias64);
-    if (d->fwd_small[1] >= 0 || d->bwd_small[1] >= 0 || d->wg_small[1] >= 0) {
-      char f[64], b[64], wg[64];
-      snprintf(f, sizeof(f), "corr64_%dx64x16[e%c](S=%d,L=%d)", d->fwd64_rows, e64(d->fwd64), d->fwd64.ksplit, 2 + (d->fwd64.ksplit > 1));
-      snprintf(b, sizeof(b), "corr64_%dx64x16[e%c](S=%d,L=%d)", d->bwd64_rows, e64(d->bwd64), d->bwd64.ksplit,
-               2 + (d->bwd64.ksplit > 1) + (d->bwd_zero_fill != 0));
-      snprintf(wg, sizeof(wg), "wgrad64_%dx64x16(S=%d,L=2)", d->wg64_rows, a.S);
-      small_names(d, 1, f, b, wg, sizeof(f));
-      snprintf(d->names64, sizeof(d->names64), "fwd=%s;bwd_data=%s;bwd_filter=%s;bwd_bias=%s", f, b, wg, bias64);
-    }
+    auto corr64_name = [](char* buf, size_t len, int32_t rows, const CorrArgs& c, int32_t zero_fill) {
+      snprintf(buf, len, "corr64_%dx64x16[e%c](S=%d,L=%d)", rows, c.simple_epilogue ? 's' : 'p', c.ksplit, 2 + (c.ksplit > 1) + (zero_fill != 0));
+    };
+    char f[64], b[64], wg[64];
+    if (d->fwd_small[1] < 0) corr64_name(f, sizeof(f), d->fwd64_rows, d->fwd64, 0);
+    if (d->bwd_small[1] < 0) corr64_name(b, sizeof(b), d->bwd64_rows, d->bwd64, d->bwd_zero_fill);
+    if (d->wg_small[1] < 0) snprintf(wg, sizeof(wg), "wgrad64_%dx64x16(S=%d,L=2)", d->wg64_rows, a.S);
+    small_names(d, 1, f, b, wg, sizeof(f));
+    snprintf(d->names64, sizeof(d->names64), "fwd=%s;bwd_data=%s;bwd_filter=%s;bwd_bias=%s", f, b, wg, bias64);
     d->ws_bytes64 = d->fwd64_ws;
     if (d->bwd64_ws > d->ws_bytes64) d->ws_bytes64 = d->bwd64_ws;
     if (d->wg64_ws > d->ws_bytes64) d->ws_bytes64 = d->wg64_ws;
@@ -1954,11 +1968,15 @@ static int create_desc(conv_desc_t** out, const conv_params_t* pp, bool one_laun
     // checked stores with compares, plain pointers), staging of the filter gradient (lds/reg), one or
     // two launches of the bias gradient
     char f[64], b[64], wg[64];
-    corr_variant_name(f, sizeof(f), d->fwd_tile, d->fwd, 0, d->fwd_thin);
-    corr_variant_name(b, sizeof(b), d->bwd_tile, d->bwd, d->bwd_zero_fill, d->bwd_thin);
-    if (d->fwd_split >= 0) split_variant_name(f, sizeof(f), d->fwd_split, d->fwd_sp, 0);
-    if (d->bwd_split >= 0) split_variant_name(b, sizeof(b), d->bwd_split, d->bwd_sp, d->bwd_zero_fill);
-    snprintf(wg, sizeof(wg), "%s[m%d,%s,e%c](S=%d,L=2)", wgrad_tile_name(d->wg_tile), d->wg.bounds_mode,
+    if (d->fwd_split >= 0)
+      split_variant_name(f, sizeof(f), d->fwd_split, d->fwd_sp, 0);
+    else if (d->fwd_small[0] < 0)
+      corr_variant_name(f, sizeof(f), d->fwd_tile, d->fwd, 0, d->fwd_thin);
+    if (d->bwd_split >= 0)
+      split_variant_name(b, sizeof(b), d->bwd_split, d->bwd_sp, d->bwd_zero_fill);
+    else if (d->bwd_small[0] < 0)
+      corr_variant_name(b, sizeof(b), d->bwd_tile, d->bwd, d->bwd_zero_fill, d->bwd_thin);
+    if (d->wg_split < 0 && d->wg_small[0] < 0) snprintf(wg, sizeof(wg), "%s[m%d,%s,e%c](S=%d,L=2)", wgrad_tile_name(d->wg_tile), d->wg.bounds_mode,
              d->wg_tile == WGRAD_128x128 ? "lds" : "reg", 4 * Kg * kred <= ((int64_t)1 << 30) ? 'r' : 'p', d->wg.S);
     if (d->wg_split >= 0) {
       int32_t rows, taps;
