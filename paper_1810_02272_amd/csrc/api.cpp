@@ -1072,8 +1072,9 @@ CorrChoice choose_corr(CorrArgs& a, PackArgs& k, int32_t& tile, int64_t cg_in, i
     return c;
   }
   plan_corr(a, k, out_elems, zero_fill, tile);
-  c.pack_bytes = (size_t)a.G * (size_t)a.KP * (size_t)a.MP * 4 + (size_t)a.KP * sizeof(KTabEntry);
   if (one_launch) c.small = configure_corr_small(a, k, w_elems, out_elems, zero_fill, 4, tiled_time(a, tile, out_elems, backward, zero_fill), small);
+  // one launch uses no workspace; what it asks for stays within what the rules' tile would
+  if (c.small < 0) c.pack_bytes = (size_t)a.G * (size_t)a.KP * (size_t)a.MP * 4 + (size_t)a.KP * sizeof(KTabEntry);
   return c;
 }
 
@@ -1573,7 +1574,7 @@ static int create_desc(conv_desc_t** out, const conv_params_t* pp, bool one_laun
     d->fwd_split = c.split;
     d->fwd_small[0] = c.small;
     d->fwd_pack_bytes = c.pack_bytes;
-    const int32_t S = c.split >= 0 ? d->fwd_sp.ksplit : a.ksplit;
+    const int32_t S = c.small >= 0 ? 1 : c.split >= 0 ? d->fwd_sp.ksplit : a.ksplit;
     d->fwd_ws = d->fwd_pack_bytes + (S > 1 ? (size_t)S * y_elems * 4 : 0);
   }
 
@@ -1693,7 +1694,7 @@ static int create_desc(conv_desc_t** out, const conv_params_t* pp, bool one_laun
     d->bwd_split = c.split;
     d->bwd_small[0] = c.small;
     d->bwd_pack_bytes = c.pack_bytes;
-    const int32_t S = c.split >= 0 ? d->bwd_sp.ksplit : a.ksplit;
+    const int32_t S = c.small >= 0 ? 1 : c.split >= 0 ? d->bwd_sp.ksplit : a.ksplit;
     d->bwd_ws = d->bwd_pack_bytes + (S > 1 ? (size_t)S * x_elems * 4 : 0);
   }
 
@@ -1844,7 +1845,7 @@ static int create_desc(conv_desc_t** out, const conv_params_t* pp, bool one_laun
       const int64_t pack_elems = (int64_t)a.G * a.KP * a.MP;
       if (pack_elems >= max64 || (int64_t)a.G * a.m_tiles * a.col_tiles >= ((int64_t)1 << 31)) d->f64_ok = 0;
       ws = (size_t)pack_elems * 8 + (size_t)a.KP * sizeof(KTabEntry) +
-           (a.ksplit > 1 ? (size_t)a.ksplit * (size_t)src.out_elems * 8 : 0);
+           (a.ksplit > 1 && small < 0 ? (size_t)a.ksplit * (size_t)src.out_elems * 8 : 0);
     };
     corr64(d->fwd, d->fwd_pack, d->fwd64, d->fwd64_pack, x_elems, false, d->fwd64_ws, d->fwd64_rows, d->fwd_small[1], d->fwd_sm[1]);
     corr64(d->bwd, d->bwd_pack, d->bwd64, d->bwd64_pack, y_elems, d->bwd_zero_fill != 0, d->bwd64_ws, d->bwd64_rows, d->bwd_small[1], d->bwd_sm[1]);

@@ -42,3 +42,10 @@ def test_the_faster_kernel_is_chosen(rule):
         names = conv.conv_desc_kernel_names(d) if base == "f32" else conv.conv_desc_kernel_names_f64(d)
         got = dict(kv.split("=", 1) for kv in names.split(";"))[which]
         assert got.startswith(prefix), (pd, base, which, got, "should take %.1f us, not %.1f" % times)
+
+
+def test_one_launch_asks_for_no_partial_sums():
+    """Its passes touch no workspace: what is asked for must not hold the slices of a plan that does not run (689 KB and 1.4 MB)."""
+    d = conv.conv_desc_create(conv.ConvParams(**P(3, 40, 23, 15, 127, 1, 1, 3, 3)))
+    assert all("small" in v for v in conv.conv_desc_kernel_names(d).split(";")[:3])
+    assert 0 < conv.conv_desc_workspace_bytes(d) <= 64 << 10 and 0 < conv.conv_desc_workspace_bytes_f64(d) <= 128 << 10
