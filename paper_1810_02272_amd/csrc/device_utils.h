@@ -54,6 +54,13 @@ __device__ __forceinline__ uint32_t xcd_contiguous_block_id() {
   return x * q + (x < r ? x : r) + idx;
 }
 
+// Orders the LDS accesses of one wave's lanes for the compiler; the hardware executes them in order.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Load with an unsigned 32-bit byte offset from a uniform base (one address register per lane).
 __device__ __forceinline__ float ld_f32(const float* base, uint32_t byte_off) {
   return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + byte_off);

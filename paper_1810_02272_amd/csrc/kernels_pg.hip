@@ -248,13 +248,6 @@ __device__ __forceinline__ float segment_scan(float v, int lane, uint64_t ends, 
   return v + (reach >= 16 - (lane & 15) ? w.to_row_end * later_rows : 0.f);
 }
 
-// Orders the LDS accesses of one wave's lanes for the compiler; the hardware executes them in order.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Episodes of the steps [b, end), n of them, lane l holding one past the last step of episode l.
 __device__ __forceinline__ void discount_run(const float* __restrict__ reward, float* __restrict__ discounted, int b, int end, int my_end,
                                              int n, int lane, float gamma, const ScanWeights& w, uint32_t (&marks)[kChunksInFlight][64]) {

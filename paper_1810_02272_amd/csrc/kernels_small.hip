@@ -483,13 +483,13 @@ __global__ __launch_bounds__(64 * WAVES) void wgrad_small_kernel(const WgradSmal
   int b = b0 + wv;
   if (b < b1) {
     fill(b, 0);
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();  // a lane reads what others wrote
 #pragma unroll
     for (int gi = 0; gi < 4; ++gi) load(0, gi, av[gi], bv[gi]);
     int buf = 1;
     for (; b < b1; b += WAVES, buf ^= 1) {
       fill(b + WAVES, buf);  // past the last block: nothing is read from the blobs
-      __builtin_amdgcn_wave_barrier();
+      wave_sync();  // a lane reads what others wrote
 #pragma unroll
       for (int gi = 0; gi < 4; ++gi) {
 #pragma unroll
