@@ -859,7 +859,7 @@ void plan_corr(CorrArgs& a, PackArgs& k, int64_t out_elems, bool zero_fill, int3
 
 // The time of a pass on the tiled fp32 kernels, as planned, against which the one-launch kernel is held.  Below 0.7 GFLOP CorrModel is 8
 // to 17 % short of it; a fit of its own to 51740 timings -- every tile, 1 to 16 slices -- is 5 to 10 % off (rms) on 19000 others.  20 -> 50
-// channels, 5x5 at 12x12, batch 64, backward data: 23.7 us on the tiles, 23.6 here, 21.7 by CorrModel; 19.5 in one launch.
+// channels, 5x5 at 12x12, batch 64, backward data: 23.7 us on the tiles, 24.8 here, 21.7 by CorrModel; 19.5 in one launch.
 double tiled_time(const CorrArgs& a, int32_t tile, int64_t out_elems, bool backward, bool zero_fill) {
   static const double kCost[CORR_TILE_COUNT][5] = {  // alone, shared, with compares, with masks, workgroup
       {0.397, 0.599, 0.186, 0.145, 2.023}, {0.294, 0.263, 0.108, 0.111, 1.164}, {0.448, 0.334, 0.234, 0.167, 2.082},
@@ -876,13 +876,7 @@ double tiled_time(const CorrArgs& a, int32_t tile, int64_t out_elems, bool backw
   return (backward ? 1.05 : 0.98) * rest + zero_fill_model(zero_fill, out_mb);
 }
 
-// Modelled times (us) of the one-launch kernels: a launch; then per tile the wave's chain of reduction groups (blocks of 64
-// places in the filter gradient), the groups that a compute unit's workgroups share, and those workgroups.
-struct SmallCost {
-  double chain, shared, workgroup;
-};
-
-// The same for a pass on the tiled kernels of doubles, as planned, on tiles of `rows`: launches, packed weights, partial sums and output
+// The time of a pass on the tiled kernels of doubles, as planned, on tiles of `rows`: launches, packed weights, partial sums and output
 // (MB), then per tile the chunks that one workgroup walks alone, those that the workgroups of a compute unit share, and these
 // workgroups; a forward pass 3 % less, backward data 4 % more.  A fit to 12665 timings of up to 6 GFLOP -- every tile, 1 to 16 slices; 6
 // to 8 % off (rms) from the smallest to the largest, on 16796 others as well.
@@ -943,6 +937,12 @@ void plan_corr64(CorrArgs& a, int64_t out_elems, int32_t& rows) {
   a.chunks_per_split = (int32_t)ceil_div(all, best_S);
   a.ksplit = (int32_t)ceil_div(all, a.chunks_per_split);
 }
+
+// Modelled times (us) of the one-launch kernels: a launch; then per tile the wave's chain of reduction groups (blocks of 64
+// places in the filter gradient), the groups that a compute unit's workgroups share, and those workgroups.
+struct SmallCost {
+  double chain, shared, workgroup;
+};
 
 // Decides whether corr_small_kernel runs this correlation instead of the launches of `base`, which are modelled to take `old`
 // us; fills a and returns its tile, -1 if it does not.
@@ -1151,6 +1151,7 @@ int32_t configure_wgrad_small(const WgradArgs& w, int64_t N, int32_t elem_bytes,
   const int64_t steps = ceil_div(w.cols_per_split, 32), per_cu = ceil_div((int64_t)w.G * w.m_tiles * w.n_tiles * w.S, 256);
   const double old = o[0] + o[1] * w.S * w_mb + (double)steps * (o[2] + o[3] * area) +
                      (double)(per_cu * steps) * (o[4] + o[5] * area + (elem_bytes == 4 && w.bounds_mode == 1 ? 0.32 : 0.0)) + o[6] * (double)per_cu;
+  // Of other gradients, over fewer than 64 places, 430 of floats take 0.55 of the tiles' time and 400 of doubles 0.75, 23 over 1.1 times.
   // 1x1 layers and fully connected ones need another 1.2: rows of x far apart cost more than the fit knows (28 x 3090 -> 3506
   // outputs took 26.9 us here, 21.7 on the tiles).
   const double least = (flops < 0.5e9 ? 0.9 : 0.75) / (a.xvec == 1 && elem_bytes == 4 ? 1.2 : 1.0);

@@ -9,8 +9,8 @@
 // Bound by latency on the smallest layers: table build, one ring of loads, the wave's chain of matrix instructions, the
 // exchange and the stores are 3.5 us, which is what an empty launch takes.  From some 0.1 GFLOP on the single-element gathers
 // bind it (four cache accesses per group and column block), at up to 60 % of the matrix unit.  Device time with all launches,
-// tiled kernels -> here: 20 -> 50, 5x5 at 12x12, batch 64, forward 13.7 -> 7.5 us, backward data 22.9 -> 19.2; one image of
-// 96 -> 256 in two groups, 5x5 at 27x27, forward 22.2 -> 13.5; 12 -> 187, 5x5, stride 2 at 7x7, batch 14: 13.6 -> 4.6, 13.7 ->
+// tiled kernels -> here: 20 -> 50, 5x5 at 12x12, batch 64, forward 14.0 -> 7.0 us, backward data 23.7 -> 19.5; one image of
+// 96 -> 256 in two groups, 5x5 at 27x27, forward 22.7 -> 14.8; 12 -> 187, 5x5, stride 2 at 7x7, batch 14: 13.6 -> 4.6, 13.7 ->
 // 10.8, filter gradient 14.1 -> 4.7; 84 -> 40, 3x1 at 7x7, batch 71: 10.8 -> 5.3, 15.4 -> 6.0, 10.2 -> 7.7.
 #include <hip/hip_runtime.h>
 
