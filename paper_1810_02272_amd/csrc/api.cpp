@@ -1085,6 +1085,9 @@ int32_t configure_wgrad_small(const WgradArgs& w, int64_t N, int32_t elem_bytes,
   if (w.sh * w.sw > 1 && w.dh * w.dw > 1) return -1;  // not measured: layers with a stride and a dilation
   const double flops = 2.0 * w.Kg * w.Kred * (double)w.ncols * w.G;
   if (flops > 1e9) return -1;
+  // Doubles over fewer than 64 places: what a workgroup costs beside its one block is dearer than the fit has it.  0.71 of the tiles' time
+  // with one 16x16 tile a compute unit, 0.78 with two, 1.02 with more (up to 1.35; floats 0.73).
+  if (elem_bytes == 8 && w.ncols < 64 && (int64_t)w.G * parts_of(w.Kg, 16) * parts_of(w.Kred, 16) > 512) return -1;
   if (w.ncols < 1 || (int64_t)w.x_bytes > limit || (int64_t)w.dy_bytes > limit) return -1;
   if (w.H > 16384 || w.W > 16384 || w.ph > 4096 || w.pw > 4096) return -1;  // packed into 16 bits
   if ((TH - 1) * w.dh > 8192 || (int64_t)(w.kw - 1) * w.dw > 8192) return -1;

@@ -31,6 +31,8 @@ CASES = {
         (P(2, 4, 4, 4, 153, 3, 7, 3, 3, 1, 3), "f64", "fwd", "corrsmall64", (4.2, 9.6)),
         (P(45, 24, 8, 8, 2, 1, 1), "f64", "bwd_data", "corrsmall64", (3.5, 7.4)),
         (P(12, 177, 3, 3, 2, 2, 2), "f64", "bwd_filter", "smallwgrad64", (3.4, 5.7)),
+        (P(12, 378, 5, 5, 3, 5, 5, 3, 3, 1, 1), "f64", "bwd_filter", "wgrad64", (5.3, 7.7)),
+        (P(5, 88, 3, 3, 39, 11, 11, 1, 1, 5, 5), "f64", "bwd_filter", "wgrad64", (10.5, 15.3)),
     ],
 }
 
