@@ -1022,7 +1022,10 @@ int32_t configure_corr_small(const CorrArgs& base, const PackArgs& k, int64_t w_
   static const double kNear[2][4][2] = {{{0.86, 0.22}, {0.71, 0.17}, {0.88, 0.27}, {0.93, 0.07}}, {{0.79, 0.28}, {0.90, 0.17}, {0.90, 0.17}, {0.94, 0.15}}};
   const double* const near = kNear[elem_bytes == 8][a.wmode];
   const double fill = (double)a.Mrows / (double)round_up(a.Mrows, 16 * kCorrSmallTiles[best].mb);
-  const double meet = elem_bytes == 4 && a.wmode == 2 ? (T % 64 == 0 ? 0.19 : T % 16 == 0 ? 0.07 : 0.0) : 0.0;
+  double meet = elem_bytes == 4 && a.wmode == 2 ? (T % 64 == 0 ? 0.19 : T % 16 == 0 ? 0.07 : 0.0) : 0.0;
+  // Outputs of up to nine pixels gather from an image for every one or two columns.  Over long reductions that is 0 to 60 % dearer: of 123
+  // such forward passes 28 were over 1.1 times the tiles' time, 9 of the 84 still taken so are.
+  if (elem_bytes == 4 && a.wmode == 0 && a.P <= 9 && groups >= 80) meet = 0.12;
   here = launches + 0.15 + (here - launches) * (near[0] + near[1] * fill + meet);
   const double margin = elem_bytes == 4 && flops >= 0.7e9 ? 0.9 : 0.95;
   if (here > margin * old) return -1;

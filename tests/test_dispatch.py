@@ -19,6 +19,8 @@ CASES = {
     "small_passes_are_modelled_in_their_range": [
         (P(64, 20, 12, 12, 50, 5, 5), "f32", "bwd_data", "corrsmall_32x16x4[w3]", (19.5, 23.7)),
         (P(64, 20, 12, 12, 50, 5, 5), "f32", "fwd", "corrsmall_32x16x4[w0]", (7.0, 14.0)),
+        (P(32, 249, 3, 3, 206, 3, 3, 2, 2), "f32", "fwd", "corr_m16_16x64x16", (11.6, 18.7)),
+        (P(16, 142, 6, 6, 147, 6, 6, 1, 1, 1, 0), "f32", "fwd", "corr_m32_32x128x16", (23.1, 33.3)),
     ],
     # nothing but the modelled time keeps a size on the tiled kernels: short reductions, few columns, thin rows, few places
     "no_size_is_kept_for_the_tests": [
