@@ -13,7 +13,7 @@ MARSHAL = os.path.join(_HERE, "_marshal.so")  # Python extension over LIB (csrc/
 SOURCES = ["api.cpp", "api_ip.cpp", "kernels_corr.hip", "kernels_corr_patch.hip", "kernels_corr_thin.hip",
            "kernels_small.hip", "kernels_corr_split.hip", "kernels_wgrad_split.hip", "kernels_wgrad.hip", "kernels_bias.hip",
            "kernels_ip.hip", "kernels_pg.hip", "kernels_f64.hip", "kernels_direct.hip", "static_workspace.hip"]
-HEADERS = ["internal.h", "device_utils.h", "corr_epilogue.h", "split_bf16.h"]
+HEADERS = ["internal.h", "device_utils.h", "corr_epilogue.h", "split_bf16.h", "split_f16.h"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

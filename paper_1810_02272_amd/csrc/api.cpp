@@ -192,14 +192,15 @@ void corr_variant_name(char* buf, size_t len, int32_t tile, const CorrArgs& a, i
     snprintf(buf, len, "%s[m%d,e%c](S=%d,L=%d)", corr_tile_name(tile), a.bounds_mode, e, a.ksplit, launches);
 }
 
-// "corrsplit_<tile>[p<patch units per thread>, fold<taps per channel>, cols or rows<channel groups>,e<epilogue form>](S,L)"
+// "corrsplit_<tile>[p<patch units per thread>, fold<taps per channel>, cols or rows<channel groups>,e<epilogue form>](S,L)",
+// with "half" before L for the f16 split
 void split_variant_name(char* buf, size_t len, int32_t tile, const CorrSplitArgs& a, int zero_fill) {
   int32_t bm, bn, mt;
   split_tile_shape(tile, &bm, &bn, &mt);
   const char e = a.simple_epilogue ? 's' : ((uint32_t)a.out_elems < (1u << 29) ? 'r' : 'p');
-  snprintf(buf, len, "corrsplit_m%d_%dx%d[%s%d,e%c](S=%d,L=%d)", mt, bm, bn, a.fold.subs ? a.fold.pixels ? "rows" : "cols" : a.fold.ff > 1 ? "fold" : "p",
+  snprintf(buf, len, "corrsplit_m%d_%dx%d[%s%d,e%c](S=%d,%sL=%d)", mt, bm, bn, a.fold.subs ? a.fold.pixels ? "rows" : "cols" : a.fold.ff > 1 ? "fold" : "p",
            a.fold.subs ? a.fold.subs : a.fold.ff > 1 ? a.fold.ff : split_patch_units(a.PSZ, bn), e,
-           a.ksplit, 2 + (a.ksplit > 1) + (zero_fill != 0));
+           a.ksplit, a.half ? "half," : "", 2 + (a.ksplit > 1) + (zero_fill != 0));
 }
 
 // "<kernel>_<rows>x<columns>x<waves>[w<how the weights are read>, or v<16-byte loads of x>](S,L)"
@@ -504,30 +505,67 @@ bool folded_grid(int64_t cg, int64_t kh, int64_t kw, int64_t sh, int64_t sw, int
   return g.f.fw % 4 == 0 && g.f.Uw % 4 == 0 && dw == 1 && pw % 4 == 0;
 }
 
+// Whether sums of K products take f16 terms where bf16 terms would add up `bf16_K` of them in a slice: where their error is no
+// larger (squares of the 2-norms, in units of 2^-24: split_f16.h) on inputs half of which are zero, as behind a ReLU -- zeros add
+// no rounding to a sum, so it is well below on dense ones (640 indices: 2.39 -> 1.99 dense, 1.80 -> 1.93 half zeros; 768: 2.64 ->
+// 2.02 and 2.00 -> 1.95; 1152: 3.31 -> 2.57 and 2.53 -> 2.54).  Returns the steps (of `step` indices, in whole `unit`s) between two
+// moves of the sums' leading bits, or 0 for bf16 terms.  A move costs time (every 128 indices instead of 400: 57.3 GFLOP 160 ->
+// 176 us), so the stretches are as long as a quarter less error than the bf16 terms' allows, 128 indices where that is out of reach.
+int32_t half_interval(double K, double bf16_K, double step, int32_t unit) {
+  const double bf16 = 0.0047 * bf16_K;
+  auto error = [&](int32_t steps) {
+    const double part = (double)steps * step < K ? (double)steps * step : K;
+    return 2.1 + 0.0047 * part + 0.04 * K / part;
+  };
+  int32_t steps = unit;
+  while ((double)steps * step < 128) steps += unit;
+  if (error(steps) > bf16) return 0;
+  while ((double)steps * step < K && error(steps + unit) < 0.75 * bf16) steps += unit;
+  return steps;
+}
+
+// The same for corr_split_kernel: `cps` of `chunks` chunks of T taps in a slice.  The tiles that hold several steps' weights move the
+// leading bits between chunks only.  The samples are of four neighbours (and of eight weights: reductions are longer).
+int32_t corr_half_interval(const CorrArgs& base, int32_t tile, int32_t mt, int64_t T, int64_t chunks, int64_t cps, int64_t bf16_cps) {
+  if (base.in_bytes < 16) return 0;
+  const int32_t step = mt == 32 ? 16 : 32;
+  const bool by_chunk = tile == SPLIT_64x128 || tile == SPLIT_32x256 || tile == SPLIT_32x128;
+  const double chunk = (double)base.Kred / (double)chunks;
+  return half_interval(chunk * (double)cps, chunk * (double)bf16_cps, step, by_chunk ? (int32_t)ceil_div(16 * T, step) : 2);
+}
+
 // Tile and split count of corr_split_kernel on one grid by modelled time (us); tile < 0: the patch fits none.
 // The workgroup that finishes last walks its steps alone on its compute unit (kAlone per step) or shares it with others
 // (kShared per step and workgroup); a chunk costs its patch by units per thread; S slices cost the reduce kernel and their
 // partial sums written and read.  The constants are a least-squares fit to 888 timings -- all tiles, 1 to 12 slices, 38
-// layers of 0.3 to 57 GFLOP (rms error 8 %); the choice is 2 % behind the best of each layer on average, 13 % at worst.
+// layers of 0.3 to 57 GFLOP (rms error 8 %); the choice is 2 % behind the best of each layer on average, 13 % at worst.  Those of
+// the f16 terms to 1072 timings of 40 passes of 1 to 57 GFLOP (7 %; 2 % and 12 %).
 struct SplitPlan {
-  int32_t tile;
+  int32_t tile, half;
   int64_t psz, S, units;  // units: output tiles
+  int64_t bf16_cps;       // chunks of a slice on bf16 terms
   double cost;  // modelled time without the launches and the prologue, about 10 us
   PatchDim w, h;
 };
 
-SplitPlan plan_split(const CorrArgs& base, const SplitGrid& grid, int64_t out_elems) {
-  static const double kAlone[SPLIT_TILE_COUNT] = {0.457, 0.444, 0.414, 0.376, 0.400, 0.298, 0.664};
-  static const double kShared[SPLIT_TILE_COUNT] = {0.423, 0.424, 0.250, 0.340, 0.248, 0.166, 0.613};
+SplitPlan plan_split(const CorrArgs& base, const SplitGrid& grid, int64_t out_elems, bool half, int64_t bf16_S) {
+  struct Costs {
+    double alone[SPLIT_TILE_COUNT], shared[SPLIT_TILE_COUNT], patch_alone, patch_shared, slices, slice_mb;
+  };
+  static const Costs kCosts[2] = {{{0.457, 0.444, 0.414, 0.376, 0.400, 0.298, 0.664}, {0.423, 0.424, 0.250, 0.340, 0.248, 0.166, 0.613}, 0.39, 0.25, 3.3, 0.46},
+                                  {{0.356, 0.358, 0.309, 0.301, 0.300, 0.250, 0.494}, {0.260, 0.265, 0.165, 0.227, 0.175, 0.118, 0.387}, 0.19, 0.154, 1.8, 0.472}};
+  const Costs& c = kCosts[half];
   SplitPlan plan = {};
   plan.tile = -1;
+  plan.half = half;
   const bool columns = grid.f.subs != 0, image = grid.f.ff == 1 && !columns;
+  const int64_t chunks = ceil_div(grid.f.V, columns ? 64 : 16);
+  plan.bf16_cps = bf16_S ? ceil_div(chunks, bf16_S) : 0;
   const int64_t T = grid.TH * grid.TW, PH = base.P / base.PW, ext = (grid.TH - 1) * grid.dh + 1;
   if (!columns) {
     plan.w = patch_dim(base.PW, grid.sw, (grid.TW - 1) * grid.dw + 1, image ? base.pw : 0, base.IW);
     plan.h = patch_dim(PH, grid.sh, ext, image ? base.ph : 0, base.IH);
   }
-  const int64_t chunks = ceil_div(grid.f.V, columns ? 64 : 16);
   const double out_mb = 4e-6 * (double)out_elems;
   double best = 0;
   for (int32_t t = 0; t < SPLIT_TILE_COUNT; ++t) {
@@ -547,10 +585,11 @@ SplitPlan plan_split(const CorrArgs& base, const SplitGrid& grid, int64_t out_el
     for (int64_t S = 1; S <= 16 && S <= chunks; ++S) {
       if (S > 1 && (units * S > 2048 || units > 512)) break;
       const int64_t per_cu = ceil_div(units * S, 256), cps = ceil_div(chunks, S);
+      if (half && !corr_half_interval(base, t, mt, T, chunks, cps, plan.bf16_cps)) continue;
       const double steps = (double)(cps * spc);
-      double cost = per_cu == 1 ? steps * kAlone[t] + 0.39 * (double)cps * units_per_thread
-                                : (double)per_cu * (steps * kShared[t] + 0.25 * (double)cps * units_per_thread);
-      if (S > 1) cost += 3.3 + 0.46 * (double)S * out_mb;
+      double cost = per_cu == 1 ? steps * c.alone[t] + c.patch_alone * (double)cps * units_per_thread
+                                : (double)per_cu * (steps * c.shared[t] + c.patch_shared * (double)cps * units_per_thread);
+      if (S > 1) cost += c.slices + c.slice_mb * (double)S * out_mb;
       if (plan.tile < 0 || cost < best) {
         best = plan.cost = cost;
         plan.tile = t;
@@ -561,6 +600,16 @@ SplitPlan plan_split(const CorrArgs& base, const SplitGrid& grid, int64_t out_el
     }
   }
   return plan;
+}
+
+// The cheaper of the two splits.  The f16 one's pack kernel samples both blobs: 3 us more, and 0.26 us a MB of weights.
+SplitPlan plan_split(const CorrArgs& base, const SplitGrid& grid, int64_t out_elems) {
+  const SplitPlan bf16 = plan_split(base, grid, out_elems, false, 0);
+  if (bf16.tile < 0 || grid.f.ff > 1) return bf16;
+  SplitPlan f16 = plan_split(base, grid, out_elems, true, bf16.S);
+  if (f16.tile < 0) return bf16;
+  f16.cost += 3 + 0.26 * 4e-6 * (double)base.G * base.Mrows * base.Kred;
+  return f16.cost < bf16.cost ? f16 : bf16;
 }
 
 // Decides whether corr_split_kernel runs this correlation; fills a, k and the tile.  Returns the bytes of packed
@@ -654,7 +703,16 @@ size_t configure_split(const CorrArgs& base, const PackArgs& pbase, int64_t cg_i
   a.ksplit = (int32_t)ceil_div(chunks, a.chunks_per_split);
   k.split_chunks = a.NS;
   // Six bytes a packed weight and the slices: a workspace beyond the boundary's 2^30 elements stays with the fp32 kernel (four).
-  const int64_t bytes = (int64_t)a.G * a.m_tiles * chunks * ceil_div(a.THW, mt == 32 ? 1 : 2) * (bm / mt) * 3072;
+  int64_t bytes = (int64_t)a.G * a.m_tiles * chunks * ceil_div(a.THW, mt == 32 ? 1 : 2) * (bm / mt) * 3072;
+  if (plan.half) {
+    a.half = k.half = 1;
+    a.lead_steps = corr_half_interval(base, tile, mt, a.THW, chunks, a.chunks_per_split, plan.bf16_cps);
+    const uint32_t stage = pixels ? split_half_stage(4, bn) : split_half_stage(columns ? 4 : split_patch_units(a.PSZ, bn), 0);
+    a.patch_stages = 2 * stage + split_half_lead(bm, bn) <= 80 * 1024 ? 2 : 1;  // two workgroups per compute unit
+    k.in_elems = a.in_bytes / 4;
+    k.w_elems = (uint32_t)(pbase.G * pbase.Kg * pbase.Cg * pbase.kh * pbase.kw);
+    bytes += kSampleBytes;
+  }
   if (bytes + (a.ksplit > 1 ? 4 * a.ksplit * out_elems : 0) >= 4 * kMaxElems) {
     tile = -1;
     return 0;
@@ -682,35 +740,55 @@ int32_t configure_wgrad_split(const WgradArgs& w, int32_t fp32_tile, int64_t N, 
   // Tile and splits by modelled time (us), as in configure_split: a chunk is four steps; a fit to 580 timings of
   // all tiles and 1 to 12 quarters of a resident grid on the same layers (rms error 5 %; the choice is 1 % behind the
   // best on average, 12 % at worst).
-  static const double kAlone[WSPLIT_TILE_COUNT] = {1.40, 1.19, 1.18, 1.06, 0.64, 1.04};
-  static const double kShared[WSPLIT_TILE_COUNT] = {1.09, 0.985, 0.97, 0.90, 0.52, 0.89};
+  // The second line, for the f16 terms, is a fit to 589 timings of 20 layers of 1 to 57 GFLOP (6 %; 1 % and 7 %); their samples
+  // cost 3 us.  They take sums of one slice long enough for them.
+  struct Costs {
+    double alone[WSPLIT_TILE_COUNT], shared[WSPLIT_TILE_COUNT], patch_alone, patch_shared, slice_mb, workgroup, fixed;
+  };
+  static const Costs kCosts[2] = {{{1.40, 1.19, 1.18, 1.06, 0.64, 1.04}, {1.09, 0.985, 0.97, 0.90, 0.52, 0.89}, 0.37, 0.16, 0.66, 0.73, 0},
+                                  {{0.973, 0.854, 0.866, 0.785, 0.525, 0.819}, {0.708, 0.650, 0.622, 0.566, 0.380, 0.633}, 0.339, 0.187, 0.556, 2.07, 3.2}};
   const int64_t chunks = ceil_div(total_runs, chunk_runs), max_by_ws = ((int64_t)8 << 20) / w_elems;
   const double units_per_thread = (double)split_patch_units(psz), w_mb = 4e-6 * (double)w_elems;
-  int32_t best = -1;
+  int32_t best = -1, best_lead = 0;
   int64_t best_cps = 0;
   double best_cost = 0, least_work = 0;
-  for (int32_t t = 0; t < WSPLIT_TILE_COUNT; ++t) {
-    int32_t rows, taps;
-    wgrad_split_shape(t, &rows, &taps);
-    const double work = (double)round_up(w.Kg, rows) * (double)round_up(w.khw, taps) * (double)(16 * c16);
-    if (least_work == 0 || work < least_work) least_work = work;
-    const int64_t tiles = (int64_t)w.G * ceil_div(w.Kg, rows) * ceil_div(w.khw, taps) * c16;
-    for (int64_t places = 256; places <= 512; places += 256) {
-      int64_t S = places / tiles;
-      if (S > max_by_ws) S = max_by_ws;
-      if (S > 256) S = 256;
-      if (S > chunks) S = chunks;
-      if (S < 1) S = 1;
-      const int64_t cps = ceil_div(chunks, S), per_cu = ceil_div(tiles * ceil_div(chunks, cps), 256);
-      const double cost = 0.66 * (double)S * w_mb + 0.73 * (double)per_cu +
-                          (per_cu == 1 ? (double)cps * (4 * kAlone[t] + 0.37 * units_per_thread)
-                                       : (double)(per_cu * cps) * (4 * kShared[t] + 0.16 * units_per_thread));
-      if (best < 0 || cost < best_cost) {
-        best = t;
-        best_cost = cost;
-        best_cps = cps;
+  const double chunk_pix = (double)w.ncols / (double)chunks;
+  // The samples are of four neighbours.  Blocks and runs that hold less than 45 % of real work stay with what the bf16 terms are
+  // compared with (20 -> 320, 5x5 at 2x3, 42 %: 137 us fp32, 142 bf16 terms, 118 f16 terms).
+  const auto half_fits = [&](double work) {
+    return w.x_bytes >= 16 && w.dy_bytes >= 16 && work * 8.0 * (double)total_runs <= 2.2 * (double)w.Kg * w.Kred * (double)w.ncols;
+  };
+  int64_t bf16_cps = 0;  // of the best plan on bf16 terms
+  for (int half = 0; half < 2; ++half) {
+    const Costs& c = kCosts[half];
+    for (int32_t t = 0; t < WSPLIT_TILE_COUNT; ++t) {
+      int32_t rows, taps;
+      wgrad_split_shape(t, &rows, &taps);
+      const double work = (double)round_up(w.Kg, rows) * (double)round_up(w.khw, taps) * (double)(16 * c16);
+      if (least_work == 0 || work < least_work) least_work = work;
+      if (half && !half_fits(work)) continue;
+      const int64_t tiles = (int64_t)w.G * ceil_div(w.Kg, rows) * ceil_div(w.khw, taps) * c16;
+      for (int64_t places = 256; places <= 512; places += 256) {
+        int64_t S = places / tiles;
+        if (S > max_by_ws) S = max_by_ws;
+        if (S > 256) S = 256;
+        if (S > chunks) S = chunks;
+        if (S < 1) S = 1;
+        const int64_t cps = ceil_div(chunks, S), per_cu = ceil_div(tiles * ceil_div(chunks, cps), 256);
+        const int32_t lead = half ? half_interval(chunk_pix * (double)cps, chunk_pix * (double)bf16_cps, chunk_pix, 1) : 0;
+        if (half && !lead) continue;
+        const double cost = c.fixed + c.slice_mb * (double)S * w_mb + c.workgroup * (double)per_cu +
+                            (per_cu == 1 ? (double)cps * (4 * c.alone[t] + c.patch_alone * units_per_thread)
+                                         : (double)(per_cu * cps) * (4 * c.shared[t] + c.patch_shared * units_per_thread));
+        if (best < 0 || cost < best_cost) {
+          best = t;
+          best_cost = cost;
+          best_cps = cps;
+          best_lead = lead;
+        }
       }
     }
+    bf16_cps = best_cps;
   }
   // Fewer chunks than that cannot be shared out (4 chunks, 0.5 GFLOP: 18.8 us fp32, 21.2 split; 5, 2.4 GFLOP: 58.6, 62.9).
   if (chunks < 8) return -1;
@@ -776,6 +854,12 @@ int32_t configure_wgrad_split(const WgradArgs& w, int32_t fp32_tile, int64_t N, 
   a.chunks = (int32_t)chunks;
   a.chunks_per_split = (int32_t)best_cps;
   a.S = (int32_t)ceil_div(chunks, best_cps);
+  if (best_lead) {
+    a.half = 1;
+    a.lead_chunks = best_lead;
+    const uint32_t rest = 2 * 4 * 8 * (uint32_t)chunk_runs + split_half_lead(rows, 16 * taps);
+    a.patch_stages = 128 * (uint32_t)a.PSZ + rest <= 80 * 1024 ? 2 : 1;  // two workgroups per compute unit
+  }
   const int64_t tiles = (int64_t)a.G * a.m_tiles * a.n_tiles;
   if (a.S * (w_elems + a.n_tiles * K) >= kMaxElems || tiles * a.S >= ((int64_t)1 << 31)) return -1;
   return best;
@@ -1176,8 +1260,11 @@ int launch_split(int32_t tile, const PackSplitArgs& pack, const CorrSplitArgs& p
   PackSplitArgs k = pack;
   k.w = w;
   k.A = static_cast<float*>(ws);
+  k.in = in;
+  k.scale = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + pack_bytes - kSampleBytes);
   if (const int e = launch_pack_split(tile, k, stream)) return e;
   CorrSplitArgs a = plan;
+  a.scale = k.scale;
   a.A = k.A;
   a.in = in;
   a.bias = bias;
@@ -1990,8 +2077,8 @@ static int create_desc(conv_desc_t** out, const conv_params_t* pp, bool one_laun
       int32_t rows, taps;
       wgrad_split_shape(d->wg_split, &rows, &taps);
       const int32_t psz = d->wg_sp.PSZ;
-      snprintf(wg, sizeof(wg), "splitwgrad_%dx%dx16[p%d,st%d](S=%d,L=2)", rows, taps, split_patch_units(psz),
-               d->wg_sp.patch_stages, d->wg_sp.S);
+      snprintf(wg, sizeof(wg), "splitwgrad_%dx%dx16[p%d,st%d](S=%d,%sL=2)", rows, taps, split_patch_units(psz),
+               d->wg_sp.patch_stages, d->wg_sp.S, d->wg_sp.half ? "half," : "");
     }
     small_names(d, 0, f, b, wg, sizeof(f));
     if (d->use_direct) {

@@ -125,7 +125,21 @@ struct CorrSplitArgs : CorrArgs {
   SplitFold fold;            // what the patch's grid and channels stand for
   int32_t patch_stages;      // patch stages in LDS (1 or 2)
   int32_t share_w, share_h;  // padding columns / rows that neighbouring patch rows / images share
+  // f16 split (split_f16.h): steps between two moves of the sums' leading bits, and what the pack kernel leaves behind the
+  // packed weights: the largest value of each of its samples of the input, and the weights' power of two
+  int32_t half, lead_steps;
+  uint32_t* scale;
 };
+
+constexpr int kSampleBlocks = 64;
+constexpr uint32_t kSampleBytes = 512;  // kSampleBlocks + 1 words, kept to whole lines
+
+// LDS of the f16 form: a patch stage of units_per_thread units (the pixel form, of tiles of bn columns: four groups of bn + 1
+// positions and two halves), and the leading bits of a tile's sums.
+constexpr uint32_t split_half_stage(int32_t units_per_thread, int32_t pixel_bn) {
+  return 32u * (uint32_t)(pixel_bn ? 8 * (pixel_bn + 1) : 256 * units_per_thread);
+}
+constexpr uint32_t split_half_lead(int32_t bm, int32_t bn) { return 2u * (uint32_t)(bm * bn); }
 
 constexpr int kPatchEPT = 3;  // patch elements per thread and channel: PSZ <= 3 * 256
 
@@ -155,6 +169,10 @@ struct PackArgs {
 struct PackSplitArgs : PackArgs {
   int32_t split_chunks;  // chunks of 16 channels
   SplitFold fold;
+  int32_t half;          // the f16 split: `in`, the gathered blob, and the weights are sampled
+  const float* in;
+  uint32_t in_elems, w_elems;
+  uint32_t* scale;
 };
 
 // Backward filter: part[s][g][k][nn] = sum over the split's columns of dy * gathered x.
@@ -203,6 +221,7 @@ struct WgradSplitArgs {
   // patch geometry (see corr_split_kernel)
   int32_t PWID, PSZ, ext, share_h, patch_stages;
   Magic mPWID, mRSEG;
+  int32_t half, lead_chunks;  // f16 split: chunks between two moves of the sums' leading bits
 };
 
 // One-launch kernels of small layers (kernels_small.hip); the pointer members address floats or doubles.

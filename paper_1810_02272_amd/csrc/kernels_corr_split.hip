@@ -23,6 +23,12 @@
 // 13x13) 292 -> 174 and 309 -> 200; 6.7 GFLOP (45 -> 77, 3x5 at 51x67, stride 2 x 1) 92 -> 52 and 87 -> 50; 1.3 GFLOP (32 ->
 // 32, 5x5 at 16x16, batch 100) 29 -> 21.  172 and 115 us are the matrix instructions of the first two at 2000 TFLOP/s.
 //
+// TERMS 2: long reductions on two f16 terms (split_f16.h), half the matrix instructions.  The stage is [h, m][half][position] then,
+// 16 bytes a position.  The same passes: 57.3 GFLOP 249 -> 162 us and 269 -> 171, 38.3 GFLOP 172 -> 108 and 206 -> 129, 6.7 GFLOP 49
+// -> 38 and 53 -> 41; the pack kernel, which samples both blobs, 0.5 to 1.4 us more.  The matrix unit is busy 60 % of the cycles, at
+// the clock that the chip's power leaves (1.7 GHz); a quarter of the waves' time are waits for weights, patches and barriers.  Weights
+// two steps ahead gave nothing (108 -> 112 us where the registers hold them, spills elsewhere).
+//
 // Forms (SplitFold).  Folded taps: 3 -> 96 channels, 11x11, stride 4 at 227x227, batch 128, forward 254 -> 195 us; busy 46 %,
 // the folded patch's loads and splits (3 vector instructions to a matrix one) and 30 % of padding take the rest.  Columns
 // of 1x1 kernels use a patch element once per row tile, so splitting weighs most there: inner product 128 x 9216 -> 4096, data
@@ -34,12 +40,15 @@
 #include "device_utils.h"
 #include "internal.h"
 #include "split_bf16.h"
+#include "split_f16.h"
 
 namespace mi355conv {
 
 namespace {
 
 constexpr int kThreads = 256;
+
+typedef __attribute__((address_space(4))) uint32_t ConstWord;  // read-only for the whole kernel: scalar loads
 
 template <int MT, int MB, int NB, int WM, int WN>
 struct SplitCfg {
@@ -53,6 +62,7 @@ struct SplitCfg {
   // per step and, on small grids, alone on their SIMD: A operands several steps ahead.
   static constexpr bool BDEEP = MT == 32 && MB * NB >= 4;
   static constexpr int DEPTH = BDEEP || MT == 16 ? 1 : MB == 3 ? 2 : NB == 2 ? 3 : 8;
+  static constexpr bool LEAD_STEPS = DEPTH <= 2;  // leading bits move between steps, else between chunks
   static constexpr int WAVES = MT == 32 && MB == 1 && NB == 2 ? 3 : 2;
   static_assert(WM * WN == 4, "four waves per workgroup");
 };
@@ -61,12 +71,17 @@ enum SplitForm { IMAGE, FOLDED, COLUMNS, PIXELS };  // PIXELS: COLUMNS over imag
 
 // EPT: patch units (one position x 8 channels) per thread, 2*PSZ <= 256*EPT.
 // FORM: what the patch holds (SplitFold in internal.h).
-template <int MT, int MB, int NB, int WM, int WN, int EPT, SplitForm FORM>
+// TERMS: 3 the bf16 split, 2 the f16 split.
+template <int MT, int MB, int NB, int WM, int WN, int EPT, SplitForm FORM, int TERMS>
 __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) void corr_split_kernel(const CorrSplitArgs a) {
   using C = SplitCfg<MT, MB, NB, WM, WN>;
   using M = Mfma<MT>;
   constexpr int BM = C::BM, BN = C::BN;
-  constexpr bool FOLD = FORM == FOLDED, PIX = FORM == PIXELS, COLS = FORM == COLUMNS || PIX;
+  constexpr bool FOLD = FORM == FOLDED, PIX = FORM == PIXELS, COLS = FORM == COLUMNS || PIX, HALF = TERMS == 2;
+  static_assert(!(FOLD && HALF), "the folded form's reductions are short");
+  // Bytes from one position of a stage to the next and from one term to the next: bf16 [half][position][h, m, l], f16
+  // [h, m][half][position].
+  constexpr uint32_t POS = HALF ? 16 : 48, TERM = HALF ? split_half_stage(EPT, PIX ? BN : 0) / 2 : 16;
 
   extern __shared__ __align__(16) float smem[];  // one or two patch stages; the epilogue's tables at the end
 
@@ -121,7 +136,7 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
     const uint32_t pix = col - n * a.P;
     const uint32_t pa = mdiv(pix, a.mPW);
     const uint32_t pb = pix - pa * a.PW;
-    lanebase[j] = 48u * (COLS ? col - col0 + half * (uint32_t)a.PSZ
+    lanebase[j] = POS * (COLS ? col - col0 + half * (uint32_t)a.PSZ
                               : patch_row_base(n, pa) * (uint32_t)a.PWID + pb * a.sw + half * (uint32_t)a.PSZ);
   }
 
@@ -129,7 +144,7 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
   const __amdgpu_buffer_rsrc_t in_rsrc =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.in), 0, (int)a.in_bytes, 0x00020000);
   const uint32_t chan_bytes = 4u * (uint32_t)a.IHW;
-  const uint32_t stage_bytes = 96u * (uint32_t)a.PSZ;
+  const uint32_t stage_bytes = HALF ? 2 * TERM : 96u * (uint32_t)a.PSZ;
   FoldEntry* const fold_tab =
       reinterpret_cast<FoldEntry*>(reinterpret_cast<char*>(smem) + (uint32_t)a.patch_stages * stage_bytes);
   if (FOLD) {
@@ -219,16 +234,34 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
     }
   };
   const SplitSel sel;
+  HalfScale in_scale(0);
+  int w_scale = 0;
+  if constexpr (HALF) {  // the pack kernel's samples: uniform, through scalar loads
+    const ConstWord* const sample = (const ConstWord*)(uintptr_t)a.scale;
+    uint32_t top = 0;
+#pragma unroll
+    for (int i = 0; i < kSampleBlocks; ++i) top = sample[i] > top ? sample[i] : top;
+    in_scale = HalfScale(half_scale(top));
+    w_scale = (int)sample[kSampleBlocks];
+  }
   auto patch_store = [&](uint32_t stage_off) {
 #pragma unroll
     for (int r = 0; r < EPT; ++r) {
-      const Split8 s = split8(pr[r], sel);
       const uint32_t u = slot0 + r * kSlotStep;
-      if (PIX || u < 2u * (uint32_t)a.PSZ) {
-        u32x4* dst = reinterpret_cast<u32x4*>(reinterpret_cast<char*>(smem) + (stage_off + 48u * u));
-        dst[0] = s.h;
-        dst[1] = s.m;
-        dst[2] = s.l;
+      u32x4* dst = reinterpret_cast<u32x4*>(reinterpret_cast<char*>(smem) + (stage_off + POS * u));
+      if constexpr (HALF) {
+        const SplitHalf8 s = split_half8(pr[r], in_scale);
+        if (PIX || u < 2u * (uint32_t)a.PSZ) {
+          dst[0] = s.h;
+          dst[TERM / 16] = s.m;
+        }
+      } else {
+        const Split8 s = split8(pr[r], sel);
+        if (PIX || u < 2u * (uint32_t)a.PSZ) {
+          dst[0] = s.h;
+          dst[1] = s.m;
+          dst[2] = s.l;
+        }
       }
       __builtin_amdgcn_sched_barrier(0);  // one unit's terms in registers at a time
     }
@@ -248,10 +281,10 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
 #pragma unroll
   for (int i = 0; i < MB; ++i) alane[i] = 16u * lane + (uint32_t)(wm * MB + i) * 3u * C::FRAG;
   constexpr int DEPTH = C::DEPTH;
-  u32x4 av[DEPTH][MB][3];
+  u32x4 av[DEPTH][MB][TERMS];
   auto load_a = [&](int d, uint32_t step_off, int i) {
 #pragma unroll
-    for (int q = 0; q < 3; ++q)
+    for (int q = 0; q < TERMS; ++q)
       av[d][i][q] = __builtin_bit_cast(
           u32x4, __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, alane[i] + q * C::FRAG, (int)step_off, 0));
   };
@@ -282,7 +315,7 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
   // ---- main loop: one step = one tap (two for the 16-row instruction) of one chunk ----
   // Position of the step's tap in the patch, advanced tap by tap; behind the last tap it stays (the 16-row
   // instruction reads it once more when their number is odd, against zero weights).
-  const uint32_t tap_w = 48u * (uint32_t)a.dw, tap_h = 48u * (uint32_t)(a.dh * a.PWID) - tap_w * (uint32_t)(a.TW - 1);
+  const uint32_t tap_w = POS * (uint32_t)a.dw, tap_h = POS * (uint32_t)(a.dh * a.PWID) - tap_w * (uint32_t)(a.TW - 1);
   uint32_t pos = 0;
   int tap = 0, tj = 0;
   auto next_tap = [&]() {
@@ -296,7 +329,7 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
       }
     }
   };
-  auto load_b = [&](u32x4(&bv)[NB][3]) {  // the step's B operands; moves on to the next step
+  auto load_b = [&](u32x4(&bv)[NB][TERMS]) {  // the step's B operands; moves on to the next step
     uint32_t off = pos;
     next_tap();
     if (MT == 16) {  // the upper two k groups take the second tap
@@ -307,13 +340,13 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
     for (int j = 0; j < NB; ++j) {
       const u32x4* src = reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(smem) + (lanebase[j] + off));
 #pragma unroll
-      for (int q = 0; q < 3; ++q) bv[j][q] = src[q];
+      for (int q = 0; q < TERMS; ++q) bv[j][q] = src[q * (TERM / 16)];
     }
   };
   // One step.  A row block's A registers are reloaded with the step DEPTH ahead as soon as its last product
   // is under way; the scheduling barriers keep the compiler from holding more operands than the registers
   // have room for.
-  auto run_step = [&](int d, const u32x4(&bv)[NB][3]) {
+  auto run_step = [&](int d, const u32x4(&bv)[NB][TERMS]) {
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
       mfma_split<MT, NB>(av[d][i], bv, acc[i], lo[i]);
@@ -325,6 +358,36 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
   const bool two = a.patch_stages == 2;
   uint32_t stage = 0;
   int cc = cc_first;
+  // f16: every a.lead_steps steps the large sums' leading bits move to LDS, a place of its own for every lane.
+  constexpr int LEAD = MB * NB * M::NR / 8;  // 16-byte groups of eight sums
+  const Leading16 leading;
+  int since = 0;
+  bool led = false;
+  u32x4* const lead = reinterpret_cast<u32x4*>(reinterpret_cast<char*>(smem) + (uint32_t)a.patch_stages * stage_bytes) + t;
+  auto move_leading = [&]() {
+#pragma unroll
+    for (int q = 0; q < LEAD; ++q) {
+      u32x4 w = {0, 0, 0, 0};
+      if (led) w = lead[q * kThreads];
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        float x = acc[(8 * q + 2 * p) / M::NR / NB][(8 * q + 2 * p) / M::NR % NB][(8 * q + 2 * p) % M::NR], y = acc[(8 * q + 2 * p) / M::NR / NB][(8 * q + 2 * p) / M::NR % NB][(8 * q + 2 * p) % M::NR + 1];
+        leading.give(w[p], x, y);
+        w[p] = leading.take(x, y);
+        acc[(8 * q + 2 * p) / M::NR / NB][(8 * q + 2 * p) / M::NR % NB][(8 * q + 2 * p) % M::NR] = x;
+        acc[(8 * q + 2 * p) / M::NR / NB][(8 * q + 2 * p) / M::NR % NB][(8 * q + 2 * p) % M::NR + 1] = y;
+      }
+      lead[q * kThreads] = w;
+    }
+    led = true;
+  };
+  auto count_steps = [&](int steps) {
+    since += steps;
+    if (HALF && since >= a.lead_steps) {
+      move_leading();
+      since = 0;
+    }
+  };
   auto begin_chunk = [&]() {
     if (cc + 1 < cc_end) patch_load(cc + 1);
     pos = stage;
@@ -333,6 +396,7 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
   // Two stages: the next chunk's patch goes to the other one, whose last readers passed the last barrier; one
   // stage: to the only one, once every wave has read it.
   auto end_chunk = [&]() {
+    if (!C::LEAD_STEPS) count_steps(SPC);
     if (two)
       stage = stage ? 0 : stage_bytes;
     else
@@ -342,7 +406,7 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
   };
   if constexpr (C::BDEEP) {  // the next step's B operands are read at the start of a step
     static_assert(DEPTH == 1, "A one step ahead");
-    u32x4 bX[NB][3], bY[NB][3];
+    u32x4 bX[NB][TERMS], bY[NB][TERMS];
     while (cc < cc_end) {
       begin_chunk();
       load_b(bX);
@@ -353,11 +417,12 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
           load_b(bX);
           run_step(0, bY);
         }
+        count_steps(2);
       }
       end_chunk();
     }
   } else {
-    u32x4 bv[NB][3];
+    u32x4 bv[NB][TERMS];
     int s = 0;
     begin_chunk();
     while (cc < cc_end) {
@@ -366,6 +431,7 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
         if (cc < cc_end) {
           load_b(bv);
           run_step(d, bv);
+          if (C::LEAD_STEPS) count_steps(1);
           if (++s == SPC) {
             s = 0;
             end_chunk();
@@ -374,12 +440,31 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
         }
     }
   }
+  if constexpr (HALF) {
+    const int back = -(in_scale.e + w_scale);
 #pragma unroll
-  for (int i = 0; i < MB; ++i)
+    for (int q = 0; q < LEAD; ++q) {
+      u32x4 w = {0, 0, 0, 0};
+      if (led) w = lead[q * kThreads];
 #pragma unroll
-    for (int j = 0; j < NB; ++j)
+      for (int p = 0; p < 4; ++p) {
+        const int e = 8 * q + 2 * p, i = e / M::NR / NB, j = e / M::NR % NB, r = e % M::NR;
+        constexpr float down = 1.f / (float)(1 << kHalfShift);
+        // the small sums first: they are of the size of what the leading bits left
+        float x = __builtin_fmaf(lo[i][j][r], down, acc[i][j][r]), y = __builtin_fmaf(lo[i][j][r + 1], down, acc[i][j][r + 1]);
+        leading.give(w[p], x, y);
+        acc[i][j][r] = scale_by(x, back);
+        acc[i][j][r + 1] = scale_by(y, back);
+      }
+    }
+  } else {
 #pragma unroll
-      for (int r = 0; r < M::NR; ++r) acc[i][j][r] = (acc[i][j][r] + lo[i][j][r]) * kSplitUnscale;
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int r = 0; r < M::NR; ++r) acc[i][j][r] = (acc[i][j][r] + lo[i][j][r]) * kSplitUnscale;
+  }
 
   // ---- sums that are not finite once more on the fp32 matrix instructions (the weights put back together exactly, the
   // inputs as they are in memory): an infinity or NaN among the operands makes the split's differences NaN where the plain
@@ -461,7 +546,8 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
             const int sh = 16 * (e & 1);
-            const float v = join_bf16((uint16_t)(w[0][e >> 1] >> sh), (uint16_t)(w[1][e >> 1] >> sh), (uint16_t)(w[2][e >> 1] >> sh));
+            const uint16_t wh = (uint16_t)(w[0][e >> 1] >> sh), wmid = (uint16_t)(w[1][e >> 1] >> sh), wl = (uint16_t)(w[2][e >> 1] >> sh);
+            const float v = HALF ? join_f16(wh, wmid, wl, w_scale) : join_bf16(wh, wmid, wl);
 #pragma unroll
             for (int j = 0; j < NB; ++j) M::run(v, b[j][e], acc[i][j]);
           }
@@ -472,15 +558,60 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
   corr_epilogue<MT, MB, NB, BM, BN>(a, smem, acc, m_tile, col_tile, g, wm, wn, split);
 }
 
+// Largest of a workgroup's sampled values, in bits.
+template <int COUNT>
+__device__ __forceinline__ uint32_t sample_top(const float (&v)[COUNT]) {
+  __shared__ uint32_t top[4];
+  uint32_t m = 0;
+#pragma unroll
+  for (int i = 0; i < COUNT; ++i) {
+    const uint32_t u = sample_bits(v[i]);
+    m = u > m ? u : m;
+  }
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t u = (uint32_t)__shfl_xor((int)m, d);
+    m = u > m ? u : m;
+  }
+  if ((threadIdx.x & 63) == 0) top[threadIdx.x >> 6] = m;
+  __syncthreads();
+  const uint32_t a = top[0] > top[1] ? top[0] : top[1], b = top[2] > top[3] ? top[2] : top[3];
+  return a > b ? a : b;
+}
+
 // Packs the weights into A fragments: thread = (group, m tile, step, row block, lane), eight k values each.  Few
 // workgroups whose time is one chain of index arithmetic, loads and stores: the divisions are per thread, not
 // per k value (96 -> 256 in two groups, 5x5: 10.2 -> 7.4 us; 128 x 4096 rows: 7.2 -> 4.9).
-template <int MT>
+// TERMS 2: the f16 split.  Every workgroup takes the weights' power of two from the same 2048 of them; kSampleBlocks more
+// workgroups leave the largest of 4096 gathered values each.
+template <int MT, int TERMS>
 __global__ __launch_bounds__(256) void pack_split_kernel(const PackSplitArgs a, int blocks, int m_tiles, uint32_t total) {
   const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
-  if (idx >= total) return;
+  constexpr int kSamples = 16;  // per thread
+  float sample[TERMS == 2 ? kSamples : 1];
+  const uint32_t pack_blocks = (total + 255u) / 256u;
+  if constexpr (TERMS == 2) {
+    if (blockIdx.x >= pack_blocks) {
+      const uint32_t j0 = (idx - pack_blocks * 256u) * (kSamples / 4);
+#pragma unroll
+      for (int i = 0; i < kSamples / 4; ++i) {  // four neighbours each, spread evenly
+        const float* const at = a.in + (uint32_t)((uint64_t)(j0 + i) * (a.in_elems - 4u) / (kSampleBlocks * 256 * kSamples / 4));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sample[4 * i + e] = at[e];
+      }
+      const uint32_t top = sample_top(sample);
+      if (threadIdx.x == 0) a.scale[blockIdx.x - pack_blocks] = top;
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < kSamples; ++i) sample[i] = 0.f;
+    const float* const at = a.w + (uint32_t)((uint64_t)threadIdx.x * (a.w_elems - 8u) / 256u);  // eight neighbours
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sample[i] = at[i];
+  }
+  if (TERMS == 3 && idx >= total) return;
   const int lane = idx & 63;
-  uint32_t lin = idx >> 6;
+  uint32_t lin = (idx < total ? idx : total - 1) >> 6;  // whole waves: total is a multiple of 64
   const int blk = (int)(lin % (uint32_t)blocks);
   lin /= (uint32_t)blocks;
   const int T = a.tTHW, tps = MT == 32 ? 1 : 2, spc = (T + tps - 1) / tps;
@@ -531,8 +662,17 @@ __global__ __launch_bounds__(256) void pack_split_kernel(const PackSplitArgs a, 
     }
   }
   uint16_t out[3][8];
+  if constexpr (TERMS == 2) {
+    const HalfScale s(half_scale(sample_top(sample)));
+    if (idx == 0) a.scale[kSampleBlocks] = (uint32_t)s.e;
+    if (idx >= total) return;
+    const bool small = half_too_small(v, s);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) split1(v[e], out[0][e], out[1][e], out[2][e]);
+    for (int e = 0; e < 8; ++e) split_half1(v[e], s.e, small, out[0][e], out[1][e], out[2][e]);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) split1(v[e], out[0][e], out[1][e], out[2][e]);
+  }
   char* dst = reinterpret_cast<char*>(a.A) + (size_t)(idx >> 6) * 3072u + 16u * lane;
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
@@ -543,17 +683,26 @@ __global__ __launch_bounds__(256) void pack_split_kernel(const PackSplitArgs a, 
   }
 }
 
-template <int MT, int MB, int NB, int WM, int WN, int EPT, SplitForm FORM = IMAGE>
-int launch_split_e(const CorrSplitArgs& a, hipStream_t s) {
+template <int MT, int MB, int NB, int WM, int WN, int EPT, SplitForm FORM, int TERMS>
+int launch_split_k(const CorrSplitArgs& a, hipStream_t s) {
   using C = SplitCfg<MT, MB, NB, WM, WN>;
   const size_t tables = 16 * (C::BM + C::BN);
-  const size_t patch = 96 * (size_t)a.PSZ * a.patch_stages + (FORM == FOLDED ? a.NS * 16 * sizeof(FoldEntry) : 0);
+  const size_t patch = TERMS == 2 ? (size_t)split_half_stage(EPT, FORM == PIXELS ? C::BN : 0) * a.patch_stages + split_half_lead(C::BM, C::BN)
+                                  : 96 * (size_t)a.PSZ * a.patch_stages + (FORM == FOLDED ? a.NS * 16 * sizeof(FoldEntry) : 0);
   const size_t lds = patch > tables ? patch : tables;
   static LdsOptIn opt_in;  // more than 64 KB of LDS needs an explicit opt-in, once per process
-  if (const int e = lds_opt_in(opt_in, &corr_split_kernel<MT, MB, NB, WM, WN, EPT, FORM>, 160 * 1024)) return e;
+  if (const int e = lds_opt_in(opt_in, &corr_split_kernel<MT, MB, NB, WM, WN, EPT, FORM, TERMS>, 160 * 1024)) return e;
   const uint32_t blocks = (uint32_t)a.G * a.m_tiles * a.col_tiles * a.ksplit;
-  hipLaunchKernelGGL((corr_split_kernel<MT, MB, NB, WM, WN, EPT, FORM>), dim3(blocks), dim3(kThreads), lds, s, a);
+  hipLaunchKernelGGL((corr_split_kernel<MT, MB, NB, WM, WN, EPT, FORM, TERMS>), dim3(blocks), dim3(kThreads), lds, s, a);
   return (int)hipGetLastError();
+}
+
+template <int MT, int MB, int NB, int WM, int WN, int EPT, SplitForm FORM = IMAGE>
+int launch_split_e(const CorrSplitArgs& a, hipStream_t s) {
+  if constexpr (FORM != FOLDED)
+    if (a.half) return launch_split_k<MT, MB, NB, WM, WN, EPT, FORM, 2>(a, s);
+  if (a.half) return (int)hipErrorInvalidValue;
+  return launch_split_k<MT, MB, NB, WM, WN, EPT, FORM, 3>(a, s);
 }
 
 // The folded and the column forms: one instance per 128-column tile, for the largest patch; no rule leads a 1x1 kernel to
@@ -604,11 +753,10 @@ int launch_pack_split(int32_t tile, const PackSplitArgs& a, void* stream) {
   const int tps = mt == 32 ? 1 : 2, spc = (a.tTHW + tps - 1) / tps, blocks = bm / mt;
   const int m_tiles = (a.Mrows + bm - 1) / bm;
   const uint32_t total = (uint32_t)a.G * m_tiles * (uint32_t)(a.split_chunks * spc) * blocks * 64u;
-  const dim3 grid((total + 255) / 256);
-  if (mt == 32)
-    hipLaunchKernelGGL(pack_split_kernel<32>, grid, dim3(256), 0, (hipStream_t)stream, a, blocks, m_tiles, total);
-  else
-    hipLaunchKernelGGL(pack_split_kernel<16>, grid, dim3(256), 0, (hipStream_t)stream, a, blocks, m_tiles, total);
+  const dim3 grid((total + 255) / 256 + (a.half ? kSampleBlocks : 0));
+  auto* const kernel = mt == 32 ? a.half ? pack_split_kernel<32, 2> : pack_split_kernel<32, 3>
+                                : a.half ? pack_split_kernel<16, 2> : pack_split_kernel<16, 3>;
+  hipLaunchKernelGGL(kernel, grid, dim3(256), 0, (hipStream_t)stream, a, blocks, m_tiles, total);
   return (int)hipGetLastError();
 }
 

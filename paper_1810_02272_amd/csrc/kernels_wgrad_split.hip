@@ -16,11 +16,16 @@
 // (256 -> 384, 3x3 at 13x13) 327 -> 200, 6.7 GFLOP (45 -> 77, 3x5 at 51x67, stride 2 x 1) 95 -> 67, 1.3 GFLOP (32 -> 32,
 // 5x5 at 16x16, batch 100) 35 -> 23, with the reduce kernel, against wgrad_kernel; 172 and 115 us are the matrix
 // instructions of the first two at the 2000 TFLOP/s that a loop of them sustains.
+//
+// TERMS 2: long sums on two f16 terms (split_f16.h), half the matrix instructions, positions of 64 bytes.  Every workgroup samples
+// both blobs for the powers of two while its first loads are under way.  The first three layers, without the reduce kernel: 349 ->
+// 236 us, 219 -> 150, 67 -> 54.
 #include <hip/hip_runtime.h>
 
 #include "device_utils.h"
 #include "internal.h"
 #include "split_bf16.h"
+#include "split_f16.h"
 
 namespace mi355conv {
 
@@ -33,11 +38,14 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4* LdsTrPtr;
 typedef __attribute__((address_space(3))) char* LdsChar;
 
-// MB x NB blocks of 16 x 16 per wave; EPT: patch units (position x 8 channels) per thread.
-template <int WM, int WN, int MB, int NB, int EPT>
+// MB x NB blocks of 16 x 16 per wave; EPT: patch units (position x 8 channels) per thread; TERMS: 3 the bf16 split, 2 the
+// f16 split.
+template <int WM, int WN, int MB, int NB, int EPT, int TERMS>
 __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSplitArgs a) {
   using M = Mfma<16>;
   constexpr int BM = WM * MB * 16;
+  constexpr bool HALF = TERMS == 2;
+  constexpr uint32_t POS = 32 * TERMS;  // bytes of a patch position
   static_assert(WM * WN == 4, "four waves per workgroup");
 
   extern __shared__ __align__(16) char smem[];  // position tables of two chunks, then one or two patch stages
@@ -68,7 +76,7 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
       __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.dy), 0, (int)a.dy_bytes, 0x00020000);
   const uint32_t chan_bytes = 4u * (uint32_t)(a.H * a.W);
   const uint32_t chan0 = (g * (uint32_t)a.Cg + (uint32_t)c16 * 16u) * chan_bytes;
-  const uint32_t stage_bytes = 96u * (uint32_t)a.PSZ;
+  const uint32_t stage_bytes = POS * (uint32_t)a.PSZ;
   constexpr uint32_t kTables = 2u * 4u * kChunkPix;
   // (image, first pixel) of run q
   auto run_pos = [&](uint32_t q, uint32_t& n, uint32_t& p) {
@@ -94,7 +102,7 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
       const uint32_t pa = mdiv(p, a.mPW), pb = p - pa * a.PW;
       const uint32_t s = n - n0;
       const uint32_t row = s == 0 ? (pa - a0) * a.sh : R0 + (s - 1) * RS + pa * a.sh;
-      entry = 96u * (row * (uint32_t)a.PWID + pb * a.sw);
+      entry = POS * (row * (uint32_t)a.PWID + pb * a.sw);
     }
 #pragma unroll
     for (int r = 0; r < EPT; ++r) {
@@ -122,18 +130,27 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
     }
   };
   const SplitSel sel;
+  HalfScale x_scale(0), dy_scale(0);
   auto patch_store = [&](uint32_t table, uint32_t stage) {
     if (t < kChunkPix) *reinterpret_cast<uint32_t*>(smem + table + 4u * t) = entry;
 #pragma unroll
     for (int r = 0; r < EPT; ++r) {
-      const Split8 s = split8(pr[r], sel);
       const uint32_t u = t + r * kThreads;
-      if (u < 2u * (uint32_t)a.PSZ) {
-        const uint32_t hf = u >= (uint32_t)a.PSZ ? 1u : 0u;
-        u32x4* dst = reinterpret_cast<u32x4*>(smem + kTables + stage + 96u * (u - hf * (uint32_t)a.PSZ) + 16u * hf);
-        dst[0] = s.h;
-        dst[2] = s.m;
-        dst[4] = s.l;
+      const uint32_t hf = u >= (uint32_t)a.PSZ ? 1u : 0u;
+      u32x4* dst = reinterpret_cast<u32x4*>(smem + kTables + stage + POS * (u - hf * (uint32_t)a.PSZ) + 16u * hf);
+      if constexpr (HALF) {
+        const SplitHalf8 s = split_half8(pr[r], x_scale);
+        if (u < 2u * (uint32_t)a.PSZ) {
+          dst[0] = s.h;
+          dst[2] = s.m;
+        }
+      } else {
+        const Split8 s = split8(pr[r], sel);
+        if (u < 2u * (uint32_t)a.PSZ) {
+          dst[0] = s.h;
+          dst[2] = s.m;
+          dst[4] = s.l;
+        }
       }
       __builtin_amdgcn_sched_barrier(0);  // one unit's terms in registers at a time
     }
@@ -184,7 +201,7 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
     int tp = tap0 + j;
     if (tp > a.khw - 1) tp = a.khw - 1;  // blocks past the last tap are never stored
     const int ti = tp / a.kw, tj = tp - ti * a.kw;
-    tap_off[j] = (uint32_t)__builtin_amdgcn_readfirstlane(96 * (ti * a.dh * a.PWID + tj * a.dw));
+    tap_off[j] = (uint32_t)__builtin_amdgcn_readfirstlane((int)POS * (ti * a.dh * a.PWID + tj * a.dw));
   }
 
   // ---- bias gradient from the same read of dy: every wave sums its rows over the chunks ch with
@@ -196,9 +213,72 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
   for (int i = 0; i < MB; ++i) bsum[i] = 0.f;
 
   const bool two = a.patch_stages == 2;
+  // f16: the powers of two, from the same 2048 values of each blob in every workgroup, four neighbours at a time.
+  auto sample_scales = [&]() {
+    uint32_t top[2] = {0, 0};
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const float* const blob = b ? a.dy : a.x;
+      const uint32_t last = (b ? a.dy_bytes : a.x_bytes) / 4u - 4u;
+      float v[8];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const float* const at = blob + (uint32_t)((uint64_t)(2 * t + i) * last / (2 * kThreads));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[4 * i + e] = at[e];
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const uint32_t u = sample_bits(v[e]);
+        top[b] = u > top[b] ? u : top[b];
+      }
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t u = (uint32_t)__shfl_xor((int)top[b], d);
+        top[b] = u > top[b] ? u : top[b];
+      }
+    }
+    uint32_t* const red = reinterpret_cast<uint32_t*>(smem);
+    if (lane == 0) red[2 * wv] = top[0], red[2 * wv + 1] = top[1];
+    __syncthreads();
+    uint32_t best[2] = {0, 0};
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) best[b] = red[2 * w + b] > best[b] ? red[2 * w + b] : best[b];
+    x_scale = HalfScale(__builtin_amdgcn_readfirstlane(half_scale(best[0])));
+    dy_scale = HalfScale(__builtin_amdgcn_readfirstlane(half_scale(best[1])));
+    __syncthreads();
+  };
+  // f16: every a.lead_chunks chunks the large sums' leading bits move to LDS, a place of its own for every lane.
+  constexpr int LEAD = MB * NB / 2;  // 16-byte groups of eight sums
+  static_assert(MB * NB % 2 == 0, "whole groups");
+  const Leading16 leading;
+  bool led = false;
+  u32x4* const lead = reinterpret_cast<u32x4*>(smem + kTables + (uint32_t)a.patch_stages * stage_bytes) + t;
+  auto move_leading = [&]() {
+#pragma unroll
+    for (int q = 0; q < LEAD; ++q) {
+      u32x4 w = {0, 0, 0, 0};
+      if (led) w = lead[q * kThreads];
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        M::Acc& c = acc[(2 * q + p / 2) / NB][(2 * q + p / 2) % NB];
+        float u = c[2 * (p & 1)], v = c[2 * (p & 1) + 1];
+        leading.give(w[p], u, v);
+        w[p] = leading.take(u, v);
+        c[2 * (p & 1)] = u;
+        c[2 * (p & 1) + 1] = v;
+      }
+      lead[q * kThreads] = w;
+    }
+    led = true;
+  };
+  int since = 0;
   if (chunk_first < chunk_end) {
     patch_load(chunk_first);
     load_dy(chunk_first * kChunkSteps);
+    if constexpr (HALF) sample_scales();
     patch_store(0, 0);
   }
   __syncthreads();
@@ -213,7 +293,7 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
     for (int s = 0; s < kChunkSteps; ++s) {
       // this step's dy operands: masked, summed, split; then the next step's loads.  Only an image's last run has anything to
       // mask: a test for the wave instead of a select per value, which the two multiplications of a split pair cost.
-      u32x4 av[MB][3];
+      u32x4 av[MB][TERMS];
       if (__any(valid < 8)) {
 #pragma unroll
         for (int i = 0; i < MB; ++i)
@@ -224,10 +304,16 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
       for (int i = 0; i < MB; ++i) {
         const float(&v)[8] = raw[i];
         if (my_turn) bsum[i] += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
-        const Split8 sp = split8(v, sel);
-        av[i][0] = sp.h;
-        av[i][1] = sp.m;
-        av[i][2] = sp.l;
+        if constexpr (HALF) {
+          const SplitHalf8 sp = split_half8(v, dy_scale);
+          av[i][0] = sp.h;
+          av[i][1] = sp.m;
+        } else {
+          const Split8 sp = split8(v, sel);
+          av[i][0] = sp.h;
+          av[i][1] = sp.m;
+          av[i][2] = sp.l;
+        }
       }
       const int step = ch * kChunkSteps + s;
       load_dy(step < last_step ? step + 1 : step);
@@ -236,11 +322,11 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
       const uint32_t fix = kTables + stage + 8u * (uint32_t)(lane & 3);
       const uint32_t b0 = *reinterpret_cast<const uint32_t*>(smem + table + 4u * px) + fix;
       const uint32_t b1 = *reinterpret_cast<const uint32_t*>(smem + table + 4u * px + 16u) + fix;
-      u32x4 bv[2][3];
-      auto load_b = [&](int j, u32x4(&b)[3]) {
+      u32x4 bv[2][TERMS];
+      auto load_b = [&](int j, u32x4(&b)[TERMS]) {
         const uint32_t o0 = b0 + tap_off[j], o1 = b1 + tap_off[j];
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
+        for (int q = 0; q < TERMS; ++q) {
           const s16x4 x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsTrPtr)((LdsChar)smem + o0 + 32 * q));
           const s16x4 x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsTrPtr)((LdsChar)smem + o1 + 32 * q));
           const uint2 y0 = __builtin_bit_cast(uint2, x0), y1 = __builtin_bit_cast(uint2, x1);
@@ -255,15 +341,28 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
       for (int j = 0; j < NB; ++j) {
         if (j + 1 < NB) load_b(j + 1, bv[(j + 1) & 1]);
         __builtin_amdgcn_sched_barrier(0);  // the next block's reads before this block's products, not behind them
-        constexpr int pa[5] = {2, 0, 1, 1, 0}, pb[5] = {0, 2, 1, 0, 1};
+        if constexpr (HALF) {
 #pragma unroll
-        for (int q = 0; q < 5; ++q)
+          for (int i = 0; i < MB; ++i) mfma_f16<16>(av[i][1], bv[j & 1][0], lo[i][j]);
 #pragma unroll
-          for (int i = 0; i < MB; ++i) mfma_bf16<16>(av[i][pa[q]], bv[j & 1][pb[q]], lo[i][j]);
+          for (int i = 0; i < MB; ++i) mfma_f16<16>(av[i][0], bv[j & 1][0], acc[i][j]);
 #pragma unroll
-        for (int i = 0; i < MB; ++i) mfma_bf16<16>(av[i][0], bv[j & 1][0], acc[i][j]);
+          for (int i = 0; i < MB; ++i) mfma_f16<16>(av[i][0], bv[j & 1][1], lo[i][j]);
+        } else {
+          constexpr int pa[5] = {2, 0, 1, 1, 0}, pb[5] = {0, 2, 1, 0, 1};
+#pragma unroll
+          for (int q = 0; q < 5; ++q)
+#pragma unroll
+            for (int i = 0; i < MB; ++i) mfma_bf16<16>(av[i][pa[q]], bv[j & 1][pb[q]], lo[i][j]);
+#pragma unroll
+          for (int i = 0; i < MB; ++i) mfma_bf16<16>(av[i][0], bv[j & 1][0], acc[i][j]);
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
+    }
+    if (HALF && ++since == a.lead_chunks && more) {
+      move_leading();
+      since = 0;
     }
     table ^= 4u * kChunkPix;
     if (two)
@@ -293,12 +392,30 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
     }
   }
 
+  if constexpr (HALF) {
+    const int back = -(x_scale.e + dy_scale.e);
 #pragma unroll
-  for (int i = 0; i < MB; ++i)
+    for (int q = 0; q < LEAD; ++q) {
+      u32x4 w = {0, 0, 0, 0};
+      if (led) w = lead[q * kThreads];
 #pragma unroll
-    for (int j = 0; j < NB; ++j)
+      for (int p = 0; p < 4; ++p) {
+        const int i = (2 * q + p / 2) / NB, j = (2 * q + p / 2) % NB, r = 2 * (p & 1);
+        constexpr float down = 1.f / (float)(1 << kHalfShift);
+        float u = __builtin_fmaf(lo[i][j][r], down, acc[i][j][r]), v = __builtin_fmaf(lo[i][j][r + 1], down, acc[i][j][r + 1]);
+        leading.give(w[p], u, v);
+        acc[i][j][r] = scale_by(u, back);
+        acc[i][j][r + 1] = scale_by(v, back);
+      }
+    }
+  } else {
 #pragma unroll
-      for (int r = 0; r < M::NR; ++r) acc[i][j][r] = (acc[i][j][r] + lo[i][j][r]) * kSplitUnscale;
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int r = 0; r < M::NR; ++r) acc[i][j][r] = (acc[i][j][r] + lo[i][j][r]) * kSplitUnscale;
+  }
 
   const int c = c16 * 16 + (lane & 15);
   // ---- sums that are not finite once more on the fp32 matrix instructions (see corr_split_kernel); channels past the
@@ -374,15 +491,21 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
     }
 }
 
+template <int WM, int WN, int MB, int NB, int EPT, int TERMS>
+int launch_k(const WgradSplitArgs& a, hipStream_t s) {
+  constexpr int BM = WM * MB * 16;
+  const size_t lds = 2 * 4 * kChunkPix + 32 * TERMS * (size_t)a.PSZ * a.patch_stages + (TERMS == 2 ? split_half_lead(BM, WN * NB * 16) : 0);
+  const size_t red = 4 * WN * BM;
+  static LdsOptIn opt_in;  // more than 64 KB of LDS needs an explicit opt-in, once per process
+  if (const int e = lds_opt_in(opt_in, &wgrad_split_kernel<WM, WN, MB, NB, EPT, TERMS>, 160 * 1024)) return e;
+  const uint32_t blocks = (uint32_t)a.G * a.S * a.m_tiles * a.n_tiles;
+  hipLaunchKernelGGL((wgrad_split_kernel<WM, WN, MB, NB, EPT, TERMS>), dim3(blocks), dim3(kThreads), lds > red ? lds : red, s, a);
+  return (int)hipGetLastError();
+}
+
 template <int WM, int WN, int MB, int NB, int EPT>
 int launch_e(const WgradSplitArgs& a, hipStream_t s) {
-  const size_t lds = 2 * 4 * kChunkPix + 96 * (size_t)a.PSZ * a.patch_stages;
-  const size_t red = 4 * WN * WM * MB * 16;
-  static LdsOptIn opt_in;  // more than 64 KB of LDS needs an explicit opt-in, once per process
-  if (const int e = lds_opt_in(opt_in, &wgrad_split_kernel<WM, WN, MB, NB, EPT>, 160 * 1024)) return e;
-  const uint32_t blocks = (uint32_t)a.G * a.S * a.m_tiles * a.n_tiles;
-  hipLaunchKernelGGL((wgrad_split_kernel<WM, WN, MB, NB, EPT>), dim3(blocks), dim3(kThreads), lds > red ? lds : red, s, a);
-  return (int)hipGetLastError();
+  return a.half ? launch_k<WM, WN, MB, NB, EPT, 2>(a, s) : launch_k<WM, WN, MB, NB, EPT, 3>(a, s);
 }
 
 template <int WM, int WN, int MB, int NB>

@@ -273,6 +273,42 @@ SPLIT_CASES = [
     P(4700, 90, 2, 3, 77, 3, 3, 1, 1, 1, 1),
     P(901, 61, 3, 9, 96, 3, 5, 3, 1, 1, 1, 1, 1),
     P(1603, 45, 3, 3, 77, 3, 5, 1, 1, 1, 2),
+    P(5, 107, 53, 20, 409, 7, 7, 2, 2, 4, 0, 2, 2, 1),  # strided data gradient in slices
+]
+
+# With SPLIT_CASES, every instance of the split kernels for the f16 terms (test_half_parity_gpu.py).
+HALF_CASES = [
+    P(40, 128, 16, 12, 357, 3, 5, 1, 2, 1, 1, 1, 1, 1),
+    P(19, 31, 19, 18, 388, 5, 5, 1, 1, 3, 3, 1, 1, 1),
+    P(18, 141, 53, 5, 267, 4, 3, 1, 1, 1, 2, 2, 2, 1),
+    P(2340, 1251, 1, 1, 814, 1, 1, 1, 1, 0, 0, 1, 1, 1),
+    P(46, 383, 18, 10, 122, 4, 3, 1, 1, 2, 0, 2, 2, 1),
+    P(45, 188, 18, 36, 104, 3, 5, 2, 1, 2, 2, 1, 1, 2),
+    P(1174, 1956, 1, 1, 1522, 1, 1, 2, 1, 0, 0, 1, 1, 2),
+    P(11, 624, 27, 39, 466, 1, 1, 2, 1, 0, 1, 1, 1, 1),
+    P(28, 123, 43, 30, 217, 1, 9, 2, 2, 1, 1, 1, 1, 1),
+    P(22, 57, 16, 37, 385, 5, 5, 2, 1, 0, 3, 2, 2, 1),
+    P(11, 352, 11, 13, 562, 4, 3, 1, 1, 2, 1, 1, 1, 2),
+    P(19, 297, 10, 33, 82, 3, 5, 1, 1, 0, 2, 1, 1, 1),
+    P(54, 20, 12, 37, 385, 4, 3, 1, 1, 0, 1, 1, 1, 1),
+    P(3, 374, 34, 41, 46, 7, 3, 1, 1, 4, 1, 1, 1, 1),
+    P(45, 135, 28, 29, 68, 7, 1, 1, 1, 3, 0, 1, 1, 1),
+    P(5, 283, 45, 20, 442, 3, 3, 1, 2, 0, 2, 2, 2, 1),
+    P(56, 165, 24, 10, 137, 2, 3, 1, 1, 2, 2, 1, 1, 1),
+    P(18, 602, 27, 16, 36, 7, 3, 1, 1, 4, 2, 2, 2, 2),
+    P(50, 99, 32, 36, 87, 1, 9, 1, 2, 0, 5, 1, 1, 1),
+    P(1, 343, 45, 46, 326, 1, 9, 1, 1, 0, 5, 1, 1, 1),
+    P(5, 1354, 47, 42, 291, 1, 1, 1, 2, 0, 1, 1, 1, 1),
+    P(15, 328, 25, 11, 116, 4, 3, 1, 1, 1, 1, 1, 1, 1),
+    P(50, 26, 41, 11, 200, 5, 5, 1, 2, 1, 1, 1, 1, 1),
+    P(40, 173, 18, 8, 266, 7, 3, 1, 1, 0, 2, 2, 2, 1),
+    P(17, 196, 12, 18, 120, 7, 7, 1, 1, 3, 1, 1, 1, 2),
+    P(27, 301, 3, 52, 321, 7, 3, 1, 2, 2, 0, 1, 1, 1),
+    P(41, 72, 6, 45, 153, 3, 5, 1, 1, 2, 0, 1, 1, 1),
+    P(58, 378, 50, 24, 26, 7, 1, 2, 1, 3, 0, 1, 1, 1),
+    P(49, 32, 27, 37, 376, 3, 5, 1, 2, 1, 1, 1, 1, 2),
+    P(39, 107, 49, 3, 267, 4, 3, 1, 2, 3, 2, 1, 1, 1),
+    P(12, 996, 30, 41, 144, 1, 1, 1, 1, 1, 1, 2, 2, 1),
 ]
 
 # More rows of padding than a window has, on images so small that column tiles and chunks start in an image's last rows:

@@ -1,0 +1,127 @@
+"""The split kernels on two f16 terms (split_f16.h) against the oracle.
+
+Tolerance.  An operand is off by at most 2^-23 of itself and a product misses another 2^-22, of random sign; the sums are rounded
+once per 16 or 32 indices as on the bf16 terms.  Over 32 indices and more the operands' part is below a fifth of
+2^-24 sqrt(K/16 + 32), the bound of test_split_parity_gpu.py, which holds here too.  Sums that the terms cannot hold come from
+the fp32 matrix instructions, which round every second index: 2^-24 sqrt(K/2 + 32).
+"""
+import re
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1810_02272_amd as conv
+from oracle import OracleParams
+from paper_1810_02272_amd import workloads
+from parity_cases import HALF_CASES, SPLIT_CASES, P
+from parity_metric import nerr
+from test_parity_gpu import TOL, check_filter_and_bias_in_one_pass, run_all
+from test_split_parity_gpu import CORR, WGRAD, names, norm_error
+
+PASSES = ("fwd", "bwd_data", "bwd_filter")
+MIXED = P(24, 128, 28, 28, 128, 3, 3, 1, 1, 1, 1)  # all three passes on f16 terms
+PIXELS = P(4096, 1400, 1, 1, 1400, 1, 1)
+
+
+def test_cases_select_every_instance():
+    corr, wgrad = set(), set()
+    for pd in HALF_CASES + SPLIT_CASES:
+        n = names(pd)
+        for which in PASSES[:2]:
+            m = CORR.match(n[which])
+            if m and "half" in n[which]:
+                corr |= {(m[1], m[3] if m[2] == "p" else m[2]), (which, m[4], int(m[5]) > 1)}
+        m = WGRAD.match(n["bwd_filter"])
+        if m and "half" in n["bwd_filter"]:
+            wgrad |= {(m[1], m[2]), m[3]}
+    tiles = ["m32_128x128", "m32_64x256", "m32_64x128", "m32_96x128", "m32_32x256", "m32_32x128", "m16_48x256"]
+    want = {(t, u) for t in tiles for u in ("34" if t.endswith("x256") else "234")}
+    want |= {(t, f) for t in ("m32_128x128", "m32_64x128", "m32_96x128") for f in ("cols", "rows")}
+    want |= {("fwd", "s", s) for s in (False, True)} | {("bwd_data", e, s) for e in "sr" for s in (False, True)}
+    assert want - corr == set()
+    assert {(t, u) for t in ("128x9", "128x8", "64x16", "32x28", "32x12", "96x8") for u in "234"} | {"1", "2"} <= wgrad
+
+
+def test_short_sums_stay_on_the_bf16_terms():
+    """The operands' error is below the sums' from about 620 indices on; slices count by themselves."""
+    assert "half" not in names(P(64, 64, 28, 28, 128, 3, 3, 1, 1, 1, 1))["fwd"]
+    assert "half" in names(P(64, 80, 28, 28, 128, 3, 3, 1, 1, 1, 1))["fwd"]
+    for n, c, k in ((128, 9216, 4096), (300, 5000, 3000), (64, 2048, 2048), (900, 700, 900)):
+        name = names(P(n, c, 1, 1, k, 1, 1))["fwd"]
+        if "half" in name:
+            assert c / int(re.search(r"S=(\d+)", name)[1]) > 600, name
+
+
+def passes_of(pd, dev, host):
+    """(name, kernel, result, reference, reduction length) of the three passes"""
+    op, kernels, taps = OracleParams(**pd), names(pd), pd["kernel_h"] * pd["kernel_w"]
+    ys = oracle.output_shape(op)
+    y, dx, dw = dev
+    return (("y", kernels["fwd"], y, oracle.forward(op, *host[:3]), pd["c"] // pd["group"] * taps),
+            ("dx", kernels["bwd_data"], dx, oracle.backward_data(op, host[1], host[3]), pd["num_output"] // pd["group"] * taps),
+            ("dw", kernels["bwd_filter"], dw, oracle.backward_filter(op, host[0], host[3]), ys[0] * ys[2] * ys[3]))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("i", range(len(HALF_CASES)))
+def test_half_full_compare(i):
+    pd = HALF_CASES[i]
+    print("half case", i, pd, names(pd), flush=True)
+    op = OracleParams(**pd)
+    x, w, b, dy = workloads.random_inputs(oracle.x_shape(op), oracle.w_shape(op), oracle.output_shape(op), 9100 + 10 * i)
+    d, ws, dev_in, (y, dx, dw, db) = run_all(pd, x, w, b, dy)
+    host = (x.numpy(), w.numpy(), b.numpy(), dy.numpy())
+    for name, kernel, got, ref, terms in passes_of(pd, (y, dx, dw), host):
+        assert nerr(got, ref) <= TOL, (pd, name)
+        if "split" in kernel:
+            assert norm_error(got, ref) <= 2.0 ** -24 * np.sqrt(terms / 16 + 32), (pd, name, norm_error(got, ref))
+    check_filter_and_bias_in_one_pass(pd, op, d, ws, dev_in, dw, oracle.backward_bias(op, host[3]), host)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("pd", [MIXED, PIXELS], ids=["image", "rows"])
+@pytest.mark.parametrize("case", ["tiny_images", "huge_image", "tiny_weights", "outliers", "zeros", "relu", "denormals"])
+def test_ranges_beyond_f16(pd, case):
+    """Images, weights and single values far from the sample's size: every image and every output channel keeps the bound by itself."""
+    assert all("half" in names(pd)[p] for p in PASSES[:2])
+    op = OracleParams(**pd)
+    x, w, b, dy = workloads.random_inputs(oracle.x_shape(op), oracle.w_shape(op), oracle.output_shape(op), 9900)
+    b = b * 0
+    if case == "tiny_images":
+        for t in (x, dy):
+            t[3] *= 2.0 ** -20
+            t[5] *= 2.0 ** -30
+            t[6] *= 2.0 ** -70
+    elif case == "huge_image":
+        x[2] *= 2.0 ** 40
+        dy[2] *= 2.0 ** 40
+    elif case == "tiny_weights":
+        w[7] *= 2.0 ** -40
+        w[:, 16:32] *= 2.0 ** -28
+    elif case == "outliers":
+        for t in (x, dy, w):
+            t.view(-1)[t.numel() // 3 + 5] = 1e9
+    elif case == "zeros":
+        x.zero_()
+        w[:, 8:].zero_()
+    elif case == "relu":
+        x, dy = x.clamp(min=0), torch.where(dy > 0, dy, torch.zeros_like(dy))
+    else:
+        x, dy = x * 2.0 ** -130, dy * 2.0 ** -130
+    d, ws, _, (y, dx, dw, db) = run_all(pd, x, w, b, dy)
+    host = (x.numpy(), w.numpy(), b.numpy(), dy.numpy())
+    for name, kernel, got, ref, terms in passes_of(pd, (y, dx, dw), host):
+        if case == "denormals" and name == "dw":
+            assert not got.any()  # products of 2^-260
+            continue
+        # one large term leaves every later partial sum at full size, and the roundings to it need not be of random sign
+        g, bound = got.cpu().double().numpy(), 2.0 ** -24 * (terms / 2 + 32 if case == "outliers" else np.sqrt(terms / 2 + 32))
+        # output channels of dw; images of y and dx, and their channels (of one pixel each they may be single sums, which cancel)
+        for axis in ((0,) if name == "dw" or pd is PIXELS else (0, 1)):
+            err = np.linalg.norm(np.moveaxis(g - ref, axis, 0).reshape(g.shape[axis], -1), axis=1)
+            size = np.linalg.norm(np.moveaxis(ref, axis, 0).reshape(g.shape[axis], -1), axis=1)
+            if case == "denormals":
+                size = size + 2.0 ** -149 * 2 ** 24 * np.sqrt(g.size / g.shape[axis])  # results are denormal themselves
+            assert np.all(err <= bound * size), (name, kernel, axis, np.max(err / np.maximum(size, 1e-300)) / bound)
