@@ -720,6 +720,45 @@ size_t configure_split(const CorrArgs& base, const PackArgs& pbase, int64_t cg_i
   return (size_t)bytes;
 }
 
+// The layer's own part of the arguments.
+void wgrad_split_args(const WgradArgs& w, int64_t N, WgradSplitArgs& a) {
+  a = WgradSplitArgs();
+  a.dy_bytes = w.dy_bytes;
+  a.x_bytes = w.x_bytes;
+  a.N = (int32_t)N;
+  a.P = w.P;
+  a.PW = w.PW;
+  a.PH = w.P / w.PW;
+  a.mPW = w.mPW;
+  a.runs = (int32_t)ceil_div(w.P, 8);
+  a.mRuns = make_magic((uint32_t)a.runs);
+  a.Kg = w.Kg;
+  a.Ktot = w.Ktot;
+  a.Cg = w.Cg;
+  a.C = w.C;
+  a.H = w.H;
+  a.W = w.W;
+  a.kw = w.kw;
+  a.khw = w.khw;
+  a.sh = w.sh;
+  a.sw = w.sw;
+  a.dh = w.dh;
+  a.dw = w.dw;
+  a.ph = w.ph;
+  a.pw = w.pw;
+  a.Kred = w.Kred;
+}
+
+// Modelled time (us) of the fp32 filter gradient, see configure_wgrad_split.
+double wgrad_fp32_time(const WgradArgs& w, int32_t fp32_tile, double w_mb) {
+  int32_t bm, bn, bk;
+  wgrad_tile_shape(fp32_tile, &bm, &bn, &bk);
+  static const double kFp32Step[WGRAD_TILE_COUNT] = {1.74, 1.45, 1.04, 0.634, 0.978};
+  const double bounds = (double)(bm * bn) / 16384.0 * (w.bounds_mode == 1 ? 0.51 : w.bounds_mode == 2 ? 0.29 : 0.0);
+  const int64_t per_cu = ceil_div((int64_t)w.G * w.m_tiles * w.n_tiles * w.S, 256);
+  return 13.2 + 0.375 * (double)w.S * w_mb + (double)(per_cu * ceil_div(w.cols_per_split, 32)) * (kFp32Step[fp32_tile] + bounds);
+}
+
 // Decides whether wgrad_split_kernel runs the backward filter instead of the fp32 kernel on its tile and split; fills a and
 // returns its own tile, -1 if it does not.
 int32_t configure_wgrad_split(const WgradArgs& w, int32_t fp32_tile, int64_t N, int64_t K, int64_t w_elems, WgradSplitArgs& a) {
@@ -799,46 +838,16 @@ int32_t configure_wgrad_split(const WgradArgs& w, int32_t fp32_tile, int64_t N, 
   int32_t bm, bn, bk;
   wgrad_tile_shape(pick_wgrad_tile(w.Kg, w.Kred), &bm, &bn, &bk);
   if (least_work > (flops < 2.5e9 ? 1.12 : flops < 4.5e9 ? 1.45 : 2.0) * (double)round_up(w.Kg, bm) * (double)round_up(w.Kred, bn)) return -1;
-  wgrad_tile_shape(fp32_tile, &bm, &bn, &bk);
   // The rest by modelled times (us).  The fp32 kernel's: workgroups of a compute unit times the 32-column steps of one, by
   // tile and by what the bounds test costs it, and its slices; a fit to 825 filter gradients of 0.4 to 20 GFLOP (rms error
   // 5 %; 7 % on 1288, the split kernel's 8 %).  A run holds pixels of one image, so best_cost counts the zeros that fill an
   // image's last run.  Of those 1288 the lines above let through, 139 were more than 3 % slower than fp32 (one pixel, 512 -> 512,
   // 3x3, batch 2048: 134 us fp32, 390 split; 48 x 249 -> 266, 2x2 taps on tiles of eight: 62 and 78), with this line 16, at
   // worst 11 %; 26 that gained more than 3 % stay behind with them, at best 434 -> 293 us.
-  static const double kFp32Step[WGRAD_TILE_COUNT] = {1.74, 1.45, 1.04, 0.634, 0.978};
-  const double bounds = (double)(bm * bn) / 16384.0 * (w.bounds_mode == 1 ? 0.51 : w.bounds_mode == 2 ? 0.29 : 0.0);
-  const int64_t per_cu = ceil_div((int64_t)w.G * w.m_tiles * w.n_tiles * w.S, 256);
-  const double fp32 = 13.2 + 0.375 * (double)w.S * w_mb +
-                      (double)(per_cu * ceil_div(w.cols_per_split, 32)) * (kFp32Step[fp32_tile] + bounds);
-  if (8.4 + 0.99 * best_cost > fp32) return -1;
+  if (8.4 + 0.99 * best_cost > wgrad_fp32_time(w, fp32_tile, w_mb)) return -1;
   int32_t rows, taps;
   wgrad_split_shape(best, &rows, &taps);
-  a = WgradSplitArgs();
-  a.dy_bytes = w.dy_bytes;
-  a.x_bytes = w.x_bytes;
-  a.N = (int32_t)N;
-  a.P = w.P;
-  a.PW = w.PW;
-  a.PH = (int32_t)PH;
-  a.mPW = w.mPW;
-  a.runs = (int32_t)runs;
-  a.mRuns = make_magic((uint32_t)runs);
-  a.Kg = w.Kg;
-  a.Ktot = w.Ktot;
-  a.Cg = w.Cg;
-  a.C = w.C;
-  a.H = w.H;
-  a.W = w.W;
-  a.kw = w.kw;
-  a.khw = w.khw;
-  a.sh = w.sh;
-  a.sw = w.sw;
-  a.dh = w.dh;
-  a.dw = w.dw;
-  a.ph = w.ph;
-  a.pw = w.pw;
-  a.Kred = w.Kred;
+  wgrad_split_args(w, N, a);
   a.part_stride = (int32_t)w_elems;
   a.G = w.G;
   a.m_tiles = (int32_t)ceil_div(w.Kg, rows);
@@ -862,6 +871,90 @@ int32_t configure_wgrad_split(const WgradArgs& w, int32_t fp32_tile, int64_t N, 
   }
   const int64_t tiles = (int64_t)a.G * a.m_tiles * a.n_tiles;
   if (a.S * (w_elems + a.n_tiles * K) >= kMaxElems || tiles * a.S >= ((int64_t)1 << 31)) return -1;
+  return best;
+}
+
+// The same on the folded grid of a layer with few channels, f16 terms only: its tile, or -1.
+int32_t configure_wgrad_fold(const WgradArgs& w, int32_t fp32_tile, int64_t N, int64_t K, int64_t w_elems, WgradSplitArgs& a) {
+  const double flops = 2.0 * w.Kg * w.Kred * (double)w.ncols * w.G;
+  if (w.ncols < 1 || flops < 1e9 || w.x_bytes > (1u << 30) || w.dy_bytes > (1u << 31) - 32 || w.x_bytes < 16 || w.dy_bytes < 16) return -1;
+  SplitGrid grid;
+  if ((int64_t)w.Cg * 100 >= round_up(w.Cg, 16) * 70 ||
+      !folded_grid(w.Cg, w.khw / w.kw, w.kw, w.sh, w.sw, w.dh, w.dw, w.pw, grid))
+    return -1;
+  const int64_t T = grid.TH * grid.TW, V = grid.f.V, part = K * T * V;
+  if (part > ((int64_t)8 << 20)) return -1;  // one slice is within the fixed scratch array
+  const int64_t ext = (grid.TH - 1) * grid.dh + 1;
+  const PatchDim dim_w = patch_dim(w.PW, grid.sw, (grid.TW - 1) * grid.dw + 1, 0, w.W);
+  const PatchDim dim_h = patch_dim(w.P / w.PW, grid.sh, ext, 0, w.H);
+  const int64_t runs = ceil_div(w.P, 8), total_runs = N * runs, chunk_runs = wgrad_split_chunk_runs();
+  const int64_t max_rows = max_patch_rows(total_runs, runs, chunk_runs, 8, w.P, w.PW, grid.sh, ext, dim_h.pitch, 512 / dim_w.pitch);
+  const int64_t psz = max_rows * dim_w.pitch + dim_w.share;
+  if (psz > 512) return -1;
+  const int64_t c16 = ceil_div(V, 16), chunks = ceil_div(total_runs, chunk_runs);
+  if (chunks < 8) return -1;
+  // A fit to 135 timings of 16 layers (rms error 5 %).  A patch unit is dearer than the image's: its table entries, and two loads with
+  // a test of every element's column.
+  static const double kAlone[WFOLD_TILE_COUNT] = {0.834, 0.849, 0.747, 0.325}, kShared[WFOLD_TILE_COUNT] = {0.459, 0.466, 0.396, 0.088};
+  const double units_per_thread = psz <= 384 ? 3 : 4, chunk_pix = (double)w.ncols / (double)chunks, part_mb = 4e-6 * (double)part;
+  int32_t best = -1, best_lead = 0;
+  int64_t best_cps = 0;
+  double best_cost = 0;
+  for (int32_t t = 0; t < WFOLD_TILE_COUNT; ++t) {
+    int32_t rows, taps;
+    wgrad_fold_shape(t, &rows, &taps);
+    const int64_t tiles = (int64_t)w.G * ceil_div(w.Kg, rows) * ceil_div(T, taps) * c16;
+    for (int64_t places = 256; places <= 512; places += 256) {
+      int64_t S = places / tiles;
+      if (S > ((int64_t)8 << 20) / part) S = ((int64_t)8 << 20) / part;
+      if (S > 256) S = 256;
+      if (S > chunks) S = chunks;
+      if (S < 1) S = 1;
+      const int64_t cps = ceil_div(chunks, S), per_cu = ceil_div(tiles * ceil_div(chunks, cps), 256);
+      const double pix = chunk_pix * (double)cps;
+      const int32_t lead = half_interval(pix, pix, chunk_pix, 1);
+      if (!lead) continue;
+      const double cost = 6.9 + 0.604 * (double)S * part_mb + 3.43 * (double)per_cu +
+                          (per_cu == 1 ? (double)cps * (4 * kAlone[t] + 0.669 * units_per_thread)
+                                       : (double)(per_cu * cps) * (4 * kShared[t] + 0.580 * units_per_thread));
+      if (best < 0 || cost < best_cost) {
+        best = t;
+        best_cost = cost;
+        best_cps = cps;
+        best_lead = lead;
+      }
+    }
+  }
+  if (best < 0 || 1.08 * best_cost > wgrad_fp32_time(w, fp32_tile, 4e-6 * (double)w_elems)) return -1;
+  int32_t rows, taps;
+  wgrad_fold_shape(best, &rows, &taps);
+  wgrad_split_args(w, N, a);
+  a.fold = grid.f;
+  a.kw = (int32_t)grid.TW;
+  a.khw = (int32_t)T;
+  a.sh = (int32_t)grid.sh;
+  a.sw = (int32_t)grid.sw;
+  a.dh = (int32_t)grid.dh;
+  a.dw = (int32_t)grid.dw;
+  a.Kred = (int32_t)(T * V);
+  a.part_stride = (int32_t)part;
+  a.G = w.G;
+  a.m_tiles = (int32_t)ceil_div(w.Kg, rows);
+  a.tap_tiles = (int32_t)ceil_div(T, taps);
+  a.n_tiles = (int32_t)(c16 * a.tap_tiles);
+  a.PWID = (int32_t)dim_w.pitch;
+  a.PSZ = (int32_t)psz;
+  a.ext = (int32_t)ext;
+  a.share_h = 0;
+  a.mPWID = make_magic((uint32_t)dim_w.pitch);
+  a.mRSEG = make_magic((uint32_t)dim_h.pitch);
+  a.chunks = (int32_t)chunks;
+  a.chunks_per_split = (int32_t)best_cps;
+  a.S = (int32_t)ceil_div(chunks, best_cps);
+  a.half = 1;
+  a.lead_chunks = best_lead;
+  const uint32_t rest = 2 * 4 * 8 * (uint32_t)chunk_runs + split_half_lead(rows, 16 * taps) + 128 * (uint32_t)c16;
+  a.patch_stages = 128 * (uint32_t)a.PSZ + rest <= 80 * 1024 ? 2 : 1;  // two workgroups per compute unit
   return best;
 }
 
@@ -1501,16 +1594,16 @@ int run_backward_filter(const conv_desc* d, const float* x, const float* dy, flo
     }
     e = launch_wgrad_small(d->wg_small[0], sa, false, hip_stream);
     if (e || sa.S == 1) return e ? record_hip_error(e) : CONV_OK;
-  } else if (d->wg_split >= 0) {
+  } else if (d->wg_split >= 0 || d->wg_fold >= 0) {
     WgradSplitArgs sa = d->wg_sp;
     a.S = sa.S;
     a.n_tiles = sa.n_tiles;
-    if (db) a.bias_part = a.part + (size_t)a.S * w_elems;
+    if (db) a.bias_part = a.part + (size_t)a.S * sa.part_stride;
     sa.dy = dy;
     sa.x = x;
     sa.part = a.part;
     sa.bias_part = a.bias_part;
-    if (!empty) e = launch_wgrad_split(d->wg_split, sa, hip_stream);
+    if (!empty) e = d->wg_fold >= 0 ? launch_wgrad_fold(d->wg_fold, sa, hip_stream) : launch_wgrad_split(d->wg_split, sa, hip_stream);
   } else if (!empty) {
     if (db) a.bias_part = a.part + (size_t)a.S * w_elems;  // row sums of dy ride along, behind the filter partials
     e = launch_wgrad(d->wg_tile, a, hip_stream);
@@ -1534,7 +1627,19 @@ int run_backward_filter(const conv_desc* d, const float* x, const float* dy, flo
     r.count2 = d->p.num_output;
     r.S2 = empty ? 0 : a.S * a.n_tiles;
   }
-  if (d->wg_split >= 0 && !d->use_direct && d->wg_sp.khw > 1) {
+  if (d->wg_fold >= 0 && !d->use_direct) {
+    ReduceFoldArgs rf;
+    static_cast<ReduceArgs&>(rf) = r;
+    rf.count = d->wg_sp.part_stride;
+    rf.taps = d->wg_sp.khw;
+    rf.tap_channels = d->wg_sp.fold.V;
+    rf.mRow = make_magic((uint32_t)d->wg_sp.Kred);
+    rf.mTapChannels = make_magic((uint32_t)rf.tap_channels);
+    rf.fold = d->wg_sp.fold;
+    rf.channels = d->wg_sp.Cg;
+    rf.grid_w = d->wg_sp.kw;
+    e = launch_reduce_fold(rf, hip_stream);
+  } else if (d->wg_split >= 0 && !d->use_direct && d->wg_sp.khw > 1) {
     ReduceTapsArgs rt;
     static_cast<ReduceArgs&>(rt) = r;
     rt.taps = d->wg_sp.khw;
@@ -1878,10 +1983,11 @@ static int create_desc(conv_desc_t** out, const conv_params_t* pp, bool one_laun
       return CONV_ESHAPE;
     }
     d->wg_split = configure_wgrad_split(a, d->wg_tile, N, K, w_elems, d->wg_sp);
-    d->wg_small[0] = d->wg_split >= 0 || !one_launch ? -1 : configure_wgrad_small(a, N, 4, bm, bn, d->wg_sm[0]);
-    if (d->wg_split >= 0) {
-      d->wg_ws = (size_t)d->wg_sp.S * (size_t)w_elems * 4;
-      d->wgb_ws = (size_t)d->wg_sp.S * (size_t)(w_elems + d->wg_sp.n_tiles * K) * 4;
+    d->wg_fold = d->wg_split >= 0 ? -1 : configure_wgrad_fold(a, d->wg_tile, N, K, w_elems, d->wg_sp);
+    d->wg_small[0] = d->wg_split >= 0 || d->wg_fold >= 0 || !one_launch ? -1 : configure_wgrad_small(a, N, 4, bm, bn, d->wg_sm[0]);
+    if (d->wg_split >= 0 || d->wg_fold >= 0) {
+      d->wg_ws = (size_t)d->wg_sp.S * (size_t)d->wg_sp.part_stride * 4;
+      d->wgb_ws = (size_t)d->wg_sp.S * (size_t)(d->wg_sp.part_stride + d->wg_sp.n_tiles * K) * 4;
     }
   }
 
@@ -2071,8 +2177,14 @@ static int create_desc(conv_desc_t** out, const conv_params_t* pp, bool one_laun
       split_variant_name(b, sizeof(b), d->bwd_split, d->bwd_sp, d->bwd_zero_fill);
     else if (d->bwd_small[0] < 0)
       corr_variant_name(b, sizeof(b), d->bwd_tile, d->bwd, d->bwd_zero_fill, d->bwd_thin);
-    if (d->wg_split < 0 && d->wg_small[0] < 0) snprintf(wg, sizeof(wg), "%s[m%d,%s,e%c](S=%d,L=2)", wgrad_tile_name(d->wg_tile), d->wg.bounds_mode,
+    if (d->wg_split < 0 && d->wg_fold < 0 && d->wg_small[0] < 0) snprintf(wg, sizeof(wg), "%s[m%d,%s,e%c](S=%d,L=2)", wgrad_tile_name(d->wg_tile), d->wg.bounds_mode,
              d->wg_tile == WGRAD_128x128 ? "lds" : "reg", 4 * Kg * kred <= ((int64_t)1 << 30) ? 'r' : 'p', d->wg.S);
+    if (d->wg_fold >= 0) {
+      int32_t rows, taps;
+      wgrad_fold_shape(d->wg_fold, &rows, &taps);
+      snprintf(wg, sizeof(wg), "splitwgrad_fold%d_%dx%dx16[p%d,st%d](S=%d,half,L=2)", d->wg_sp.fold.ff, rows, taps,
+               split_patch_units(d->wg_sp.PSZ), d->wg_sp.patch_stages, d->wg_sp.S);
+    }
     if (d->wg_split >= 0) {
       int32_t rows, taps;
       wgrad_split_shape(d->wg_split, &rows, &taps);

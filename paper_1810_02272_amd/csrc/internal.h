@@ -222,6 +222,7 @@ struct WgradSplitArgs {
   int32_t PWID, PSZ, ext, share_h, patch_stages;
   Magic mPWID, mRSEG;
   int32_t half, lead_chunks;  // f16 split: chunks between two moves of the sums' leading bits
+  SplitFold fold;             // folded form: what the channels and taps stand for (kw, khw, sh, sw: the grid's; Cg: the layer's)
 };
 
 // One-launch kernels of small layers (kernels_small.hip); the pointer members address floats or doubles.
@@ -277,6 +278,13 @@ struct ReduceArgs {
 struct ReduceTapsArgs : ReduceArgs {
   int32_t taps, tap_channels;  // at least two taps
   Magic mRow, mTapChannels;    // divisions by taps * tap_channels and tap_channels
+};
+
+// Partials of the folded form, [row][grid tap][folded channel]: count of them; places beyond the kernel's taps have no element in
+// dst, the weight blob.
+struct ReduceFoldArgs : ReduceTapsArgs {
+  SplitFold fold;
+  int32_t channels, grid_w;  // of the group; grid taps per row
 };
 
 // Element-wise and column-sum helpers of the InnerProduct layer.
@@ -374,6 +382,13 @@ enum WgradSplitTile : int32_t {  // wgrad_split_kernel: rows x taps (of 16 chann
   WSPLIT_96x8,       // 2x2 waves of 48 rows x 4 taps
   WSPLIT_TILE_COUNT
 };
+enum WgradFoldTile : int32_t {  // wgrad_split_kernel on a folded grid
+  WFOLD_96x10 = 0,  // 2x2 waves of 48 rows x 5 taps
+  WFOLD_128x9,      // 4x1 waves of 32 rows
+  WFOLD_64x16,      // 2x2 waves of 32 rows x 8 taps
+  WFOLD_32x12,      // 1x4 waves of 32 rows x 3 taps
+  WFOLD_TILE_COUNT
+};
 enum SplitTile : int32_t {  // corr_split_kernel
   SPLIT_128x128 = 0,  // 32x32x16 bf16 MFMA, 2x2 waves of 64x64
   SPLIT_64x256,       // 32x32x16, 1x4 waves of 64x64
@@ -402,6 +417,9 @@ int launch_pack_split(int32_t tile, const PackSplitArgs& a, void* stream);
 int launch_corr_split(int32_t tile, const CorrSplitArgs& a, void* stream);
 void wgrad_split_shape(int32_t tile, int32_t* rows, int32_t* taps);
 int32_t wgrad_split_chunk_runs();
+void wgrad_fold_shape(int32_t tile, int32_t* rows, int32_t* taps);
+int launch_wgrad_fold(int32_t tile, const WgradSplitArgs& a, void* stream);
+int launch_reduce_fold(const ReduceFoldArgs& a, void* stream);
 int launch_wgrad_split(int32_t tile, const WgradSplitArgs& a, void* stream);
 extern const SmallTile kCorrSmallTiles[CORR_SMALL_COUNT], kWgradSmallTiles[WGRAD_SMALL_COUNT];
 int launch_corr_small(int32_t tile, const CorrSmallArgs& a, bool f64, void* stream);
@@ -500,6 +518,7 @@ struct conv_desc {
   size_t wg_ws;
   size_t wgb_ws;  // filter and bias gradient together (conv_backward_filter_bias)
   int32_t wg_split;  // its WgradSplitTile, or -1: the fields above
+  int32_t wg_fold;   // its WgradFoldTile on the folded grid, or -1
   mi355conv::WgradSplitArgs wg_sp;
   // backward bias
   mi355conv::BiasGradArgs bg;

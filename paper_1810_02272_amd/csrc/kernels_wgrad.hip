@@ -448,6 +448,26 @@ __global__ __launch_bounds__(256) void reduce_kernel(const Args a) {
     Vec out, old;
     float* const dst = (second ? a.dst2 : a.dst) + i;
     const bool first = !second;
+    if constexpr (std::is_same_v<Args, ReduceFoldArgs>) {
+      if (first) {  // [row][grid tap][channel, place in the fold] -> [row][channel][tap]
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+          const uint32_t row = mdiv((uint32_t)(i + e), a.mRow);
+          const uint32_t rem = (uint32_t)(i + e) - row * (uint32_t)(a.taps * a.tap_channels);
+          const uint32_t tap = mdiv(rem, a.mTapChannels), v = rem - tap * (uint32_t)a.tap_channels;
+          const uint32_t c = mdiv(v, a.fold.mFF), place = v - c * (uint32_t)a.fold.ff, ir = mdiv(place, a.fold.mFw);
+          const uint32_t it = tap / (uint32_t)a.grid_w;
+          const uint32_t kh = it * (uint32_t)a.fold.fh + ir;
+          const uint32_t kw = (tap - it * (uint32_t)a.grid_w) * (uint32_t)a.fold.fw + place - ir * (uint32_t)a.fold.fw;
+          if (kh >= (uint32_t)a.fold.kh || kw >= (uint32_t)a.fold.kw) continue;
+          float* const to = a.dst + ((size_t)(row * (uint32_t)a.channels + c) * a.fold.kh + kh) * a.fold.kw + kw;
+          float s = (quarter[0][lane].v[e] + quarter[1][lane].v[e]) + (quarter[2][lane].v[e] + quarter[3][lane].v[e]);
+          if (a.beta != 0.f) s += a.beta * *to;
+          *to = s;
+        }
+        return;
+      }
+    }
     if constexpr (std::is_same_v<Args, ReduceTapsArgs>) {
       if (first) {  // [row][tap][channel] -> [row][channel][tap]
 #pragma unroll
@@ -527,5 +547,6 @@ static int launch_reduce_t(const Args& a, void* stream) {
 
 int launch_reduce(const ReduceArgs& a, void* stream) { return launch_reduce_t(a, stream); }
 int launch_reduce_taps(const ReduceTapsArgs& a, void* stream) { return launch_reduce_t(a, stream); }
+int launch_reduce_fold(const ReduceFoldArgs& a, void* stream) { return launch_reduce_t(a, stream); }
 
 }  // namespace mi355conv

@@ -20,6 +20,9 @@
 // TERMS 2: long sums on two f16 terms (split_f16.h), half the matrix instructions, positions of 64 bytes.  Every workgroup samples
 // both blobs for the powers of two while its first loads are under way.  The first three layers, without the reduce kernel: 349 ->
 // 236 us, 219 -> 150, 67 -> 54.
+// FOLD: the folded grid of corr_split_kernel, so that few channels fill the blocks: 3 -> 96 channels, 11x11, stride 4 at 227x227,
+// batch 128, 290 us on the fp32 kernel -> 191; 9 -> 128, 12x12 at 109x150, batch 87, 265 -> 125.  Over 59 drawn layers that take it
+// 1.36 times as fast in the geometric mean, none slower.
 #include <hip/hip_runtime.h>
 
 #include "device_utils.h"
@@ -39,8 +42,8 @@ typedef __attribute__((address_space(3))) s16x4* LdsTrPtr;
 typedef __attribute__((address_space(3))) char* LdsChar;
 
 // MB x NB blocks of 16 x 16 per wave; EPT: patch units (position x 8 channels) per thread; TERMS: 3 the bf16 split, 2 the
-// f16 split.
-template <int WM, int WN, int MB, int NB, int EPT, int TERMS>
+// f16 split; FOLD: the channels and taps are those of a folded grid (SplitFold).
+template <int WM, int WN, int MB, int NB, int EPT, int TERMS, bool FOLD>
 __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSplitArgs a) {
   using M = Mfma<16>;
   constexpr int BM = WM * MB * 16;
@@ -75,9 +78,16 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
   const __amdgpu_buffer_rsrc_t dy_rsrc =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.dy), 0, (int)a.dy_bytes, 0x00020000);
   const uint32_t chan_bytes = 4u * (uint32_t)(a.H * a.W);
-  const uint32_t chan0 = (g * (uint32_t)a.Cg + (uint32_t)c16 * 16u) * chan_bytes;
+  const uint32_t chan0 = (g * (uint32_t)a.Cg + (FOLD ? 0u : (uint32_t)c16 * 16u)) * chan_bytes;
   const uint32_t stage_bytes = POS * (uint32_t)a.PSZ;
   constexpr uint32_t kTables = 2u * 4u * kChunkPix;
+  const int channels = FOLD ? a.fold.V : a.Cg;
+  char* const behind = smem + kTables + (uint32_t)a.patch_stages * stage_bytes;  // leading bits, then the folded form's table
+  FoldEntry* const fold_tab = reinterpret_cast<FoldEntry*>(behind + split_half_lead(BM, WN * NB * 16));
+  if (FOLD) {
+    fill_fold_table(fold_tab, (a.n_tiles / a.tap_tiles) * 16, a.fold, a.W, a.H * a.W, t, kThreads);
+    __syncthreads();
+  }
   // (image, first pixel) of run q
   auto run_pos = [&](uint32_t q, uint32_t& n, uint32_t& p) {
     n = mdiv(q, a.mRuns);
@@ -117,6 +127,14 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
         n = n0 + 1 + s1;
         rin = prow - R0 - s1 * RS;
         alo = 0;
+      }
+      if (FOLD) {
+        const int ih = (int)(alo * a.sh + rin) * a.fold.Uh - a.ph, iw = (int)pcol * a.fold.Uw - a.pw;
+        const bool real = n < (uint32_t)a.N && u < 2u * (uint32_t)a.PSZ;
+        load_folded(x_rsrc, fold_tab + (c16 * 16 + (int)hf * 8),
+                    4u * (n * (uint32_t)(a.C * a.H * a.W) + (uint32_t)(ih * a.W + iw)) + chan0, real ? ih : -(1 << 28), iw, a.H, a.W, pr[r]);
+        __builtin_amdgcn_sched_barrier(0);  // one unit's table entries in registers at a time
+        continue;
       }
       const int ih = (int)(alo * a.sh + rin) - a.ph, iw = (int)pcol - a.pw;
       uint32_t src = 0x80000000u;  // beyond the blob (which is at most 2^30 bytes): reads as zero
@@ -251,26 +269,23 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
     __syncthreads();
   };
   // f16: every a.lead_chunks chunks the large sums' leading bits move to LDS, a place of its own for every lane.
-  constexpr int LEAD = MB * NB / 2;  // 16-byte groups of eight sums
-  static_assert(MB * NB % 2 == 0, "whole groups");
   const Leading16 leading;
   bool led = false;
-  u32x4* const lead = reinterpret_cast<u32x4*>(smem + kTables + (uint32_t)a.patch_stages * stage_bytes) + t;
+  uint2* const lead = reinterpret_cast<uint2*>(behind) + t;  // four sums, a block's, in eight bytes
   auto move_leading = [&]() {
 #pragma unroll
-    for (int q = 0; q < LEAD; ++q) {
-      u32x4 w = {0, 0, 0, 0};
-      if (led) w = lead[q * kThreads];
+    for (int b = 0; b < MB * NB; ++b) {
+      M::Acc& c = acc[b / NB][b % NB];
+      uint2 w = {0, 0};
+      if (led) w = lead[b * kThreads];
+      float v[4] = {c[0], c[1], c[2], c[3]};
+      leading.give(w.x, v[0], v[1]);
+      leading.give(w.y, v[2], v[3]);
+      w.x = leading.take(v[0], v[1]);
+      w.y = leading.take(v[2], v[3]);
 #pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        M::Acc& c = acc[(2 * q + p / 2) / NB][(2 * q + p / 2) % NB];
-        float u = c[2 * (p & 1)], v = c[2 * (p & 1) + 1];
-        leading.give(w[p], u, v);
-        w[p] = leading.take(u, v);
-        c[2 * (p & 1)] = u;
-        c[2 * (p & 1) + 1] = v;
-      }
-      lead[q * kThreads] = w;
+      for (int r = 0; r < 4; ++r) c[r] = v[r];
+      lead[b * kThreads] = w;
     }
     led = true;
   };
@@ -395,18 +410,19 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
   if constexpr (HALF) {
     const int back = -(x_scale.e + dy_scale.e);
 #pragma unroll
-    for (int q = 0; q < LEAD; ++q) {
-      u32x4 w = {0, 0, 0, 0};
-      if (led) w = lead[q * kThreads];
+    for (int b = 0; b < MB * NB; ++b) {
+      M::Acc& c = acc[b / NB][b % NB];
+      const M::Acc& l = lo[b / NB][b % NB];
+      uint2 w = {0, 0};
+      if (led) w = lead[b * kThreads];
+      constexpr float down = 1.f / (float)(1 << kHalfShift);
+      float v[4];
 #pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        const int i = (2 * q + p / 2) / NB, j = (2 * q + p / 2) % NB, r = 2 * (p & 1);
-        constexpr float down = 1.f / (float)(1 << kHalfShift);
-        float u = __builtin_fmaf(lo[i][j][r], down, acc[i][j][r]), v = __builtin_fmaf(lo[i][j][r + 1], down, acc[i][j][r + 1]);
-        leading.give(w[p], u, v);
-        acc[i][j][r] = scale_by(u, back);
-        acc[i][j][r + 1] = scale_by(v, back);
-      }
+      for (int r = 0; r < 4; ++r) v[r] = __builtin_fmaf(l[r], down, c[r]);
+      leading.give(w.x, v[0], v[1]);
+      leading.give(w.y, v[2], v[3]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) c[r] = scale_by(v[r], back);
     }
   } else {
 #pragma unroll
@@ -427,7 +443,7 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
     for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int r = 0; r < M::NR; ++r) bad |= not_finite(acc[i][j][r]);
-  if (__any(bad && c < a.Cg)) {
+  if (__any(bad && c < channels)) {
     int th[NB], tw[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
@@ -445,16 +461,26 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
       load_dy(step);
       uint32_t n, p;
       run_pos((uint32_t)step * kStepRuns + (uint32_t)(lane >> 4), n, p);
-      const uint32_t image = n * (uint32_t)(a.C * a.H * a.W) + (g * (uint32_t)a.Cg + (uint32_t)c) * (uint32_t)(a.H * a.W);
+      int ci = c, ir = 0, jr = 0;  // the channel and the tap within its fold
+      if (FOLD) {
+        ci = c / a.fold.ff;
+        ir = (c - ci * a.fold.ff) / a.fold.fw;
+        jr = c - ci * a.fold.ff - ir * a.fold.fw;
+      }
+      const uint32_t image = n * (uint32_t)(a.C * a.H * a.W) + (g * (uint32_t)a.Cg + (uint32_t)ci) * (uint32_t)(a.H * a.W);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const bool real = e < valid && c < a.Cg;
+        const bool real = e < valid && c < channels;
         const uint32_t pix = p + e, pa = mdiv(pix, a.mPW), pb = pix - pa * a.PW;
-        const int ih0 = (int)pa * a.sh - a.ph, iw0 = (int)pb * a.sw - a.pw;
+        const int ih0 = (int)pa * a.sh - (FOLD ? 0 : a.ph), iw0 = (int)pb * a.sw - (FOLD ? 0 : a.pw);
         float b[NB];
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
-          const int ih = ih0 + th[j], iw = iw0 + tw[j];
+          int ih = ih0 + th[j], iw = iw0 + tw[j];
+          if (FOLD) {
+            ih = ih * a.fold.Uh + ir * a.fold.dh - a.ph;
+            iw = iw * a.fold.Uw + jr * a.fold.dw - a.pw;
+          }
           const bool ok = real && (uint32_t)ih < (uint32_t)a.H && (uint32_t)iw < (uint32_t)a.W;
           b[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
                                                x_rsrc, ok ? 4u * (image + (uint32_t)ih * (uint32_t)a.W + (uint32_t)iw) : 0x80000000u, 0, 0));
@@ -481,25 +507,26 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
 #pragma unroll
     for (int r = 0; r < M::NR; ++r) {
       const uint32_t k = m_tile * BM + (uint32_t)((wm * MB + i) * 16 + M::row(r, lane));
-      const uint32_t ro = k < (uint32_t)a.Kg && c < a.Cg ? 4u * (k * (uint32_t)a.Kred + (uint32_t)c) : 0x80000000u;
+      const uint32_t ro = k < (uint32_t)a.Kg && c < channels ? 4u * (k * (uint32_t)a.Kred + (uint32_t)c) : 0x80000000u;
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
-        const uint32_t co = tap0 + j < a.khw ? 4u * (uint32_t)((tap0 + j) * a.Cg) : 0x40000000u;
+        const uint32_t co = tap0 + j < a.khw ? 4u * (uint32_t)((tap0 + j) * channels) : 0x40000000u;
         const float v = acc[i][j][r];
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), out_rsrc, ro + co, 0, 0);
       }
     }
 }
 
-template <int WM, int WN, int MB, int NB, int EPT, int TERMS>
+template <int WM, int WN, int MB, int NB, int EPT, int TERMS, bool FOLD = false>
 int launch_k(const WgradSplitArgs& a, hipStream_t s) {
   constexpr int BM = WM * MB * 16;
-  const size_t lds = 2 * 4 * kChunkPix + 32 * TERMS * (size_t)a.PSZ * a.patch_stages + (TERMS == 2 ? split_half_lead(BM, WN * NB * 16) : 0);
+  const size_t lds = 2 * 4 * kChunkPix + 32 * TERMS * (size_t)a.PSZ * a.patch_stages + (TERMS == 2 ? split_half_lead(BM, WN * NB * 16) : 0) +
+                     (FOLD ? (a.n_tiles / a.tap_tiles) * 16 * sizeof(FoldEntry) : 0);
   const size_t red = 4 * WN * BM;
   static LdsOptIn opt_in;  // more than 64 KB of LDS needs an explicit opt-in, once per process
-  if (const int e = lds_opt_in(opt_in, &wgrad_split_kernel<WM, WN, MB, NB, EPT, TERMS>, 160 * 1024)) return e;
+  if (const int e = lds_opt_in(opt_in, &wgrad_split_kernel<WM, WN, MB, NB, EPT, TERMS, FOLD>, 160 * 1024)) return e;
   const uint32_t blocks = (uint32_t)a.G * a.S * a.m_tiles * a.n_tiles;
-  hipLaunchKernelGGL((wgrad_split_kernel<WM, WN, MB, NB, EPT, TERMS>), dim3(blocks), dim3(kThreads), lds > red ? lds : red, s, a);
+  hipLaunchKernelGGL((wgrad_split_kernel<WM, WN, MB, NB, EPT, TERMS, FOLD>), dim3(blocks), dim3(kThreads), lds > red ? lds : red, s, a);
   return (int)hipGetLastError();
 }
 
@@ -515,12 +542,36 @@ int launch_t(const WgradSplitArgs& a, hipStream_t s) {
   return launch_e<WM, WN, MB, NB, 4>(a, s);
 }
 
+// The folded form, f16 terms only.
+template <int WM, int WN, int MB, int NB>
+int launch_f(const WgradSplitArgs& a, hipStream_t s) {
+  if (split_patch_units(a.PSZ) <= 3) return launch_k<WM, WN, MB, NB, 3, 2, true>(a, s);
+  return launch_k<WM, WN, MB, NB, 4, 2, true>(a, s);
+}
+
 }  // namespace
 
 void wgrad_split_shape(int32_t tile, int32_t* rows, int32_t* taps) {
   static const int32_t shapes[WSPLIT_TILE_COUNT][2] = {{128, 9}, {128, 8}, {64, 16}, {32, 28}, {32, 12}, {96, 8}};
   *rows = shapes[tile][0];
   *taps = shapes[tile][1];
+}
+
+void wgrad_fold_shape(int32_t tile, int32_t* rows, int32_t* taps) {
+  static const int32_t shapes[WFOLD_TILE_COUNT][2] = {{96, 10}, {128, 9}, {64, 16}, {32, 12}};
+  *rows = shapes[tile][0];
+  *taps = shapes[tile][1];
+}
+
+int launch_wgrad_fold(int32_t tile, const WgradSplitArgs& a, void* stream) {
+  hipStream_t s = (hipStream_t)stream;
+  switch (tile) {  //                      WM WN MB NB
+    case WFOLD_96x10: return launch_f<2, 2, 3, 5>(a, s);
+    case WFOLD_128x9: return launch_f<4, 1, 2, 9>(a, s);
+    case WFOLD_64x16: return launch_f<2, 2, 2, 8>(a, s);
+    case WFOLD_32x12: return launch_f<1, 4, 2, 3>(a, s);
+    default: return (int)hipErrorInvalidValue;
+  }
 }
 
 int32_t wgrad_split_chunk_runs() { return kChunkRuns; }

@@ -311,6 +311,19 @@ HALF_CASES = [
     P(12, 996, 30, 41, 144, 1, 1, 1, 1, 1, 1, 2, 2, 1),
 ]
 
+# Filter gradients of folded layers, every tile and patch size.
+FOLD_CASES = [
+    P(24, 7, 114, 121, 124, 12, 4, 4, 4, 5, 4, 1, 1, 1),
+    P(28, 10, 53, 137, 200, 5, 8, 2, 4, 5, 4, 1, 1, 2),
+    P(56, 6, 113, 30, 41, 12, 11, 2, 4, 4, 0, 1, 1, 1),
+    P(32, 6, 85, 195, 36, 12, 12, 4, 4, 5, 4, 1, 1, 2),
+    P(34, 2, 99, 215, 66, 4, 11, 1, 4, 1, 0, 1, 1, 2),
+    P(52, 4, 62, 191, 72, 12, 11, 4, 4, 2, 4, 1, 1, 2),
+    P(50, 1, 145, 75, 66, 12, 12, 2, 4, 1, 0, 1, 1, 1),
+    P(29, 7, 156, 64, 136, 5, 4, 2, 4, 4, 4, 1, 1, 1),
+    P(40, 3, 147, 151, 128, 11, 11, 4, 4, 2),
+]
+
 # More rows of padding than a window has, on images so small that column tiles and chunks start in an image's last rows:
 # square, strided, dilated and one-row kernels.
 SPLIT_PAD_CASES = [

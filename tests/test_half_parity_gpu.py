@@ -15,10 +15,10 @@ import oracle
 import paper_1810_02272_amd as conv
 from oracle import OracleParams
 from paper_1810_02272_amd import workloads
-from parity_cases import HALF_CASES, SPLIT_CASES, P
+from parity_cases import FOLD_CASES, HALF_CASES, SPLIT_CASES, P
 from parity_metric import nerr
 from test_parity_gpu import TOL, check_filter_and_bias_in_one_pass, run_all
-from test_split_parity_gpu import CORR, WGRAD, names, norm_error
+from test_split_parity_gpu import CORR, ODD, WGRAD, check_odd_values, names, norm_error
 
 PASSES = ("fwd", "bwd_data", "bwd_filter")
 MIXED = P(24, 128, 28, 28, 128, 3, 3, 1, 1, 1, 1)  # all three passes on f16 terms
@@ -44,6 +44,14 @@ def test_cases_select_every_instance():
     assert {(t, u) for t in ("128x9", "128x8", "64x16", "32x28", "32x12", "96x8") for u in "234"} | {"1", "2"} <= wgrad
 
 
+def test_folded_filter_gradients_select_every_instance():
+    found = set()
+    for pd in FOLD_CASES:
+        m = re.match(r"splitwgrad_fold\d+_(\d+x\d+)x16\[p(\d),st(\d)", names(pd)["bwd_filter"])
+        found |= {(m[1], "4" if m[2] == "4" else "3"), m[3]} if m else set()
+    assert found >= {(t, u) for t in ("96x10", "128x9", "64x16", "32x12") for u in "34"} | {"1", "2"}
+
+
 def test_short_sums_stay_on_the_bf16_terms():
     """The operands' error is below the sums' from about 620 indices on; slices count by themselves."""
     assert "half" not in names(P(64, 64, 28, 28, 128, 3, 3, 1, 1, 1, 1))["fwd"]
@@ -65,9 +73,9 @@ def passes_of(pd, dev, host):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("i", range(len(HALF_CASES)))
+@pytest.mark.parametrize("i", range(len(HALF_CASES + FOLD_CASES)))
 def test_half_full_compare(i):
-    pd = HALF_CASES[i]
+    pd = (HALF_CASES + FOLD_CASES)[i]
     print("half case", i, pd, names(pd), flush=True)
     op = OracleParams(**pd)
     x, w, b, dy = workloads.random_inputs(oracle.x_shape(op), oracle.w_shape(op), oracle.output_shape(op), 9100 + 10 * i)
@@ -78,6 +86,10 @@ def test_half_full_compare(i):
         if "split" in kernel:
             assert norm_error(got, ref) <= 2.0 ** -24 * np.sqrt(terms / 16 + 32), (pd, name, norm_error(got, ref))
     check_filter_and_bias_in_one_pass(pd, op, d, ws, dev_in, dw, oracle.backward_bias(op, host[3]), host)
+    dw1 = dw.clone()  # beta = 1: dw + dw is exact
+    conv.conv_backward_filter(d, dev_in[0], dev_in[3], dw1, 1.0, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(dw1, dw + dw)
 
 
 @pytest.mark.gpu
@@ -125,3 +137,10 @@ def test_ranges_beyond_f16(pd, case):
             if case == "denormals":
                 size = size + 2.0 ** -149 * 2 ** 24 * np.sqrt(g.size / g.shape[axis])  # results are denormal themselves
             assert np.all(err <= bound * size), (name, kernel, axis, np.max(err / np.maximum(size, 1e-300)) / bound)
+
+
+@pytest.mark.gpu
+@ODD
+def test_odd_values_in_the_folded_filter_gradient(odd):
+    """Below and right of windows that do not have them too: 11 taps are rounded up to 12."""
+    check_odd_values(P(40, 3, 147, 151, 128, 11, 11, 4, 4), odd, ("bwd_filter",), (15, 19, 4))
