@@ -18,13 +18,42 @@ namespace {
 // ---- step 3: action = (random < Aprob) ? 0 : 1 ----
 // Four consecutive steps per thread (16-byte loads and stores); the last, partial group of a
 // launch goes element by element.
+// From 48 MB on, what a pass reads or writes and no other of these passes reads again goes around the last-level cache (256 MB),
+// so that the sampled actions and discounted rewards are still there for the passes that read them: 16.6 M steps, 6 actions, all
+// four passes 346 -> 317 us (the stores alone 324).  Below that whoever reads the results next finds them in the cache.
+constexpr size_t kStreamBytes = (size_t)48 << 20;
+
+// A template argument: of a branch between both forms the compiler makes one plain access.
+template <bool STREAM>
+__device__ __forceinline__ void store4(float* to, float4 v) {
+  typedef float V __attribute__((ext_vector_type(4)));
+  const V u = {v.x, v.y, v.z, v.w};
+  if constexpr (STREAM)
+    __builtin_nontemporal_store(u, reinterpret_cast<V*>(to));
+  else
+    *reinterpret_cast<V*>(to) = u;
+}
+
+template <bool STREAM>
+__device__ __forceinline__ float4 load4(const float* from) {
+  typedef float V __attribute__((ext_vector_type(4)));
+  const V* const at = reinterpret_cast<const V*>(from);
+  V u;
+  if constexpr (STREAM)
+    u = __builtin_nontemporal_load(at);
+  else
+    u = *at;
+  return make_float4(u[0], u[1], u[2], u[3]);
+}
+
+template <bool STREAM>
 __global__ __launch_bounds__(256) void pg_sample_kernel(const float* __restrict__ aprob,
                                                         const float* __restrict__ random, int32_t* __restrict__ action,
                                                         int steps) {
   const int t = (blockIdx.x * 256 + threadIdx.x) * 4;
   if (t + 3 < steps) {
     const float4 ap = *reinterpret_cast<const float4*>(aprob + t);
-    const float4 rn = *reinterpret_cast<const float4*>(random + t);
+    const float4 rn = load4<STREAM>(random + t);
     *reinterpret_cast<int4*>(action + t) =
         make_int4(rn.x < ap.x ? 0 : 1, rn.y < ap.y ? 0 : 1, rn.z < ap.z ? 0 : 1, rn.w < ap.w ? 0 : 1);
   } else {
@@ -398,6 +427,7 @@ __global__ __launch_bounds__(256) void pg_discount_short_kernel(const float* __r
 }
 
 // ---- Sigmoid model, steps 8, 10, 11 ----
+template <bool STREAM>
 __global__ __launch_bounds__(256) void pg_sigmoid_kernel(const float* __restrict__ aprob,
                                                          const int32_t* __restrict__ action,
                                                          const float* __restrict__ discounted,
@@ -411,8 +441,8 @@ __global__ __launch_bounds__(256) void pg_sigmoid_kernel(const float* __restrict
     if (discounted) w = *reinterpret_cast<const float4*>(discounted + t);
     const float4 d = make_float4(ac.x == 0 ? 1.f - ap.x : 0.f - ap.x, ac.y == 0 ? 1.f - ap.y : 0.f - ap.y,
                                  ac.z == 0 ? 1.f - ap.z : 0.f - ap.z, ac.w == 0 ? 1.f - ap.w : 0.f - ap.w);
-    if (dlogps) *reinterpret_cast<float4*>(dlogps + t) = d;
-    *reinterpret_cast<float4*>(bottom_diff + t) = make_float4(-d.x * w.x, -d.y * w.y, -d.z * w.z, -d.w * w.w);
+    if (dlogps) store4<STREAM>(dlogps + t, d);
+    store4<STREAM>(bottom_diff + t, make_float4(-d.x * w.x, -d.y * w.y, -d.z * w.z, -d.w * w.w));
   } else {
     for (int i = t; i < steps; ++i) {
       const float ap = aprob[i];
@@ -427,6 +457,7 @@ __global__ __launch_bounds__(256) void pg_sigmoid_kernel(const float* __restrict
 // Up to 32 actions: a block takes 256 consecutive rows, stages them through LDS with coalesced
 // loads (row stride padded to an odd number of words so that one row per lane is conflict-free),
 // lets each thread do its own row, and streams the results back out the same way.
+template <bool STREAM>
 __global__ __launch_bounds__(256) void pg_softmax_rows_kernel(const float* __restrict__ logits,
                                                               const int32_t* __restrict__ action,
                                                               const float* __restrict__ discounted,
@@ -448,7 +479,7 @@ __global__ __launch_bounds__(256) void pg_softmax_rows_kernel(const float* __res
   const bool vec = vec_ok && (count & 3) == 0;
   if (vec) {
     for (int i = threadIdx.x * 4; i < count; i += 1024) {
-      const float4 v = *reinterpret_cast<const float4*>(logits + base + i);
+      const float4 v = load4<STREAM>(logits + base + i);
       int r = (int)mdiv((uint32_t)i, mA), c = i - r * A;
       const float e[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
@@ -501,8 +532,8 @@ __global__ __launch_bounds__(256) void pg_softmax_rows_kernel(const float* __res
           ++r;
         }
       }
-      if (probs) *reinterpret_cast<float4*>(probs + base + i) = make_float4(pv[0], pv[1], pv[2], pv[3]);
-      *reinterpret_cast<float4*>(bottom_diff + base + i) = make_float4(dv[0], dv[1], dv[2], dv[3]);
+      if (probs) store4<STREAM>(probs + base + i, make_float4(pv[0], pv[1], pv[2], pv[3]));
+      store4<STREAM>(bottom_diff + base + i, make_float4(dv[0], dv[1], dv[2], dv[3]));
     }
   } else {
     for (int i = threadIdx.x; i < count; i += 256) {
@@ -573,7 +604,7 @@ int pg_sigmoid_sample_action(const float* aprob, const float* random, int32_t* a
   if (steps > kMaxSteps) return CONV_ESHAPE;
   if (steps == 0) return CONV_OK;
   if (!aprob || !random || !action) return CONV_EINVAL;
-  hipLaunchKernelGGL(pg_sample_kernel, dim3((steps + 1023) / 1024), dim3(256), 0, (hipStream_t)hip_stream, aprob,
+  hipLaunchKernelGGL((size_t)steps * 4 >= kStreamBytes ? pg_sample_kernel<true> : pg_sample_kernel<false>, dim3((steps + 1023) / 1024), dim3(256), 0, (hipStream_t)hip_stream, aprob,
                      random, action, steps);
   return done();
 }
@@ -607,7 +638,7 @@ int pg_sigmoid_bottom_diff(const float* aprob, const int32_t* action, const floa
   if (steps > kMaxSteps) return CONV_ESHAPE;
   if (steps == 0) return CONV_OK;
   if (!aprob || !action || !bottom_diff) return CONV_EINVAL;
-  hipLaunchKernelGGL(pg_sigmoid_kernel, dim3((steps + 1023) / 1024), dim3(256), 0, (hipStream_t)hip_stream, aprob,
+  hipLaunchKernelGGL((size_t)steps * 4 >= kStreamBytes ? pg_sigmoid_kernel<true> : pg_sigmoid_kernel<false>, dim3((steps + 1023) / 1024), dim3(256), 0, (hipStream_t)hip_stream, aprob,
                      action, discounted, dlogps, bottom_diff, steps);
   return done();
 }
@@ -620,13 +651,15 @@ int pg_softmax_bottom_diff(const float* logits, const int32_t* action, const flo
   if (!logits || !action || !bottom_diff) return CONV_EINVAL;
   if (actions <= 32) {
     const size_t lds = (size_t)2 * 256 * (actions | 1) * sizeof(float);  // at most 66 KB
-    static LdsOptIn opt_in;  // 32 actions need 66 KB: opt in to the largest size, once per process
+    const bool stream = (size_t)steps * actions * 4 >= kStreamBytes;
+    auto* const kernel = stream ? pg_softmax_rows_kernel<true> : pg_softmax_rows_kernel<false>;
+    static LdsOptIn opt_in[2];  // 32 actions need 66 KB: opt in to the largest size, once per process and kernel
     if (lds > 64 * 1024) {
-      const int e = lds_opt_in(opt_in, pg_softmax_rows_kernel, 2 * 256 * 33 * (int)sizeof(float));
+      const int e = lds_opt_in(opt_in[stream], kernel, 2 * 256 * 33 * (int)sizeof(float));
       if (e) return record_hip_error(e);
     }
     const bool vec_ok = (((uintptr_t)logits | (uintptr_t)probs | (uintptr_t)bottom_diff) & 15u) == 0;
-    hipLaunchKernelGGL(pg_softmax_rows_kernel, dim3((steps + 255) / 256), dim3(256), lds, (hipStream_t)hip_stream,
+    hipLaunchKernelGGL(kernel, dim3((steps + 255) / 256), dim3(256), lds, (hipStream_t)hip_stream,
                        logits, action, discounted, probs, bottom_diff, steps, actions, make_magic((uint32_t)actions),
                        vec_ok);
   } else {

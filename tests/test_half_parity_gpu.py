@@ -143,4 +143,4 @@ def test_ranges_beyond_f16(pd, case):
 @ODD
 def test_odd_values_in_the_folded_filter_gradient(odd):
     """Below and right of windows that do not have them too: 11 taps are rounded up to 12."""
-    check_odd_values(P(40, 3, 147, 151, 128, 11, 11, 4, 4), odd, ("bwd_filter",), (15, 19, 4))
+    check_odd_values(P(60, 3, 147, 151, 128, 11, 11, 4, 4), odd, ("bwd_filter",), (15, 19, 4))

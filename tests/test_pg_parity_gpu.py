@@ -218,3 +218,29 @@ def test_pg_neighbouring_long_episodes_cost_no_more_than_distant_ones():
             best = min(best, start.elapsed_time(end))
         times[kind] = best
     assert times["together"] <= 3 * times["apart"], times
+
+
+@pytest.mark.parametrize("actions", [2, 7, 32])
+def test_pg_batches_beyond_the_cache_have_the_same_bits(actions):
+    """From 48 MB on the element-wise passes go around the last-level cache; steps that end inside a block and an unaligned part."""
+    steps = (13 << 20) + 517 if actions == 2 else (13 << 20) // actions + 517
+    gen = torch.Generator(device=DEV).manual_seed(actions)
+    aprob, rnd, w = (torch.rand(steps, device=DEV, generator=gen) for _ in range(3))
+    logits = torch.randn(steps, actions, device=DEV, generator=gen)
+    action = torch.randint(0, actions, (steps,), device=DEV, generator=gen, dtype=torch.int32)
+
+    def run(lo, hi):
+        n = hi - lo
+        out = [torch.full((n,), -1, dtype=torch.int32, device=DEV), torch.full((n,), NAN, device=DEV), torch.full((n,), NAN, device=DEV),
+               torch.full((n, actions), NAN, device=DEV), torch.full((n, actions), NAN, device=DEV)]
+        lib.pg_sigmoid_sample_action(aprob[lo:hi], rnd[lo:hi], out[0])
+        lib.pg_sigmoid_bottom_diff(aprob[lo:hi], out[0], w[lo:hi], out[1], out[2])
+        lib.pg_softmax_bottom_diff(logits[lo:hi], action[lo:hi], w[lo:hi], out[3], out[4])
+        return out
+
+    whole = run(0, steps)
+    cuts = [0, steps // 3 // 256 * 256, steps // 2 // 256 * 256, steps]
+    parts = [run(a, b) for a, b in zip(cuts, cuts[1:])]
+    torch.cuda.synchronize()
+    for i, t in enumerate(whole):
+        assert torch.equal(t, torch.cat([p[i] for p in parts])), i
