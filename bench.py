@@ -30,6 +30,7 @@ PEAK_FP64_MFMA_TFLOPS = 78.6   # ... and fp64
 # fp32 products of the split kernels: operands split exactly in three bf16 terms, six bf16 matrix products for one fp32
 # product, at the nominal dense bf16 rate of 2.5 PFLOP/s
 PEAK_SPLIT_MFMA_TFLOPS = 2500.0 / 6.0
+PEAK_HALF_MFMA_TFLOPS = 2500.0 / 3.0  # two f16 terms, three products
 PEAK_HBM_GBS = 8000.0
 
 
@@ -413,7 +414,8 @@ def main():
                     "algorithmic_bytes_per_launch": bytes_launch}
     else:
         achieved = dlayer.flop_per_pass / (dms * 1e-3) / 1e12
-        pass_peak = round(PEAK_SPLIT_MFMA_TFLOPS, 1) if "split" in kernel_names.get(dp, dp) else peak
+        kernel = kernel_names.get(dp, dp)
+        pass_peak = peak if "split" not in kernel else round(PEAK_HALF_MFMA_TFLOPS if "half" in kernel else PEAK_SPLIT_MFMA_TFLOPS, 1)
         roofline = {"bound": "mfma", "achieved": round(achieved, 2), "peak": pass_peak,
                     "unit": "TFLOP/s", "frac": round(achieved / pass_peak, 4), "traffic": None}
     roofline.update({"kernel": kernel_names.get(dp, dp), "layer": dl, "pass": dp, "avg_ms": round(dms, 5),

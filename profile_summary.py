@@ -12,7 +12,7 @@ profiles/hbm_traffic.json (which bench.py reports as ``roofline.traffic``).  Dis
 matched to (layer, pass) by their order inside a step (the main kernel of each pass, per layer);
 ``--workload`` names the bench.py workload the two runs were made with.
 ``sq`` condenses a run with SQ_BUSY_CYCLES SQ_WAVE_CYCLES SQ_VALU_MFMA_BUSY_CYCLES
-SQ_INSTS_VALU_MFMA_MOPS_F32 (_BF16 for the split kernels, _F64 for the double path) SQ_WAIT_INST_ANY SQ_LDS_BANK_CONFLICT SQ_INSTS_MFMA SQ_INSTS_VALU into MFMA
+SQ_INSTS_VALU_MFMA_MOPS_F32 (_BF16 or _F16 for the split kernels, _F64 for the double path) SQ_WAIT_INST_ANY SQ_LDS_BANK_CONFLICT SQ_INSTS_MFMA SQ_INSTS_VALU into MFMA
 utilisation per kernel (counters are summed over 32 shader engines / 1024 SIMDs of the chip).
 """
 from __future__ import annotations
@@ -122,7 +122,7 @@ def sq(directory: str) -> None:
         v = {k: sum(x) / len(x) for k, x in c.items()}
         cyc = v["SQ_BUSY_CYCLES"] / 32.0
         print(f"{name:50s} {blocks:6d} {cyc / 1e3:8.0f} {100 * v['SQ_VALU_MFMA_BUSY_CYCLES'] / 1024 / cyc:8.1f}% "
-              f"{sum(v.get('SQ_INSTS_VALU_MFMA_MOPS_' + t, 0.0) for t in ('F32', 'F64', 'BF16')) * 512 / 1e9:11.2f} "
+              f"{sum(v.get('SQ_INSTS_VALU_MFMA_MOPS_' + t, 0.0) for t in ('F32', 'F64', 'BF16', 'F16')) * 512 / 1e9:11.2f} "
               f"{v['SQ_WAVE_CYCLES'] * 4 / 1024 / cyc:10.2f} "
               f"{100 * v['SQ_WAIT_INST_ANY'] / v['SQ_WAVE_CYCLES']:4.0f}% "
               f"{(v['SQ_INSTS_VALU'] - v['SQ_INSTS_MFMA']) / v['SQ_INSTS_MFMA']:9.2f} {v['SQ_LDS_BANK_CONFLICT']:9.0f}")
