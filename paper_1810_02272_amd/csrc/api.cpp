@@ -199,7 +199,7 @@ void split_variant_name(char* buf, size_t len, int32_t tile, const CorrSplitArgs
   split_tile_shape(tile, &bm, &bn, &mt);
   const char e = a.simple_epilogue ? 's' : ((uint32_t)a.out_elems < (1u << 29) ? 'r' : 'p');
   snprintf(buf, len, "corrsplit_m%d_%dx%d[%s%d,e%c](S=%d,%sL=%d)", mt, bm, bn, a.fold.subs ? a.fold.pixels ? "rows" : "cols" : a.fold.ff > 1 ? "fold" : "p",
-           a.fold.subs ? a.fold.subs : a.fold.ff > 1 ? a.fold.ff : split_patch_units(a.PSZ, bn), e,
+           a.fold.subs ? a.fold.subs : a.fold.ff > 1 ? a.fold.ff : split_patch_units(a.PSZ + a.half, bn), e,
            a.ksplit, a.half ? "half," : "", 2 + (a.ksplit > 1) + (zero_fill != 0));
 }
 
@@ -527,7 +527,7 @@ int32_t half_interval(double K, double bf16_K, double step, int32_t unit) {
 // The same for corr_split_kernel: `cps` of `chunks` chunks of T taps in a slice.  The tiles that hold several steps' weights move the
 // leading bits between chunks only.  The samples are of four neighbours (and of eight weights: reductions are longer).
 int32_t corr_half_interval(const CorrArgs& base, int32_t tile, int32_t mt, int64_t T, int64_t chunks, int64_t cps, int64_t bf16_cps) {
-  if (base.in_bytes < 16) return 0;
+  if (cps > kUnheldChunks) return 0;
   const int32_t step = mt == 32 ? 16 : 32;
   const bool by_chunk = tile == SPLIT_64x128 || tile == SPLIT_32x256 || tile == SPLIT_32x128;
   const double chunk = (double)base.Kred / (double)chunks;
@@ -578,10 +578,10 @@ SplitPlan plan_split(const CorrArgs& base, const SplitGrid& grid, int64_t out_el
                                               512 / plan.w.pitch);
       psz = max_rows * plan.w.pitch + plan.w.share;
     }
-    if (psz > 512) continue;
+    if (psz + (half && image) > 512) continue;  // with kUnheldBytes
     const int64_t units = (int64_t)base.G * ceil_div(base.Mrows, bm) * ceil_div(base.ncols, bn);
     const int64_t spc = ceil_div(T, mt == 32 ? 1 : 2);
-    const double units_per_thread = image ? (double)split_patch_units(psz, bn) : 4.0;
+    const double units_per_thread = image ? (double)split_patch_units(psz + half, bn) : 4.0;
     for (int64_t S = 1; S <= 16 && S <= chunks; ++S) {
       if (S > 1 && (units * S > 2048 || units > 512)) break;
       const int64_t per_cu = ceil_div(units * S, 256), cps = ceil_div(chunks, S);
@@ -602,12 +602,26 @@ SplitPlan plan_split(const CorrArgs& base, const SplitGrid& grid, int64_t out_el
   return plan;
 }
 
+// Fragments of packed weights of a plan (row blocks x steps), and what they take in the workspace: three KB each on bf16 terms, on
+// f16 terms five, a word, and the samples.
+int64_t split_fragments(const CorrArgs& base, const SplitGrid& grid, int32_t tile) {
+  int32_t bm, bn, mt;
+  split_tile_shape(tile, &bm, &bn, &mt);
+  return base.G * ceil_div(base.Mrows, bm) * (bm / mt) * ceil_div(grid.f.V, grid.f.subs ? 64 : 16) *
+         ceil_div(grid.TH * grid.TW, mt == 32 ? 1 : 2);
+}
+
+int64_t split_pack_bytes(int64_t fragments, bool half) {
+  return half ? fragments * 5120 + round_up(4 * fragments, 512) + kSampleBytes : fragments * 3072;
+}
+
 // The cheaper of the two splits.  The f16 one's pack kernel samples both blobs: 3 us more, and 0.26 us a MB of weights.
 SplitPlan plan_split(const CorrArgs& base, const SplitGrid& grid, int64_t out_elems) {
   const SplitPlan bf16 = plan_split(base, grid, out_elems, false, 0);
   if (bf16.tile < 0 || grid.f.ff > 1) return bf16;
   SplitPlan f16 = plan_split(base, grid, out_elems, true, bf16.S);
   if (f16.tile < 0) return bf16;
+  if (split_pack_bytes(split_fragments(base, grid, f16.tile), true) + (f16.S > 1 ? 4 * f16.S * out_elems : 0) >= 4 * kMaxElems) return bf16;
   f16.cost += 3 + 0.26 * 4e-6 * (double)base.G * base.Mrows * base.Kred;
   return f16.cost < bf16.cost ? f16 : bf16;
 }
@@ -703,15 +717,19 @@ size_t configure_split(const CorrArgs& base, const PackArgs& pbase, int64_t cg_i
   a.ksplit = (int32_t)ceil_div(chunks, a.chunks_per_split);
   k.split_chunks = a.NS;
   // Six bytes a packed weight and the slices: a workspace beyond the boundary's 2^30 elements stays with the fp32 kernel (four).
-  int64_t bytes = (int64_t)a.G * a.m_tiles * chunks * ceil_div(a.THW, mt == 32 ? 1 : 2) * (bm / mt) * 3072;
+  const int64_t fragments = split_fragments(base, grid, tile), bytes = split_pack_bytes(fragments, plan.half);
   if (plan.half) {
     a.half = k.half = 1;
     a.lead_steps = corr_half_interval(base, tile, mt, a.THW, chunks, a.chunks_per_split, plan.bf16_cps);
-    const uint32_t stage = pixels ? split_half_stage(4, bn) : split_half_stage(columns ? 4 : split_patch_units(a.PSZ, bn), 0);
-    a.patch_stages = 2 * stage + split_half_lead(bm, bn) <= 80 * 1024 ? 2 : 1;  // two workgroups per compute unit
+    const uint32_t stage = pixels ? split_half_stage(4, bn) : split_half_stage(columns ? 4 : split_patch_units(a.PSZ + 1, bn), 0);
+    const uint32_t behind = split_half_lead(bm, bn) + (columns && !pixels ? kUnheldBytes : 0);
+    a.patch_stages = 2 * stage + behind <= 80 * 1024 ? 2 : 1;  // two workgroups per compute unit
+    const int64_t per_sample = ceil_div(n_img, kSamples);
+    a.mSample = make_magic((uint32_t)per_sample);
     k.in_elems = a.in_bytes / 4;
+    k.sample_elems = (uint32_t)(per_sample * a.in_img_stride);
+    k.fragments = (uint32_t)fragments;
     k.w_elems = (uint32_t)(pbase.G * pbase.Kg * pbase.Cg * pbase.kh * pbase.kw);
-    bytes += kSampleBytes;
   }
   if (bytes + (a.ksplit > 1 ? 4 * a.ksplit * out_elems : 0) >= 4 * kMaxElems) {
     tile = -1;
@@ -866,7 +884,7 @@ int32_t configure_wgrad_split(const WgradArgs& w, int32_t fp32_tile, int64_t N, 
   if (best_lead) {
     a.half = 1;
     a.lead_chunks = best_lead;
-    const uint32_t rest = 2 * 4 * 8 * (uint32_t)chunk_runs + split_half_lead(rows, 16 * taps);
+    const uint32_t rest = 2 * 4 * 8 * (uint32_t)chunk_runs + split_half_lead(rows, 16 * taps) + kUnheldWgradBytes;
     a.patch_stages = 128 * (uint32_t)a.PSZ + rest <= 80 * 1024 ? 2 : 1;  // two workgroups per compute unit
   }
   const int64_t tiles = (int64_t)a.G * a.m_tiles * a.n_tiles;
@@ -953,7 +971,7 @@ int32_t configure_wgrad_fold(const WgradArgs& w, int32_t fp32_tile, int64_t N, i
   a.S = (int32_t)ceil_div(chunks, best_cps);
   a.half = 1;
   a.lead_chunks = best_lead;
-  const uint32_t rest = 2 * 4 * 8 * (uint32_t)chunk_runs + split_half_lead(rows, 16 * taps) + 128 * (uint32_t)c16;
+  const uint32_t rest = 2 * 4 * 8 * (uint32_t)chunk_runs + split_half_lead(rows, 16 * taps) + kUnheldWgradBytes + 128 * (uint32_t)c16;
   a.patch_stages = 128 * (uint32_t)a.PSZ + rest <= 80 * 1024 ? 2 : 1;  // two workgroups per compute unit
   return best;
 }
@@ -1354,10 +1372,14 @@ int launch_split(int32_t tile, const PackSplitArgs& pack, const CorrSplitArgs& p
   k.w = w;
   k.A = static_cast<float*>(ws);
   k.in = in;
-  k.scale = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + pack_bytes - kSampleBytes);
+  if (k.half) {
+    k.unheld = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + (size_t)k.fragments * 5120);
+    k.scale = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + pack_bytes - kSampleBytes);
+  }
   if (const int e = launch_pack_split(tile, k, stream)) return e;
   CorrSplitArgs a = plan;
   a.scale = k.scale;
+  a.unheld = k.unheld;
   a.A = k.A;
   a.in = in;
   a.bias = bias;

@@ -13,16 +13,17 @@ namespace mi355conv {
 //   coltab[col] = {offset, row, column, -}                   (column = (image, a, b))
 // An element is stored when (row shift + row, column shift + column) lies inside the output
 // image; rows past the matrix edge and columns past the batch carry a shift that fails the test.
-// Must be entered after a barrier: the tables overwrite the pipeline buffers at `smem`.
+// Must be entered after a barrier: the tables overwrite the pipeline buffers at `smem`.  `again`: the sums are added to what the
+// same call's first sums, with bias, have left in the output or the slice.
 template <int MT, int MB, int NB, int BM, int BN, typename Acc>
 __device__ __forceinline__ void corr_epilogue(const CorrArgs& a, float* smem, Acc (&acc)[MB][NB], uint32_t m_tile,
-                                              uint32_t col_tile, uint32_t g, int wm, int wn, uint32_t split = 0) {
+                                              uint32_t col_tile, uint32_t g, int wm, int wn, uint32_t split = 0, bool again = false) {
   using M = Mfma<MT>;
   // With a split reduction every split writes its raw partial sums, in the output blob's own
   // layout, to its slice of the workspace; a reduce kernel adds the slices and the bias.
   float* const out = a.ksplit > 1 ? a.part + (size_t)split * a.out_elems : a.out;
-  const float* const bias = a.ksplit > 1 ? nullptr : a.bias;
-  const bool accumulate = a.accumulate != 0 && a.ksplit <= 1;
+  const float* const bias = a.ksplit > 1 || again ? nullptr : a.bias;
+  const bool accumulate = again || (a.accumulate != 0 && a.ksplit <= 1);
   const int t = threadIdx.x, lane = t & 63;
   int4* rowtab = reinterpret_cast<int4*>(smem);
   int4* coltab = rowtab + BM;

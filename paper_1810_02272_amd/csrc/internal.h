@@ -126,13 +126,16 @@ struct CorrSplitArgs : CorrArgs {
   int32_t patch_stages;      // patch stages in LDS (1 or 2)
   int32_t share_w, share_h;  // padding columns / rows that neighbouring patch rows / images share
   // f16 split (split_f16.h): steps between two moves of the sums' leading bits, and what the pack kernel leaves behind the
-  // packed weights: the largest value of each of its samples of the input, and the weights' power of two
+  // packed weights: the largest value of a sample of every group of images, the weights' power of two, and for every fragment
+  // of weights whether it has one that the f16 terms do not hold
   int32_t half, lead_steps;
-  uint32_t* scale;
+  Magic mSample;  // division by the images of a sample
+  const uint32_t *scale, *unheld;
 };
 
-constexpr int kSampleBlocks = 64;
-constexpr uint32_t kSampleBytes = 512;  // kSampleBlocks + 1 words, kept to whole lines
+constexpr int kSamples = 256;               // groups of images
+constexpr uint32_t kSampleBytes = 1536;     // kSamples + 1 words, kept to whole lines
+constexpr uint32_t kWeakSample = 1u << 31;  // mark of a sample with few values that are not zero
 
 // LDS of the f16 form: a patch stage of units_per_thread units (the pixel form, of tiles of bn columns: four groups of bn + 1
 // positions and two halves), and the leading bits of a tile's sums.
@@ -140,6 +143,12 @@ constexpr uint32_t split_half_stage(int32_t units_per_thread, int32_t pixel_bn) 
   return 32u * (uint32_t)(pixel_bn ? 8 * (pixel_bn + 1) : 256 * units_per_thread);
 }
 constexpr uint32_t split_half_lead(int32_t bm, int32_t bn) { return 2u * (uint32_t)(bm * bn); }
+// A bit for each chunk of a slice that the f16 terms do not hold: in the last unit of a stage, which patches leave free; the column
+// form's fill it, and there they are behind the leading bits.
+constexpr uint32_t kUnheldBytes = 16;
+constexpr int64_t kUnheldChunks = 8 * kUnheldBytes;
+// The filter gradient's: the numbers of the last two chunks whose patch is not held, and a bit for each 128th of a slice.
+constexpr uint32_t kUnheldWgradBytes = 32;
 
 constexpr int kPatchEPT = 3;  // patch elements per thread and channel: PSZ <= 3 * 256
 
@@ -171,8 +180,9 @@ struct PackSplitArgs : PackArgs {
   SplitFold fold;
   int32_t half;          // the f16 split: `in`, the gathered blob, and the weights are sampled
   const float* in;
-  uint32_t in_elems, w_elems;
-  uint32_t* scale;
+  uint32_t in_elems, sample_elems, w_elems;  // of a group of images
+  uint32_t fragments;
+  uint32_t *scale, *unheld;
 };
 
 // Backward filter: part[s][g][k][nn] = sum over the split's columns of dy * gathered x.

@@ -23,11 +23,12 @@
 // 13x13) 292 -> 174 and 309 -> 200; 6.7 GFLOP (45 -> 77, 3x5 at 51x67, stride 2 x 1) 92 -> 52 and 87 -> 50; 1.3 GFLOP (32 ->
 // 32, 5x5 at 16x16, batch 100) 29 -> 21.  172 and 115 us are the matrix instructions of the first two at 2000 TFLOP/s.
 //
-// TERMS 2: long reductions on two f16 terms (split_f16.h), half the matrix instructions.  The stage is [h, m][half][position] then,
+// HALF: long reductions on two f16 terms (split_f16.h), half the matrix instructions.  The stage is [h, m][half][position] then,
 // 16 bytes a position.  The same passes: 57.3 GFLOP 249 -> 162 us and 269 -> 171, 38.3 GFLOP 172 -> 108 and 206 -> 129, 6.7 GFLOP 49
 // -> 38 and 53 -> 41; the pack kernel, which samples both blobs, 0.5 to 1.4 us more.  The matrix unit is busy 60 % of the cycles, at
 // the clock that the chip's power leaves (1.7 GHz); a quarter of the waves' time are waits for weights, patches and barriers.  Weights
 // two steps ahead gave nothing (108 -> 112 us where the registers hold them, spills elsewhere).
+// AGAIN: what a workgroup's HALF sums had to leave out, chunk by chunk, it adds on the bf16 terms behind them.
 //
 // Forms (SplitFold).  Folded taps: 3 -> 96 channels, 11x11, stride 4 at 227x227, batch 128, forward 254 -> 195 us; busy 46 %,
 // the folded patch's loads and splits (3 vector instructions to a matrix one) and 30 % of padding take the rest.  Columns
@@ -48,22 +49,24 @@ namespace {
 
 constexpr int kThreads = 256;
 
-typedef __attribute__((address_space(4))) uint32_t ConstWord;  // read-only for the whole kernel: scalar loads
+enum SplitTerms { BF16, HALF, AGAIN };  // three bf16 terms; two f16 terms; the bf16 terms of what those left out
 
-template <int MT, int MB, int NB, int WM, int WN>
+template <int MT, int MB, int NB, int WM, int WN, SplitTerms KIND = BF16, int EPT = 4>
 struct SplitCfg {
   static constexpr int BM = WM * MB * MT;
   static constexpr int BN = WN * NB * MT;
   static constexpr int BLOCKS = WM * MB;            // row blocks of a tile
   static constexpr int TPS = MT == 32 ? 1 : 2;      // taps per step: a 16-row instruction takes 32 k values
   static constexpr uint32_t FRAG = 1024;            // bytes of one operand fragment (64 lanes x 8 bf16)
-  static constexpr uint32_t STEP = BLOCKS * 3 * FRAG;
+  // Fragments of a row block and step: the three bf16 terms', which two f16 terms' precede where there are such sums.
+  static constexpr uint32_t BLOCK = (KIND == BF16 ? 3 : 5) * FRAG, FIRST = KIND == AGAIN ? 2 * FRAG : 0, STEP = BLOCKS * BLOCK;
   // 64x64 per wave: B operands a step ahead, two waves per SIMD.  The smaller tiles run few matrix instructions
   // per step and, on small grids, alone on their SIMD: A operands several steps ahead.
   static constexpr bool BDEEP = MT == 32 && MB * NB >= 4;
   static constexpr int DEPTH = BDEEP || MT == 16 ? 1 : MB == 3 ? 2 : NB == 2 ? 3 : 8;
   static constexpr bool LEAD_STEPS = DEPTH <= 2;  // leading bits move between steps, else between chunks
-  static constexpr int WAVES = MT == 32 && MB == 1 && NB == 2 ? 3 : 2;
+  // per SIMD; the f16 form's stages of more than two units per thread leave room for two workgroups anyway
+  static constexpr int WAVES = MT == 32 && MB == 1 && NB == 2 && (KIND == BF16 || EPT == 2) ? 3 : 2;
   static_assert(WM * WN == 4, "four waves per workgroup");
 };
 
@@ -71,27 +74,37 @@ enum SplitForm { IMAGE, FOLDED, COLUMNS, PIXELS };  // PIXELS: COLUMNS over imag
 
 // EPT: patch units (one position x 8 channels) per thread, 2*PSZ <= 256*EPT.
 // FORM: what the patch holds (SplitFold in internal.h).
-// TERMS: 3 the bf16 split, 2 the f16 split.
-template <int MT, int MB, int NB, int WM, int WN, int EPT, SplitForm FORM, int TERMS>
-__global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) void corr_split_kernel(const CorrSplitArgs a) {
-  using C = SplitCfg<MT, MB, NB, WM, WN>;
+// `left_out`: the chunks of the slice that the f16 terms do not hold, found by HALF, added by AGAIN.
+struct LeftOut {
+  uint64_t bits[2];
+  __device__ __forceinline__ bool has(int i) const { return (i < 64 ? bits[0] : bits[1]) >> (i & 63) & 1; }
+};
+static_assert(kUnheldChunks == 128, "LeftOut");
+
+template <int MT, int MB, int NB, int WM, int WN, int EPT, SplitForm FORM, SplitTerms KIND>
+__device__ __forceinline__ void corr_split(const CorrSplitArgs& a, LeftOut& left_out) {
+  using C = SplitCfg<MT, MB, NB, WM, WN, KIND>;
   using M = Mfma<MT>;
-  constexpr int BM = C::BM, BN = C::BN;
-  constexpr bool FOLD = FORM == FOLDED, PIX = FORM == PIXELS, COLS = FORM == COLUMNS || PIX, HALF = TERMS == 2;
-  static_assert(!(FOLD && HALF), "the folded form's reductions are short");
+  constexpr int BM = C::BM, BN = C::BN, TERMS = KIND == HALF ? 2 : 3;
+  constexpr bool FOLD = FORM == FOLDED, PIX = FORM == PIXELS, COLS = FORM == COLUMNS || PIX;
+  static_assert(!(FOLD && KIND != BF16), "the folded form's reductions are short");
   // Bytes from one position of a stage to the next and from one term to the next: bf16 [half][position][h, m, l], f16
   // [h, m][half][position].
-  constexpr uint32_t POS = HALF ? 16 : 48, TERM = HALF ? split_half_stage(EPT, PIX ? BN : 0) / 2 : 16;
+  constexpr uint32_t POS = KIND == HALF ? 16 : 48, TERM = KIND == HALF ? split_half_stage(EPT, PIX ? BN : 0) / 2 : 16;
 
   extern __shared__ __align__(16) float smem[];  // one or two patch stages; the epilogue's tables at the end
 
-  const int t = threadIdx.x;
+  int t = threadIdx.x;
+  uint32_t lin = xcd_contiguous_block_id();
+  if constexpr (KIND == AGAIN) {  // what depends on these is computed here again, not kept in registers over the first sums
+    asm volatile("" : "+v"(t));
+    asm volatile("" : "+s"(lin));
+  }
   const int lane = t & 63;
   const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wm = wv / WN, wn = wv % WN;
 
   // column tile fastest: the workgroups of an XCD share one row tile's packed weights in its L2
-  uint32_t lin = xcd_contiguous_block_id();
   const uint32_t col_tile = lin % (uint32_t)a.col_tiles;
   lin /= (uint32_t)a.col_tiles;
   const uint32_t m_tile = lin % (uint32_t)a.m_tiles;
@@ -124,6 +137,26 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
     patch_elems = (patch_row_base(n, pa) + ext) * (uint32_t)a.PWID + a.share_w;
   }
 
+  // ---- f16: every group of images has a power of two of its own, from its sample; the few values of a weak one do not count
+  // against all samples' largest.  Columns and patch positions belong to one image each. ----
+  uint32_t top_sample = 0;
+  if constexpr (KIND == HALF) {
+#pragma unroll
+    for (int i = 0; i < kSamples / 64; ++i) {
+      const uint32_t u = a.scale[64 * i + lane] & ~kWeakSample;
+      top_sample = u > top_sample ? u : top_sample;
+    }
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t u = (uint32_t)__shfl_xor((int)top_sample, d);
+      top_sample = u > top_sample ? u : top_sample;
+    }
+  }
+  auto image_scale = [&](uint32_t n) {
+    const uint32_t s = a.scale[mdiv(n, a.mSample)];
+    return half_scale(s & kWeakSample ? top_sample : s);
+  };
+
   // ---- per-lane B columns: byte address of (column, its half of the chunk) inside a patch stage ----
   const uint32_t kgrp = lane / MT;  // which 8 k values of a step this lane feeds
   const uint32_t half = kgrp & 1;
@@ -144,7 +177,7 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
   const __amdgpu_buffer_rsrc_t in_rsrc =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.in), 0, (int)a.in_bytes, 0x00020000);
   const uint32_t chan_bytes = 4u * (uint32_t)a.IHW;
-  const uint32_t stage_bytes = HALF ? 2 * TERM : 96u * (uint32_t)a.PSZ;
+  const uint32_t stage_bytes = KIND == HALF ? 2 * TERM : 96u * (uint32_t)a.PSZ;
   FoldEntry* const fold_tab =
       reinterpret_cast<FoldEntry*>(reinterpret_cast<char*>(smem) + (uint32_t)a.patch_stages * stage_bytes);
   if (FOLD) {
@@ -159,6 +192,7 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
   const uint32_t slot0 = PIX ? (t & 1u) * (uint32_t)a.PSZ + ((t >> 1) & 3u) * (uint32_t)a.PWID + (uint32_t)(t >> 3) : (uint32_t)t;
   constexpr uint32_t kSlotStep = PIX ? kThreads / 8 : kThreads;  // a thread's units in the stage
   uint32_t psrc[EPT];
+  int pscale[KIND == HALF ? EPT : 1];  // power of two of the unit's image
   int prow_in[FOLD ? EPT : 1], pcol_in[FOLD ? EPT : 1];
 #pragma unroll
   for (int r = 0; r < EPT; ++r) {
@@ -166,10 +200,12 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
     const uint32_t hf = u >= (uint32_t)a.PSZ ? 1u : 0u;
     const uint32_t e = u - hf * (uint32_t)a.PSZ;
     uint32_t src = 0x80000000u;  // beyond the blob (which is at most 2^30 bytes): reads as zero
+    if (KIND == HALF) pscale[r] = 0;
     if (FOLD) prow_in[r] = -(1 << 28), pcol_in[r] = 0;  // fails every bounds test
     if (PIX) {
       const uint32_t col = col0 + (uint32_t)(t >> 3) + r * kSlotStep;
       if (col <= col_last) src = 4u * (col * (uint32_t)a.in_img_stride + g * (uint32_t)a.in_grp_stride) + 32u * (t & 7u);
+      if (KIND == HALF) pscale[r] = image_scale(col < col_last ? col : col_last);
     } else if (e < patch_elems && u < 2u * (uint32_t)a.PSZ) {
       const uint32_t prow = mdiv(e, a.mPWID);  // COLS: the group of 16 channels
       const uint32_t pcol = e - prow * a.PWID;
@@ -197,15 +233,26 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
         if (n < (uint32_t)a.Nimg) src = at, prow_in[r] = ih, pcol_in[r] = iw;
       } else if ((uint32_t)ih < (uint32_t)a.IH && (uint32_t)iw < (uint32_t)a.IW && n < (uint32_t)a.Nimg) {
         src = at + (COLS ? prow * 16u + hf * 8u : hf * 8u) * chan_bytes;
+        if (KIND == HALF) pscale[r] = image_scale(n);
       }
     }
     psrc[r] = src;
   }
-  // Channels past the group's last read the next group's (or, past the blob, zero): their packed weights
-  // are zero.
+  // Channels past the group's last read the next group's or image's (or, past the blob, zero): their packed weights are zero.  They
+  // need not be of a size with this image's, so the f16 form takes zeros.
+  constexpr int kChunkChannels = COLS ? 64 : 16;
   float pr[EPT][8];
+  const int T = a.THW, SPC = (T + C::TPS - 1) / C::TPS;  // taps and steps per chunk
+  const int cc_first = (int)split * a.chunks_per_split;  // chunks of 16 channels
+  uint32_t w_unheld = 0;  // f16: a weight of the chunk is not held
   auto patch_load = [&](int cc) {
-    const uint32_t coff = (uint32_t)(cc * (COLS ? 64 : 16)) * chan_bytes;
+    if constexpr (KIND == HALF) {
+      const int count = SPC * C::BLOCKS;
+      const uint32_t* const at = a.unheld + ((size_t)(g * a.m_tiles + m_tile) * a.NS + cc) * count;
+      w_unheld = 0;
+      for (int i = t; i < count; i += kThreads) w_unheld |= at[i];
+    }
+    const uint32_t coff = (uint32_t)(cc * kChunkChannels) * chan_bytes;
 #pragma unroll
     for (int r = 0; r < EPT; ++r) {
       uint32_t src = psrc[r];
@@ -234,23 +281,32 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
     }
   };
   const SplitSel sel;
-  HalfScale in_scale(0);
-  int w_scale = 0;
-  if constexpr (HALF) {  // the pack kernel's samples: uniform, through scalar loads
-    const ConstWord* const sample = (const ConstWord*)(uintptr_t)a.scale;
-    uint32_t top = 0;
+  uint32_t* const unheld = reinterpret_cast<uint32_t*>(
+      reinterpret_cast<char*>(smem) + (FORM == COLUMNS ? (uint32_t)a.patch_stages * stage_bytes + split_half_lead(BM, BN) : TERM - kUnheldBytes));
+  auto patch_store = [&](uint32_t stage_off, int cc) {
+    bool out = w_unheld != 0;
+    const int left = a.fold.V - cc * kChunkChannels;
+    if (KIND == HALF && left < kChunkChannels) {
+      uint32_t u0 = (uint32_t)t;
+      asm volatile("" : "+v"(u0));  // what depends on it is computed here, in the last chunk only
 #pragma unroll
-    for (int i = 0; i < kSampleBlocks; ++i) top = sample[i] > top ? sample[i] : top;
-    in_scale = HalfScale(half_scale(top));
-    w_scale = (int)sample[kSampleBlocks];
-  }
-  auto patch_store = [&](uint32_t stage_off) {
+      for (int r = 0; r < EPT; ++r) {
+        const uint32_t u = u0 + r * kThreads, hf = u >= (uint32_t)a.PSZ ? 1u : 0u;
+        const int first = PIX ? 8 * (int)(u0 & 7u) : (int)(hf * 8u + (COLS ? mdiv(u - hf * (uint32_t)a.PSZ, a.mPWID) * 16u : 0u));
+#pragma unroll
+        for (int e = 0; e < 8; ++e) pr[r][e] = first + e < left ? pr[r][e] : 0.f;
+      }
+    }
 #pragma unroll
     for (int r = 0; r < EPT; ++r) {
       const uint32_t u = slot0 + r * kSlotStep;
       u32x4* dst = reinterpret_cast<u32x4*>(reinterpret_cast<char*>(smem) + (stage_off + POS * u));
-      if constexpr (HALF) {
-        const SplitHalf8 s = split_half8(pr[r], in_scale);
+      if constexpr (KIND == HALF) {
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = scale_by(pr[r][e], pscale[r]);
+        const SplitHalf8 s = split_half8(v);
+        out |= half_unheld(v);
         if (PIX || u < 2u * (uint32_t)a.PSZ) {
           dst[0] = s.h;
           dst[TERM / 16] = s.m;
@@ -265,11 +321,10 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
       }
       __builtin_amdgcn_sched_barrier(0);  // one unit's terms in registers at a time
     }
+    if (KIND == HALF && out) atomicOr(unheld + ((cc - cc_first) >> 5), 1u << ((cc - cc_first) & 31));
   };
 
   // ---- A fragments of this workgroup's steps ----
-  const int T = a.THW, SPC = (T + C::TPS - 1) / C::TPS;  // taps and steps per chunk
-  const int cc_first = (int)split * a.chunks_per_split;  // chunks of 16 channels
   int cc_end = cc_first + a.chunks_per_split;
   if (cc_end > a.NS) cc_end = a.NS;
   const char* Ag = reinterpret_cast<const char*>(a.A) +
@@ -279,7 +334,7 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
       __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(Ag), 0, (int)a_bytes, 0x00020000);
   uint32_t alane[MB];
 #pragma unroll
-  for (int i = 0; i < MB; ++i) alane[i] = 16u * lane + (uint32_t)(wm * MB + i) * 3u * C::FRAG;
+  for (int i = 0; i < MB; ++i) alane[i] = 16u * lane + (uint32_t)(wm * MB + i) * C::BLOCK + C::FIRST;
   constexpr int DEPTH = C::DEPTH;
   u32x4 av[DEPTH][MB][TERMS];
   auto load_a = [&](int d, uint32_t step_off, int i) {
@@ -302,14 +357,32 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
   auto a_advance = [&]() {
     if (a_off + C::STEP < a_bytes) a_off += C::STEP;
   };
-  patch_load(cc_first);
+  auto fill_a = [&](int depth) {
 #pragma unroll
-  for (int d = 0; d < DEPTH; ++d) {
+    for (int d = 0; d < depth; ++d) {
 #pragma unroll
-    for (int i = 0; i < MB; ++i) load_a(d, a_off, i);
-    a_advance();
+      for (int i = 0; i < MB; ++i) load_a(d, a_off, i);
+      a_advance();
+    }
+  };
+  auto jump_a = [&](int cc) {  // to a chunk's first step
+    const uint32_t off = (uint32_t)((cc - cc_first) * SPC) * C::STEP;
+    a_off = off < a_bytes ? off : a_bytes - C::STEP;
+  };
+  int cc = cc_first;
+  auto following = [&](int i) {  // the next chunk that was left out
+    do ++i;
+    while (i < cc_end && !left_out.has(i - cc_first));
+    return i;
+  };
+  if constexpr (KIND == AGAIN) cc = following(cc_first - 1);
+  patch_load(cc);
+  if constexpr (KIND != AGAIN) fill_a(DEPTH);
+  if constexpr (KIND == HALF) {
+    if (t < kUnheldBytes / 4) unheld[t] = 0;
+    __syncthreads();
   }
-  patch_store(0);
+  patch_store(0, cc);
   __syncthreads();
 
   // ---- main loop: one step = one tap (two for the 16-row instruction) of one chunk ----
@@ -357,7 +430,6 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
   };
   const bool two = a.patch_stages == 2;
   uint32_t stage = 0;
-  int cc = cc_first;
   // f16: every a.lead_steps steps the large sums' leading bits move to LDS, a place of its own for every lane.
   constexpr int LEAD = MB * NB * M::NR / 8;  // 16-byte groups of eight sums
   const Leading16 leading;
@@ -383,7 +455,7 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
   };
   auto count_steps = [&](int steps) {
     since += steps;
-    if (HALF && since >= a.lead_steps) {
+    if (KIND == HALF && since >= a.lead_steps) {
       move_leading();
       since = 0;
     }
@@ -396,35 +468,76 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
   // Two stages: the next chunk's patch goes to the other one, whose last readers passed the last barrier; one
   // stage: to the only one, once every wave has read it.
   auto end_chunk = [&]() {
-    if (!C::LEAD_STEPS) count_steps(SPC);
     if (two)
       stage = stage ? 0 : stage_bytes;
     else
       __syncthreads();
-    if (++cc < cc_end) patch_store(stage);
+    if (++cc < cc_end) patch_store(stage, cc);
     __syncthreads();
   };
-  if constexpr (C::BDEEP) {  // the next step's B operands are read at the start of a step
+  auto leave_out = [&]() {  // whether to, uniformly
+    if constexpr (KIND == HALF)
+      if (cc < cc_end) return (__builtin_amdgcn_readfirstlane(unheld[(cc - cc_first) >> 5]) >> ((cc - cc_first) & 31) & 1) != 0;
+    return false;
+  };
+  if constexpr (KIND == AGAIN) {
+    u32x4 bv[NB][TERMS];
+    while (cc < cc_end) {
+      const int next = following(cc);
+      if (next < cc_end) patch_load(next);
+      pos = 0;
+      tap = tj = 0;
+      jump_a(cc);
+      fill_a(1);
+#pragma unroll 1
+      for (int s = 0; s < SPC; ++s) {
+        load_b(bv);
+        run_step(0, bv);
+      }
+      cc = next;
+      __syncthreads();
+      if (cc < cc_end) patch_store(0, cc);
+      __syncthreads();
+    }
+  } else if constexpr (C::BDEEP) {  // the next step's B operands are read at the start of a step
     static_assert(DEPTH == 1, "A one step ahead");
     u32x4 bX[NB][TERMS], bY[NB][TERMS];
     while (cc < cc_end) {
       begin_chunk();
-      load_b(bX);
-      for (int s = 0; s < SPC; s += 2) {
-        load_b(bY);
-        run_step(0, bX);
-        if (s + 1 < SPC) {
-          load_b(bX);
-          run_step(0, bY);
+      if (leave_out()) {
+        jump_a(cc + 1);
+        fill_a(DEPTH);
+      } else {
+        load_b(bX);
+        for (int s = 0; s < SPC; s += 2) {
+          load_b(bY);
+          run_step(0, bX);
+          if (s + 1 < SPC) {
+            load_b(bX);
+            run_step(0, bY);
+          }
+          count_steps(2);
         }
-        count_steps(2);
       }
       end_chunk();
     }
   } else {
     u32x4 bv[NB][TERMS];
     int s = 0;
-    begin_chunk();
+    auto next_chunk = [&]() {
+      if constexpr (KIND == HALF)
+        if (leave_out()) {  // the steps go on, on zeros: leaving the ring of weights costs the registers of both ways
+#pragma unroll
+          for (int r = 0; r < EPT; ++r) {
+            const uint32_t u = slot0 + r * kSlotStep;
+            u32x4* dst = reinterpret_cast<u32x4*>(reinterpret_cast<char*>(smem) + (stage + POS * u));
+            if (PIX || u < 2u * (uint32_t)a.PSZ) dst[0] = dst[TERM / 16] = u32x4{0, 0, 0, 0};
+          }
+          __syncthreads();
+        }
+      begin_chunk();
+    };
+    next_chunk();
     while (cc < cc_end) {
 #pragma unroll
       for (int d = 0; d < DEPTH; ++d)
@@ -434,14 +547,24 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
           if (C::LEAD_STEPS) count_steps(1);
           if (++s == SPC) {
             s = 0;
+            if (!C::LEAD_STEPS) count_steps(SPC);
             end_chunk();
-            begin_chunk();
+            next_chunk();
           }
         }
     }
   }
-  if constexpr (HALF) {
-    const int back = -(in_scale.e + w_scale);
+  if constexpr (KIND == HALF) {
+    const int w_scale = (int)a.scale[kSamples];
+    int back[NB];  // what takes the powers of two out of the sums of a column
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const uint32_t col = col0 + (wn * NB + j) * MT + lane % MT;
+      back[j] = -(image_scale(mdiv(col < col_last ? col : col_last, a.mP)) + w_scale);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      left_out.bits[i] = (uint64_t)__builtin_amdgcn_readfirstlane(unheld[2 * i + 1]) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane(unheld[2 * i]);
 #pragma unroll
     for (int q = 0; q < LEAD; ++q) {
       u32x4 w = {0, 0, 0, 0};
@@ -449,12 +572,11 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
 #pragma unroll
       for (int p = 0; p < 4; ++p) {
         const int e = 8 * q + 2 * p, i = e / M::NR / NB, j = e / M::NR % NB, r = e % M::NR;
-        constexpr float down = 1.f / (float)(1 << kHalfShift);
         // the small sums first: they are of the size of what the leading bits left
-        float x = __builtin_fmaf(lo[i][j][r], down, acc[i][j][r]), y = __builtin_fmaf(lo[i][j][r + 1], down, acc[i][j][r + 1]);
+        float x = __builtin_fmaf(lo[i][j][r], kHalfDown, acc[i][j][r]), y = __builtin_fmaf(lo[i][j][r + 1], kHalfDown, acc[i][j][r + 1]);
         leading.give(w[p], x, y);
-        acc[i][j][r] = scale_by(x, back);
-        acc[i][j][r + 1] = scale_by(y, back);
+        acc[i][j][r] = scale_by(x, back[j]);
+        acc[i][j][r + 1] = scale_by(y, back[j]);
       }
     }
   } else {
@@ -470,7 +592,7 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
   // inputs as they are in memory): an infinity or NaN among the operands makes the split's differences NaN where the plain
   // sum may be infinite.  Every wave for itself, over the steps of the main loop: lane for lane an fp32 instruction takes the
   // e-th of the eight k values that the lane feeds to the bf16 one.  256 -> 384, 3x3 at 13x13, batch 128, forward: one NaN
-  // 190 -> 490 us, all NaN 600 (with scalar multiply-adds 16 and 18 ms). ----
+  // 190 -> 490 us, all NaN 600 (with scalar multiply-adds 16 and 18 ms).  The f16 terms' sums have finite operands. ----
   bool bad = false;
 #pragma unroll
   for (int i = 0; i < MB; ++i)
@@ -478,7 +600,7 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
     for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int r = 0; r < M::NR; ++r) bad |= not_finite(acc[i][j][r]);
-  if (__any(bad)) {
+  if (KIND != HALF && __any(bad)) {
     int ln = lane;
     asm volatile("" : "+v"(ln));  // what depends on it is computed here again, not kept in registers over the main loop
     const uint32_t kg = (uint32_t)ln / MT, hf = kg & 1;
@@ -501,9 +623,10 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
       img[j] = n * (uint32_t)a.in_img_stride + g * (uint32_t)a.in_grp_stride;
     }
     const int channels = FOLD || COLS ? a.fold.V : a.Cg_in;
-    uint32_t off = 0;
-    for (int ch = cc_first; ch < cc_end; ++ch)
-      for (int st = 0; st < SPC; ++st, off += C::STEP) {
+    for (int ch = cc_first; ch < cc_end; ++ch) {
+      if (KIND == AGAIN && !left_out.has(ch - cc_first)) continue;
+      for (int st = 0; st < SPC; ++st) {
+        const uint32_t off = (uint32_t)((ch - cc_first) * SPC + st) * C::STEP;
         const int tp = st * C::TPS + (int)(kg >> 1);  // (kg >> 1) is 0 for the 32-row instruction
         const int c0 = (COLS ? ch * 64 + tp * 16 : ch * 16) + (int)hf * 8;
         const int ti = COLS ? 0 : tp / a.TW, tj = COLS ? 0 : tp - ti * a.TW;
@@ -542,20 +665,32 @@ __global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN>::WAVES)) vo
 #pragma unroll
           for (int q = 0; q < 3; ++q)
             w[q] = __builtin_bit_cast(
-                u32x4, __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, 16u * (uint32_t)ln + ((uint32_t)(wm * MB + i) * 3u + q) * C::FRAG, (int)off, 0));
+                u32x4, __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, 16u * (uint32_t)ln + (uint32_t)(wm * MB + i) * C::BLOCK + C::FIRST + q * C::FRAG, (int)off, 0));
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
             const int sh = 16 * (e & 1);
             const uint16_t wh = (uint16_t)(w[0][e >> 1] >> sh), wmid = (uint16_t)(w[1][e >> 1] >> sh), wl = (uint16_t)(w[2][e >> 1] >> sh);
-            const float v = HALF ? join_f16(wh, wmid, wl, w_scale) : join_bf16(wh, wmid, wl);
+            const float v = join_bf16(wh, wmid, wl);
 #pragma unroll
             for (int j = 0; j < NB; ++j) M::run(v, b[j][e], acc[i][j]);
           }
         }
       }
+    }
   }
 
-  corr_epilogue<MT, MB, NB, BM, BN>(a, smem, acc, m_tile, col_tile, g, wm, wn, split);
+  corr_epilogue<MT, MB, NB, BM, BN>(a, smem, acc, m_tile, col_tile, g, wm, wn, split, KIND == AGAIN);
+}
+
+template <int MT, int MB, int NB, int WM, int WN, int EPT, SplitForm FORM, SplitTerms KIND>
+__global__ __launch_bounds__(kThreads, (SplitCfg<MT, MB, NB, WM, WN, KIND, EPT>::WAVES)) void corr_split_kernel(const CorrSplitArgs a) {
+  LeftOut left_out = {{0, 0}};
+  corr_split<MT, MB, NB, WM, WN, EPT, FORM, KIND>(a, left_out);
+  if constexpr (KIND == HALF)
+    if (left_out.bits[0] | left_out.bits[1]) {
+      __syncthreads();  // the epilogue's tables have been read
+      corr_split<MT, MB, NB, WM, WN, EPT, FORM, AGAIN>(a, left_out);
+    }
 }
 
 // Largest of a workgroup's sampled values, in bits.
@@ -582,29 +717,38 @@ __device__ __forceinline__ uint32_t sample_top(const float (&v)[COUNT]) {
 // Packs the weights into A fragments: thread = (group, m tile, step, row block, lane), eight k values each.  Few
 // workgroups whose time is one chain of index arithmetic, loads and stores: the divisions are per thread, not
 // per k value (96 -> 256 in two groups, 5x5: 10.2 -> 7.4 us; 128 x 4096 rows: 7.2 -> 4.9).
-// TERMS 2: the f16 split.  Every workgroup takes the weights' power of two from the same 2048 of them; kSampleBlocks more
-// workgroups leave the largest of 4096 gathered values each.
+// TERMS 2: the f16 split and, behind its fragments, the bf16 ones.  Every workgroup takes the weights' power of two from the same 2048
+// of them; behind the packing ones a wave for each group of images leaves the largest of 1024 of its gathered values.
 template <int MT, int TERMS>
 __global__ __launch_bounds__(256) void pack_split_kernel(const PackSplitArgs a, int blocks, int m_tiles, uint32_t total) {
   const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
-  constexpr int kSamples = 16;  // per thread
-  float sample[TERMS == 2 ? kSamples : 1];
+  float sample[TERMS == 2 ? 8 : 1];
   const uint32_t pack_blocks = (total + 255u) / 256u;
   if constexpr (TERMS == 2) {
     if (blockIdx.x >= pack_blocks) {
-      const uint32_t j0 = (idx - pack_blocks * 256u) * (kSamples / 4);
+      const uint32_t group = (idx >> 6) - pack_blocks * 4u, lane = idx & 63u, first = group * a.sample_elems;
+      uint32_t top = 0, real = 0;
+      if ((uint64_t)group * a.sample_elems < a.in_elems) {  // the whole wave
+        const uint32_t left = a.in_elems - first, count = left < a.sample_elems ? left : a.sample_elems;
 #pragma unroll
-      for (int i = 0; i < kSamples / 4; ++i) {  // four neighbours each, spread evenly
-        const float* const at = a.in + (uint32_t)((uint64_t)(j0 + i) * (a.in_elems - 4u) / (kSampleBlocks * 256 * kSamples / 4));
+        for (int i = 0; i < 4; ++i) {  // four neighbours each, spread evenly; of an image of less than four values, the last
+          const uint32_t at = (uint32_t)((uint64_t)(4 * lane + i) * (count - (count < 4u ? count : 4u)) / 256u);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sample[4 * i + e] = at[e];
+          for (uint32_t e = 0; e < 4; ++e) {
+            const uint32_t u = sample_bits(a.in[first + (at + e < count ? at + e : count - 1u)]);
+            top = u > top ? u : top;
+            real += (uint32_t)__popcll(__ballot(u != 0));
+          }
+        }
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+          const uint32_t u = (uint32_t)__shfl_xor((int)top, d);
+          top = u > top ? u : top;
+        }
       }
-      const uint32_t top = sample_top(sample);
-      if (threadIdx.x == 0) a.scale[blockIdx.x - pack_blocks] = top;
+      if (lane == 0) a.scale[group] = real < 32 ? top | kWeakSample : top;
       return;
     }
-#pragma unroll
-    for (int i = 0; i < kSamples; ++i) sample[i] = 0.f;
     const float* const at = a.w + (uint32_t)((uint64_t)threadIdx.x * (a.w_elems - 8u) / 256u);  // eight neighbours
 #pragma unroll
     for (int i = 0; i < 8; ++i) sample[i] = at[i];
@@ -661,19 +805,27 @@ __global__ __launch_bounds__(256) void pack_split_kernel(const PackSplitArgs a, 
       }
     }
   }
-  uint16_t out[3][8];
+  char* dst = reinterpret_cast<char*>(a.A) + (size_t)(idx >> 6) * (TERMS == 2 ? 5120u : 3072u) + 16u * lane;
   if constexpr (TERMS == 2) {
-    const HalfScale s(half_scale(sample_top(sample)));
-    if (idx == 0) a.scale[kSampleBlocks] = (uint32_t)s.e;
+    const int scale = half_scale(sample_top(sample));
+    if (idx == 0) a.scale[kSamples] = (uint32_t)scale;
     if (idx >= total) return;
-    const bool small = half_too_small(v, s);
+    float f[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) split_half1(v[e], s.e, small, out[0][e], out[1][e], out[2][e]);
-  } else {
+    for (int e = 0; e < 8; ++e) f[e] = scale_by(v[e], scale);
+    const uint64_t unheld = __ballot(half_unheld(f));
+    if (lane == 0) a.unheld[idx >> 6] = unheld != 0;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) split1(v[e], out[0][e], out[1][e], out[2][e]);
+    for (int e = 0; e < 8; ++e)
+      if (!(__builtin_fabsf(f[e]) <= kHalfCeil)) f[e] = 0.f;  // finite terms, for chunks that are left out as zeros
+    const SplitHalf8 s = split_half8(f);
+    *reinterpret_cast<u32x4*>(dst) = s.h;
+    *reinterpret_cast<u32x4*>(dst + 1024) = s.m;
+    dst += 2048;
   }
-  char* dst = reinterpret_cast<char*>(a.A) + (size_t)(idx >> 6) * 3072u + 16u * lane;
+  uint16_t out[3][8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) split1(v[e], out[0][e], out[1][e], out[2][e]);
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
     u32x4 v;
@@ -683,26 +835,28 @@ __global__ __launch_bounds__(256) void pack_split_kernel(const PackSplitArgs a, 
   }
 }
 
-template <int MT, int MB, int NB, int WM, int WN, int EPT, SplitForm FORM, int TERMS>
+template <int MT, int MB, int NB, int WM, int WN, int EPT, SplitForm FORM, SplitTerms KIND>
 int launch_split_k(const CorrSplitArgs& a, hipStream_t s) {
   using C = SplitCfg<MT, MB, NB, WM, WN>;
-  const size_t tables = 16 * (C::BM + C::BN);
-  const size_t patch = TERMS == 2 ? (size_t)split_half_stage(EPT, FORM == PIXELS ? C::BN : 0) * a.patch_stages + split_half_lead(C::BM, C::BN)
-                                  : 96 * (size_t)a.PSZ * a.patch_stages + (FORM == FOLDED ? a.NS * 16 * sizeof(FoldEntry) : 0);
-  const size_t lds = patch > tables ? patch : tables;
+  const size_t tables = 16 * (C::BM + C::BN), plain = 96 * (size_t)a.PSZ;
+  size_t lds = KIND == HALF ? (size_t)split_half_stage(EPT, FORM == PIXELS ? C::BN : 0) * a.patch_stages + split_half_lead(C::BM, C::BN) +
+                                  (FORM == COLUMNS ? kUnheldBytes : 0)
+                            : plain * a.patch_stages + (FORM == FOLDED ? a.NS * 16 * sizeof(FoldEntry) : 0);
+  if (lds < tables) lds = tables;
+  if (lds < plain) lds = plain;  // one stage for what HALF leaves out
   static LdsOptIn opt_in;  // more than 64 KB of LDS needs an explicit opt-in, once per process
-  if (const int e = lds_opt_in(opt_in, &corr_split_kernel<MT, MB, NB, WM, WN, EPT, FORM, TERMS>, 160 * 1024)) return e;
+  if (const int e = lds_opt_in(opt_in, &corr_split_kernel<MT, MB, NB, WM, WN, EPT, FORM, KIND>, 160 * 1024)) return e;
   const uint32_t blocks = (uint32_t)a.G * a.m_tiles * a.col_tiles * a.ksplit;
-  hipLaunchKernelGGL((corr_split_kernel<MT, MB, NB, WM, WN, EPT, FORM, TERMS>), dim3(blocks), dim3(kThreads), lds, s, a);
+  hipLaunchKernelGGL((corr_split_kernel<MT, MB, NB, WM, WN, EPT, FORM, KIND>), dim3(blocks), dim3(kThreads), lds, s, a);
   return (int)hipGetLastError();
 }
 
 template <int MT, int MB, int NB, int WM, int WN, int EPT, SplitForm FORM = IMAGE>
 int launch_split_e(const CorrSplitArgs& a, hipStream_t s) {
   if constexpr (FORM != FOLDED)
-    if (a.half) return launch_split_k<MT, MB, NB, WM, WN, EPT, FORM, 2>(a, s);
+    if (a.half) return launch_split_k<MT, MB, NB, WM, WN, EPT, FORM, HALF>(a, s);
   if (a.half) return (int)hipErrorInvalidValue;
-  return launch_split_k<MT, MB, NB, WM, WN, EPT, FORM, 3>(a, s);
+  return launch_split_k<MT, MB, NB, WM, WN, EPT, FORM, BF16>(a, s);
 }
 
 // The folded and the column forms: one instance per 128-column tile, for the largest patch; no rule leads a 1x1 kernel to
@@ -710,16 +864,17 @@ int launch_split_e(const CorrSplitArgs& a, hipStream_t s) {
 template <int MT, int MB, int NB, int WM, int WN>
 int launch_split_t(const CorrSplitArgs& a, hipStream_t s) {
   constexpr int BM = SplitCfg<MT, MB, NB, WM, WN>::BM, BN = SplitCfg<MT, MB, NB, WM, WN>::BN;
+  const int units = split_patch_units(a.PSZ + a.half, BN);
   if constexpr (BN <= 128 && BM >= 64) {
     if (a.fold.pixels) return launch_split_e<MT, MB, NB, WM, WN, 4, PIXELS>(a, s);
     if (a.fold.subs) return launch_split_e<MT, MB, NB, WM, WN, 4, COLUMNS>(a, s);
   }
   if constexpr (BN <= 128) {
     if (a.fold.ff > 1) return launch_split_e<MT, MB, NB, WM, WN, 4, FOLDED>(a, s);
-    if (split_patch_units(a.PSZ, BN) == 2) return launch_split_e<MT, MB, NB, WM, WN, 2>(a, s);
+    if (units == 2) return launch_split_e<MT, MB, NB, WM, WN, 2>(a, s);
   }
   if (a.fold.subs || a.fold.ff > 1) return (int)hipErrorInvalidValue;
-  if (split_patch_units(a.PSZ, BN) == 3) return launch_split_e<MT, MB, NB, WM, WN, 3>(a, s);
+  if (units == 3) return launch_split_e<MT, MB, NB, WM, WN, 3>(a, s);
   return launch_split_e<MT, MB, NB, WM, WN, 4>(a, s);
 }
 
@@ -753,7 +908,7 @@ int launch_pack_split(int32_t tile, const PackSplitArgs& a, void* stream) {
   const int tps = mt == 32 ? 1 : 2, spc = (a.tTHW + tps - 1) / tps, blocks = bm / mt;
   const int m_tiles = (a.Mrows + bm - 1) / bm;
   const uint32_t total = (uint32_t)a.G * m_tiles * (uint32_t)(a.split_chunks * spc) * blocks * 64u;
-  const dim3 grid((total + 255) / 256 + (a.half ? kSampleBlocks : 0));
+  const dim3 grid((total + 255) / 256 + (a.half ? kSamples / 4 : 0));
   auto* const kernel = mt == 32 ? a.half ? pack_split_kernel<32, 2> : pack_split_kernel<32, 3>
                                 : a.half ? pack_split_kernel<16, 2> : pack_split_kernel<16, 3>;
   hipLaunchKernelGGL(kernel, grid, dim3(256), 0, (hipStream_t)stream, a, blocks, m_tiles, total);

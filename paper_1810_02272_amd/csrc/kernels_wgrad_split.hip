@@ -17,9 +17,10 @@
 // 5x5 at 16x16, batch 100) 35 -> 23, with the reduce kernel, against wgrad_kernel; 172 and 115 us are the matrix
 // instructions of the first two at the 2000 TFLOP/s that a loop of them sustains.
 //
-// TERMS 2: long sums on two f16 terms (split_f16.h), half the matrix instructions, positions of 64 bytes.  Every workgroup samples
+// HALF: long sums on two f16 terms (split_f16.h), half the matrix instructions, positions of 64 bytes.  Every workgroup samples
 // both blobs for the powers of two while its first loads are under way.  The first three layers, without the reduce kernel: 349 ->
 // 236 us, 219 -> 150, 67 -> 54.
+// AGAIN: what a workgroup's HALF sums had to leave out, step by step, it adds on the bf16 terms behind them.
 // FOLD: the folded grid of corr_split_kernel, so that few channels fill the blocks: 3 -> 96 channels, 11x11, stride 4 at 227x227,
 // batch 128, 290 us on the fp32 kernel -> 191; 9 -> 128, 12x12 at 109x150, batch 87, 265 -> 125.  Over 59 drawn layers that take it
 // 1.36 times as fast in the geometric mean, none slower.
@@ -41,24 +42,37 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4* LdsTrPtr;
 typedef __attribute__((address_space(3))) char* LdsChar;
 
-// MB x NB blocks of 16 x 16 per wave; EPT: patch units (position x 8 channels) per thread; TERMS: 3 the bf16 split, 2 the
-// f16 split; FOLD: the channels and taps are those of a folded grid (SplitFold).
-template <int WM, int WN, int MB, int NB, int EPT, int TERMS, bool FOLD>
-__global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSplitArgs a) {
+enum SplitTerms { BF16, HALF, AGAIN };  // three bf16 terms; two f16 terms; the bf16 terms of what those left out
+
+// What HALF leaves for AGAIN: the blobs' powers of two, and the 128ths of the slice with chunks that AGAIN must look at -- a step that
+// was left out it knows by the same test of the same values.
+struct LeftOut {
+  int x_scale, dy_scale;
+  uint64_t bits[2];
+  __device__ __forceinline__ bool has(int i) const { return (i < 64 ? bits[0] : bits[1]) >> (i & 63) & 1; }
+};
+
+// MB x NB blocks of 16 x 16 per wave; EPT: patch units (position x 8 channels) per thread; FOLD: the channels and taps are those of a
+// folded grid (SplitFold).
+template <int WM, int WN, int MB, int NB, int EPT, SplitTerms KIND, bool FOLD>
+__device__ __forceinline__ void wgrad_split(const WgradSplitArgs& a, LeftOut& left_out) {
   using M = Mfma<16>;
-  constexpr int BM = WM * MB * 16;
-  constexpr bool HALF = TERMS == 2;
+  constexpr int BM = WM * MB * 16, TERMS = KIND == HALF ? 2 : 3;
   constexpr uint32_t POS = 32 * TERMS;  // bytes of a patch position
   static_assert(WM * WN == 4, "four waves per workgroup");
 
   extern __shared__ __align__(16) char smem[];  // position tables of two chunks, then one or two patch stages
 
-  const int t = threadIdx.x;
+  int t = threadIdx.x;
+  uint32_t lin = xcd_contiguous_block_id();
+  if constexpr (KIND == AGAIN) {  // what depends on these is computed here again, not kept in registers over the first sums
+    asm volatile("" : "+v"(t));
+    asm volatile("" : "+s"(lin));
+  }
   const int lane = t & 63;
   const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wm = wv / WN, wn = wv % WN;
 
-  uint32_t lin = xcd_contiguous_block_id();
   const uint32_t m_tile = lin % (uint32_t)a.m_tiles;
   lin /= (uint32_t)a.m_tiles;
   const uint32_t n_tile = lin % (uint32_t)a.n_tiles;
@@ -82,8 +96,12 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
   const uint32_t stage_bytes = POS * (uint32_t)a.PSZ;
   constexpr uint32_t kTables = 2u * 4u * kChunkPix;
   const int channels = FOLD ? a.fold.V : a.Cg;
-  char* const behind = smem + kTables + (uint32_t)a.patch_stages * stage_bytes;  // leading bits, then the folded form's table
-  FoldEntry* const fold_tab = reinterpret_cast<FoldEntry*>(behind + split_half_lead(BM, WN * NB * 16));
+  // behind the stages: leading bits, the numbers of the last two chunks whose patch is not held with the bits of left_out, the folded
+  // form's table
+  char* const behind = smem + kTables + (KIND == AGAIN ? 1u : (uint32_t)a.patch_stages) * stage_bytes;
+  uint32_t* const unheld = reinterpret_cast<uint32_t*>(behind + (KIND == HALF ? split_half_lead(BM, WN * NB * 16) : 0));
+  FoldEntry* const fold_tab = reinterpret_cast<FoldEntry*>(reinterpret_cast<char*>(unheld) + kUnheldWgradBytes);
+  const int coarse = a.chunks_per_split > 128 ? 32 - __builtin_clz((uint32_t)(a.chunks_per_split - 1) >> 7) : 0;  // of the 128ths
   if (FOLD) {
     fill_fold_table(fold_tab, (a.n_tiles / a.tap_tiles) * 16, a.fold, a.W, a.H * a.W, t, kThreads);
     __syncthreads();
@@ -97,7 +115,15 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
   uint32_t entry = 0;  // this thread's entry of the chunk's position table (threads below kChunkPix)
   // The chunk's first segment starts at output row a0 of image n0; its patch rows and those of later images are
   // counted as in corr_split_kernel.
+  // A thread's units, from its number anew for every chunk: the f16 form has no registers for what depends on it, and a word that comes
+  // back from scratch memory between the loads waits for those before it (128 -> 128, 3x3 at 56x56, batch 64: 309 us so, 240 now).
+  auto unit0 = [&]() {
+    uint32_t u = (uint32_t)t;
+    if constexpr (KIND != BF16) asm volatile("" : "+v"(u));
+    return u;
+  };
   auto patch_load = [&](int chunk) {
+    const uint32_t u0 = unit0();
     uint32_t q0 = (uint32_t)chunk * kChunkRuns, n0, p0;
     run_pos(q0, n0, p0);
     const uint32_t a0 = mdiv(p0, a.mPW);
@@ -105,8 +131,8 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
     const uint32_t RS = ((uint32_t)a.PH - 1) * a.sh + a.ext - a.share_h;
     {
       uint32_t n, p;
-      run_pos(q0 + (uint32_t)(t >> 3) % kChunkRuns, n, p);
-      p += t & 7;
+      run_pos(q0 + (u0 >> 3) % kChunkRuns, n, p);
+      p += u0 & 7;
       if (p > (uint32_t)a.P - 1) p = (uint32_t)a.P - 1;  // filled-up run: any position, dy is zero
       if (n > (uint32_t)a.N - 1) n = n0, p = p0;         // past the last image: the same
       const uint32_t pa = mdiv(p, a.mPW), pb = p - pa * a.PW;
@@ -116,7 +142,7 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
     }
 #pragma unroll
     for (int r = 0; r < EPT; ++r) {
-      const uint32_t u = t + r * kThreads;
+      const uint32_t u = u0 + r * kThreads;
       const uint32_t hf = u >= (uint32_t)a.PSZ ? 1u : 0u;
       const uint32_t e = u - hf * (uint32_t)a.PSZ;
       const uint32_t prow = mdiv(e, a.mPWID);
@@ -140,7 +166,7 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
       uint32_t src = 0x80000000u;  // beyond the blob (which is at most 2^30 bytes): reads as zero
       if ((uint32_t)ih < (uint32_t)a.H && (uint32_t)iw < (uint32_t)a.W && n < (uint32_t)a.N && u < 2u * (uint32_t)a.PSZ)
         src = 4u * (n * (uint32_t)(a.C * a.H * a.W) + (uint32_t)ih * a.W + iw) + chan0 + hf * 8u * chan_bytes;
-      // channels past the group's last read the next group's (or, past the blob, zero): columns never stored
+      // channels past the group's last read the next group's or image's (or, past the blob, zero): columns never stored
 #pragma unroll
       for (int c8 = 0; c8 < 8; ++c8)
         pr[r][c8] = __builtin_bit_cast(
@@ -148,21 +174,32 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
     }
   };
   const SplitSel sel;
-  HalfScale x_scale(0), dy_scale(0);
-  auto patch_store = [&](uint32_t table, uint32_t stage) {
-    if (t < kChunkPix) *reinterpret_cast<uint32_t*>(smem + table + 4u * t) = entry;
+  auto patch_store = [&](uint32_t table, uint32_t stage, int chunk) {
+    bool out = false;
+    const uint32_t u0 = unit0();
+    if (u0 < kChunkPix) *reinterpret_cast<uint32_t*>(smem + table + 4u * u0) = entry;
 #pragma unroll
     for (int r = 0; r < EPT; ++r) {
-      const uint32_t u = t + r * kThreads;
+      const uint32_t u = u0 + r * kThreads;
       const uint32_t hf = u >= (uint32_t)a.PSZ ? 1u : 0u;
+      if (KIND != BF16 && !FOLD && c16 * 16 + 16 > a.Cg)  // need not be of a size with this group's
+#pragma unroll
+        for (int e = 0; e < 8; ++e) pr[r][e] = c16 * 16 + (int)hf * 8 + e < a.Cg ? pr[r][e] : 0.f;
       u32x4* dst = reinterpret_cast<u32x4*>(smem + kTables + stage + POS * (u - hf * (uint32_t)a.PSZ) + 16u * hf);
-      if constexpr (HALF) {
-        const SplitHalf8 s = split_half8(pr[r], x_scale);
-        if (u < 2u * (uint32_t)a.PSZ) {
-          dst[0] = s.h;
-          dst[2] = s.m;
+      if constexpr (KIND != BF16) {
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = scale_by(pr[r][e], left_out.x_scale);
+        out |= half_unheld(v);
+        if constexpr (KIND == HALF) {
+          const SplitHalf8 s = split_half8(v);
+          if (u < 2u * (uint32_t)a.PSZ) {
+            dst[0] = s.h;
+            dst[2] = s.m;
+          }
         }
-      } else {
+      }
+      if constexpr (KIND != HALF) {
         const Split8 s = split8(pr[r], sel);
         if (u < 2u * (uint32_t)a.PSZ) {
           dst[0] = s.h;
@@ -172,6 +209,7 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
       }
       __builtin_amdgcn_sched_barrier(0);  // one unit's terms in registers at a time
     }
+    if (KIND != BF16 && out) unheld[chunk & 1] = (uint32_t)chunk + 1u;
   };
 
   // ---- dy: lane l takes run l/16 of a step and row l%16 of each of its wave's row blocks ----
@@ -224,13 +262,13 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
 
   // ---- bias gradient from the same read of dy: every wave sums its rows over the chunks ch with
   // ch % (n_tiles*WN) == n_tile*WN + wn (see wgrad_kernel) ----
-  const bool row_sums = a.bias_part != nullptr;
+  const bool row_sums = a.bias_part != nullptr && KIND != AGAIN;
   const uint32_t turn = (uint32_t)(n_tile * WN + wn), turns = (uint32_t)(a.n_tiles * WN);
   float bsum[MB];
 #pragma unroll
   for (int i = 0; i < MB; ++i) bsum[i] = 0.f;
 
-  const bool two = a.patch_stages == 2;
+  const bool two = a.patch_stages == 2 && KIND != AGAIN;
   // f16: the powers of two, from the same 2048 values of each blob in every workgroup, four neighbours at a time.
   auto sample_scales = [&]() {
     uint32_t top[2] = {0, 0};
@@ -264,8 +302,8 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
     for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int w = 0; w < 4; ++w) best[b] = red[2 * w + b] > best[b] ? red[2 * w + b] : best[b];
-    x_scale = HalfScale(__builtin_amdgcn_readfirstlane(half_scale(best[0])));
-    dy_scale = HalfScale(__builtin_amdgcn_readfirstlane(half_scale(best[1])));
+    left_out.x_scale = __builtin_amdgcn_readfirstlane(half_scale(best[0]));
+    left_out.dy_scale = __builtin_amdgcn_readfirstlane(half_scale(best[1]));
     __syncthreads();
   };
   // f16: every a.lead_chunks chunks the large sums' leading bits move to LDS, a place of its own for every lane.
@@ -290,48 +328,33 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
     led = true;
   };
   int since = 0;
-  if (chunk_first < chunk_end) {
-    patch_load(chunk_first);
-    load_dy(chunk_first * kChunkSteps);
-    if constexpr (HALF) sample_scales();
-    patch_store(0, 0);
+  auto following = [&](int i) {  // the next chunk
+    do ++i;
+    while (KIND == AGAIN && i < chunk_end && !left_out.has((i - chunk_first) >> coarse));
+    return i;
+  };
+  int ch = following(chunk_first - 1);
+  if (KIND != BF16 && t < (int)kUnheldWgradBytes / 4) unheld[t] = 0;
+  if (KIND == AGAIN) __syncthreads();  // HALF's next barrier comes with the samples
+  if (ch < chunk_end) {
+    patch_load(ch);
+    load_dy(ch * kChunkSteps);
+    if constexpr (KIND == HALF) sample_scales();
+    patch_store(0, 0, ch);
   }
   __syncthreads();
 
   const int last_step = chunk_end * kChunkSteps - 1;
   uint32_t stage = 0, table = 0;
-  for (int ch = chunk_first; ch < chunk_end; ++ch) {
-    const bool more = ch + 1 < chunk_end;
-    if (more) patch_load(ch + 1);
+  while (ch < chunk_end) {
+    const int next = following(ch);
+    const bool more = next < chunk_end;
+    // a patch that is not held leaves out (HALF) or brings in (AGAIN) all steps of its chunk
+    const bool patch_out = KIND != BF16 && __builtin_amdgcn_readfirstlane(unheld[ch & 1]) == (uint32_t)ch + 1u;
+    if (more) patch_load(next);
     const bool my_turn = row_sums && (uint32_t)(ch - chunk_first) % turns == turn;
 #pragma unroll 1
     for (int s = 0; s < kChunkSteps; ++s) {
-      // this step's dy operands: masked, summed, split; then the next step's loads.  Only an image's last run has anything to
-      // mask: a test for the wave instead of a select per value, which the two multiplications of a split pair cost.
-      u32x4 av[MB][TERMS];
-      if (__any(valid < 8)) {
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) raw[i][e] = e < valid ? raw[i][e] : 0.f;
-      }
-#pragma unroll
-      for (int i = 0; i < MB; ++i) {
-        const float(&v)[8] = raw[i];
-        if (my_turn) bsum[i] += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
-        if constexpr (HALF) {
-          const SplitHalf8 sp = split_half8(v, dy_scale);
-          av[i][0] = sp.h;
-          av[i][1] = sp.m;
-        } else {
-          const Split8 sp = split8(v, sel);
-          av[i][0] = sp.h;
-          av[i][1] = sp.m;
-          av[i][2] = sp.l;
-        }
-      }
-      const int step = ch * kChunkSteps + s;
-      load_dy(step < last_step ? step + 1 : step);
       // positions of the two quads of pixels this lane names in the transposing reads, with its channel quad
       const uint32_t px = (uint32_t)s * 32u + (uint32_t)(lane >> 4) * 8u + (uint32_t)((lane & 15) >> 2);
       const uint32_t fix = kTables + stage + 8u * (uint32_t)(lane & 3);
@@ -351,12 +374,53 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
           b[q][3] = y1.y;
         }
       };
+      // this step's dy operands: masked, summed, split; then the next step's loads.  Only an image's last run has anything to
+      // mask: a test for the wave instead of a select per value, which the two multiplications of a split pair cost.
+      u32x4 av[MB][TERMS];
+      bool out = false;
+      if (__any(valid < 8)) {
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) raw[i][e] = e < valid ? raw[i][e] : 0.f;
+      }
+#pragma unroll
+      for (int i = 0; i < MB; ++i) {
+        const float(&v)[8] = raw[i];
+        if (my_turn) bsum[i] += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+        if constexpr (KIND != BF16) {
+          float scaled[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) scaled[e] = scale_by(v[e], left_out.dy_scale);
+          if constexpr (KIND == HALF) {
+            const SplitHalf8 sp = split_half8(scaled);
+            av[i][0] = sp.h;
+            av[i][1] = sp.m;
+            asm volatile("" : "+v"(av[i][1]));  // here, or the operands stay in registers until the test below is decided
+          }
+          out |= half_unheld(scaled);
+        }
+        if constexpr (KIND != HALF) {
+          const Split8 sp = split8(v, sel);
+          av[i][0] = sp.h;
+          av[i][1] = sp.m;
+          av[i][2] = sp.l;
+        }
+      }
+      const int step = ch * kChunkSteps + s;
+      load_dy(s + 1 < kChunkSteps ? step + 1 : more ? next * kChunkSteps : step);
+      if constexpr (KIND != BF16) {
+        const bool left = patch_out || __any(out);
+        if (KIND == HALF && left && lane == 0)
+          atomicOr(unheld + 2 + ((ch - chunk_first) >> coarse >> 5), 1u << ((ch - chunk_first) >> coarse & 31));
+        if (left == (KIND == HALF)) continue;
+      }
       load_b(0, bv[0]);
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
         if (j + 1 < NB) load_b(j + 1, bv[(j + 1) & 1]);
         __builtin_amdgcn_sched_barrier(0);  // the next block's reads before this block's products, not behind them
-        if constexpr (HALF) {
+        if constexpr (KIND == HALF) {
 #pragma unroll
           for (int i = 0; i < MB; ++i) mfma_f16<16>(av[i][1], bv[j & 1][0], lo[i][j]);
 #pragma unroll
@@ -375,7 +439,7 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    if (HALF && ++since == a.lead_chunks && more) {
+    if (KIND == HALF && ++since == a.lead_chunks && more) {
       move_leading();
       since = 0;
     }
@@ -384,7 +448,8 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
       stage = stage ? 0 : stage_bytes;
     else
       __syncthreads();
-    if (more) patch_store(table, stage);
+    if (more) patch_store(table, stage, next);
+    ch = next;
     __syncthreads();
   }
 
@@ -407,18 +472,20 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
     }
   }
 
-  if constexpr (HALF) {
-    const int back = -(x_scale.e + dy_scale.e);
+  if constexpr (KIND == HALF) {
+    const int back = -(left_out.x_scale + left_out.dy_scale);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      left_out.bits[i] = (uint64_t)__builtin_amdgcn_readfirstlane(unheld[2 * i + 3]) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane(unheld[2 * i + 2]);
 #pragma unroll
     for (int b = 0; b < MB * NB; ++b) {
       M::Acc& c = acc[b / NB][b % NB];
       const M::Acc& l = lo[b / NB][b % NB];
       uint2 w = {0, 0};
       if (led) w = lead[b * kThreads];
-      constexpr float down = 1.f / (float)(1 << kHalfShift);
       float v[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) v[r] = __builtin_fmaf(l[r], down, c[r]);
+      for (int r = 0; r < 4; ++r) v[r] = __builtin_fmaf(l[r], kHalfDown, c[r]);
       leading.give(w.x, v[0], v[1]);
       leading.give(w.y, v[2], v[3]);
 #pragma unroll
@@ -434,8 +501,8 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
   }
 
   const int c = c16 * 16 + (lane & 15);
-  // ---- sums that are not finite once more on the fp32 matrix instructions (see corr_split_kernel); channels past the
-  // group's last are the next group's and never stored ----
+  // ---- sums that are not finite once more on the fp32 matrix instructions (see corr_split_kernel), behind f16 sums the whole slice's;
+  // channels past the group's last are the next group's and never stored ----
   bool bad = false;
 #pragma unroll
   for (int i = 0; i < MB; ++i)
@@ -443,7 +510,8 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
     for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int r = 0; r < M::NR; ++r) bad |= not_finite(acc[i][j][r]);
-  if (__any(bad && c < channels)) {
+  const bool redo = KIND != HALF && __any(bad && c < channels);
+  if (redo) {
     int th[NB], tw[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
@@ -511,28 +579,42 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSpl
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
         const uint32_t co = tap0 + j < a.khw ? 4u * (uint32_t)((tap0 + j) * channels) : 0x40000000u;
-        const float v = acc[i][j][r];
+        float v = acc[i][j][r];
+        if (KIND == AGAIN && !redo) v += __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(out_rsrc, ro + co, 0, 0));
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), out_rsrc, ro + co, 0, 0);
       }
     }
 }
 
-template <int WM, int WN, int MB, int NB, int EPT, int TERMS, bool FOLD = false>
+template <int WM, int WN, int MB, int NB, int EPT, SplitTerms KIND, bool FOLD>
+__global__ __launch_bounds__(kThreads, 2) void wgrad_split_kernel(const WgradSplitArgs a) {
+  LeftOut left_out = {0, 0, {0, 0}};
+  wgrad_split<WM, WN, MB, NB, EPT, KIND, FOLD>(a, left_out);
+  if constexpr (KIND == HALF)
+    if (left_out.bits[0] | left_out.bits[1]) {
+      __syncthreads();  // LDS is free
+      wgrad_split<WM, WN, MB, NB, EPT, AGAIN, FOLD>(a, left_out);
+    }
+}
+
+template <int WM, int WN, int MB, int NB, int EPT, SplitTerms KIND, bool FOLD = false>
 int launch_k(const WgradSplitArgs& a, hipStream_t s) {
   constexpr int BM = WM * MB * 16;
-  const size_t lds = 2 * 4 * kChunkPix + 32 * TERMS * (size_t)a.PSZ * a.patch_stages + (TERMS == 2 ? split_half_lead(BM, WN * NB * 16) : 0) +
-                     (FOLD ? (a.n_tiles / a.tap_tiles) * 16 * sizeof(FoldEntry) : 0);
-  const size_t red = 4 * WN * BM;
+  const size_t tables = 2 * 4 * kChunkPix, red = 4 * WN * BM;
+  const size_t behind = (KIND == HALF ? kUnheldWgradBytes : 0) + (FOLD ? (a.n_tiles / a.tap_tiles) * 16 * sizeof(FoldEntry) : 0);
+  size_t lds = tables + (KIND == HALF ? 64 : 96) * (size_t)a.PSZ * a.patch_stages + (KIND == HALF ? split_half_lead(BM, WN * NB * 16) : 0) + behind;
+  const size_t again = tables + 96 * (size_t)a.PSZ + behind;  // one stage for what HALF leaves out
+  if (lds < again) lds = again;
   static LdsOptIn opt_in;  // more than 64 KB of LDS needs an explicit opt-in, once per process
-  if (const int e = lds_opt_in(opt_in, &wgrad_split_kernel<WM, WN, MB, NB, EPT, TERMS, FOLD>, 160 * 1024)) return e;
+  if (const int e = lds_opt_in(opt_in, &wgrad_split_kernel<WM, WN, MB, NB, EPT, KIND, FOLD>, 160 * 1024)) return e;
   const uint32_t blocks = (uint32_t)a.G * a.S * a.m_tiles * a.n_tiles;
-  hipLaunchKernelGGL((wgrad_split_kernel<WM, WN, MB, NB, EPT, TERMS, FOLD>), dim3(blocks), dim3(kThreads), lds > red ? lds : red, s, a);
+  hipLaunchKernelGGL((wgrad_split_kernel<WM, WN, MB, NB, EPT, KIND, FOLD>), dim3(blocks), dim3(kThreads), lds > red ? lds : red, s, a);
   return (int)hipGetLastError();
 }
 
 template <int WM, int WN, int MB, int NB, int EPT>
 int launch_e(const WgradSplitArgs& a, hipStream_t s) {
-  return a.half ? launch_k<WM, WN, MB, NB, EPT, 2>(a, s) : launch_k<WM, WN, MB, NB, EPT, 3>(a, s);
+  return a.half ? launch_k<WM, WN, MB, NB, EPT, HALF>(a, s) : launch_k<WM, WN, MB, NB, EPT, BF16>(a, s);
 }
 
 template <int WM, int WN, int MB, int NB>
@@ -545,8 +627,8 @@ int launch_t(const WgradSplitArgs& a, hipStream_t s) {
 // The folded form, f16 terms only.
 template <int WM, int WN, int MB, int NB>
 int launch_f(const WgradSplitArgs& a, hipStream_t s) {
-  if (split_patch_units(a.PSZ) <= 3) return launch_k<WM, WN, MB, NB, 3, 2, true>(a, s);
-  return launch_k<WM, WN, MB, NB, 4, 2, true>(a, s);
+  if (split_patch_units(a.PSZ) <= 3) return launch_k<WM, WN, MB, NB, 3, HALF, true>(a, s);
+  return launch_k<WM, WN, MB, NB, 4, HALF, true>(a, s);
 }
 
 }  // namespace

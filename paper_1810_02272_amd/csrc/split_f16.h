@@ -1,7 +1,8 @@
 // Two-way f16 split of fp32 operands for the f16 matrix instructions of gfx950.
 //
-// A float a, times a power of two that is the same for the whole blob, is taken as h + m with h = f16(a) and m = f16(a - h),
-// m kept times 2^11 so that both have the exponents of the operand: 22 to 24 of its bits, off by 2^-23 of it at most.  A
+// A float a, times a power of two, is taken as h + m with h = f16(a) and m = f16(a - h), m kept times 2^11 so that both have the
+// exponents of the operand (the scheme of Ootomo and Yokota, "Recovering single precision accuracy from Tensor Cores while
+// surpassing the FP32 theoretical peak performance", 2022): 22 to 24 of its bits, off by 2^-23 of it at most.  A
 // product is the three partial products hh, hm, mh, each exact, summed in fp32 by the matrix unit; what is left out (mm) is below
 // 2^-22 |ab|.  Half the matrix instructions of the three-way bf16 split (split_bf16.h), two thirds of the bytes in LDS and
 // registers.
@@ -12,10 +13,12 @@
 // matrix unit's accumulator every few hundred indices (Leading16 below), so that it rounds short sums only; the rule in api.cpp
 // takes this split where both together are below what the three-way split loses.
 //
-// Range.  f16 ends at 65504 and keeps 11 bits down to 2^-14: the power of two puts the largest of a sample of the blob at 2^11,
-// which leaves 2^5 above and 2^23 below.  An operand beyond 65504 makes its sums infinite or NaN, and eight neighbours whose largest
-// is below 2^-12 and not zero are given a NaN on purpose; the kernels compute sums that are not finite again on the fp32 matrix
-// instructions, from operands that hold every bit.
+// Range.  f16 ends at 65504 and keeps 11 bits down to 2^-14: the power of two puts the largest of a sample at 2^12 to 2^13, which
+// leaves 2^3 above.  A value is held as said from 2^-14 on and, within 2^-36, to 2^-18 of itself from 2^-18 on: 2^-30 of the
+// sample's largest, where one of 10^9 normally distributed ones is.  A value that is not held -- above 65504, not a number, or below
+// 2^-18 and not zero -- keeps the chunk or the step that it is in out of these sums; the kernels add those behind, on the three-way
+// split.  That goes by each value and not by the largest of some: neighbours need not be terms of the same sums, nor meet weights of
+// one size.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -29,15 +32,17 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kHalfShift = 11;             // m is held times 2^11
-constexpr int kHalfTop = 11;               // exponent of the sample's largest operand
-constexpr float kHalfTiny = 0x1p-12f;      // eight operands below that are not held well
-constexpr uint32_t kHalfNans = 0x7e007e00u;
+constexpr float kHalfUp = (float)(1 << kHalfShift), kHalfDown = 1.f / kHalfUp;
+constexpr int kHalfTop = 12;               // exponent of the sample's largest operand
+constexpr int kHalfLeast = -16;            // of the power of two: fp32's smallest denormals are not scaled to zero
+constexpr uint32_t kHalfFloor = 2u * 0x36800000u - 1u;  // nonzero_order of 2^-18, the smallest operand that is held
+constexpr float kHalfCeil = 65504.f;                    // the largest
 
-// Power of two for a blob whose sample's largest magnitude has these bits (0: an empty or all-zero sample).
+// Power of two for a sample whose largest magnitude has these bits (0: an empty or all-zero sample).
 __device__ __forceinline__ int half_scale(uint32_t bits) {
   if (bits == 0) return 0;
-  const int e = bits >> 23 ? (int)(bits >> 23) - 127 : 31 - __builtin_clz(bits) - 149;
-  return kHalfTop - e;
+  const int e = kHalfTop - (bits >> 23 ? (int)(bits >> 23) - 127 : 31 - __builtin_clz(bits) - 149);
+  return e < kHalfLeast ? kHalfLeast : e;
 }
 
 // Bits of |v| for the sample; infinities and NaN do not count.
@@ -48,25 +53,28 @@ __device__ __forceinline__ uint32_t sample_bits(float v) {
 
 __device__ __forceinline__ float scale_by(float v, int e) { return __builtin_amdgcn_ldexpf(v, e); }
 
-// One blob's power of two, and the unscaled bound below which eight neighbours are too small (minus one, in bits).
-struct HalfScale {
-  int e;
-  uint32_t tiny;
-  __device__ __forceinline__ explicit HalfScale(int exponent) : e(exponent) {
-    const uint32_t u = __builtin_bit_cast(uint32_t, scale_by(kHalfTiny, -exponent));
-    tiny = u ? u - 1 : 0;
-  }
-};
-
+// Largest magnitude, NaN if there is one.
 __device__ __forceinline__ float max3_abs(float a, float b, float c) {
   float r;
-  asm("v_max3_f32 %0, |%1|, |%2|, |%3|" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  asm("v_maximum3_f32 %0, |%1|, |%2|, |%3|" : "=v"(r) : "v"(a), "v"(b), "v"(c));
   return r;
 }
 
-__device__ __forceinline__ bool half_too_small(const float (&v)[8], const HalfScale& s) {
-  const float mx = max3_abs(max3_abs(max3_abs(v[0], v[1], v[2]), v[3], v[4]), max3_abs(v[5], v[6], v[7]), 0.f);
-  return __builtin_bit_cast(uint32_t, mx) - 1u < s.tiny;
+// Bits of |v| twice, less one: the smallest of them is that of the smallest operand that is not zero.
+__device__ __forceinline__ uint32_t nonzero_order(float v) { return (__builtin_bit_cast(uint32_t, v) << 1) - 1u; }
+
+__device__ __forceinline__ uint32_t least3(uint32_t a, uint32_t b, uint32_t c) {
+  const uint32_t m = a < b ? a : b;
+  return m < c ? m : c;
+}
+
+// Whether a scaled operand among eight is not held.
+__device__ __forceinline__ bool half_unheld(const float (&s)[8]) {
+  const uint32_t least = least3(least3(nonzero_order(s[0]), nonzero_order(s[1]), nonzero_order(s[2])),
+                                least3(nonzero_order(s[3]), nonzero_order(s[4]), nonzero_order(s[5])),
+                                least3(nonzero_order(s[6]), nonzero_order(s[7]), 0xffffffffu));
+  const float most = max3_abs(max3_abs(max3_abs(s[0], s[1], s[2]), s[3], s[4]), max3_abs(s[5], s[6], s[7]), 0.f);
+  return least < kHalfFloor || !(most <= kHalfCeil);
 }
 
 struct SplitHalf8 {  // eight consecutive reduction indices of one row or column
@@ -80,50 +88,21 @@ __device__ __forceinline__ uint32_t pack_f16(float a, float b) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
-__device__ __forceinline__ SplitHalf8 split_half8(const float (&v)[8], const HalfScale& s) {
+// Of scaled operands.
+__device__ __forceinline__ SplitHalf8 split_half8(const float (&s)[8]) {
   SplitHalf8 r;
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
-    const float a = v[2 * p], b = v[2 * p + 1];
-    uint32_t pair = pack_f16(scale_by(a, s.e), scale_by(b, s.e));
+    const float a = s[2 * p], b = s[2 * p + 1];
+    uint32_t pair = pack_f16(a, b);
     asm("" : "+v"(pair));  // or each half is converted once more by itself
     r.h[p] = pair;
     const f16x2 h = __builtin_bit_cast(f16x2, pair);
-    constexpr float up = (float)(1 << kHalfShift);
-    r.m[p] = pack_f16(__builtin_fmaf((float)h[0], -up, scale_by(a, s.e + kHalfShift)),
-                      __builtin_fmaf((float)h[1], -up, scale_by(b, s.e + kHalfShift)));
+    float ra = __builtin_fmaf((float)h[0], -kHalfUp, a * kHalfUp), rb = __builtin_fmaf((float)h[1], -kHalfUp, b * kHalfUp);
+    asm("" : "+v"(ra), "+v"(rb));  // or both are multiply-adds into half a register, which take 2.6 times an instruction's time each
+    r.m[p] = pack_f16(ra, rb);
   }
-  if (half_too_small(v, s)) r.h[0] = kHalfNans;
   return r;
-}
-
-// The same for the pack kernel, with a third term that holds the bits that are left.  A weight that the terms cannot hold, or
-// one of eight that are too small, becomes a NaN with its own bits in the other two terms.
-constexpr uint16_t kHalfEscape = 0x7e00;
-
-__device__ __forceinline__ void split_half1(float a, int e, bool escape, uint16_t& h, uint16_t& m, uint16_t& l) {
-  const float s = scale_by(a, e);
-  if (!(__builtin_fabsf(s) < 65504.f) || (escape && a != 0.f)) {
-    const uint32_t u = __builtin_bit_cast(uint32_t, a);
-    h = kHalfEscape;
-    m = (uint16_t)(u >> 16);
-    l = (uint16_t)u;
-    return;
-  }
-  constexpr float up = (float)(1 << kHalfShift);
-  const _Float16 th = (_Float16)s;
-  const float r = (s - (float)th) * up;
-  const _Float16 tm = (_Float16)r;
-  h = __builtin_bit_cast(uint16_t, th);
-  m = __builtin_bit_cast(uint16_t, tm);
-  l = __builtin_bit_cast(uint16_t, (_Float16)((r - (float)tm) * up));
-}
-
-__device__ __forceinline__ float join_f16(uint16_t h, uint16_t m, uint16_t l, int e) {
-  if (h == kHalfEscape) return __builtin_bit_cast(float, (uint32_t)m << 16 | l);
-  auto term = [](uint16_t x) { return (float)__builtin_bit_cast(_Float16, x); };
-  constexpr float down = 1.f / (float)(1 << kHalfShift);
-  return scale_by(term(h) + (term(m) + term(l) * down) * down, -e);
 }
 
 template <int MT>

@@ -2,8 +2,9 @@
 
 Tolerance.  An operand is off by at most 2^-23 of itself and a product misses another 2^-22, of random sign; the sums are rounded
 once per 16 or 32 indices as on the bf16 terms.  Over 32 indices and more the operands' part is below a fifth of
-2^-24 sqrt(K/16 + 32), the bound of test_split_parity_gpu.py, which holds here too.  Sums that the terms cannot hold come from
-the fp32 matrix instructions, which round every second index: 2^-24 sqrt(K/2 + 32).
+2^-24 sqrt(K/16 + 32), the bound of test_split_parity_gpu.py, which holds here too.  Operands that the terms cannot hold come from
+the bf16 terms, within the same bound, or, where those cannot either, from the fp32 matrix instructions, which round every second
+index: 2^-24 sqrt(K/2 + 32).
 """
 import re
 
@@ -97,7 +98,7 @@ def test_half_full_compare(i):
 @pytest.mark.parametrize("case", ["tiny_images", "huge_image", "tiny_weights", "outliers", "zeros", "relu", "denormals"])
 def test_ranges_beyond_f16(pd, case):
     """Images, weights and single values far from the sample's size: every image and every output channel keeps the bound by itself."""
-    assert all("half" in names(pd)[p] for p in PASSES[:2])
+    assert all("half" in names(pd)[p] for p in (PASSES[:2] if pd is PIXELS else PASSES))
     op = OracleParams(**pd)
     x, w, b, dy = workloads.random_inputs(oracle.x_shape(op), oracle.w_shape(op), oracle.output_shape(op), 9900)
     b = b * 0
@@ -128,15 +129,80 @@ def test_ranges_beyond_f16(pd, case):
         if case == "denormals" and name == "dw":
             assert not got.any()  # products of 2^-260
             continue
-        # one large term leaves every later partial sum at full size, and the roundings to it need not be of random sign
-        g, bound = got.cpu().double().numpy(), 2.0 ** -24 * (terms / 2 + 32 if case == "outliers" else np.sqrt(terms / 2 + 32))
-        # output channels of dw; images of y and dx, and their channels (of one pixel each they may be single sums, which cancel)
-        for axis in ((0,) if name == "dw" or pd is PIXELS else (0, 1)):
+        g, bound = got.cpu().double().numpy(), 2.0 ** -24 * np.sqrt(terms / 2 + 32)
+        if case == "outliers":
+            # one large term leaves every later partial sum at full size, and the roundings to it need not be of random sign; by
+            # element, so that the large ones do not stand for the others
+            mag = [np.abs(v) for v in host]
+            size = {"y": lambda: oracle.forward(op, *mag[:3]), "dx": lambda: oracle.backward_data(op, mag[1], mag[3]),
+                    "dw": lambda: oracle.backward_filter(op, mag[0], mag[3])}[name]()
+            assert np.all(np.abs(g - ref) <= 2.0 ** -24 * (terms / 2 + 32) * size), (name, kernel)
+            continue
+        # both channels of dw; images of y and dx, and their channels (of one pixel each they may be single sums, which cancel)
+        for axis in ((0,) if pd is PIXELS else (0, 1)):
             err = np.linalg.norm(np.moveaxis(g - ref, axis, 0).reshape(g.shape[axis], -1), axis=1)
             size = np.linalg.norm(np.moveaxis(ref, axis, 0).reshape(g.shape[axis], -1), axis=1)
             if case == "denormals":
                 size = size + 2.0 ** -149 * 2 ** 24 * np.sqrt(g.size / g.shape[axis])  # results are denormal themselves
             assert np.all(err <= bound * size), (name, kernel, axis, np.max(err / np.maximum(size, 1e-300)) / bound)
+
+
+RAGGED = P(40, 180, 20, 21, 204, 3, 3, 1, 1, 1, 1, g=2)  # 90 and 102 channels a group: the last eight of a group are not its own
+FOLDED = FOLD_CASES[4]  # 1 x 4 taps to a channel of the fold: two of the image's channels in eight
+
+
+def errors_by(axes, got, ref, terms, group=1):
+    """Largest error of a slice along one of `axes`, in units of the slice's own bound; `group`: every group's channels of dw apart"""
+    if group > 1:
+        per = ref.shape[0] // group
+        return max(errors_by(axes, got[i * per:(i + 1) * per], ref[i * per:(i + 1) * per], terms) for i in range(group))
+    g, worst = got.cpu().double().numpy().reshape(ref.shape), 0.0
+    for axis in axes:
+        err = np.linalg.norm(np.moveaxis(g - ref, axis, 0).reshape(g.shape[axis], -1), axis=1)
+        size = np.linalg.norm(np.moveaxis(ref, axis, 0).reshape(g.shape[axis], -1), axis=1)
+        worst = max(worst, float(np.max(err / size)) / (2.0 ** -24 * np.sqrt(terms / 2 + 32)))
+    return worst
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("r", [22, 30, 44, 60])
+@pytest.mark.parametrize("pd", [MIXED, RAGGED, FOLDED, PIXELS], ids=["image", "ragged", "folded", "rows"])
+def test_dim_channels_of_the_filter_gradient(pd, r):
+    """One channel of x and one of dy far below the others: their parts of dw are sums over them alone."""
+    assert "half" in names(pd)["bwd_filter"] or pd is PIXELS
+    op = OracleParams(**pd)
+    x, w, b, dy = workloads.random_inputs(oracle.x_shape(op), oracle.w_shape(op), oracle.output_shape(op), 9901)
+    x[:, pd["c"] // 2] *= 2.0 ** -r
+    dy[:, 6] *= 2.0 ** -r
+    _, _, _, (_, _, dw, _) = run_all(pd, x, w, b, dy)
+    ys = oracle.output_shape(op)
+    assert errors_by((0, 1), dw, oracle.backward_filter(op, x.numpy(), dy.numpy()), ys[0] * ys[2] * ys[3], pd["group"]) <= 1
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("r", [22, 30, 44, 60])
+@pytest.mark.parametrize("how", ["equalised", "hidden"])
+@pytest.mark.parametrize("pd", [MIXED, RAGGED, PIXELS], ids=["image", "ragged", "rows"])
+def test_channels_of_different_sizes_in_one_sum(pd, how, r):
+    """Every eighth reduction channel 2^-r of the others with weights 2^r of theirs, which leaves the sums as they are; or the
+    others 2^-r of every eighth, whose weights are zero."""
+    assert all("half" in names(pd)[p] for p in PASSES[:2])
+    op, taps = OracleParams(**pd), pd["kernel_h"] * pd["kernel_w"]
+    for which in PASSES[:2]:
+        x, w, b, dy = workloads.random_inputs(oracle.x_shape(op), oracle.w_shape(op), oracle.output_shape(op), 9902)
+        b = b * 0
+        blob, per_group = (x, pd["c"] // pd["group"]) if which == "fwd" else (dy, pd["num_output"] // pd["group"])
+        eighth = torch.arange(per_group) % 8 == 3
+        scale = torch.where(eighth == (how == "equalised"), 2.0 ** -r, 1.0)
+        blob *= scale.repeat(pd["group"]).view(1, -1, 1, 1)
+        by_w = 1 / scale if how == "equalised" else torch.where(eighth, 0.0, 1.0)
+        w *= by_w.view(1, -1, 1, 1) if which == "fwd" else by_w.repeat(pd["group"]).view(-1, 1, 1, 1)
+        _, _, _, (y, dx, _, _) = run_all(pd, x, w, b, dy)
+        if which == "fwd":
+            got, ref = y, oracle.forward(op, x.numpy(), w.numpy(), b.numpy())
+        else:
+            got, ref = dx, oracle.backward_data(op, w.numpy(), dy.numpy())
+        assert errors_by((0,) if pd is PIXELS else (0, 1), got, ref, per_group * taps) <= 1, which
 
 
 @pytest.mark.gpu
