@@ -284,7 +284,7 @@ __device__ __forceinline__ void corr_split(const CorrSplitArgs& a, LeftOut& left
   uint32_t* const unheld = reinterpret_cast<uint32_t*>(
       reinterpret_cast<char*>(smem) + (FORM == COLUMNS ? (uint32_t)a.patch_stages * stage_bytes + split_half_lead(BM, BN) : TERM - kUnheldBytes));
   auto patch_store = [&](uint32_t stage_off, int cc) {
-    bool out = w_unheld != 0;
+    HalfRange range;
     const int left = a.fold.V - cc * kChunkChannels;
     if (KIND == HALF && left < kChunkChannels) {
       uint32_t u0 = (uint32_t)t;
@@ -306,7 +306,7 @@ __device__ __forceinline__ void corr_split(const CorrSplitArgs& a, LeftOut& left
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = scale_by(pr[r][e], pscale[r]);
         const SplitHalf8 s = split_half8(v);
-        out |= half_unheld(v);
+        range.add(v);
         if (PIX || u < 2u * (uint32_t)a.PSZ) {
           dst[0] = s.h;
           dst[TERM / 16] = s.m;
@@ -321,7 +321,7 @@ __device__ __forceinline__ void corr_split(const CorrSplitArgs& a, LeftOut& left
       }
       __builtin_amdgcn_sched_barrier(0);  // one unit's terms in registers at a time
     }
-    if (KIND == HALF && out) atomicOr(unheld + ((cc - cc_first) >> 5), 1u << ((cc - cc_first) & 31));
+    if (KIND == HALF && (range.unheld() || w_unheld)) atomicOr(unheld + ((cc - cc_first) >> 5), 1u << ((cc - cc_first) & 31));
   };
 
   // ---- A fragments of this workgroup's steps ----
@@ -813,7 +813,9 @@ __global__ __launch_bounds__(256) void pack_split_kernel(const PackSplitArgs a, 
     float f[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) f[e] = scale_by(v[e], scale);
-    const uint64_t unheld = __ballot(half_unheld(f));
+    HalfRange range;
+    range.add(f);
+    const uint64_t unheld = __ballot(range.unheld());
     if (lane == 0) a.unheld[idx >> 6] = unheld != 0;
 #pragma unroll
     for (int e = 0; e < 8; ++e)

@@ -116,7 +116,7 @@ __device__ __forceinline__ void wgrad_split(const WgradSplitArgs& a, LeftOut& le
   // The chunk's first segment starts at output row a0 of image n0; its patch rows and those of later images are
   // counted as in corr_split_kernel.
   // A thread's units, from its number anew for every chunk: the f16 form has no registers for what depends on it, and a word that comes
-  // back from scratch memory between the loads waits for those before it (128 -> 128, 3x3 at 56x56, batch 64: 309 us so, 240 now).
+  // back from scratch memory between the loads waits for those before it (128 -> 128, 3x3 at 56x56, batch 64: 309 us so, 226 now).
   auto unit0 = [&]() {
     uint32_t u = (uint32_t)t;
     if constexpr (KIND != BF16) asm volatile("" : "+v"(u));
@@ -175,7 +175,7 @@ __device__ __forceinline__ void wgrad_split(const WgradSplitArgs& a, LeftOut& le
   };
   const SplitSel sel;
   auto patch_store = [&](uint32_t table, uint32_t stage, int chunk) {
-    bool out = false;
+    HalfRange range;
     const uint32_t u0 = unit0();
     if (u0 < kChunkPix) *reinterpret_cast<uint32_t*>(smem + table + 4u * u0) = entry;
 #pragma unroll
@@ -190,7 +190,7 @@ __device__ __forceinline__ void wgrad_split(const WgradSplitArgs& a, LeftOut& le
         float v[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = scale_by(pr[r][e], left_out.x_scale);
-        out |= half_unheld(v);
+        range.add(v);
         if constexpr (KIND == HALF) {
           const SplitHalf8 s = split_half8(v);
           if (u < 2u * (uint32_t)a.PSZ) {
@@ -209,7 +209,7 @@ __device__ __forceinline__ void wgrad_split(const WgradSplitArgs& a, LeftOut& le
       }
       __builtin_amdgcn_sched_barrier(0);  // one unit's terms in registers at a time
     }
-    if (KIND != BF16 && out) unheld[chunk & 1] = (uint32_t)chunk + 1u;
+    if (KIND != BF16 && range.unheld()) unheld[chunk & 1] = (uint32_t)chunk + 1u;
   };
 
   // ---- dy: lane l takes run l/16 of a step and row l%16 of each of its wave's row blocks ----
@@ -269,17 +269,24 @@ __device__ __forceinline__ void wgrad_split(const WgradSplitArgs& a, LeftOut& le
   for (int i = 0; i < MB; ++i) bsum[i] = 0.f;
 
   const bool two = a.patch_stages == 2 && KIND != AGAIN;
-  // f16: the powers of two, from the same 2048 values of each blob in every workgroup, four neighbours at a time.
+  // f16: the powers of two, from 2048 values of each blob, four neighbours at a time: those images' that the slice's runs belong to,
+  // from anywhere in the image, a quarter of the slice a wave.  Images need not be of one size: a quarter alone 2^6 above the others
+  // does not decide.
   auto sample_scales = [&]() {
     uint32_t top[2] = {0, 0};
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-      const float* const blob = b ? a.dy : a.x;
-      const uint32_t last = (b ? a.dy_bytes : a.x_bytes) / 4u - 4u;
+      const uint32_t image = (uint32_t)(b ? a.Ktot * a.P : a.C * a.H * a.W), all = (b ? a.dy_bytes : a.x_bytes) / 4u;
       float v[8];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        const float* const at = blob + (uint32_t)((uint64_t)(2 * t + i) * last / (2 * kThreads));
+        const uint32_t j = 2u * (uint32_t)t + i;
+        uint32_t n, p;
+        run_pos((uint32_t)chunk_first * kChunkRuns + (uint32_t)((uint64_t)j * (uint32_t)((chunk_end - chunk_first) * kChunkRuns) / (2 * kThreads)), n, p);
+        if (n > (uint32_t)a.N - 1) n = (uint32_t)a.N - 1;
+        uint32_t off = n * image + __umulhi(j * 2654435769u, image);
+        if (off > all - 4u) off = all - 4u;
+        const float* const at = (b ? a.dy : a.x) + off;
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[4 * i + e] = at[e];
       }
@@ -297,11 +304,18 @@ __device__ __forceinline__ void wgrad_split(const WgradSplitArgs& a, LeftOut& le
     uint32_t* const red = reinterpret_cast<uint32_t*>(smem);
     if (lane == 0) red[2 * wv] = top[0], red[2 * wv + 1] = top[1];
     __syncthreads();
-    uint32_t best[2] = {0, 0};
+    uint32_t best[2];
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < 2; ++b) {
+      uint32_t first = 0, second = 0;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) best[b] = red[2 * w + b] > best[b] ? red[2 * w + b] : best[b];
+      for (int w = 0; w < 4; ++w) {
+        const uint32_t u = red[2 * w + b], below = u < first ? u : first;
+        second = below > second ? below : second;
+        first = u > first ? u : first;
+      }
+      best[b] = second != 0 && first - second > 6u << 23 ? second : first;
+    }
     left_out.x_scale = __builtin_amdgcn_readfirstlane(half_scale(best[0]));
     left_out.dy_scale = __builtin_amdgcn_readfirstlane(half_scale(best[1]));
     __syncthreads();
@@ -377,7 +391,7 @@ __device__ __forceinline__ void wgrad_split(const WgradSplitArgs& a, LeftOut& le
       // this step's dy operands: masked, summed, split; then the next step's loads.  Only an image's last run has anything to
       // mask: a test for the wave instead of a select per value, which the two multiplications of a split pair cost.
       u32x4 av[MB][TERMS];
-      bool out = false;
+      HalfRange range;
       if (__any(valid < 8)) {
 #pragma unroll
         for (int i = 0; i < MB; ++i)
@@ -398,7 +412,7 @@ __device__ __forceinline__ void wgrad_split(const WgradSplitArgs& a, LeftOut& le
             av[i][1] = sp.m;
             asm volatile("" : "+v"(av[i][1]));  // here, or the operands stay in registers until the test below is decided
           }
-          out |= half_unheld(scaled);
+          range.add(scaled);
         }
         if constexpr (KIND != HALF) {
           const Split8 sp = split8(v, sel);
@@ -410,7 +424,7 @@ __device__ __forceinline__ void wgrad_split(const WgradSplitArgs& a, LeftOut& le
       const int step = ch * kChunkSteps + s;
       load_dy(s + 1 < kChunkSteps ? step + 1 : more ? next * kChunkSteps : step);
       if constexpr (KIND != BF16) {
-        const bool left = patch_out || __any(out);
+        const bool left = patch_out || __any(range.unheld());
         if (KIND == HALF && left && lane == 0)
           atomicOr(unheld + 2 + ((ch - chunk_first) >> coarse >> 5), 1u << ((ch - chunk_first) >> coarse & 31));
         if (left == (KIND == HALF)) continue;

@@ -14,9 +14,9 @@
 // takes this split where both together are below what the three-way split loses.
 //
 // Range.  f16 ends at 65504 and keeps 11 bits down to 2^-14: the power of two puts the largest of a sample at 2^12 to 2^13, which
-// leaves 2^3 above.  A value is held as said from 2^-14 on and, within 2^-36, to 2^-18 of itself from 2^-18 on: 2^-30 of the
-// sample's largest, where one of 10^9 normally distributed ones is.  A value that is not held -- above 65504, not a number, or below
-// 2^-18 and not zero -- keeps the chunk or the step that it is in out of these sums; the kernels add those behind, on the three-way
+// leaves 2^3 above.  A value is held as said from 2^-14 on and, within 2^-36, to 2^-20 of itself from 2^-16 on: 2^-28 of the
+// sample's largest, where one of 10^8 normally distributed ones is.  A value that is not held -- above 65504, not a number, or below
+// 2^-16 and not zero -- keeps the chunk or the step that it is in out of these sums; the kernels add those behind, on the three-way
 // split.  That goes by each value and not by the largest of some: neighbours need not be terms of the same sums, nor meet weights of
 // one size.
 #pragma once
@@ -35,7 +35,7 @@ constexpr int kHalfShift = 11;             // m is held times 2^11
 constexpr float kHalfUp = (float)(1 << kHalfShift), kHalfDown = 1.f / kHalfUp;
 constexpr int kHalfTop = 12;               // exponent of the sample's largest operand
 constexpr int kHalfLeast = -16;            // of the power of two: fp32's smallest denormals are not scaled to zero
-constexpr uint32_t kHalfFloor = 2u * 0x36800000u - 1u;  // nonzero_order of 2^-18, the smallest operand that is held
+constexpr uint32_t kHalfFloor = 2u * 0x37800000u - 1u;  // nonzero_order of 2^-16, the smallest operand that is held
 constexpr float kHalfCeil = 65504.f;                    // the largest
 
 // Power of two for a sample whose largest magnitude has these bits (0: an empty or all-zero sample).
@@ -68,14 +68,20 @@ __device__ __forceinline__ uint32_t least3(uint32_t a, uint32_t b, uint32_t c) {
   return m < c ? m : c;
 }
 
-// Whether a scaled operand among eight is not held.
-__device__ __forceinline__ bool half_unheld(const float (&s)[8]) {
-  const uint32_t least = least3(least3(nonzero_order(s[0]), nonzero_order(s[1]), nonzero_order(s[2])),
-                                least3(nonzero_order(s[3]), nonzero_order(s[4]), nonzero_order(s[5])),
-                                least3(nonzero_order(s[6]), nonzero_order(s[7]), 0xffffffffu));
-  const float most = max3_abs(max3_abs(max3_abs(s[0], s[1], s[2]), s[3], s[4]), max3_abs(s[5], s[6], s[7]), 0.f);
-  return least < kHalfFloor || !(most <= kHalfCeil);
-}
+// Range of operands: the smallest nonzero_order and the largest magnitude so far.
+struct HalfRange {
+  uint32_t least = 0xffffffffu;
+  float most = 0.f;
+  __device__ __forceinline__ void add(const float (&s)[8]) {
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+      least = least3(nonzero_order(s[e]), nonzero_order(s[e + 1]), least);
+      most = max3_abs(s[e], s[e + 1], most);
+    }
+  }
+  // Of scaled operands: whether one is not held.
+  __device__ __forceinline__ bool unheld() const { return least < kHalfFloor || !(most <= kHalfCeil); }
+};
 
 struct SplitHalf8 {  // eight consecutive reduction indices of one row or column
   u32x4 h, m;

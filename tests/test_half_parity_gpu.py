@@ -19,7 +19,7 @@ from paper_1810_02272_amd import workloads
 from parity_cases import FOLD_CASES, HALF_CASES, SPLIT_CASES, P
 from parity_metric import nerr
 from test_parity_gpu import TOL, check_filter_and_bias_in_one_pass, run_all
-from test_split_parity_gpu import CORR, ODD, WGRAD, check_odd_values, names, norm_error
+from test_split_parity_gpu import CORR, DEV, ODD, WGRAD, check_odd_values, names, norm_error
 
 PASSES = ("fwd", "bwd_data", "bwd_filter")
 MIXED = P(24, 128, 28, 28, 128, 3, 3, 1, 1, 1, 1)  # all three passes on f16 terms
@@ -203,6 +203,38 @@ def test_channels_of_different_sizes_in_one_sum(pd, how, r):
         else:
             got, ref = dx, oracle.backward_data(op, w.numpy(), dy.numpy())
         assert errors_by((0,) if pd is PIXELS else (0, 1), got, ref, per_group * taps) <= 1, which
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("pd", [P(64, 256, 13, 13, 384, 3, 3, 1, 1, 1, 1), P(32, 128, 56, 56, 128, 3, 3, 1, 1, 1, 1)], ids=["13x13", "56x56"])
+def test_an_image_far_below_the_others_costs_little(pd):
+    """1.0 to 1.2 times a pass, and 1.6 where the image is half of a slice of the filter gradient (made of NaN: 3 to 5 times)."""
+    assert all("half" in names(pd)[p] for p in PASSES)
+    d, op = conv.conv_desc_create(conv.ConvParams(**pd)), OracleParams(**pd)
+    x, w, b, dy = (t.to(DEV) for t in workloads.random_inputs(oracle.x_shape(op), oracle.w_shape(op), oracle.output_shape(op), 9903))
+    y, dx, dw, db = torch.empty_like(dy), torch.empty_like(x), torch.empty_like(w), torch.empty_like(b)
+    ws = torch.empty((conv.conv_desc_workspace_bytes(d) + 7) // 8, device=DEV, dtype=torch.float64)
+    x1, dy1 = x.clone(), dy.clone()
+    for t in (x1, dy1):
+        t[pd["n"] // 2] *= 2.0 ** -30
+
+    def ms(call):
+        best = float("inf")
+        for _ in range(4):
+            start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            start.record()
+            for _ in range(5):
+                call()
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, start.elapsed_time(end))
+        return best
+
+    for which, call in (("fwd", lambda x, dy: conv.conv_forward(d, x, w, b, y, ws)),
+                        ("bwd_data", lambda x, dy: conv.conv_backward_data(d, w, dy, dx, ws)),
+                        ("bwd_filter", lambda x, dy: conv.conv_backward_filter_bias(d, x, dy, dw, db, 0.0, ws))):
+        plain, uneven = ms(lambda: call(x, dy)), ms(lambda: call(x1, dy1))
+        assert uneven < 2 * plain, (which, plain, uneven)
 
 
 @pytest.mark.gpu
