@@ -505,12 +505,15 @@ bool folded_grid(int64_t cg, int64_t kh, int64_t kw, int64_t sh, int64_t sw, int
   return g.f.fw % 4 == 0 && g.f.Uw % 4 == 0 && dw == 1 && pw % 4 == 0;
 }
 
-// Whether sums of K products take f16 terms where bf16 terms would add up `bf16_K` of them in a slice: where their error is no
-// larger (squares of the 2-norms, in units of 2^-24: split_f16.h) on inputs half of which are zero, as behind a ReLU -- zeros add
-// no rounding to a sum, so it is well below on dense ones (640 indices: 2.39 -> 1.99 dense, 1.80 -> 1.93 half zeros; 768: 2.64 ->
-// 2.02 and 2.00 -> 1.95; 1152: 3.31 -> 2.57 and 2.53 -> 2.54).  Returns the steps (of `step` indices, in whole `unit`s) between two
-// moves of the sums' leading bits, or 0 for bf16 terms.  A move costs time (every 128 indices instead of 400: 57.3 GFLOP 160 ->
-// 176 us), so the stretches are as long as a quarter less error than the bf16 terms' allows, 128 indices where that is out of reach.
+// Whether sums of K products take f16 terms where bf16 terms would add up `bf16_K` of them in a slice: where their error is smaller on
+// inputs without zeros, by a margin (squares of the 2-norms, in units of 2^-24: split_f16.h).  Zeros add no rounding to a sum, but what
+// the operands lose stays.  Measured, bf16 -> f16 terms, for inputs without zeros, with a half and with a tenth that is not zero:
+//   3x3 forward, K = 648: 2.35 -> 1.95, 1.81 -> 1.94, 0.93 -> 1.77; 1152: 3.21 -> 2.39, 2.49 -> 2.36, 1.18 -> 1.97;
+//   2304: 4.68 -> 3.50, 3.65 -> 3.47, 1.65 -> 2.72;
+//   filter gradient, both blobs so, 1394 a slice: 3.76 -> 3.03, 2.21 -> 2.87, 1.01 -> 1.80; 1261: 3.61 -> 2.80, 2.25 -> 2.73, 1.30 -> 1.98.
+// Returns the steps (of `step` indices, in whole `unit`s) between two moves of the sums' leading bits, or 0 for bf16 terms.  A move
+// costs time (every 128 indices instead of 400: 57.3 GFLOP 160 -> 176 us), so the stretches are as long as a quarter less error than
+// the bf16 terms' allows, 128 indices where that is out of reach.
 int32_t half_interval(double K, double bf16_K, double step, int32_t unit) {
   const double bf16 = 0.0047 * bf16_K;
   auto error = [&](int32_t steps) {
