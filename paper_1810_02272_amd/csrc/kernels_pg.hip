@@ -15,13 +15,15 @@ namespace mi355conv {
 
 namespace {
 
-// ---- step 3: action = (random < Aprob) ? 0 : 1 ----
-// Four consecutive steps per thread (16-byte loads and stores); the last, partial group of a
-// launch goes element by element.
-// From 48 MB on, what a pass reads or writes and no other of these passes reads again goes around the last-level cache (256 MB),
-// so that the sampled actions and discounted rewards are still there for the passes that read them: 16.6 M steps, 6 actions, all
-// four passes 346 -> 317 us (the stores alone 324).  Below that whoever reads the results next finds them in the cache.
-constexpr size_t kStreamBytes = (size_t)48 << 20;
+// Where a model's passes touch more than the last-level cache holds, what a pass reads or writes and no other of them reads again goes
+// around it, so that the sampled actions and discounted rewards are still there for the passes that read them.  A step is seven words of
+// the Sigmoid model's, three rows and three words of the Softmax model's.  Measured (us, all through the cache -> around it): Sigmoid
+// passes, 6 M steps (168 MB) 40.8 -> 41.2, 8 M 52.5 -> 53.5, 10 M 67.6 -> 65.4, 16 M 114.8 -> 101.7; Softmax pass with the discounted
+// rewards, 6 actions, 2 M steps (168 MB) 32.8 -> 37.1, 4 M (336 MB) 69.0 -> 64.4, 8 M 131 -> 116, and with a following kernel that
+// reads bottom_diff 47.4 -> 53.0, 93.7 -> 93.3, 199 -> 188; 12 actions, 8 M 239 -> 210.  From about 14 actions on what stays in the cache
+// is too little beside the rows (14 actions, 8 M steps 275 -> 273; 18, 351 -> 359; 24, 488 -> 506).
+constexpr size_t kCacheBytes = (size_t)256 << 20;
+constexpr int kStreamActions = 14;
 
 // A template argument: of a branch between both forms the compiler makes one plain access.
 template <bool STREAM>
@@ -46,6 +48,9 @@ __device__ __forceinline__ float4 load4(const float* from) {
   return make_float4(u[0], u[1], u[2], u[3]);
 }
 
+// ---- step 3: action = (random < Aprob) ? 0 : 1 ----
+// Four consecutive steps per thread (16-byte loads and stores); the last, partial group of a
+// launch goes element by element.
 template <bool STREAM>
 __global__ __launch_bounds__(256) void pg_sample_kernel(const float* __restrict__ aprob,
                                                         const float* __restrict__ random, int32_t* __restrict__ action,
@@ -604,7 +609,7 @@ int pg_sigmoid_sample_action(const float* aprob, const float* random, int32_t* a
   if (steps > kMaxSteps) return CONV_ESHAPE;
   if (steps == 0) return CONV_OK;
   if (!aprob || !random || !action) return CONV_EINVAL;
-  hipLaunchKernelGGL((size_t)steps * 4 >= kStreamBytes ? pg_sample_kernel<true> : pg_sample_kernel<false>, dim3((steps + 1023) / 1024), dim3(256), 0, (hipStream_t)hip_stream, aprob,
+  hipLaunchKernelGGL((size_t)steps * 28 > kCacheBytes ? pg_sample_kernel<true> : pg_sample_kernel<false>, dim3((steps + 1023) / 1024), dim3(256), 0, (hipStream_t)hip_stream, aprob,
                      random, action, steps);
   return done();
 }
@@ -638,7 +643,7 @@ int pg_sigmoid_bottom_diff(const float* aprob, const int32_t* action, const floa
   if (steps > kMaxSteps) return CONV_ESHAPE;
   if (steps == 0) return CONV_OK;
   if (!aprob || !action || !bottom_diff) return CONV_EINVAL;
-  hipLaunchKernelGGL((size_t)steps * 4 >= kStreamBytes ? pg_sigmoid_kernel<true> : pg_sigmoid_kernel<false>, dim3((steps + 1023) / 1024), dim3(256), 0, (hipStream_t)hip_stream, aprob,
+  hipLaunchKernelGGL((size_t)steps * 28 > kCacheBytes ? pg_sigmoid_kernel<true> : pg_sigmoid_kernel<false>, dim3((steps + 1023) / 1024), dim3(256), 0, (hipStream_t)hip_stream, aprob,
                      action, discounted, dlogps, bottom_diff, steps);
   return done();
 }
@@ -651,7 +656,7 @@ int pg_softmax_bottom_diff(const float* logits, const int32_t* action, const flo
   if (!logits || !action || !bottom_diff) return CONV_EINVAL;
   if (actions <= 32) {
     const size_t lds = (size_t)2 * 256 * (actions | 1) * sizeof(float);  // at most 66 KB
-    const bool stream = (size_t)steps * actions * 4 >= kStreamBytes;
+    const bool stream = actions <= kStreamActions && (size_t)steps * (12 * actions + 12) > kCacheBytes;
     auto* const kernel = stream ? pg_softmax_rows_kernel<true> : pg_softmax_rows_kernel<false>;
     static LdsOptIn opt_in[2];  // 32 actions need 66 KB: opt in to the largest size, once per process and kernel
     if (lds > 64 * 1024) {

@@ -220,10 +220,11 @@ def test_pg_neighbouring_long_episodes_cost_no_more_than_distant_ones():
     assert times["together"] <= 3 * times["apart"], times
 
 
-@pytest.mark.parametrize("actions", [2, 7, 32])
+@pytest.mark.parametrize("actions", [2, 7, 14, 15])
 def test_pg_batches_beyond_the_cache_have_the_same_bits(actions):
-    """From 48 MB on the element-wise passes go around the last-level cache; steps that end inside a block and an unaligned part."""
-    steps = (13 << 20) + 517 if actions == 2 else (13 << 20) // actions + 517
+    """Batches that the passes touch more of than the last-level cache holds go around it, of up to 14 actions: the bits of their
+    parts, which do not.  Steps that end inside a block, and blobs that start between two 16-byte words."""
+    steps = (10 << 20) + 517 if actions == 2 else (270 << 20) // (12 * actions + 12) + 517
     gen = torch.Generator(device=DEV).manual_seed(actions)
     aprob, rnd, w = (torch.rand(steps, device=DEV, generator=gen) for _ in range(3))
     logits = torch.randn(steps, actions, device=DEV, generator=gen)
@@ -244,3 +245,9 @@ def test_pg_batches_beyond_the_cache_have_the_same_bits(actions):
     torch.cuda.synchronize()
     for i, t in enumerate(whole):
         assert torch.equal(t, torch.cat([p[i] for p in parts])), i
+    shifted = torch.empty(steps * actions + 1, device=DEV)[1:].view(steps, actions)
+    shifted.copy_(logits)
+    probs, diff = (torch.full((steps * actions + 1,), NAN, device=DEV)[1:].view(steps, actions) for _ in range(2))
+    lib.pg_softmax_bottom_diff(shifted, action, w, probs, diff)
+    torch.cuda.synchronize()
+    assert shifted.data_ptr() % 16 == 4 and torch.equal(probs, whole[3]) and torch.equal(diff, whole[4])
