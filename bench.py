@@ -31,6 +31,13 @@ PEAK_FP64_MFMA_TFLOPS = 78.6   # ... and fp64
 # product, at the nominal dense bf16 rate of 2.5 PFLOP/s
 PEAK_SPLIT_MFMA_TFLOPS = 2500.0 / 6.0
 PEAK_HALF_MFMA_TFLOPS = 2500.0 / 3.0  # two f16 terms, three products
+
+
+def peak_of(kernel, plain):
+    """Peak rate of the matrix instructions of a kernel by its name, `plain` without a split."""
+    return plain if "split" not in kernel else PEAK_HALF_MFMA_TFLOPS if "half" in kernel else PEAK_SPLIT_MFMA_TFLOPS
+
+
 PEAK_HBM_GBS = 8000.0
 
 
@@ -394,6 +401,13 @@ def main():
             row["launches"] = sum(launches.values())
         per_layer.append(row)
 
+    peak_seconds = 0.0  # of a step's matrix work
+    for t in state:
+        kernels = dict(kv.split("=", 1) for kv in kernel_names_of(t["desc"]).split(";"))
+        for name in passes:
+            if name in flop_passes:
+                peak_seconds += t["layer"].flop_per_pass / 1e12 / peak_of(kernels[name.replace("filter_bias", "filter")], peak)
+
     # dominant launch: the (layer, pass) with the largest average duration
     dl, dp = dominant
     dms = sum(e0.elapsed_time(e1) for _, _, e0, e1 in dom_events) / len(dom_events)
@@ -415,7 +429,7 @@ def main():
     else:
         achieved = dlayer.flop_per_pass / (dms * 1e-3) / 1e12
         kernel = kernel_names.get(dp, dp)
-        pass_peak = peak if "split" not in kernel else round(PEAK_HALF_MFMA_TFLOPS if "half" in kernel else PEAK_SPLIT_MFMA_TFLOPS, 1)
+        pass_peak = round(peak_of(kernel, peak), 1)
         roofline = {"bound": "mfma", "achieved": round(achieved, 2), "peak": pass_peak,
                     "unit": "TFLOP/s", "frac": round(achieved / pass_peak, 4), "traffic": None}
     roofline.update({"kernel": kernel_names.get(dp, dp), "layer": dl, "pass": dp, "avg_ms": round(dms, 5),
@@ -446,7 +460,8 @@ def main():
                                + " (N=%d each), %s, beta=0, bias=0" % (layers[0].m if is_ip else layers[0].n,
                                                                        "+".join(passes)),
                    "frac_of_%s_mfma_peak" % ("fp64" if f64 else "fp32"): round(value / 1e3 / peak, 4),
-                   **({} if f64 else {"frac_of_split_mfma_peak": round(value / 1e3 / PEAK_SPLIT_MFMA_TFLOPS, 4)}),
+                   # every pass at the peak of the matrix instructions that its kernel uses
+                   **({} if f64 else {"frac_of_split_mfma_peak": round(value * 1e9 * peak_seconds / flop_step, 4)}),
                    "cache": ("cold: %s tensor sets per layer rotated every step"
                              % "/".join(str(len(t["sets"])) for t in state)) if args.cold_cache
                             else "warm: the same tensors every step",
