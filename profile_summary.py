@@ -60,11 +60,11 @@ def trace(directory: str) -> None:
     agg: "OrderedDict[tuple, list]" = OrderedDict()
     for r in rows:
         blocks = int(r["Grid_Size_X"]) // max(int(r["Workgroup_Size_X"]), 1)
-        key = (_short(r["Kernel_Name"])[:58], blocks, r["LDS_Block_Size"])
+        key = (_short(r["Kernel_Name"])[:66], blocks, r["LDS_Block_Size"])
         agg.setdefault(key, []).append(int(r["End_Timestamp"]) - int(r["Start_Timestamp"]))
-    print(f"{'kernel':58s} {'blocks':>7s} {'LDS B':>6s} {'calls':>5s} {'avg us':>9s} {'min us':>9s} {'max us':>9s}")
+    print(f"{'kernel':66s} {'blocks':>7s} {'LDS B':>6s} {'calls':>5s} {'avg us':>9s} {'min us':>9s} {'max us':>9s}")
     for (name, blocks, lds), v in agg.items():
-        print(f"{name:58s} {blocks:7d} {lds:>6s} {len(v):5d} {sum(v) / len(v) / 1e3:9.1f} {min(v) / 1e3:9.1f} "
+        print(f"{name:66s} {blocks:7d} {lds:>6s} {len(v):5d} {sum(v) / len(v) / 1e3:9.1f} {min(v) / 1e3:9.1f} "
               f"{max(v) / 1e3:9.1f}")
 
 
@@ -114,14 +114,14 @@ def sq(directory: str) -> None:
         name = _short(r["Kernel_Name"])
         if not any(m in name for m in MAIN[:5] + ("corr64_kernel", "wgrad64_kernel")):
             continue
-        key = (name[:50], int(r["Grid_Size"]) // max(int(r["Workgroup_Size"]), 1))
+        key = (name[:66], int(r["Grid_Size"]) // max(int(r["Workgroup_Size"]), 1))
         agg.setdefault(key, {}).setdefault(r["Counter_Name"], []).append(float(r["Counter_Value"]))
-    print(f"{'kernel':50s} {'blocks':>6s} {'kcycles':>8s} {'MFMA busy':>9s} {'GFLOP(mfma)':>11s} {'waves/SIMD':>10s} "
+    print(f"{'kernel':66s} {'blocks':>6s} {'kcycles':>8s} {'MFMA busy':>9s} {'GFLOP(mfma)':>11s} {'waves/SIMD':>10s} "
           f"{'wait':>5s} {'VALU/MFMA':>9s} {'LDS confl':>9s}")
     for (name, blocks), c in agg.items():
         v = {k: sum(x) / len(x) for k, x in c.items()}
         cyc = v["SQ_BUSY_CYCLES"] / 32.0
-        print(f"{name:50s} {blocks:6d} {cyc / 1e3:8.0f} {100 * v['SQ_VALU_MFMA_BUSY_CYCLES'] / 1024 / cyc:8.1f}% "
+        print(f"{name:66s} {blocks:6d} {cyc / 1e3:8.0f} {100 * v['SQ_VALU_MFMA_BUSY_CYCLES'] / 1024 / cyc:8.1f}% "
               f"{sum(v.get('SQ_INSTS_VALU_MFMA_MOPS_' + t, 0.0) for t in ('F32', 'F64', 'BF16', 'F16')) * 512 / 1e9:11.2f} "
               f"{v['SQ_WAVE_CYCLES'] * 4 / 1024 / cyc:10.2f} "
               f"{100 * v['SQ_WAIT_INST_ANY'] / v['SQ_WAVE_CYCLES']:4.0f}% "
