@@ -14,7 +14,8 @@ namespace mi355conv {
 // An element is stored when (row shift + row, column shift + column) lies inside the output
 // image; rows past the matrix edge and columns past the batch carry a shift that fails the test.
 // Must be entered after a barrier: the tables overwrite the pipeline buffers at `smem`.  `again`: the sums are added to what the
-// same call's first sums, with bias, have left in the output or the slice.
+// same call's first sums, with bias, have left in the output or the slice; all loads come before the stores, which they would wait for one
+// by one.
 template <int MT, int MB, int NB, int BM, int BN, typename Acc>
 __device__ __forceinline__ void corr_epilogue(const CorrArgs& a, float* smem, Acc (&acc)[MB][NB], uint32_t m_tile,
                                               uint32_t col_tile, uint32_t g, int wm, int wn, uint32_t split = 0, bool again = false) {
@@ -23,7 +24,7 @@ __device__ __forceinline__ void corr_epilogue(const CorrArgs& a, float* smem, Ac
   // layout, to its slice of the workspace; a reduce kernel adds the slices and the bias.
   float* const out = a.ksplit > 1 ? a.part + (size_t)split * a.out_elems : a.out;
   const float* const bias = a.ksplit > 1 || again ? nullptr : a.bias;
-  const bool accumulate = again || (a.accumulate != 0 && a.ksplit <= 1);
+  const bool accumulate = !again && a.accumulate != 0 && a.ksplit <= 1;
   const int t = threadIdx.x, lane = t & 63;
   int4* rowtab = reinterpret_cast<int4*>(smem);
   int4* coltab = rowtab + BM;
@@ -64,6 +65,16 @@ __device__ __forceinline__ void corr_epilogue(const CorrArgs& a, float* smem, Ac
     uint32_t co[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j) co[j] = (uint32_t)coltab[(wn * NB + j) * MT + lane % MT].x;
+    if (again)
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int r = 0; r < M::NR; ++r) {
+          const uint32_t ro = (uint32_t)rowtab[(wm * MB + i) * MT + M::row(r, lane)].x;
+#pragma unroll
+          for (int j = 0; j < NB; ++j)
+            acc[i][j][r] += __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(out_rsrc, ro + co[j], 0, 0));
+        }
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
@@ -123,6 +134,20 @@ __device__ __forceinline__ void corr_epilogue(const CorrArgs& a, float* smem, Ac
     // of the buffer store drops it -- no branch around the store, 32-bit offsets.
     const __amdgpu_buffer_rsrc_t out_rsrc =
         __builtin_amdgcn_make_buffer_rsrc(out, 0, (int)(4u * (uint32_t)a.out_elems), 0x00020000);
+    if (again)
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int r = 0; r < M::NR; ++r) {
+          const int4 rt = rowtab[(wm * MB + i) * MT + M::row(r, lane)];
+#pragma unroll
+          for (int j = 0; j < NB; ++j) {
+            const int hh = rt.y + ct[j].y, ww = rt.z + ct[j].z;
+            const bool ok = ((uint32_t)hh < (uint32_t)a.OHd) & ((uint32_t)ww < (uint32_t)a.OWd);
+            const uint32_t off = ok ? 4u * (uint32_t)(rt.x + ct[j].x) : 0x80000000u;
+            acc[i][j][r] += __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(out_rsrc, off, 0, 0));
+          }
+        }
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
@@ -153,7 +178,7 @@ __device__ __forceinline__ void corr_epilogue(const CorrArgs& a, float* smem, Ac
         if ((uint32_t)hh < (uint32_t)a.OHd && (uint32_t)ww < (uint32_t)a.OWd) {
           float* const dst = out + (rt.x + ct[j].x);
           const float v = acc[i][j][r] + bb;
-          *dst = accumulate ? *dst + v : v;
+          *dst = accumulate || again ? *dst + v : v;
         }
       }
     }

@@ -24,11 +24,15 @@
 // 32, 5x5 at 16x16, batch 100) 29 -> 21.  172 and 115 us are the matrix instructions of the first two at 2000 TFLOP/s.
 //
 // HALF: long reductions on two f16 terms (split_f16.h), half the matrix instructions.  The stage is [h, m][half][position] then,
-// 16 bytes a position.  The same passes: 57.3 GFLOP 249 -> 162 us and 269 -> 171, 38.3 GFLOP 172 -> 108 and 206 -> 129, 6.7 GFLOP 49
-// -> 38 and 53 -> 41; the pack kernel, which samples both blobs, 0.5 to 1.4 us more.  The matrix unit is busy 60 % of the cycles, at
-// the clock that the chip's power leaves (1.7 GHz); a quarter of the waves' time are waits for weights, patches and barriers.  Weights
-// two steps ahead gave nothing (108 -> 112 us where the registers hold them, spills elsewhere).
-// AGAIN: what a workgroup's HALF sums had to leave out, chunk by chunk, it adds on the bf16 terms behind them.
+// 16 bytes a position.  The same passes: 57.3 GFLOP 249 -> 166 us and 269 -> 166, 38.3 GFLOP 172 -> 114 and 206 -> 137, 6.7 GFLOP 49
+// -> 37 and 53 -> 40 (without the test of every value 2 % less); the pack kernel, which samples both blobs and writes both splits, 1
+// to 2.5 us more.  The matrix unit is busy 50 to 55 % of the cycles, at the clock that the chip's power leaves (1.7 GHz); a quarter to
+// two fifths of the waves' time are waits for weights, patches and barriers.  Weights two steps ahead gave nothing (108 -> 112 us where
+// the registers hold them, spills elsewhere).
+// AGAIN: what a workgroup's HALF sums had to leave out, chunk by chunk, it adds on the bf16 terms behind them.  A chunk of 5.6 M values
+// that is left out costs 7 to 11 us, all of them 1.8 times a pass (57.3 GFLOP, forward: 168 -> 316 us, of which weights far below the
+// others are the cause for a third of the rows).  Both splits' instructions on one set of accumulators, chunk by chunk, cost hundreds of
+// spilled registers.
 //
 // Forms (SplitFold).  Folded taps: 3 -> 96 channels, 11x11, stride 4 at 227x227, batch 128, forward 254 -> 195 us; busy 46 %,
 // the folded patch's loads and splits (3 vector instructions to a matrix one) and 30 % of padding take the rest.  Columns
@@ -488,6 +492,11 @@ __device__ __forceinline__ void corr_split(const CorrSplitArgs& a, LeftOut& left
       pos = 0;
       tap = tj = 0;
       jump_a(cc);
+      // a look at every line of the chunk's weights, which nobody else may read: from memory they are a microsecond or two away, step by step
+      uint32_t seen = 0;
+      for (uint32_t i = 128u * (uint32_t)t; i < (uint32_t)SPC * C::STEP; i += 128u * kThreads)
+        seen |= __builtin_amdgcn_raw_buffer_load_b32(a_rsrc, i, (int)a_off, 0);
+      asm volatile("" : : "v"(seen));
       fill_a(1);
 #pragma unroll 1
       for (int s = 0; s < SPC; ++s) {

@@ -19,8 +19,10 @@
 //
 // HALF: long sums on two f16 terms (split_f16.h), half the matrix instructions, positions of 64 bytes.  Every workgroup samples
 // both blobs for the powers of two while its first loads are under way.  The first three layers, without the reduce kernel: 349 ->
-// 236 us, 219 -> 150, 67 -> 54.
-// AGAIN: what a workgroup's HALF sums had to leave out, step by step, it adds on the bf16 terms behind them.
+// 228 us, 219 -> 153, 67 -> 57, of which the test of every value is 6 to 8 %: each of a row's column tiles tests it again.
+// AGAIN: what a workgroup's HALF sums had to leave out, step by step, it adds on the bf16 terms behind them.  128 -> 128, 3x3 at 56x56,
+// batch 64: 228 us, with one image 2^-30 of the others 235, with every image of a size of its own 345, with one channel of x and one of dy
+// 2^-30 of theirs, which leaves out every step, 474 (343 on bf16 terms alone).
 // FOLD: the folded grid of corr_split_kernel, so that few channels fill the blocks: 3 -> 96 channels, 11x11, stride 4 at 227x227,
 // batch 128, 290 us on the fp32 kernel -> 191; 9 -> 128, 12x12 at 109x150, batch 87, 265 -> 125.  Over 59 drawn layers that take it
 // 1.36 times as fast in the geometric mean, none slower.
@@ -584,20 +586,25 @@ __device__ __forceinline__ void wgrad_split(const WgradSplitArgs& a, LeftOut& le
   float* dst = a.part + (size_t)split * a.part_stride + (size_t)g * ((size_t)a.Kg * a.Kred);
   const __amdgpu_buffer_rsrc_t out_rsrc =
       __builtin_amdgcn_make_buffer_rsrc(dst, 0, (int)(4u * (uint32_t)a.Kg * (uint32_t)a.Kred), 0x00020000);
+  auto each = [&](auto&& act) {
 #pragma unroll
-  for (int i = 0; i < MB; ++i)
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
-    for (int r = 0; r < M::NR; ++r) {
-      const uint32_t k = m_tile * BM + (uint32_t)((wm * MB + i) * 16 + M::row(r, lane));
-      const uint32_t ro = k < (uint32_t)a.Kg && c < channels ? 4u * (k * (uint32_t)a.Kred + (uint32_t)c) : 0x80000000u;
+      for (int r = 0; r < M::NR; ++r) {
+        const uint32_t k = m_tile * BM + (uint32_t)((wm * MB + i) * 16 + M::row(r, lane));
+        const uint32_t ro = k < (uint32_t)a.Kg && c < channels ? 4u * (k * (uint32_t)a.Kred + (uint32_t)c) : 0x80000000u;
 #pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const uint32_t co = tap0 + j < a.khw ? 4u * (uint32_t)((tap0 + j) * channels) : 0x40000000u;
-        float v = acc[i][j][r];
-        if (KIND == AGAIN && !redo) v += __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(out_rsrc, ro + co, 0, 0));
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), out_rsrc, ro + co, 0, 0);
+        for (int j = 0; j < NB; ++j) act(i, j, r, ro + (tap0 + j < a.khw ? 4u * (uint32_t)((tap0 + j) * channels) : 0x40000000u));
       }
-    }
+  };
+  if (KIND == AGAIN && !redo)  // all loads before the stores, which they would wait for one by one
+    each([&](int i, int j, int r, uint32_t off) {
+      acc[i][j][r] += __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(out_rsrc, off, 0, 0));
+    });
+  each([&](int i, int j, int r, uint32_t off) {
+    const float v = acc[i][j][r];
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), out_rsrc, off, 0, 0);
+  });
 }
 
 template <int WM, int WN, int MB, int NB, int EPT, SplitTerms KIND, bool FOLD>
