@@ -53,6 +53,33 @@ def test_folded_filter_gradients_select_every_instance():
     assert found >= {(t, u) for t in ("96x10", "128x9", "64x16", "32x12") for u in "34"} | {"1", "2"}
 
 
+WIDE = P(130, 2064, 13, 13, 512, 3, 1, 1, 1, 1, 0)  # a grid that fills the chip, 129 chunks: one more than a slice's bits
+
+
+def test_many_chunks_take_the_least_slices_that_hold_them():
+    for c, slices in ((2048, 1), (2064, 2), (4096, 2), (4112, 3)):
+        assert f"(S={slices},half" in names(dict(WIDE, c=c))["fwd"], c
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("r", [0, 40])
+def test_many_chunks_in_slices(r):
+    """r: the last channel, the second slice's last, 2^-r of the others in half of the images"""
+    d, n = conv.conv_desc_create(conv.ConvParams(**WIDE)), 4
+    gen = torch.Generator(device=DEV).manual_seed(9904)
+    x, w, b = (torch.randn(s, device=DEV, generator=gen) for s in ((130, 2064, 13, 13), (512, 2064, 3, 1), (512,)))
+    x[::2, -1] *= 2.0 ** -r
+    y = torch.full(conv.conv_desc_output_shape(d), float("nan"), device=DEV)
+    ws = torch.full(((conv.conv_desc_workspace_bytes(d) + 7) // 8,), float("nan"), device=DEV, dtype=torch.float64)
+    conv.conv_forward(d, x, w, b, y, ws)
+    assert not torch.isnan(y).any()
+    for first in (0, 126):
+        cols = torch.nn.functional.unfold(x[first:first + n].double(), (3, 1), padding=(1, 0))
+        ref = torch.matmul(w.double().view(512, -1), cols).view(n, 512, 13, 13) + b.double().view(1, -1, 1, 1)
+        err = (y[first:first + n] - ref).flatten(1).norm(dim=1) / ref.flatten(1).norm(dim=1)
+        assert float(err.max()) <= 2.0 ** -24 * np.sqrt(6192 / 16 + 32)
+
+
 def test_short_sums_stay_on_the_bf16_terms():
     """The operands' error is below the sums' from about 620 indices on; slices count by themselves."""
     assert "half" not in names(P(64, 64, 28, 28, 128, 3, 3, 1, 1, 1, 1))["fwd"]
