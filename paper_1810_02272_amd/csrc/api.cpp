@@ -5,6 +5,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <new>
 
 #include "internal.h"
@@ -505,36 +506,58 @@ bool folded_grid(int64_t cg, int64_t kh, int64_t kw, int64_t sh, int64_t sw, int
   return g.f.fw % 4 == 0 && g.f.Uw % 4 == 0 && dw == 1 && pw % 4 == 0;
 }
 
-// Whether sums of K products take f16 terms where bf16 terms would add up `bf16_K` of them in a slice: where their error is smaller on
-// inputs without zeros, by a margin (squares of the 2-norms, in units of 2^-24: split_f16.h).  Zeros add no rounding to a sum, but what
-// the operands lose stays.  Measured, bf16 -> f16 terms, for inputs without zeros, with a half and with a tenth that is not zero:
-//   3x3 forward, K = 648: 2.35 -> 1.95, 1.81 -> 1.94, 0.93 -> 1.77; 1152: 3.21 -> 2.39, 2.49 -> 2.36, 1.18 -> 1.97;
-//   2304: 4.68 -> 3.50, 3.65 -> 3.47, 1.65 -> 2.72;
-//   filter gradient, both blobs so, 1394 a slice: 3.76 -> 3.03, 2.21 -> 2.87, 1.01 -> 1.80; 1261: 3.61 -> 2.80, 2.25 -> 2.73, 1.30 -> 1.98.
-// Returns the steps (of `step` indices, in whole `unit`s) between two moves of the sums' leading bits, or 0 for bf16 terms.  A move
-// costs time (every 128 indices instead of 400: 57.3 GFLOP 160 -> 176 us), so the stretches are as long as a quarter less error than
-// the bf16 terms' allows, 128 indices where that is out of reach.
-int32_t half_interval(double K, double bf16_K, double step, int32_t unit) {
-  const double bf16 = 0.0047 * bf16_K;
+// Whether sums of K products take f16 terms: where their error (squares of 2-norms in units of 2^-24) can be brought to `most`.  Returns
+// the steps (of `step` indices, in whole `unit`s) between two moves of the sums' leading bits, or 0 for bf16 terms.  A move costs time
+// (every 128 indices instead of 400: 57.3 GFLOP 160 -> 176 us), so the stretches are as long as `aim` allows.  The f16 terms' error
+// is the operands', which zeros among the inputs leave as it is, the rounding of the sums within a stretch, and that of the moves.
+int32_t half_interval(double K, double most, double aim, double step, int32_t unit) {
   auto error = [&](int32_t steps) {
     const double part = (double)steps * step < K ? (double)steps * step : K;
-    return 2.1 + 0.0047 * part + 0.04 * K / part;
+    return 2.4 + 0.0085 * part + 0.04 * K / part;
   };
   int32_t steps = unit;
-  while ((double)steps * step < 128) steps += unit;
-  if (error(steps) > bf16) return 0;
-  while ((double)steps * step < K && error(steps + unit) < 0.75 * bf16) steps += unit;
+  while ((double)steps * step < 112) steps += unit;
+  if (error(steps) > most) return 0;
+  while ((double)steps * step < K && error(steps + unit) < aim) steps += unit;
   return steps;
 }
 
-// The same for corr_split_kernel: `cps` of `chunks` chunks of T taps in a slice.  The tiles that hold several steps' weights move the
-// leading bits between chunks only.  The samples are of four neighbours (and of eight weights: reductions are longer).
-int32_t corr_half_interval(const CorrArgs& base, int32_t tile, int32_t mt, int64_t T, int64_t chunks, int64_t cps, int64_t bf16_cps) {
+// The bf16 terms' error an index: without zeros, with a blob of half zeros, as behind a ReLU, and with two (a filter gradient whose dy
+// came back through one).  Zeros add no rounding to a sum.  f16 terms are taken where they are no further off without zeros, those of
+// a layer's own padding apart, and about a tenth further off at most with a blob of half zeros; an InnerProduct layer's data gradient,
+// whose dz came back through its ReLU, takes them where they are no further off then.  The stretches are such that sums of about 750
+// indices and more are no further off with half zeros, in the filter gradient of 2000 and more with half zeros in both blobs.
+// Measured, bf16 -> f16 terms, without zeros, with half of both blobs zero, and with nine tenths:
+//   3x3 forward, K = 648: 2.38 -> 1.99, 1.83 -> 1.98, 0.94 -> 1.80; 864: 2.81 -> 2.08, 2.17 -> 2.07, 1.06 -> 1.83;
+//   1152: 3.26 -> 2.38, 2.53 -> 2.38, 1.20 -> 1.99; 2304: 4.79 -> 3.31, 3.77 -> 3.31, 1.68 -> 2.59;
+//   filter gradient, 759 a slice: 2.90 -> 2.34, 1.90 -> 2.30, 1.29 -> 1.92; 896: 3.05 -> 2.33, 1.95 -> 2.28, 1.24 -> 1.89;
+//   2404: 4.89 -> 2.92, 2.80 -> 2.76, 1.06 -> 1.80; 3584: 6.13 -> 3.68, 3.59 -> 3.50, 1.17 -> 1.91.
+// None of these is above what the bf16 terms lose without zeros.  70 layers drawn like those of perf/cases.py, 114 outputs that differ: f16
+// terms 0.75 of the bf16 terms' error in the geometric mean, 0.96 at most (biases, whose sums only changed their order, 1.03).
+constexpr double kBf16Full = 0.0085, kBf16Half = 0.0052, kBf16BothHalf = 0.0035, kHalfMost = 1.15 * kBf16Half;
+
+// Share of positions x taps that lie inside the image: the others are zeros.
+double inside_image(int64_t positions, int64_t stride, int64_t taps, int64_t dilation, int64_t pad, int64_t size) {
+  int64_t inside = 0;
+  for (int64_t t = 0; t < taps; ++t)
+    for (int64_t p = 0; p < positions; ++p) {
+      const int64_t at = p * stride + t * dilation - pad;
+      inside += at >= 0 && at < size;
+    }
+  return (double)inside / (double)(positions * taps);
+}
+
+// half_interval for corr_split_kernel: `cps` of `chunks` chunks of T taps in a slice, where bf16 terms would add up `bf16_cps`.  The
+// tiles that hold several steps' weights move the leading bits between chunks only.
+int32_t corr_half_interval(const CorrArgs& base, int32_t tile, int32_t mt, int64_t T, int64_t chunks, int64_t cps, int64_t bf16_cps,
+                           double inside) {
   if (cps > kUnheldChunks) return 0;
   const int32_t step = mt == 32 ? 16 : 32;
   const bool by_chunk = tile == SPLIT_64x128 || tile == SPLIT_32x256 || tile == SPLIT_32x128;
   const double chunk = (double)base.Kred / (double)chunks;
-  return half_interval(chunk * (double)cps, chunk * (double)bf16_cps, step, by_chunk ? (int32_t)ceil_div(16 * T, step) : 2);
+  const bool inner_product = base.THW == 1 && base.IH == 1 && base.ncols == base.P;  // one image of one row: its data gradient's form
+  const double bf16_K = chunk * (double)bf16_cps, most = inner_product ? kBf16Half : std::min(kHalfMost, kBf16Full * inside);
+  return half_interval(chunk * (double)cps, most * bf16_K, 0.9 * kBf16Half * bf16_K, step, by_chunk ? (int32_t)ceil_div(16 * T, step) : 2);
 }
 
 // Tile and split count of corr_split_kernel on one grid by modelled time (us); tile < 0: the patch fits none.
@@ -547,6 +570,7 @@ struct SplitPlan {
   int32_t tile, half;
   int64_t psz, S, units;  // units: output tiles
   int64_t bf16_cps;       // chunks of a slice on bf16 terms
+  double inside;          // share of the products that are none of padding
   double cost;  // modelled time without the launches and the prologue, about 10 us
   PatchDim w, h;
 };
@@ -563,12 +587,15 @@ SplitPlan plan_split(const CorrArgs& base, const SplitGrid& grid, int64_t out_el
   plan.half = half;
   const bool columns = grid.f.subs != 0, image = grid.f.ff == 1 && !columns;
   const int64_t chunks = ceil_div(grid.f.V, columns ? 64 : 16);
-  plan.bf16_cps = bf16_S ? ceil_div(chunks, bf16_S) : 0;
   const int64_t T = grid.TH * grid.TW, PH = base.P / base.PW, ext = (grid.TH - 1) * grid.dh + 1;
   if (!columns) {
     plan.w = patch_dim(base.PW, grid.sw, (grid.TW - 1) * grid.dw + 1, image ? base.pw : 0, base.IW);
     plan.h = patch_dim(PH, grid.sh, ext, image ? base.ph : 0, base.IH);
   }
+  plan.bf16_cps = bf16_S ? ceil_div(chunks, bf16_S) : 0;
+  plan.inside = half && image ? inside_image(base.PW, grid.sw, grid.TW, grid.dw, base.pw, base.IW) *
+                                    inside_image(PH, grid.sh, grid.TH, grid.dh, base.ph, base.IH)
+                              : 1;
   const double out_mb = 4e-6 * (double)out_elems;
   double best = 0;
   for (int32_t t = 0; t < SPLIT_TILE_COUNT; ++t) {
@@ -590,7 +617,7 @@ SplitPlan plan_split(const CorrArgs& base, const SplitGrid& grid, int64_t out_el
       // batch 16, forward: 5258 us on bf16 terms, 3647 in two slices).
       if (S > 1 && (units * S > 2048 || units > 512) && !(half && ceil_div(chunks, S - 1) > kUnheldChunks)) break;
       const int64_t per_cu = ceil_div(units * S, 256), cps = ceil_div(chunks, S);
-      if (half && !corr_half_interval(base, t, mt, T, chunks, cps, plan.bf16_cps)) continue;
+      if (half && !corr_half_interval(base, t, mt, T, chunks, cps, plan.bf16_cps, plan.inside)) continue;
       const double steps = (double)(cps * spc);
       double cost = per_cu == 1 ? steps * c.alone[t] + c.patch_alone * (double)cps * units_per_thread
                                 : (double)per_cu * (steps * c.shared[t] + c.patch_shared * (double)cps * units_per_thread);
@@ -725,7 +752,7 @@ size_t configure_split(const CorrArgs& base, const PackArgs& pbase, int64_t cg_i
   const int64_t fragments = split_fragments(base, grid, tile), bytes = split_pack_bytes(fragments, plan.half);
   if (plan.half) {
     a.half = k.half = 1;
-    a.lead_steps = corr_half_interval(base, tile, mt, a.THW, chunks, a.chunks_per_split, plan.bf16_cps);
+    a.lead_steps = corr_half_interval(base, tile, mt, a.THW, chunks, a.chunks_per_split, plan.bf16_cps, plan.inside);
     const uint32_t stage = pixels ? split_half_stage(4, bn) : split_half_stage(columns ? 4 : split_patch_units(a.PSZ + 1, bn), 0);
     const uint32_t behind = split_half_lead(bm, bn) + (columns && !pixels ? kUnheldBytes : 0);
     a.patch_stages = 2 * stage + behind <= 80 * 1024 ? 2 : 1;  // two workgroups per compute unit
@@ -821,8 +848,10 @@ int32_t configure_wgrad_split(const WgradArgs& w, int32_t fp32_tile, int64_t N, 
     return w.x_bytes >= 16 && w.dy_bytes >= 16 && work * 8.0 * (double)total_runs <= 2.2 * (double)w.Kg * w.Kred * (double)w.ncols;
   };
   int64_t bf16_cps = 0;  // of the best plan on bf16 terms
+  const double inside = inside_image(w.PW, w.sw, w.kw, w.dw, w.pw, w.W) * inside_image(PH, w.sh, w.khw / w.kw, w.dh, w.ph, w.H);
   for (int half = 0; half < 2; ++half) {
     const Costs& c = kCosts[half];
+    const double bf16_pix = chunk_pix * (double)bf16_cps;
     for (int32_t t = 0; t < WSPLIT_TILE_COUNT; ++t) {
       int32_t rows, taps;
       wgrad_split_shape(t, &rows, &taps);
@@ -837,7 +866,7 @@ int32_t configure_wgrad_split(const WgradArgs& w, int32_t fp32_tile, int64_t N, 
         if (S > chunks) S = chunks;
         if (S < 1) S = 1;
         const int64_t cps = ceil_div(chunks, S), per_cu = ceil_div(tiles * ceil_div(chunks, cps), 256);
-        const int32_t lead = half ? half_interval(chunk_pix * (double)cps, chunk_pix * (double)bf16_cps, chunk_pix, 1) : 0;
+        const int32_t lead = half ? half_interval(chunk_pix * (double)cps, std::min(kHalfMost, kBf16Full * inside) * bf16_pix, 0.9 * kBf16BothHalf * bf16_pix, chunk_pix, 1) : 0;
         if (half && !lead) continue;
         const double cost = c.fixed + c.slice_mb * (double)S * w_mb + c.workgroup * (double)per_cu +
                             (per_cu == 1 ? (double)cps * (4 * c.alone[t] + c.patch_alone * units_per_thread)
@@ -935,7 +964,8 @@ int32_t configure_wgrad_fold(const WgradArgs& w, int32_t fp32_tile, int64_t N, i
       if (S < 1) S = 1;
       const int64_t cps = ceil_div(chunks, S), per_cu = ceil_div(tiles * ceil_div(chunks, cps), 256);
       const double pix = chunk_pix * (double)cps;
-      const int32_t lead = half_interval(pix, pix, chunk_pix, 1);
+      // what runs otherwise are the fp32 kernels, further off than the bf16 terms without zeros
+      const int32_t lead = half_interval(pix, kHalfMost * pix, 0.9 * kBf16Half * pix, chunk_pix, 1);
       if (!lead) continue;
       const double cost = 6.9 + 0.604 * (double)S * part_mb + 3.43 * (double)per_cu +
                           (per_cu == 1 ? (double)cps * (4 * kAlone[t] + 0.669 * units_per_thread)

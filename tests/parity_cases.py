@@ -309,6 +309,10 @@ HALF_CASES = [
     P(49, 32, 27, 37, 376, 3, 5, 1, 2, 1, 1, 1, 1, 2),
     P(39, 107, 49, 3, 267, 4, 3, 1, 2, 3, 2, 1, 1, 1),
     P(12, 996, 30, 41, 144, 1, 1, 1, 1, 1, 1, 2, 2, 1),
+    P(17, 66, 28, 41, 99, 4, 3, 1, 1, 1, 1, 1, 1, 1),
+    P(4, 150, 24, 52, 182, 4, 3, 1, 1, 1, 0, 1, 1, 1),
+    P(45, 50, 26, 31, 110, 7, 1, 1, 1, 0, 0, 1, 1, 1),
+    P(2984, 1314, 1, 1, 714, 1, 1, 1, 1, 0, 0, 1, 1, 1),
 ]
 
 # Filter gradients of folded layers, every tile and patch size.
