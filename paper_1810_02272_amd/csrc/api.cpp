@@ -530,10 +530,11 @@ int32_t half_interval(double K, double most, double aim, double step, int32_t un
 // Measured, bf16 -> f16 terms, without zeros, with half of both blobs zero, and with nine tenths:
 //   3x3 forward, K = 648: 2.38 -> 1.99, 1.83 -> 1.98, 0.94 -> 1.80; 864: 2.81 -> 2.08, 2.17 -> 2.07, 1.06 -> 1.83;
 //   1152: 3.26 -> 2.38, 2.53 -> 2.38, 1.20 -> 1.99; 2304: 4.79 -> 3.31, 3.77 -> 3.31, 1.68 -> 2.59;
-//   filter gradient, 759 a slice: 2.90 -> 2.34, 1.90 -> 2.30, 1.29 -> 1.92; 896: 3.05 -> 2.33, 1.95 -> 2.28, 1.24 -> 1.89;
+//   filter gradient, 759 a slice: 2.90 -> 2.34, 1.90 -> 2.30, 1.29 -> 1.92; 1024: 3.25 -> 2.54, 2.03 -> 2.44, 1.22 -> 1.88;
+//   896: 3.05 -> 2.33, 1.95 -> 2.28, 1.24 -> 1.89;
 //   2404: 4.89 -> 2.92, 2.80 -> 2.76, 1.06 -> 1.80; 3584: 6.13 -> 3.68, 3.59 -> 3.50, 1.17 -> 1.91.
 // None of these is above what the bf16 terms lose without zeros.  70 layers drawn like those of perf/cases.py, 114 outputs that differ: f16
-// terms 0.75 of the bf16 terms' error in the geometric mean, 0.96 at most (biases, whose sums only changed their order, 1.03).
+// terms 0.76 of the bf16 terms' error in the geometric mean, 0.96 at most (biases, whose sums only changed their order, 1.03).
 constexpr double kBf16Full = 0.0085, kBf16Half = 0.0052, kBf16BothHalf = 0.0035, kHalfMost = 1.15 * kBf16Half;
 
 // Share of positions x taps that lie inside the image: the others are zeros.
@@ -851,7 +852,9 @@ int32_t configure_wgrad_split(const WgradArgs& w, int32_t fp32_tile, int64_t N, 
   const double inside = inside_image(w.PW, w.sw, w.kw, w.dw, w.pw, w.W) * inside_image(PH, w.sh, w.khw / w.kw, w.dh, w.ph, w.H);
   for (int half = 0; half < 2; ++half) {
     const Costs& c = kCosts[half];
-    const double bf16_pix = chunk_pix * (double)bf16_cps;
+    // Half zeros in both blobs count from sums on that two chunks a stretch are enough for: a move every chunk costs what the
+    // instructions save (45 -> 77, 3x5 at 51x67, batch 37, 758 a slice: 57 -> 70 us, 67 on bf16 terms).
+    const double bf16_pix = chunk_pix * (double)bf16_cps, aim = (bf16_pix < 1500 ? kHalfMost : 0.9 * kBf16BothHalf) * bf16_pix;
     for (int32_t t = 0; t < WSPLIT_TILE_COUNT; ++t) {
       int32_t rows, taps;
       wgrad_split_shape(t, &rows, &taps);
@@ -866,7 +869,7 @@ int32_t configure_wgrad_split(const WgradArgs& w, int32_t fp32_tile, int64_t N, 
         if (S > chunks) S = chunks;
         if (S < 1) S = 1;
         const int64_t cps = ceil_div(chunks, S), per_cu = ceil_div(tiles * ceil_div(chunks, cps), 256);
-        const int32_t lead = half ? half_interval(chunk_pix * (double)cps, std::min(kHalfMost, kBf16Full * inside) * bf16_pix, 0.9 * kBf16BothHalf * bf16_pix, chunk_pix, 1) : 0;
+        const int32_t lead = half ? half_interval(chunk_pix * (double)cps, std::min(kHalfMost, kBf16Full * inside) * bf16_pix, aim, chunk_pix, 1) : 0;
         if (half && !lead) continue;
         const double cost = c.fixed + c.slice_mb * (double)S * w_mb + c.workgroup * (double)per_cu +
                             (per_cu == 1 ? (double)cps * (4 * c.alone[t] + c.patch_alone * units_per_thread)

@@ -24,8 +24,8 @@
 // 32, 5x5 at 16x16, batch 100) 29 -> 21.  172 and 115 us are the matrix instructions of the first two at 2000 TFLOP/s.
 //
 // HALF: long reductions on two f16 terms (split_f16.h), half the matrix instructions.  The stage is [h, m][half][position] then,
-// 16 bytes a position.  The same passes: 57.3 GFLOP 249 -> 166 us and 269 -> 166, 38.3 GFLOP 172 -> 114 and 206 -> 137, 6.7 GFLOP 49
-// -> 37 and 53 -> 40 (without the test of every value 2 % less); the pack kernel, which samples both blobs and writes both splits, 1
+// 16 bytes a position.  The same passes: 57.3 GFLOP 249 -> 171 us and 269 -> 172, 38.3 GFLOP 172 -> 115 and 206 -> 141, 6.7 GFLOP 49
+// -> 40 and 53 -> 44 (without the test of every value 2 % less); the pack kernel, which samples both blobs and writes both splits, 1
 // to 2.5 us more.  The matrix unit is busy 50 to 55 % of the cycles, at the clock that the chip's power leaves (1.7 GHz); a quarter to
 // two fifths of the waves' time are waits for weights, patches and barriers.  Weights two steps ahead gave nothing (108 -> 112 us where
 // the registers hold them, spills elsewhere).

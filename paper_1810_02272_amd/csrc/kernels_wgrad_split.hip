@@ -19,7 +19,7 @@
 //
 // HALF: long sums on two f16 terms (split_f16.h), half the matrix instructions, positions of 64 bytes.  Every workgroup samples
 // both blobs for the powers of two while its first loads are under way.  The first three layers, without the reduce kernel: 349 ->
-// 228 us, 219 -> 153, 67 -> 57, of which the test of every value is 6 to 8 %: each of a row's column tiles tests it again.
+// 236 us, 219 -> 160, 67 -> 70 (its leading bits move every chunk), of which the test of every value is 6 to 8 %: each of a row's column tiles tests it again.
 // AGAIN: what a workgroup's HALF sums had to leave out, step by step, it adds on the bf16 terms behind them.  128 -> 128, 3x3 at 56x56,
 // batch 64: 228 us, with one image 2^-30 of the others 235, with every image of a size of its own 345, with one channel of x and one of dy
 // 2^-30 of theirs, which leaves out every step, 474 (343 on bf16 terms alone).
